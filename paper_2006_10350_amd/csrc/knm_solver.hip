@@ -384,151 +384,187 @@ __global__ __launch_bounds__(256) void panel_update_t_kernel(const double *__res
 }
 
 // ---- leaf of the blocked factorisation --------------------------------------------------------
-// One workgroup factorises a diagonal block of order nb <= 128 in LDS (upper triangle packed by
-// rows, right-looking, two barriers per pivot) and inverts the factor in place there.
-// Everything above the leaf is products with these small inverses on the matrix cores.
-// The kernel keeps to 70 KB of LDS so that it can share a CU with a workgroup of the rank-k
+// One workgroup factorises a diagonal block of order nb <= 128 in LDS and inverts the factor there;
+// everything above the leaf is products with these small inverses on the matrix cores.
+//
+// A leaf is a serial chain, one workgroup with the rest of the chip waiting or (look-ahead) busy with
+// the trailing update, so what counts is its latency.  The block is cut into 16 x 16 tiles.  Per tile
+// row the elimination runs in registers: a lane holds one column of 16 entries, lanes 0-15 of every
+// wavefront the diagonal tile, the other 48 lanes three more tiles of the row (or, as right-hand
+// side, the identity, which the same elimination turns into the inverse of the diagonal tile), and the
+// 16 pivots and multipliers are read from the lanes of the diagonal tile as scalars, so that no
+// step of the chain waits for a barrier or for LDS.  The trailing tiles are updated on the matrix
+// cores, two barriers per tile row.  The tile inverses are then merged in place, pair by pair
+// (16 -> 32 -> 64 -> 128), again on the matrix cores.  57 us per 128 x 128 block; eliminating row by
+// row from LDS with two barriers per pivot took 347 us.
+// The kernel keeps to 73 KB of LDS so that it can share a CU with a workgroup of the rank-k
 // kernel: during the factorisation's look-ahead it runs beside the trailing update.
 constexpr int kLeaf = 128;
 constexpr int kLeafThreads = 512;
-constexpr int kLeafPacked = kLeaf * (kLeaf + 1) / 2;
+constexpr int kLeafWaves = kLeafThreads / 64;
+constexpr int kLeafTiles = kLeaf / 16;
 
-struct LeafShared {
-    double P[kLeafPacked]; // (i, j), i <= j, at i nb - i (i - 1) / 2 + (j - i)
-    double rowk[kLeaf];
-    double dinv[kLeaf];
-    double rrow[2][kLeaf];
-};
+typedef double leaf_d4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ int leaf_row_start(int i, int nb) { return i * nb - i * (i - 1) / 2; }
+// 16 x 16 tile (bi, bj), bi <= bj, of the upper triangle; entry (i, j) of a tile at i 16 + (j ^ i): rows and columns
+// are both read without bank conflicts
+__device__ __forceinline__ int leaf_tile(int bi, int bj) { return (bj * (bj + 1) / 2 + bi) * 256; }
+__device__ __forceinline__ int leaf_at(int i, int j) { return i * 16 + (j ^ i); }
 
-// entry (i, j), i <= j, of the block at A: A[i + j lda] (upper storage) or A[j + i lda] (lower)
-__device__ __forceinline__ void leaf_load(LeafShared &sh, const double *A, int64_t lda, int nb, int lower)
+__device__ __forceinline__ double lane_value(double x, int lane)
 {
-    for (int e = threadIdx.x; e < nb * kLeaf; e += kLeafThreads) {
-        // upper storage: column j of the block, row i contiguous; lower: row i, column j contiguous
-        const int u = e & (kLeaf - 1), w = e >> 7;
-        const int i = lower ? w : u, j = lower ? u : w;
-        if (i <= j && j < nb) sh.P[leaf_row_start(i, nb) + (j - i)] = A[u + w * lda];
+    const uint64_t v = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), lane);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// 1 / sqrt(d) for a normal positive d: the hardware's estimate (about 26 bits) and one third-order Newton step
+__device__ __forceinline__ double inverse_sqrt(double d)
+{
+    const double y = __builtin_amdgcn_rsq(d);
+    const double e = fma(-(d * y), y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// c (16 x 16, accumulator layout: entry r of lane l is row 4 r + l / 16, column l % 16) += A^T B or (plain) A B for
+// tiles of LDS
+template <bool TRANS>
+__device__ __forceinline__ void leaf_product(leaf_d4 &c, const double *A, const double *B, int lane)
+{
+    const int l15 = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const int k = 4 * s + q;
+        const double av = TRANS ? A[leaf_at(k, l15)] : A[leaf_at(l15, k)];
+        const double bv = B[leaf_at(k, l15)];
+        c = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, c, 0, 0, 0);
     }
 }
 
-// W (nb x nb, column-major, ldw; written whole, zeros below the diagonal) <- inverse of the upper
-// triangular factor R packed in sh.P, whose reciprocal diagonal is in sh.dinv; sh.P is overwritten
-// by the inverse.  Rows are done in lockstep, last to first:
-//   W[i, c] = -(sum_{i < j <= c} R[i, j] W[j, c]) / R[i, i],
-// with row i of R first copied aside (its storage then takes row i of W), so R[i, j] is a
-// broadcast read and W[j, c] is contiguous across the columns c.  A column belongs to four
-// adjacent lanes, which split the sum over j.  One workgroup has its CU nearly to itself, so
-// the loops are unrolled by hand to keep several LDS reads in flight.
-__device__ __forceinline__ void leaf_invert(LeafShared &sh, int nb, double *W, int64_t ldw)
-{
-    const int tid = threadIdx.x;
-    const int c = tid >> 2, part = tid & 3;
-    const bool live = c < nb;
-    if (tid == 0) sh.P[leaf_row_start(nb - 1, nb)] = sh.dinv[nb - 1];
-    for (int i = nb - 2; i >= 0; --i) {
-        double *rr = sh.rrow[i & 1];
-        const int ri = leaf_row_start(i, nb);
-        if (tid > i && tid < nb) rr[tid] = sh.P[ri + (tid - i)];
-        __syncthreads(); // row i of R is aside, row i + 1 of W is complete
-        double s0 = 0.0, s1 = 0.0;
-        int j = i + 1 + part;
-        int pw = leaf_row_start(j, nb) + (c - j); // W[j, c]; four rows on it moves by 4 nb - 4 j - 10
-        for (; j + 4 < nb; j += 8) {
-            const int pw1 = pw + 4 * nb - 4 * j - 10;
-            const double a0 = (live && j <= c) ? rr[j] * sh.P[pw] : 0.0;
-            const double a1 = (live && j + 4 <= c) ? rr[j + 4] * sh.P[pw1] : 0.0;
-            s0 += a0;
-            s1 += a1;
-            pw = pw1 + 4 * nb - 4 * (j + 4) - 10;
-        }
-        if (j < nb && live && j <= c) s0 += rr[j] * sh.P[pw];
-        double s = s0 + s1;
-        s += __shfl_xor(s, 1);
-        s += __shfl_xor(s, 2);
-        if (part == 0 && live && c > i) sh.P[ri + (c - i)] = -s * sh.dinv[i];
-        if (tid == 0) sh.P[ri] = sh.dinv[i];
-    }
-    __syncthreads();
-    for (int e = tid; e < nb * kLeaf; e += kLeafThreads) {
-        const int i = e & (kLeaf - 1), j = e >> 7;
-        if (i < nb) W[i + j * ldw] = (i <= j) ? sh.P[leaf_row_start(i, nb) + (j - i)] : 0.0;
-    }
-}
-
-// Triangle of the nb x nb block at A (upper or lower storage, lda) <- its upper Cholesky factor R,
-// R^T R = A, in the same storage; W <- R^-1 (always column-major, upper).  *bad <- min(*bad, pivot0 + k + 1) for a pivot k that is not a positive finite number
-// (the factorisation then goes on with 1 in its place; the caller discards the result).
+// Triangle of the nb x nb block at A (upper storage: entry (i, j), i <= j, at A[i + j lda]; lower storage: at
+// A[j + i lda]) <- its upper Cholesky factor R, R^T R = A, in the same storage; W <- R^-1 (nb x nb, always
+// column-major with leading dimension ldw, written whole, zeros below the diagonal).  *bad <- min(*bad, pivot0 + k + 1) for a pivot
+// k that is not a positive finite number (the factorisation then goes on with 1 in its place; the caller discards
+// the result).
 __global__ __launch_bounds__(kLeafThreads) void potrf_trtri_leaf_kernel(double *__restrict__ A, int64_t lda, int nb,
                                                                        double *__restrict__ W, int64_t ldw,
                                                                        int64_t pivot0, unsigned long long *bad,
                                                                        int lower)
 {
-    __shared__ LeafShared sh;
+    __shared__ double sh[kLeafTiles * (kLeafTiles + 1) / 2 * 256];
     const int tid = threadIdx.x;
-    leaf_load(sh, A, lda, nb, lower);
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nt = (nb + 15) / 16; // tiles per side; the last one is padded with the identity
+    // load: 16 x 16 tiles, 16 consecutive threads along the contiguous index
+    for (int e = tid; e < nt * (nt + 1) / 2 * 256; e += kLeafThreads) {
+        const int tile = e >> 8, u = e & 15, v = (e >> 4) & 15;
+        int bj = 0;
+        while ((bj + 1) * (bj + 2) / 2 <= tile) ++bj;
+        const int bi = tile - bj * (bj + 1) / 2;
+        const int i = lower ? v : u, j = lower ? u : v;
+        const int gi = bi * 16 + i, gj = bj * 16 + j;
+        double x = (gi == gj) ? 1.0 : 0.0;
+        if (gi <= gj && gj < nb) x = lower ? A[gj + gi * lda] : A[gi + gj * lda];
+        sh[tile * 256 + leaf_at(i, j)] = x;
+    }
     __syncthreads();
-    const int jc = tid & (kLeaf - 1), par = tid >> 7; // trailing update: column of this thread, rows par mod 4
-    for (int k = 0; k < nb; ++k) {
-        const int rk = leaf_row_start(k, nb);
-        const double dkk = sh.P[rk];
-        const bool ok = dkk > 0.0 && dkk < 1.0e300;
-        const double rinv = ok ? 1.0 / sqrt(dkk) : 1.0;
-        if (tid == 0) {
-            if (!ok) atomicMin(bad, (unsigned long long)(pivot0 + k + 1));
-            sh.dinv[k] = rinv;
-        }
-        if (tid > k && tid < nb) { // row k, scaled; kept beside the packed copy for the update
-            const double v = sh.P[rk + (tid - k)] * rinv;
-            sh.P[rk + (tid - k)] = v;
-            sh.rowk[tid] = v;
-        }
-        __syncthreads();
-        const int j = k + 1 + jc;
-        if (j < nb) {
-            const double rj = sh.rowk[j];
-            int i = k + 1 + par;
-            int pa = leaf_row_start(i, nb) + (j - i); // (i, j); four rows on it moves by 4 nb - 4 i - 10
-            for (; i + 4 <= j; i += 8) {
-                const int pa1 = pa + 4 * nb - 4 * i - 10;
-                const double u0 = sh.rowk[i], u1 = sh.rowk[i + 4];
-                const double c0 = sh.P[pa], c1 = sh.P[pa1];
-                sh.P[pa] = c0 - u0 * rj;
-                sh.P[pa1] = c1 - u1 * rj;
-                pa = pa1 + 4 * nb - 4 * (i + 4) - 10;
+    for (int p = 0; p < nt; ++p) {
+        // slots of this tile row besides the diagonal tile: the identity, then tiles p + 1 .. nt - 1; three per wavefront
+        const int slots = nt - p;
+        const int part = lane >> 4, l15 = lane & 15;
+        double a[16]; // one column per lane
+        if (wave * 3 < slots) {
+            const int slot = wave * 3 + part - 1; // of lanes 16..63
+            const bool ident = part != 0 && slot == 0;
+            const int bj = part == 0 ? p : p + slot;
+            const bool live = part == 0 || slot < slots;
+            const double *src = sh + leaf_tile(p, live ? bj : p);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const double x = src[leaf_at(i, l15)];
+                a[i] = ident ? (i == l15 ? 1.0 : 0.0) : x;
             }
-            if (i <= j) sh.P[pa] -= sh.rowk[i] * rj;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const double d = lane_value(a[k], k);
+                const bool ok = d > 0.0 && d < 1.0e300;
+                if (!ok && tid == 0) atomicMin(bad, (unsigned long long)(pivot0 + 16 * p + k + 1));
+                const double rinv = ok ? inverse_sqrt(d) : 1.0;
+                a[k] *= rinv; // row k of R (of the right-hand sides: of L^-1 times them)
+#pragma unroll
+                for (int i = k + 1; i < 16; ++i) a[i] = fma(-lane_value(a[k], i), a[k], a[i]);
+            }
+            if (!ident && live && part != 0) {
+                double *dst = sh + leaf_tile(p, bj);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) dst[leaf_at(i, l15)] = a[i];
+            }
+            const int col = bj * 16 + l15;
+            if (!ident && live && (part != 0 || wave == 0) && col < nb) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int row = p * 16 + i;
+                    if (row <= col) A[lower ? col + row * lda : row + col * lda] = a[i];
+                }
+            }
+        }
+        __syncthreads();
+        if (wave == 0 && part == 1) {
+            // L^-1, whose transpose is the inverse of the diagonal tile, takes that tile's place (every wavefront has read it)
+            double *dst = sh + leaf_tile(p, p);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) dst[leaf_at(l15, i)] = a[i];
+        }
+        // trailing tiles lose R_p,bi^T R_p,bj
+        const int rest = nt - 1 - p;
+        for (int t = wave; t < rest * (rest + 1) / 2; t += kLeafWaves) {
+            int cj = 0;
+            while ((cj + 1) * (cj + 2) / 2 <= t) ++cj;
+            const int bj = p + 1 + cj, bi = p + 1 + t - cj * (cj + 1) / 2;
+            leaf_d4 c = {0.0, 0.0, 0.0, 0.0};
+            leaf_product<true>(c, sh + leaf_tile(p, bi), sh + leaf_tile(p, bj), lane);
+            double *dst = sh + leaf_tile(bi, bj);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dst[leaf_at(4 * r + (lane >> 4), lane & 15)] -= c[r];
         }
         __syncthreads();
     }
-    // back to A, with the diagonal of R: sh.P still holds the pivots before the square root
-    for (int e = tid; e < nb * kLeaf; e += kLeafThreads) {
-        const int u = e & (kLeaf - 1), w = e >> 7;
-        const int i = lower ? w : u, j = lower ? u : w;
-        if (i <= j && j < nb) A[u + w * lda] = (i == j) ? 1.0 / sh.dinv[i] : sh.P[leaf_row_start(i, nb) + (j - i)];
+    __syncthreads();
+    // inv([R11 R12; 0 R22]) = [W11, -W11 R12 W22; 0, W22], the off-diagonal blocks in place: R12 W22 is
+    // held in registers until every wavefront has read R12
+    for (int h = 1; h < nt; h *= 2) {
+#pragma unroll
+        for (int phase = 0; phase < 2; ++phase) {
+            leaf_d4 c[2];
+            double *dst[2];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) { // 4 h tiles, at most two per wavefront
+                const int t = wave + kLeafWaves * m;
+                const int o = (t / (h * h)) * 2 * h, i = o + (t / h) % h, j = o + h + t % h;
+                dst[m] = nullptr;
+                if (t >= kLeafTiles / 2 * h || j >= nt) continue;
+                dst[m] = sh + leaf_tile(i, j);
+                c[m] = leaf_d4{0.0, 0.0, 0.0, 0.0};
+                const int k0 = phase == 0 ? o + h : i, k1 = phase == 0 ? j + 1 : o + h;
+                for (int k = k0; k < k1; ++k) leaf_product<false>(c[m], sh + leaf_tile(i, k), sh + leaf_tile(k, j), lane);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+                if (dst[m] != nullptr) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        dst[m][leaf_at(4 * r + (lane >> 4), lane & 15)] = phase == 0 ? c[m][r] : -c[m][r];
+                }
+            __syncthreads();
+        }
     }
-    __syncthreads();
-    leaf_invert(sh, nb, W, ldw);
-}
-
-// W <- inverse of the upper triangular nb x nb diagonal blocks of a factor R (one workgroup per
-// block): leaf g sits on the diagonal of group g / blocks_per_group, at offset (g % blocks_per_group) * 128
-__global__ __launch_bounds__(kLeafThreads) void trtri_leaf_kernel(const double *__restrict__ R, int64_t ldr, int64_t M,
-                                                                 int64_t step_w_block, int blocks_per_group,
-                                                                 double *__restrict__ W, int64_t ldw, int lower)
-{
-    __shared__ LeafShared sh;
-    const int64_t g = blockIdx.x;
-    const int64_t r0 = g * kLeaf;
-    const int nb = (int)((M - r0 < kLeaf) ? M - r0 : kLeaf);
-    const double *Rb = R + r0 + r0 * ldr;
-    const int64_t grp = g / blocks_per_group, off = (g % blocks_per_group) * kLeaf;
-    double *Wb = W + grp * step_w_block + off + off * ldw;
-    leaf_load(sh, Rb, ldr, nb, lower);
-    for (int k = threadIdx.x; k < nb; k += kLeafThreads) sh.dinv[k] = 1.0 / Rb[k + k * ldr];
-    __syncthreads();
-    leaf_invert(sh, nb, Wb, ldw);
+    for (int e = tid; e < nb * kLeaf; e += kLeafThreads) {
+        const int i = e & (kLeaf - 1), j = e >> 7;
+        if (i < nb) W[i + j * ldw] = (i <= j) ? sh[leaf_tile(i >> 4, j >> 4) + leaf_at(i & 15, j & 15)] : 0.0;
+    }
 }
 
 inline dim3 grid1(int64_t n, int threads = 256) { return dim3((unsigned)((n + threads - 1) / threads)); }
@@ -777,9 +813,9 @@ int tri_solve(knm_ctx *ctx, const knm_precond *p, const double *R, const double 
     return KNM_OK;
 }
 
-// S <- mirrored inverses of the sb x sb diagonal blocks of the upper-triangular R (p->T or p->A).  The 128 x 128
-// diagonal blocks are inverted by the leaf kernel (one workgroup each); neighbouring inverses are
-// then merged level by level,  inv([R11 R12; 0 R22]) = [W11, -W11 R12 W22; 0, W22],  with two
+// S <- mirrored inverses of the sb x sb diagonal blocks of the upper-triangular R (p->T or p->A).  S holds the
+// inverses of the 128 x 128 diagonal blocks, which the leaf kernel left there, and zeros; neighbouring inverses are
+// merged level by level,  inv([R11 R12; 0 R22]) = [W11, -W11 R12 W22; 0, W22],  with two
 // block products per pair, until the blocks are sb wide; last the upper triangle of every
 // block is copied onto its lower.  `tmp` holds (sb / 2)^2 doubles.
 int invert_diag_blocks(knm_ctx *ctx, const knm_precond *p, const double *R, double *S, double *tmp)
@@ -789,11 +825,6 @@ int invert_diag_blocks(knm_ctx *ctx, const knm_precond *p, const double *R, doub
     const int sb = p->sb;
     const int64_t nblk = (M + sb - 1) / sb;
     const int64_t block = (int64_t)sb * sb;
-    hipError_t e = hipMemsetAsync(S, 0, sizeof(double) * nblk * block, ctx->stream);
-    if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipMemsetAsync", e);
-    const int64_t leaves = (M + kLeaf - 1) / kLeaf;
-    hipLaunchKernelGGL(trtri_leaf_kernel, dim3((unsigned)leaves), dim3(kLeafThreads), 0, ctx->stream, R, ld, M, block,
-                       sb / kLeaf, S, (int64_t)sb, lower);
     for (int64_t h = kLeaf; h < sb; h *= 2) {
         for (int64_t k = 0; k < nblk; ++k) {
             const int64_t k0 = k * sb;
@@ -980,8 +1011,8 @@ int precond_free(knm_precond *p)
 //   multiplied by that inverse (in place: a 128-row tile of the block product reads exactly
 //   the columns it writes).
 //   Step 3 (trailing update, M^3 / 3 of the flop) is one rank-k launch per block row.
-// `W` is a 128 x 128 scratch block, `bad` a device word initialised by the caller to ~0;
-// first_bad receives the 1-based index of the first failing pivot, or 0.
+// S (as many sb x sb column-major blocks as cover M) is cleared and receives the inverses of the 128 x 128 diagonal
+// blocks at their places; `bad` is a device word; first_bad receives the 1-based index of the first failing pivot, or 0.
 constexpr int64_t kSubPanel = 512;
 
 // events without timing, destroyed with the set
@@ -1020,8 +1051,8 @@ static int aux_stream(knm_ctx *ctx, hipStream_t *out)
 // A[c + r ld]); every product below then has its two index roles exchanged, and the pieces of a
 // block row that straddle the diagonal are split into a symmetric update (which writes one triangle
 // only) and a rectangle, because the other triangle belongs to the other factor.
-static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool lower, double *W, unsigned long long *bad,
-                        int64_t *first_bad)
+static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool lower, double *S, int sb,
+                        unsigned long long *bad, int64_t *first_bad)
 {
     TraceRange range(lower ? "knm Cholesky of T D T^T / M + lambda I" : "knm Cholesky of K_MM");
     int64_t b = ((M + 7) / 8 + 255) / 256 * 256;
@@ -1030,6 +1061,8 @@ static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool low
     const unsigned long long none = ~0ull;
     hipError_t e = hipMemcpyAsync(bad, &none, sizeof(none), hipMemcpyHostToDevice, ctx->stream);
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipMemcpyAsync", e);
+    e = hipMemsetAsync(S, 0, sizeof(double) * (size_t)((M + sb - 1) / sb) * sb * sb, ctx->stream);
+    if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipMemsetAsync", e);
     hipStream_t aux = nullptr;
     int st = aux_stream(ctx, &aux);
     if (st) return st;
@@ -1066,14 +1099,15 @@ static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool low
                 const int nbk = (int)((sw - s0 < kLeaf) ? sw - s0 : kLeaf);
                 const int64_t ncols = M - row;
                 if (s0 > 0 && !update_rows(prow, s0, row, nbk)) return fail(ctx, KNM_HIP_ERROR, "block row update launch");
+                double *W = S + (row / sb) * (int64_t)sb * sb + (row % sb) * (int64_t)(sb + 1); // sb is a multiple of 128
                 hipLaunchKernelGGL(potrf_trtri_leaf_kernel, dim3(1), dim3(kLeafThreads), 0, ctx->stream, at(row, row), ld, nbk,
-                                   W, (int64_t)kLeaf, row, bad, lower ? 1 : 0);
+                                   W, (int64_t)sb, row, bad, lower ? 1 : 0);
                 if (ncols > nbk) {
                     // the rest of the rows times the inverse: R(row + i, c) <- sum_k W(k, i) R(row + k, c)
                     double *right = at(row, row + nbk);
                     const hipError_t le =
-                        lower ? launch_gemm_f64(1, ncols - nbk, nbk, nbk, 1.0, right, ld, W, kLeaf, 0.0, right, ld, ctx->stream)
-                              : launch_gemm_f64(0, nbk, ncols - nbk, nbk, 1.0, W, kLeaf, right, ld, 0.0, right, ld, ctx->stream);
+                        lower ? launch_gemm_f64(1, ncols - nbk, nbk, nbk, 1.0, right, ld, W, sb, 0.0, right, ld, ctx->stream)
+                              : launch_gemm_f64(0, nbk, ncols - nbk, nbk, 1.0, W, sb, right, ld, 0.0, right, ld, ctx->stream);
                     if (le != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "block row solve launch");
                 }
             }
@@ -1134,9 +1168,8 @@ static int build_second_factor(knm_ctx *ctx, knm_precond *p, double lambda, cons
 {
     const int64_t M = p->M;
     *bad_pivot = 0;
-    DevBuf leaf, badbuf;
-    int st = leaf.alloc(ctx, sizeof(double) * kLeaf * kLeaf);
-    if (!st) st = badbuf.alloc(ctx, sizeof(unsigned long long));
+    DevBuf badbuf;
+    int st = badbuf.alloc(ctx, sizeof(unsigned long long));
     if (st) return st;
     {
         TraceRange range("knm triangular product T D T^T");
@@ -1145,7 +1178,7 @@ static int build_second_factor(knm_ctx *ctx, knm_precond *p, double lambda, cons
             return fail(ctx, KNM_HIP_ERROR, "triangular product launch");
     }
     int64_t pivot = 0;
-    st = chol_blocked(ctx, p->A, p->ld, M, true, leaf.as<double>(), badbuf.as<unsigned long long>(), &pivot);
+    st = chol_blocked(ctx, p->A, p->ld, M, true, p->Adinv, p->sb, badbuf.as<unsigned long long>(), &pivot);
     if (st) return st;
     if (pivot == 0) {
         const unsigned long long none = ~0ull;
@@ -1206,8 +1239,7 @@ static int precond_build_from(knm_ctx *ctx, int64_t M, const std::function<int(d
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&p->xw), sizeof(double) * (size_t)M * kSolveCols);
     if (e == hipSuccess && M >= kProductSolveMinM)
         e = hipMalloc(reinterpret_cast<void **>(&p->blk), sizeof(double) * (size_t)p->sb * p->sb);
-    DevBuf leaf;
-    if (e != hipSuccess || leaf.alloc(ctx, sizeof(double) * kLeaf * kLeaf)) {
+    if (e != hipSuccess) {
         (void)hipGetLastError();
         precond_free(p);
         return fail(ctx, KNM_ALLOC, "hipMalloc(preconditioner)", e);
@@ -1241,7 +1273,7 @@ static int precond_build_from(knm_ctx *ctx, int64_t M, const std::function<int(d
 
     int64_t host_info = 0;
     {
-        int st2 = chol_blocked(ctx, p->T, p->ld, M, false, leaf.as<double>(), badbuf.as<unsigned long long>(), &host_info);
+        int st2 = chol_blocked(ctx, p->T, p->ld, M, false, p->Tdinv, p->sb, badbuf.as<unsigned long long>(), &host_info);
         if (st2) {
             precond_free(p);
             return st2;
