@@ -23,7 +23,7 @@
 // with the rows above and with inverted diagonal blocks) and the merging of block inverses.
 //
 // A workgroup of 4 wavefronts owns a 128 x 128 tile of C, each wavefront a 64 x 64 piece as
-// 4 x 4 accumulators of v_mfma_f64_16x16x4_f64.  Operand tiles (16 deep) are staged through
+// 4 x 4 accumulators of v_mfma_f64_16x16x4_f64 (smaller tiles where there are few of them, see the launcher).  Operand tiles (16 deep) are staged through
 // LDS, double buffered, with the global loads issued a stage and a half ahead.  Two
 // workgroups share a CU (72 KB of LDS and 4 x ~225 registers each), so that one runs while the
 // other sits at its per-stage barrier: 256 x 128 tiles with one 8-wavefront workgroup per CU
@@ -40,6 +40,8 @@
 //
 // Workgroups are numbered so that the 64 that run together on an XCD (and share its L2) cover
 // a 1024 x 1024 patch of C and re-use each other's operand rows.
+#include <type_traits>
+
 #include "knm_internal.h"
 
 namespace knm {
@@ -48,24 +50,19 @@ namespace {
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
 
-#ifndef KNM_RANKK_TI
-#define KNM_RANKK_TI 128
-#endif
-constexpr int kTI = KNM_RANKK_TI; // tile rows of C
-constexpr int kTJ = 128;      // tile columns of C
-constexpr int kTK = 16;       // contraction depth of a stage
-constexpr int kWavesI = kTI / 64, kWavesJ = kTJ / 64; // wavefront grid of a workgroup
-constexpr int kThreads = 64 * kWavesI * kWavesJ;
-// LDS image of an operand tile: element (k, i) at k * stride + i, for the k-contiguous form at
-// k * stride + (i ^ k).  The strides are 16 mod 32 doubles, so the four 16-lane groups of an
+constexpr int kThreads = 256; // 2 x 2 wavefronts, each a quarter of the tile
+constexpr int kXcds = 8;
+// Tile of TI x TJ entries of C.  LDS image of an operand tile: element (k, i) at k * stride + i, for the k-contiguous form at
+// k * stride + (i ^ (k % 16)).  The strides are 16 mod 32 doubles, so the four 16-lane groups of an
 // operand read (four consecutive k) fall on alternating halves of the banks; the XOR spreads
 // the 16 k of one column, which the k-contiguous form writes at once, over 16 bank pairs.
-constexpr int kSA = kTI + 16;
-constexpr int kSB = kTJ + 16;
-constexpr int kStageDoubles = kTK * (kSA + kSB);
-constexpr int kPatchI = 1024 / kTI, kPatchJ = 1024 / kTJ; // tiles of a patch: 1024 x 1024 entries of C
-constexpr int kPatchWgs = kPatchI * kPatchJ;
-constexpr int kXcds = 8;
+template <int TI, int TJ> struct Tile {
+    // contraction depth of a stage: the small tiles have a quarter of the products per k, so they take twice the
+    // depth to cover the latency of the loads and the barrier
+    static constexpr int kTK = TI * TJ >= 128 * 128 ? 16 : 32;
+    static constexpr int kSA = TI + 16, kSB = TJ + 16;
+    static constexpr int kStageDoubles = kTK * (kSA + kSB);
+};
 
 struct RankKArgs {
     const double *A; // operand of the rows of C
@@ -81,9 +78,14 @@ struct RankKArgs {
     double alpha, beta, shift;
     int tri;           // operand is upper triangular (what is stored below its diagonal is ignored): tile column j0 starts at k = j0
     int trans_c;       // store entry (i, j) at C[j + i * ldc]
-    int patch_i;       // general product: tiles of a patch along i (kPatchWgs / patch_i along j)
+    int part;          // general product: store all entries (0), those with i <= j (1) or those with i >= j (2)
+    int patch_i, patch_j; // tiles of a patch (symmetric update: patch_j = patch_i)
     int64_t n_patch_i; // general product: patches along i
     int64_t n_patches; // patches in all (symmetric update: the upper-triangular ones)
+    // one level of the merging of block inverses (see launch_merge_inverses): blockIdx.y is the pair
+    int merge;         // 0: not such a launch, 1: first product, 2: second
+    int merge_h, merge_pairs, sb, lower;
+    int64_t M;
 };
 
 // Stage loader of one operand: a (kTK x R) tile, kPer elements per thread in kPer / VEC loads of
@@ -91,7 +93,7 @@ struct RankKArgs {
 // VEC = 2 needs every load 16-byte aligned (even leading dimension, 16-byte aligned operand).
 //   TN (FORM 0): thread -> k = VEC (tid % (16 / VEC)) .. + VEC (contiguous in memory), rows tid / (16 / VEC) + kPass r
 //   NT (FORM 1): thread -> rows VEC (tid % (R / VEC)) .. + VEC (contiguous in memory), k = tid / (R / VEC) + kStepK r
-template <int FORM, int R, int VEC> struct Fetch {
+template <int FORM, int R, int VEC, int kTK> struct Fetch {
     static constexpr int kPer = kTK * R / kThreads;
     static constexpr int kLoads = kPer / VEC;
     static constexpr int kPass = kThreads / (kTK / VEC);  // TN: row advance per load
@@ -200,7 +202,7 @@ template <int FORM, int R, int VEC> struct Fetch {
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) {
                     const int i = row_of(r, e), kk = k_of(r, e);
-                    lds[kk * stride + (FORM == 0 ? (i ^ kk) : i)] = v[r * VEC + e];
+                    lds[kk * stride + (FORM == 0 ? (i ^ (kk & 15)) : i)] = v[r * VEC + e];
                 }
             }
         }
@@ -209,17 +211,47 @@ template <int FORM, int R, int VEC> struct Fetch {
 
 // FA, FB: forms of the row and column operands; SYM: symmetric update (B = A, upper triangle of C
 // only, triangular patch enumeration); otherwise the general product C = alpha a b^T + beta C
-template <int FA, int FB, bool WEIGHTED, int VEC, bool SYM>
+template <int FA, int FB, bool WEIGHTED, int VEC, bool SYM, int TI = 128, int TJ = 128>
 __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
 {
+    constexpr int kTK = Tile<TI, TJ>::kTK, kSA = Tile<TI, TJ>::kSA, kSB = Tile<TI, TJ>::kSB;
+    constexpr int kStageDoubles = Tile<TI, TJ>::kStageDoubles;
+    constexpr int kMI = TI / 32, kMJ = TJ / 32; // 16 x 16 accumulators of a wavefront
     __shared__ double lds[2 * kStageDoubles];
+    if (!SYM && a.merge != 0) {
+        // pair (off, off + h) of block k of the inverses: A, B, C and the sizes from the arrays' bases
+        const int64_t k0 = (int64_t)(blockIdx.y / a.merge_pairs) * a.sb;
+        const int64_t nbk = (a.M - k0 < a.sb) ? a.M - k0 : a.sb;
+        const int64_t h = a.merge_h, off = 2 * h * (int64_t)(blockIdx.y % a.merge_pairs);
+        if (off + h >= nbk) return;
+        const int64_t h2 = (nbk - off - h < h) ? nbk - off - h : h; // order of the second block of the pair
+        double *const S = a.C + (k0 / a.sb) * (int64_t)a.sb * a.sb;
+        a.n = h;
+        a.nj = h2;
+        if (a.merge == 1) { // R12 W22, kept below the diagonal of the block
+            a.A += a.lower ? (k0 + off + h) + (k0 + off) * a.lda : (k0 + off) + (k0 + off + h) * a.lda;
+            a.B = S + (off + h) + (off + h) * a.sb;
+            a.C = S + (off + h) + off * a.sb;
+            a.K = h2;
+            a.extent = FA == 0 ? (h - 1) * a.lda + h2 : (h2 - 1) * a.lda + h;
+            a.extent_b = (h2 - 1) * a.sb + h2;
+        } else { // -W11 times it
+            a.A = S + off + off * a.sb;
+            a.B = S + (off + h) + off * a.sb;
+            a.C = S + off + (off + h) * a.sb;
+            a.K = h;
+            a.extent = (h - 1) * a.sb + h;
+            a.extent_b = (h - 1) * a.sb + h2;
+        }
+    }
     // workgroup -> patch -> tile: consecutive workgroup ids go to consecutive XCDs, so the
-    // workgroups of one patch are those with equal id % 8 and equal (id / 8) / kPatchWgs
+    // workgroups of one patch are those with equal id % 8 and equal (id / 8) / patch_wgs
     const int64_t g = blockIdx.x;
     const int64_t slot = g / kXcds;
-    const int64_t q = (slot / kPatchWgs) * kXcds + g % kXcds;
+    const int patch_wgs = a.patch_i * a.patch_j;
+    const int64_t q = (slot / patch_wgs) * kXcds + g % kXcds;
     if (q >= a.n_patches) return;
-    const int wq = (int)(slot % kPatchWgs);
+    const int wq = (int)(slot % patch_wgs);
     int64_t i0, j0;
     if (SYM) {
         // q = pj (pj + 1) / 2 + pi, pi <= pj
@@ -227,51 +259,53 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
         while (pj * (pj + 1) / 2 > q) --pj;
         while ((pj + 1) * (pj + 2) / 2 <= q) ++pj;
         const int64_t pi = q - pj * (pj + 1) / 2;
-        i0 = (pi * kPatchI + wq % kPatchI) * kTI;
-        j0 = (pj * kPatchJ + wq / kPatchI) * kTJ;
-        if (i0 >= a.n || j0 >= a.n || i0 > j0 + (kTJ - 1)) return; // outside C or strictly below its diagonal
+        i0 = (pi * a.patch_i + wq % a.patch_i) * TI;
+        j0 = (pj * a.patch_i + wq / a.patch_i) * TJ;
+        if (i0 >= a.n || j0 >= a.n || i0 > j0 + (TJ - 1)) return; // outside C or strictly below its diagonal
     } else {
         const int64_t pi = q % a.n_patch_i, pj = q / a.n_patch_i;
-        const int patch_j = kPatchWgs / a.patch_i;
-        i0 = (pi * a.patch_i + wq % a.patch_i) * kTI;
-        j0 = (pj * patch_j + wq / a.patch_i) * kTJ;
+        i0 = (pi * a.patch_i + wq % a.patch_i) * TI;
+        j0 = (pj * a.patch_j + wq / a.patch_i) * TJ;
         if (i0 >= a.n || j0 >= a.nj) return;
+        if ((a.part == 1 && i0 > j0 + (TJ - 1)) || (a.part == 2 && j0 > i0 + (TI - 1))) return; // nothing to store
     }
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int wi = (wave % kWavesI) * 64, wj = (wave / kWavesI) * 64;
-    const int64_t kbeg = (SYM && a.tri) ? j0 : 0; // a multiple of kTK
+    const int wi = (wave % 2) * (TI / 2), wj = (wave / 2) * (TJ / 2);
+    // (triangular factors of the merges: W22 ends at its column's diagonal, W11 starts at its row's)
+    if (!SYM && a.merge == 1 && a.K > j0 + TJ) a.K = j0 + TJ;
+    const int64_t kbeg = (SYM && a.tri) ? j0 : (!SYM && a.merge == 2) ? i0 : 0; // a multiple of kTK
     const int64_t span = (a.K - kbeg + kTK - 1) / kTK;
     const int stages = span > 0x7fffffff ? 0x7fffffff : (int)span; // launch_rank_k_upper bounds K
 
-    d4 acc[4][4];
+    d4 acc[kMI][kMJ];
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
+    for (int m = 0; m < kMI; ++m)
 #pragma unroll
-        for (int nn = 0; nn < 4; ++nn) acc[m][nn] = d4{0.0, 0.0, 0.0, 0.0};
+        for (int nn = 0; nn < kMJ; ++nn) acc[m][nn] = d4{0.0, 0.0, 0.0, 0.0};
 
     if (stages > 0) {
-        Fetch<FA, kTI, VEC> fa;
-        Fetch<FB, kTJ, VEC> fb;
+        Fetch<FA, TI, VEC, kTK> fa;
+        Fetch<FB, TJ, VEC, kTK> fb;
         fa.init(a.A, a.lda, a.extent, i0, kbeg);
         fb.init(a.B, a.ldb, a.extent_b, j0, kbeg);
         // operand registers of k-step ks of the stage in `buf`: lane l takes k = 4 ks + l / 16
         const int qk = lane >> 4, l15 = lane & 15;
-        auto read_ops = [&](const double *buf, int ks, double (&av)[4], double (&bv)[4]) {
+        auto read_ops = [&](const double *buf, int ks, double (&av)[kMI], double (&bv)[kMJ]) {
             const int krow = ks * 4 + qk;
-            const double *pa = buf + krow * kSA + wi + (FA == 0 ? (l15 ^ krow) : l15);
-            const double *pb = buf + kTK * kSA + krow * kSB + wj + (FB == 0 ? (l15 ^ krow) : l15);
+            const double *pa = buf + krow * kSA + wi + (FA == 0 ? (l15 ^ (krow & 15)) : l15);
+            const double *pb = buf + kTK * kSA + krow * kSB + wj + (FB == 0 ? (l15 ^ (krow & 15)) : l15);
 #pragma unroll
-            for (int m = 0; m < 4; ++m) av[m] = pa[m * 16];
+            for (int m = 0; m < kMI; ++m) av[m] = pa[m * 16];
 #pragma unroll
-            for (int nn = 0; nn < 4; ++nn) bv[nn] = pb[nn * 16];
+            for (int nn = 0; nn < kMJ; ++nn) bv[nn] = pb[nn * 16];
         };
-        auto products = [&](const double (&av)[4], const double (&bv)[4]) {
+        auto products = [&](const double (&av)[kMI], const double (&bv)[kMJ]) {
 #pragma unroll
-            for (int m = 0; m < 4; ++m)
+            for (int m = 0; m < kMI; ++m)
 #pragma unroll
-                for (int nn = 0; nn < 4; ++nn)
+                for (int nn = 0; nn < kMJ; ++nn)
                     acc[m][nn] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[m], bv[nn], acc[m][nn], 0, 0, 0);
         };
         // registers -> LDS for stage s (whose loads were issued earlier)
@@ -285,8 +319,8 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
             if (SYM && a.tri) {
                 // stages that still overlap the diagonal band of a tile's rows (the first few of a tile)
                 const int64_t kk0 = kbeg + (int64_t)s * kTK;
-                if (kk0 < i0 + kTI) fa.mask_lower((int)(kk0 - i0));
-                if (kk0 < j0 + kTJ) fb.mask_lower((int)(kk0 - j0));
+                if (kk0 < i0 + TI) fa.mask_lower((int)(kk0 - i0));
+                if (kk0 < j0 + TJ) fb.mask_lower((int)(kk0 - j0));
             }
             if (WEIGHTED) fb.scale();
             fa.store(buf, kSA);
@@ -304,12 +338,12 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
                 w_left -= kTK;
             }
         };
-        double a0[4], b0[4], a1[4], b1[4];
+        double av[2][kMI], bv[2][kMJ];
         fetch();
         commit(0, lds);
         if (stages > 1) fetch();
         __syncthreads();
-        read_ops(lds, 0, a0, b0);
+        read_ops(lds, 0, av[0], bv[0]);
         // Per stage: the operands of a k-step are read while the products of the one before
         // run; the next stage's tile goes to the other LDS buffer in mid-stage (its loads were
         // issued a stage earlier) and the loads of the stage after that follow; the one
@@ -320,27 +354,21 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
         // barriers, and left alone it sinks them below the barrier, which then waits for the
         // LDS stores with nothing to run; the scheduling fences keep each group where it is.
         auto stage_body = [&](int s, const double *cur, double *nxt) {
-            read_ops(cur, 1, a1, b1);
-            __builtin_amdgcn_sched_barrier(0);
-            products(a0, b0);
-            __builtin_amdgcn_sched_barrier(0);
-            read_ops(cur, 2, a0, b0);
-            __builtin_amdgcn_sched_barrier(0);
-            products(a1, b1);
-            __builtin_amdgcn_sched_barrier(0);
-            if (s + 1 < stages) {
-                commit(s + 1, nxt);
-                if (s + 2 < stages) fetch();
+            constexpr int kSteps = kTK / 4;
+#pragma unroll
+            for (int ks = 0; ks < kSteps; ++ks) {
+                const int now = ks & 1, next = now ^ 1;
+                if (ks + 2 == kSteps && s + 1 < stages) {
+                    commit(s + 1, nxt);
+                    if (s + 2 < stages) fetch();
+                }
+                if (ks + 1 == kSteps) __syncthreads();
+                if (ks + 1 < kSteps) read_ops(cur, ks + 1, av[next], bv[next]);
+                else if (s + 1 < stages) read_ops(nxt, 0, av[next], bv[next]);
+                __builtin_amdgcn_sched_barrier(0);
+                products(av[now], bv[now]);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            read_ops(cur, 3, a1, b1);
-            __builtin_amdgcn_sched_barrier(0);
-            products(a0, b0);
-            __builtin_amdgcn_sched_barrier(0);
-            __syncthreads();
-            if (s + 1 < stages) read_ops(nxt, 0, a0, b0);
-            __builtin_amdgcn_sched_barrier(0);
-            products(a1, b1);
-            __builtin_amdgcn_sched_barrier(0);
         };
         for (int s = 0; s < stages; s += 2) {
             stage_body(s, lds, lds + kStageDoubles);
@@ -350,9 +378,9 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
 
     // accumulator entry r of lane l is C[4 r + l / 16][l % 16] of its 16 x 16 block
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
+    for (int m = 0; m < kMI; ++m)
 #pragma unroll
-        for (int nn = 0; nn < 4; ++nn) {
+        for (int nn = 0; nn < kMJ; ++nn) {
             const int64_t j = j0 + wj + nn * 16 + (lane & 15);
             const int64_t ib = i0 + wi + m * 16 + (lane >> 4);
             if (j >= a.nj) continue;
@@ -360,6 +388,7 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
             for (int r = 0; r < 4; ++r) {
                 const int64_t i = ib + 4 * r;
                 if ((SYM && i > j) || i >= a.n) continue;
+                if (!SYM && ((a.part == 1 && i > j) || (a.part == 2 && i < j))) continue;
                 double *dst = a.trans_c ? a.C + j + i * a.ldc : a.C + i + j * a.ldc;
                 double v = a.alpha * acc[m][nn][r];
                 if (a.beta != 0.0) v += a.beta * *dst;
@@ -367,6 +396,35 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
                 *dst = v;
             }
         }
+}
+
+// A thread's byte offsets inside a stage must fit the 32-bit buffer offset.
+bool stage_offsets_fit(int form_nt, int64_t ld, int rows, int depth)
+{
+    const int64_t span = form_nt ? (int64_t)depth * ld + rows : (int64_t)rows * ld + depth;
+    return span * 8 < 0xffffffffLL;
+}
+
+// 64 x 64 tiles below this many 128 x 128 ones (two waves of the two workgroups a CU holds): the few wide tiles of a small
+// product leave compute units idle and each is a chain of four times the matrix instructions (33 us for a product over
+// k = 128 against 9 us).  From 256 to 2048 the fits take the same time; without small tiles M = 5000 takes 68 ms per
+// logistic fit instead of 56, M = 20000 371 ms per fit instead of 355.
+constexpr int64_t kSmallTilesBelow = 1024;
+
+// Patch of tiles that the workgroups of one XCD take together: 8 x 8, smaller where there would be fewer than four
+// per XCD (all XCDs busy counts for more than shared rows of the operands)
+void choose_patch(int64_t tiles_i, int64_t tiles_j, int *patch_i, int *patch_j)
+{
+    int pi = 8, pj = 8;
+    auto patches = [&]() { return ((tiles_i + pi - 1) / pi) * ((tiles_j + pj - 1) / pj); };
+    while (pi > 1 && pi >= 2 * tiles_i) pi /= 2;
+    while (pj > 1 && pj >= 2 * tiles_j) pj /= 2;
+    while (pi * pj > 1 && patches() < 4 * kXcds) {
+        if (pi >= pj) pi /= 2;
+        else pj /= 2;
+    }
+    *patch_i = pi;
+    *patch_j = pj;
 }
 
 } // namespace
@@ -390,36 +448,46 @@ hipError_t launch_rank_k_upper(int form_nt, int64_t n, int64_t K, double alpha, 
     a.tri = tri;
     a.trans_c = trans_c;
     a.extent = a.extent_b = K <= 0 ? 0 : (form_nt ? (K - 1) * lda + n : (n - 1) * lda + K);
-    const int64_t patch = (int64_t)kPatchI * kTI; // = kPatchJ * kTJ
-    const int64_t n_patch = (n + patch - 1) / patch;
-    a.patch_i = kPatchI;
+    a.merge = 0;
+    a.part = 0;
+    const int64_t big = (n + 127) / 128;
+    const int T = big * (big + 1) / 2 < kSmallTilesBelow ? 64 : 128;
+    const int64_t tiles = (n + T - 1) / T;
+    choose_patch((tiles + 1) / 2, tiles, &a.patch_i, &a.patch_j); // half of the square of tiles
+    if (a.patch_j < a.patch_i) a.patch_i = a.patch_j;
+    a.patch_j = a.patch_i;
+    const int64_t n_patch = (tiles + a.patch_i - 1) / a.patch_i;
     a.n_patch_i = n_patch;
     a.n_patches = n_patch * (n_patch + 1) / 2;
     const int64_t groups = (a.n_patches + kXcds - 1) / kXcds;
-    const int64_t wgs = groups * kXcds * kPatchWgs;
+    const int64_t wgs = groups * kXcds * a.patch_i * a.patch_j;
     if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
-    // a thread's byte offsets inside a stage must fit the 32-bit buffer offset
-    const int64_t span = form_nt ? (int64_t)kTK * lda + kTI : (int64_t)kTI * lda + kTK;
-    if (span * 8 >= 0xffffffffLL || K >= (int64_t)0x7fffffff * kTK) return hipErrorInvalidValue;
+    if (!stage_offsets_fit(form_nt, lda, T, 32) || K >= (int64_t)0x7fffffff * 16) return hipErrorInvalidValue;
     const dim3 grid((unsigned)wgs), block(kThreads);
-    // 16-byte loads when every one of them is aligned: tile origins are multiples of 128
+    // 16-byte loads when every one of them is aligned: tile origins are multiples of 64
     const bool vec2 = lda % 2 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
-    const int which = (form_nt ? 4 : 0) + (w ? 2 : 0) + (vec2 ? 1 : 0);
-    switch (which) {
-    case 0: hipLaunchKernelGGL((rank_k_upper_kernel<0, 0, false, 1, true>), grid, block, 0, stream, a); break;
-    case 1: hipLaunchKernelGGL((rank_k_upper_kernel<0, 0, false, 2, true>), grid, block, 0, stream, a); break;
-    case 2: hipLaunchKernelGGL((rank_k_upper_kernel<0, 0, true, 1, true>), grid, block, 0, stream, a); break;
-    case 3: hipLaunchKernelGGL((rank_k_upper_kernel<0, 0, true, 2, true>), grid, block, 0, stream, a); break;
-    case 4: hipLaunchKernelGGL((rank_k_upper_kernel<1, 1, false, 1, true>), grid, block, 0, stream, a); break;
-    case 5: hipLaunchKernelGGL((rank_k_upper_kernel<1, 1, false, 2, true>), grid, block, 0, stream, a); break;
-    case 6: hipLaunchKernelGGL((rank_k_upper_kernel<1, 1, true, 1, true>), grid, block, 0, stream, a); break;
-    default: hipLaunchKernelGGL((rank_k_upper_kernel<1, 1, true, 2, true>), grid, block, 0, stream, a); break;
-    }
+    auto launch = [&](auto form, auto weighted, auto vec) {
+        constexpr int F = decltype(form)::value, V = decltype(vec)::value;
+        constexpr bool WT = decltype(weighted)::value;
+        if (T == 64) hipLaunchKernelGGL((rank_k_upper_kernel<F, F, WT, V, true, 64, 64>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((rank_k_upper_kernel<F, F, WT, V, true>), grid, block, 0, stream, a);
+    };
+    auto with_vec = [&](auto form, auto weighted) {
+        if (vec2) launch(form, weighted, std::integral_constant<int, 2>{});
+        else launch(form, weighted, std::integral_constant<int, 1>{});
+    };
+    auto with_weights = [&](auto form) {
+        if (w) with_vec(form, std::true_type{});
+        else with_vec(form, std::false_type{});
+    };
+    if (form_nt) with_weights(std::integral_constant<int, 1>{});
+    else with_weights(std::integral_constant<int, 0>{});
     return hipGetLastError();
 }
 
 hipError_t launch_gemm_f64(int a_nt, int64_t ni, int64_t nj, int64_t K, double alpha, const double *A, int64_t lda,
-                           const double *B, int64_t ldb, double beta, double *C, int64_t ldc, hipStream_t stream, int b_nt)
+                           const double *B, int64_t ldb, double beta, double *C, int64_t ldc, hipStream_t stream, int b_nt,
+                           int part, bool in_place)
 {
     if (b_nt && !a_nt) return hipErrorInvalidValue; // not instantiated
     if (ni <= 0 || nj <= 0) return hipSuccess;
@@ -439,40 +507,90 @@ hipError_t launch_gemm_f64(int a_nt, int64_t ni, int64_t nj, int64_t K, double a
     a.shift = 0.0;
     a.tri = 0;
     a.trans_c = 0;
+    a.part = part;
+    a.merge = 0;
     a.extent = K <= 0 ? 0 : (a_nt ? (K - 1) * lda + ni : (ni - 1) * lda + K);
     a.extent_b = K <= 0 ? 0 : (b_nt ? (K - 1) * ldb + nj : (nj - 1) * ldb + K);
-    // patches of 64 tiles, as square as the shape of C allows
-    const int64_t tiles_i = (ni + kTI - 1) / kTI;
-    int patch_i = 1;
-    while (patch_i < 8 && patch_i < tiles_i) patch_i *= 2;
-    const int patch_j = kPatchWgs / patch_i;
-    a.patch_i = patch_i;
-    a.n_patch_i = (tiles_i + patch_i - 1) / patch_i;
-    const int64_t tiles_j = (nj + kTJ - 1) / kTJ;
-    a.n_patches = a.n_patch_i * ((tiles_j + patch_j - 1) / patch_j);
+    const int64_t big = ((ni + 127) / 128) * ((nj + 127) / 128);
+    int TI = 128, TJ = 128;
+    if (big < kSmallTilesBelow) {
+        // in place: a tile must hold all of the entries that are computed from the operand rows it overwrites
+        if (!in_place) TI = TJ = 64;
+        else if (a_nt) TI = 32;
+        else TJ = 32;
+    }
+    if (in_place && (a_nt ? nj > 128 : ni > 128)) return hipErrorInvalidValue;
+    const int64_t tiles_i = (ni + TI - 1) / TI, tiles_j = (nj + TJ - 1) / TJ;
+    choose_patch(tiles_i, tiles_j, &a.patch_i, &a.patch_j);
+    a.n_patch_i = (tiles_i + a.patch_i - 1) / a.patch_i;
+    a.n_patches = a.n_patch_i * ((tiles_j + a.patch_j - 1) / a.patch_j);
     const int64_t groups = (a.n_patches + kXcds - 1) / kXcds;
-    const int64_t wgs = groups * kXcds * kPatchWgs;
+    const int64_t wgs = groups * kXcds * a.patch_i * a.patch_j;
     if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
-    const int64_t span_a = a_nt ? (int64_t)kTK * lda + kTI : (int64_t)kTI * lda + kTK;
-    const int64_t span_b = b_nt ? (int64_t)kTK * ldb + kTJ : (int64_t)kTJ * ldb + kTK;
-    if (span_a * 8 >= 0xffffffffLL || span_b * 8 >= 0xffffffffLL || K >= (int64_t)0x7fffffff * kTK)
+    if (!stage_offsets_fit(a_nt, lda, TI, 32) || !stage_offsets_fit(b_nt, ldb, TJ, 32) || K >= (int64_t)0x7fffffff * 16)
         return hipErrorInvalidValue;
     const dim3 grid((unsigned)wgs), block(kThreads);
     const bool vec2 = lda % 2 == 0 && ldb % 2 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 &&
                       reinterpret_cast<uintptr_t>(B) % 16 == 0;
-    if (b_nt && vec2)
-        hipLaunchKernelGGL((rank_k_upper_kernel<1, 1, false, 2, false>), grid, block, 0, stream, a);
-    else if (b_nt)
-        hipLaunchKernelGGL((rank_k_upper_kernel<1, 1, false, 1, false>), grid, block, 0, stream, a);
-    else if (a_nt && vec2)
-        hipLaunchKernelGGL((rank_k_upper_kernel<1, 0, false, 2, false>), grid, block, 0, stream, a);
-    else if (a_nt)
-        hipLaunchKernelGGL((rank_k_upper_kernel<1, 0, false, 1, false>), grid, block, 0, stream, a);
-    else if (vec2)
-        hipLaunchKernelGGL((rank_k_upper_kernel<0, 0, false, 2, false>), grid, block, 0, stream, a);
-    else
-        hipLaunchKernelGGL((rank_k_upper_kernel<0, 0, false, 1, false>), grid, block, 0, stream, a);
+    auto launch = [&](auto fa, auto fb, auto vec) {
+        constexpr int FA = decltype(fa)::value, FB = decltype(fb)::value, V = decltype(vec)::value;
+        if (TI == 128 && TJ == 128) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false>), grid, block, 0, stream, a);
+        else if (TI == 64) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 64, 64>), grid, block, 0, stream, a);
+        else if constexpr (FA == 1 && FB == 0) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 32, 128>), grid, block, 0, stream, a);
+        else if constexpr (FA == 0 && FB == 0) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 128, 32>), grid, block, 0, stream, a);
+    };
+    auto with_forms = [&](auto vec) {
+        constexpr std::integral_constant<int, 0> tn{};
+        constexpr std::integral_constant<int, 1> nt{};
+        if (b_nt) launch(nt, nt, vec);
+        else if (a_nt) launch(nt, tn, vec);
+        else launch(tn, tn, vec);
+    };
+    if (b_nt && in_place) return hipErrorInvalidValue; // not instantiated
+    if (vec2) with_forms(std::integral_constant<int, 2>{});
+    else with_forms(std::integral_constant<int, 1>{});
     return hipGetLastError();
+}
+
+hipError_t launch_merge_inverses(const double *R, int64_t ld, int lower, int64_t M, double *S, int sb, hipStream_t stream)
+{
+    RankKArgs a = {};
+    a.ldc = sb;
+    a.sb = sb;
+    a.M = M;
+    a.lower = lower;
+    a.C = S;
+    a.beta = 0.0;
+    const unsigned blocks = (unsigned)((M + sb - 1) / sb);
+    if (!stage_offsets_fit(lower ? 0 : 1, ld, 64, 32)) return hipErrorInvalidValue;
+    const bool vec2 = ld % 2 == 0 && reinterpret_cast<uintptr_t>(R) % 16 == 0; // (S is allocated, sb a multiple of 128)
+    for (int h = 128; h < sb; h *= 2) {
+        a.merge_h = h;
+        a.merge_pairs = (sb + 2 * h - 1) / (2 * h);
+        const int tiles = h / 64;
+        a.patch_i = a.patch_j = 1;
+        a.n_patch_i = tiles;
+        a.n_patches = (int64_t)tiles * tiles;
+        const dim3 grid((unsigned)((a.n_patches + kXcds - 1) / kXcds * kXcds), blocks * (unsigned)a.merge_pairs);
+        a.merge = 1;
+        a.alpha = 1.0;
+        a.trans_c = 1;
+        a.A = R;
+        a.lda = ld;
+        a.ldb = sb;
+        if (lower && vec2) hipLaunchKernelGGL((rank_k_upper_kernel<0, 0, false, 2, false, 64, 64>), grid, dim3(kThreads), 0, stream, a);
+        else if (lower) hipLaunchKernelGGL((rank_k_upper_kernel<0, 0, false, 1, false, 64, 64>), grid, dim3(kThreads), 0, stream, a);
+        else if (vec2) hipLaunchKernelGGL((rank_k_upper_kernel<1, 0, false, 2, false, 64, 64>), grid, dim3(kThreads), 0, stream, a);
+        else hipLaunchKernelGGL((rank_k_upper_kernel<1, 0, false, 1, false, 64, 64>), grid, dim3(kThreads), 0, stream, a);
+        a.merge = 2;
+        a.alpha = -1.0;
+        a.trans_c = 0;
+        a.lda = sb;
+        hipLaunchKernelGGL((rank_k_upper_kernel<1, 1, false, 2, false, 64, 64>), grid, dim3(kThreads), 0, stream, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 } // namespace knm

@@ -136,11 +136,18 @@ hipError_t launch_rank_k_upper(int form_nt, int64_t n, int64_t K, double alpha, 
 
 // general fp64 product on the same kernel: C (ni x nj) = alpha sum_{k < K} a(i, k) b(j, k) + beta C with
 // a(i, k) = A[k + i lda] (a_nt = 0) or A[i + k lda] (a_nt = 1) and b(j, k) = B[k + j ldb] (b_nt = 0) or
-// B[j + k ldb] (b_nt = 1, only with a_nt = 1); C must not overlap A or B, except that a tile of C may be
-// exactly the operand rows it reads
+// B[j + k ldb] (b_nt = 1, only with a_nt = 1).  part: 0 stores all of C, 1 its entries with i <= j, 2 those with
+// i >= j.  C must not overlap A or B, except (in_place) that C may be B with a_nt = 0 and ni = K <= 128, or A with
+// a_nt = 1, b_nt = 0 and nj = K <= 128
 hipError_t launch_gemm_f64(int a_nt, int64_t ni, int64_t nj, int64_t K, double alpha, const double *A, int64_t lda,
                            const double *B, int64_t ldb, double beta, double *C, int64_t ldc, hipStream_t stream,
-                           int b_nt = 0);
+                           int b_nt = 0, int part = 0, bool in_place = false);
+
+// Merging of block inverses: S holds sb x sb column-major blocks (sb a multiple of 128) with the inverses of the
+// 128 x 128 diagonal blocks of an upper factor R (entry (i, j), i <= j, at R[i + j ld], or R[j + i ld] with lower);
+// on return the upper triangle of every block is the inverse of R's sb x sb diagonal block (the last one ends at
+// M), and what is below its diagonal is overwritten
+hipError_t launch_merge_inverses(const double *R, int64_t ld, int lower, int64_t M, double *S, int sb, hipStream_t stream);
 
 // Sparse inputs (knm_sparse.hip): the two sweeps of one (X, C, sigma) for CSR X and C, prepared once
 // (structure check, norms, centre lists per feature, accumulators) and then applied any number

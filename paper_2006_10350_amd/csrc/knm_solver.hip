@@ -815,35 +815,16 @@ int tri_solve(knm_ctx *ctx, const knm_precond *p, const double *R, const double 
 
 // S <- mirrored inverses of the sb x sb diagonal blocks of the upper-triangular R (p->T or p->A).  S holds the
 // inverses of the 128 x 128 diagonal blocks, which the leaf kernel left there, and zeros; neighbouring inverses are
-// merged level by level,  inv([R11 R12; 0 R22]) = [W11, -W11 R12 W22; 0, W22],  with two
-// block products per pair, until the blocks are sb wide; last the upper triangle of every
-// block is copied onto its lower.  `tmp` holds (sb / 2)^2 doubles.
-int invert_diag_blocks(knm_ctx *ctx, const knm_precond *p, const double *R, double *S, double *tmp)
+// merged level by level,  inv([R11 R12; 0 R22]) = [W11, -W11 R12 W22; 0, W22],  with two products for all pairs of
+// a level, until the blocks are sb wide; last the upper triangle of every block is copied onto its lower.
+int invert_diag_blocks(knm_ctx *ctx, const knm_precond *p, const double *R, double *S)
 {
     const int64_t M = p->M, ld = p->ld;
     const int lower = (R == p->A) ? 1 : 0;
     const int sb = p->sb;
     const int64_t nblk = (M + sb - 1) / sb;
-    const int64_t block = (int64_t)sb * sb;
-    for (int64_t h = kLeaf; h < sb; h *= 2) {
-        for (int64_t k = 0; k < nblk; ++k) {
-            const int64_t k0 = k * sb;
-            const int64_t nbk = (M - k0 < sb) ? M - k0 : sb;
-            double *Sk = S + k * block;
-            for (int64_t off = 0; off + h < nbk; off += 2 * h) {
-                const int64_t h2 = (nbk - off - h < h) ? nbk - off - h : h; // order of the second block of the pair
-                // R12 (h x h2): entry (i, k) at R12[i + k ld] in upper storage, R12[k + i ld] in lower
-                const double *R12 = lower ? R + (k0 + off + h) + (size_t)(k0 + off) * ld
-                                          : R + (k0 + off) + (size_t)(k0 + off + h) * ld;
-                const double *W11 = Sk + off + off * sb;
-                const double *W22 = Sk + (off + h) + (off + h) * sb;
-                double *W12 = Sk + off + (off + h) * sb;
-                if (launch_gemm_f64(lower ? 0 : 1, h, h2, h2, 1.0, R12, ld, W22, sb, 0.0, tmp, h, ctx->stream) != hipSuccess ||
-                    launch_gemm_f64(1, h, h2, h, -1.0, W11, sb, tmp, h, 0.0, W12, sb, ctx->stream) != hipSuccess)
-                    return fail(ctx, KNM_HIP_ERROR, "inverse merge launch");
-            }
-        }
-    }
+    if (launch_merge_inverses(R, ld, lower, M, S, sb, ctx->stream) != hipSuccess)
+        return fail(ctx, KNM_HIP_ERROR, "inverse merge launch");
     hipLaunchKernelGGL(mirror_upper_kernel, dim3((unsigned)((sb + 255) / 256), (unsigned)sb, (unsigned)nblk), dim3(256),
                        0, ctx->stream, S, sb);
     if (hipGetLastError() != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "diagonal block inversion launch");
@@ -1048,9 +1029,8 @@ static int aux_stream(knm_ctx *ctx, hipStream_t *out)
 }
 
 // `lower`: the factor and the matrix it replaces are in lower storage (entry (r, c), r <= c, at
-// A[c + r ld]); every product below then has its two index roles exchanged, and the pieces of a
-// block row that straddle the diagonal are split into a symmetric update (which writes one triangle
-// only) and a rectangle, because the other triangle belongs to the other factor.
+// A[c + r ld]); every product below then has its two index roles exchanged.  A block row that straddles the
+// diagonal is stored on its own side only, because the other triangle belongs to the other factor.
 static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool lower, double *S, int sb,
                         unsigned long long *bad, int64_t *first_bad)
 {
@@ -1073,17 +1053,12 @@ static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool low
     auto at = [&](int64_t r, int64_t c) { return lower ? A + c + (size_t)r * ld : A + r + (size_t)c * ld; };
     // rows [row, row + nr) of the columns from `col` on lose the products with rows [top, top + K)
     // of the same columns: R(row + i, col + j) -= sum_k R(top + k, row + i) R(top + k, col + j).
-    // Here col == row: the nr x nr block on the diagonal and the rectangle to its right.
+    // Here col == row: the triangle of the nr x nr block on the diagonal and the rectangle to its right.
     auto update_rows = [&](int64_t top, int64_t K, int64_t row, int64_t nr) -> bool {
         const int64_t ncols = M - row;
-        if (!lower) // upper storage: one product; what it writes below the diagonal block's diagonal is unused space
-            return launch_gemm_f64(0, nr, ncols, K, -1.0, at(top, row), ld, at(top, row), ld, 1.0, at(row, row), ld,
-                                   ctx->stream) == hipSuccess;
-        const double *P = at(top, row); // element (top + k, row + x) at P[x + k ld]
-        if (launch_rank_k_upper(1, nr, K, -1.0, P, ld, nullptr, 0, 1.0, 0.0, at(row, row), ld, ctx->stream, 1) != hipSuccess)
-            return false;
-        return ncols == nr || launch_gemm_f64(1, ncols - nr, nr, K, -1.0, P + nr, ld, P, ld, 1.0, at(row, row + nr), ld,
-                                              ctx->stream, 1) == hipSuccess;
+        const double *P = at(top, row); // element (top + k, row + x) at P[k + x ld], or P[x + k ld] in lower storage
+        return (lower ? launch_gemm_f64(1, ncols, nr, K, -1.0, P, ld, P, ld, 1.0, at(row, row), ld, ctx->stream, 1, 2)
+                      : launch_gemm_f64(0, nr, ncols, K, -1.0, P, ld, P, ld, 1.0, at(row, row), ld, ctx->stream, 0, 1)) == hipSuccess;
     };
     for (int64_t k = 0; k < nb; ++k) {
         const int64_t r0 = k * b;
@@ -1106,8 +1081,8 @@ static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool low
                     // the rest of the rows times the inverse: R(row + i, c) <- sum_k W(k, i) R(row + k, c)
                     double *right = at(row, row + nbk);
                     const hipError_t le =
-                        lower ? launch_gemm_f64(1, ncols - nbk, nbk, nbk, 1.0, right, ld, W, sb, 0.0, right, ld, ctx->stream)
-                              : launch_gemm_f64(0, nbk, ncols - nbk, nbk, 1.0, W, sb, right, ld, 0.0, right, ld, ctx->stream);
+                        lower ? launch_gemm_f64(1, ncols - nbk, nbk, nbk, 1.0, right, ld, W, sb, 0.0, right, ld, ctx->stream, 0, 0, true)
+                              : launch_gemm_f64(0, nbk, ncols - nbk, nbk, 1.0, W, sb, right, ld, 0.0, right, ld, ctx->stream, 0, 0, true);
                     if (le != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "block row solve launch");
                 }
             }
@@ -1120,20 +1095,13 @@ static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool low
         // stream meanwhile and fills the chip, which those short dependent launches cannot.
         const int64_t w2 = (rest < b) ? rest : b;
         const int64_t c0 = r0 + w;                 // first trailing row and column
-        const double *Akr = at(r0, c0);            // block row to the right of the diagonal block
-        const double *Akr2 = at(r0, c0 + w2);
+        const double *Akr2 = at(r0, c0 + w2);      // block row to the right of the columns of the next one
         const int form = lower ? 1 : 0, tc = lower ? 1 : 0;
         if (hipEventRecord(ev_rows[k], ctx->stream) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipEventRecord");
         if (k > 0 && have_rest[k - 1] && hipStreamWaitEvent(ctx->stream, ev_rest[k - 1], 0) != hipSuccess)
             return fail(ctx, KNM_HIP_ERROR, "hipStreamWaitEvent");
-        if (launch_rank_k_upper(form, w2, w, -1.0, Akr, ld, nullptr, 0, 1.0, 0.0, at(c0, c0), ld, ctx->stream, tc) != hipSuccess)
-            return fail(ctx, KNM_HIP_ERROR, "trailing update launch");
+        if (!update_rows(r0, w, c0, w2)) return fail(ctx, KNM_HIP_ERROR, "trailing update launch");
         if (rest > w2) {
-            // R(c0 + i, c0 + w2 + j) -= sum_k R(r0 + k, c0 + i) R(r0 + k, c0 + w2 + j)
-            const hipError_t le =
-                lower ? launch_gemm_f64(1, rest - w2, w2, w, -1.0, Akr2, ld, Akr, ld, 1.0, at(c0, c0 + w2), ld, ctx->stream, 1)
-                      : launch_gemm_f64(0, w2, rest - w2, w, -1.0, Akr, ld, Akr2, ld, 1.0, at(c0, c0 + w2), ld, ctx->stream);
-            if (le != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "trailing update launch");
             if (hipStreamWaitEvent(aux, ev_rows[k], 0) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipStreamWaitEvent");
             if (launch_rank_k_upper(form, rest - w2, w, -1.0, Akr2, ld, nullptr, 0, 1.0, 0.0, at(c0 + w2, c0 + w2), ld, aux,
                                     tc) != hipSuccess)
@@ -1197,9 +1165,7 @@ static int build_second_factor(knm_ctx *ctx, knm_precond *p, double lambda, cons
         *bad_pivot = pivot;
         return fail(ctx, KNM_NOT_PD, "T D T^T / M + lambda I is not positive definite");
     }
-    DevBuf merge;
-    st = merge.alloc(ctx, sizeof(double) * (size_t)(p->sb / 2) * (size_t)(p->sb / 2));
-    if (!st) st = invert_diag_blocks(ctx, p, p->A, p->Adinv, merge.as<double>());
+    st = invert_diag_blocks(ctx, p, p->A, p->Adinv);
     if (st) return st;
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "second factor"); // scratch is freed on return
     if (hipGetLastError() != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "preconditioner kernel launch");
@@ -1286,9 +1252,7 @@ static int precond_build_from(knm_ctx *ctx, int64_t M, const std::function<int(d
         return bail(KNM_NOT_PD, "K_MM + jitter I is not positive definite");
     }
     if (hipGetLastError() != hipSuccess) return bail(KNM_HIP_ERROR, "preconditioner kernel launch");
-    DevBuf merge;
-    st = merge.alloc(ctx, sizeof(double) * (size_t)(p->sb / 2) * (size_t)(p->sb / 2));
-    if (!st) st = invert_diag_blocks(ctx, p, p->T, p->Tdinv, merge.as<double>());
+    st = invert_diag_blocks(ctx, p, p->T, p->Tdinv);
     if (!st && hipStreamSynchronize(ctx->stream) != hipSuccess) st = fail(ctx, KNM_HIP_ERROR, "first factor");
     if (st) {
         precond_free(p);

@@ -1,0 +1,79 @@
+"""Edges of the kernels under the preconditioner, the solves and CG: tile and group remainders, both sides of every
+dispatch rule.  fp64 on both sides unless said otherwise."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def knm():
+    import paper_2006_10350_amd as k
+
+    k.load_library()
+    return k
+
+
+def _rand(n, d, seed):
+    return torch.randn(n, d, generator=torch.Generator().manual_seed(seed)).to(torch.float32)
+
+
+# one leaf with 1..8 tile rows, whole and ragged; two and three leaves
+@pytest.mark.parametrize("M", [1, 15, 16, 17, 48, 100, 127, 128, 129, 144, 255, 257, 384])
+def test_factors_at_leaf_edges(knm, M):
+    d, sigma, lam, jitter = 6, 1.0, 1e-4, 1e-6
+    C = _rand(M, d, 300 + M)
+    pre = knm.precond_build(C.cuda(), sigma, lam, jitter)
+    T, A = pre.factors()
+    K = oracle.kernel_matrix(C.numpy(), C.numpy(), sigma) + jitter * np.eye(M)
+    assert np.abs(np.tril(T, -1)).max() == 0.0
+    assert np.abs(T.T @ T - K).max() < 1e-13
+    assert np.abs(A.T @ A - (T @ T.T / M + lam * np.eye(M))).max() < 1e-13
+    b = torch.randn(M, 2, generator=torch.Generator().manual_seed(M), dtype=torch.float64)
+    got = pre.solve(b.cuda()).cpu().numpy()
+    assert np.abs(A @ (T @ got) - b.numpy()).max() < 1e-9 * max(1.0, np.abs(got).max())
+    pre.close()
+
+
+def test_failing_pivot_inside_a_leaf(knm):
+    C = _rand(300, 4, 5)
+    C[171] = float("nan")  # row 171: second leaf, third tile row
+    with pytest.raises(knm.KnmError) as e:
+        knm.precond_build(C.cuda(), 1.0, 1e-6, 1e-6)
+    assert e.value.status == -5 and "172" in str(e.value)
+
+
+# wide solve blocks: three levels of merged inverses, the last pair of a level and the last block ragged
+@pytest.mark.parametrize("M", [8500])
+def test_solves_with_merged_block_inverses(knm, M):
+    C = _rand(M, 12, 9)
+    pre = knm.precond_build(C.cuda(), 2.0, 1e-4, 1e-5)
+    T, A = (torch.from_numpy(x).cuda() for x in pre.factors())
+    b = torch.randn(M, 3, generator=torch.Generator().manual_seed(1), dtype=torch.float64).cuda()
+    got = pre.solve(b)
+    ref = torch.linalg.solve_triangular(T, torch.linalg.solve_triangular(A, b, upper=True), upper=True)
+    assert float((got - ref).norm() / ref.norm()) < 1e-9
+    got = pre.solve(b, transpose=True)
+    ref = torch.linalg.solve_triangular(A.T, torch.linalg.solve_triangular(T.T, b, upper=False), upper=False)
+    assert float((got - ref).norm() / ref.norm()) < 1e-9
+    pre.close()
+
+
+# more than 1024 tiles of 128 x 128: the wide tiles
+@pytest.mark.parametrize("a_nt", [False, True])
+def test_products_with_wide_tiles(knm, a_nt):
+    g = torch.Generator(device="cuda").manual_seed(3)
+    n, k = 5900, 40
+    a = torch.randn(n, k, generator=g, device="cuda", dtype=torch.float64)
+    A = (a.T if a_nt else a).contiguous()  # column-major n x k or k x n
+    C = torch.zeros(n, n, dtype=torch.float64, device="cuda")
+    knm.rank_k_update(A, C, form_nt=a_nt)
+    ref = torch.triu(a @ a.T)
+    assert float((C.T - ref).abs().max()) < 1e-12 * k
+    ni, nj = 4230, 4200
+    C = torch.zeros(nj, ni, dtype=torch.float64, device="cuda")
+    knm.block_product((a[:ni].T if a_nt else a[:ni]).contiguous(), a[:nj].contiguous(), C, a_nt=a_nt)
+    assert float((C.T - a[:ni] @ a[:nj].T).abs().max()) < 1e-12 * k
