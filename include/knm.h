@@ -130,7 +130,7 @@ int knm_t_y(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx,
  * with T^T T = K_MM and A^T A = T T^T / M + lambda I.  The two factors share one array, as in the
  * paper's in-place preconditioner (Sec. 3.1, the paragraph and figure on its memory): T in the
  * upper triangle, the transpose of A two rows below the diagonal (so that neither diagonal is
- * lost); *out owns (M + 3) M doubles of device memory at most, plus M^2 / 8 or so for the
+ * lost); *out owns (M + 3) M doubles of device memory at most, plus 2 M min(M, 2048) or so for the
  * inverted diagonal blocks of the blocked solves, until precond_free.  On KNM_NOT_PD, *bad_pivot_or_null (HOST pointer)
  * receives the 1-based failing pivot, negative if it was the second factorisation. */
 int precond_build(knm_ctx *ctx, const float *C, int64_t M, int d, int64_t ldc, float sigma,

@@ -178,11 +178,13 @@ __global__ void gather_block_kernel(const double *__restrict__ F, int64_t ld, in
 //
 // Each inverted diagonal block is stored mirrored: S[i, j] = S[j, i] = inv(R_kk)[min, max].  Both
 // the plain and the transposed product then read contiguous pieces of the columns of S.
+// Blocks of at most 2048, all about as wide: up to M = 2048 a solve is one product with the whole inverse.
+// Forming the inverses costs M sb^2 flop, next to the M^3 of the factorisations; narrower blocks (M / 16) made a
+// solve a chain of 32 launches at any M.
 inline int solve_block_width(int64_t M)
 {
-    int64_t b = ((M + 15) / 16 + 255) / 256 * 256;
-    if (b > 2048) b = 2048;
-    return (int)b;
+    const int64_t blocks = (M + 2047) / 2048;
+    return (int)(((M + blocks - 1) / blocks + 127) / 128 * 128);
 }
 
 // copy the upper triangle of every block onto its strict lower triangle
