@@ -31,7 +31,8 @@ struct knm_precond {
     double *A = nullptr;   // = buf + 2: lower storage (what is in memory is A^T, a lower triangle)
     // inverses of the sb x sb diagonal blocks of T and A (column-major blocks, each mirrored onto
     // its lower triangle, the last one padded with the identity), used by the blocked
-    // triangular solves; xw (M x kSolveCols entries) stages the solved blocks
+    // triangular solves; xw (2 M kSolveCols entries) holds the solution, and for several columns the right-hand side, of a
+    // solve under way
     int sb = 0;
     double *Tdinv = nullptr;
     double *Adinv = nullptr;
@@ -208,20 +209,13 @@ __device__ __forceinline__ double wave_sum(double s)
     return s;
 }
 
-constexpr int kSolveCols = 8; // right-hand sides a blocked triangular solve takes through the factor together
-
-// The three kernels of the blocked triangular solves work on TC right-hand sides at once (columns of
-// a column-major M x t array, ldb apart; the staged solved blocks ldx apart), tc <= TC of them live: a
-// column past tc reads the last live one and is dropped.  Every entry of the factor and of the block
-// inverses is then read once per TC columns instead of once per column.
+// One right-hand side: the three kernels below, bound by the bandwidth of the factor.
 
 // x = inv(R_kk) b (lower = 1: x[c] = sum_{i >= c} S[i, c] b[i]) or x = inv(R_kk)^T b (lower = 0:
 // x[c] = sum_{i <= c} S[i, c] b[i]) for one mirrored block S of live order nbk; one wavefront
 // per entry of x, lanes along the column of S.
-template <int TC>
 __global__ __launch_bounds__(256) void diag_apply_kernel(const double *__restrict__ S, int sb, int nbk, int lower,
-                                                        const double *__restrict__ b, int64_t ldb, int tc,
-                                                        double *__restrict__ x, int64_t ldx)
+                                                        const double *__restrict__ b, double *__restrict__ x)
 {
     const int lane = threadIdx.x & 63;
     const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -229,31 +223,15 @@ __global__ __launch_bounds__(256) void diag_apply_kernel(const double *__restric
     const double *col = S + (int64_t)c * sb;
     const int lo = lower ? c : 0;
     const int hi = lower ? nbk : c + 1;
-    const double *bq[TC];
-#pragma unroll
-    for (int q = 0; q < TC; ++q) bq[q] = b + (int64_t)(q < tc ? q : tc - 1) * ldb;
-    double s0[TC], s1[TC];
-#pragma unroll
-    for (int q = 0; q < TC; ++q) s0[q] = s1[q] = 0.0;
+    double s0 = 0.0, s1 = 0.0;
     int i = lo + lane;
     for (; i + 64 < hi; i += 128) {
-        const double a0 = col[i], a1 = col[i + 64];
-#pragma unroll
-        for (int q = 0; q < TC; ++q) {
-            s0[q] += a0 * bq[q][i];
-            s1[q] += a1 * bq[q][i + 64];
-        }
+        s0 += col[i] * b[i];
+        s1 += col[i + 64] * b[i + 64];
     }
-    if (i < hi) {
-        const double a0 = col[i];
-#pragma unroll
-        for (int q = 0; q < TC; ++q) s0[q] += a0 * bq[q][i];
-    }
-#pragma unroll
-    for (int q = 0; q < TC; ++q) {
-        const double s = wave_sum(s0[q] + s1[q]);
-        if (lane == 0 && q < tc) x[(int64_t)q * ldx + c] = s;
-    }
+    if (i < hi) s0 += col[i] * b[i];
+    const double s = wave_sum(s0 + s1);
+    if (lane == 0) x[c] = s;
 }
 
 constexpr int kPanelWaves = 8;  // wavefronts of a panel_update_n workgroup, sharing the columns
@@ -264,59 +242,42 @@ constexpr int kPanelCols = 4;   // columns of one panel_update_t wavefront
 // rows above the block of an upper-storage factor in its plain solve, the rows below the block of a
 // lower-storage factor in its transposed solve.  Workgroups past the row range copy x into
 // b[k0 : k0 + nbk].
-template <int TC>
 __global__ __launch_bounds__(kPanelWaves * 64) void panel_update_n_kernel(const double *__restrict__ R, int64_t M,
                                                                          int64_t k0, int nbk, int64_t r_lo,
                                                                          int64_t r_hi, const double *__restrict__ x,
-                                                                         int64_t ldx, double *__restrict__ b, int64_t ldb,
-                                                                         int tc)
+                                                                         double *__restrict__ b)
 {
-    __shared__ double part[kPanelWaves][TC][kPanelRows];
+    __shared__ double part[kPanelWaves][kPanelRows];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t row_groups = (r_hi - r_lo + kPanelRows - 1) / kPanelRows;
     if ((int64_t)blockIdx.x >= row_groups) {
         const int64_t i = ((int64_t)blockIdx.x - row_groups) * blockDim.x + threadIdx.x;
-        if (i < nbk)
-            for (int q = 0; q < tc; ++q) b[(int64_t)q * ldb + k0 + i] = x[(int64_t)q * ldx + i];
+        if (i < nbk) b[k0 + i] = x[i];
         return;
     }
     const int64_t r = r_lo + (int64_t)blockIdx.x * kPanelRows + lane;
     const bool live = r < r_hi;
     const double *p = R + (live ? r : r_lo) + k0 * M;
-    const double *xq[TC];
-#pragma unroll
-    for (int q = 0; q < TC; ++q) xq[q] = x + (int64_t)(q < tc ? q : tc - 1) * ldx;
-    double s0[TC], s1[TC];
-#pragma unroll
-    for (int q = 0; q < TC; ++q) s0[q] = s1[q] = 0.0;
+    double s0 = 0.0, s1 = 0.0;
     int j = w;
     for (; j + 7 * kPanelWaves < nbk; j += 8 * kPanelWaves) {
         double a[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) a[u] = p[(int64_t)(j + u * kPanelWaves) * M];
 #pragma unroll
-        for (int q = 0; q < TC; ++q) {
-#pragma unroll
-            for (int u = 0; u < 8; u += 2) {
-                s0[q] += a[u] * xq[q][j + u * kPanelWaves];
-                s1[q] += a[u + 1] * xq[q][j + (u + 1) * kPanelWaves];
-            }
+        for (int u = 0; u < 8; u += 2) {
+            s0 += a[u] * x[j + u * kPanelWaves];
+            s1 += a[u + 1] * x[j + (u + 1) * kPanelWaves];
         }
     }
-    for (; j < nbk; j += kPanelWaves) {
-        const double a0 = p[(int64_t)j * M];
-#pragma unroll
-        for (int q = 0; q < TC; ++q) s0[q] += a0 * xq[q][j];
-    }
-#pragma unroll
-    for (int q = 0; q < TC; ++q) part[w][q][lane] = s0[q] + s1[q];
+    for (; j < nbk; j += kPanelWaves) s0 += p[(int64_t)j * M] * x[j];
+    part[w][lane] = s0 + s1;
     __syncthreads();
-    // wavefront q adds up right-hand side q (TC <= kPanelWaves)
-    if (w < TC && w < tc && live) {
+    if (w == 0 && live) {
         double s = 0.0;
-        for (int u = 0; u < kPanelWaves; ++u) s += part[u][w][lane];
-        b[(int64_t)w * ldb + r] -= s;
+        for (int u = 0; u < kPanelWaves; ++u) s += part[u][lane];
+        b[r] -= s;
     }
 }
 
@@ -324,65 +285,178 @@ __global__ __launch_bounds__(kPanelWaves * 64) void panel_update_n_kernel(const 
 // columns right of the block of an upper-storage factor in its transposed solve, the columns left of
 // the block of a lower-storage factor in its plain solve.  One wavefront per kPanelCols columns, lanes
 // along the rows.  Workgroups past the column range copy x into b[k0 : k0 + nbk].
-template <int TC>
 __global__ __launch_bounds__(256) void panel_update_t_kernel(const double *__restrict__ R, int64_t M, int64_t k0,
                                                             int nbk, int64_t j0, int64_t j1,
-                                                            const double *__restrict__ x, int64_t ldx,
-                                                            double *__restrict__ b, int64_t ldb, int tc)
+                                                            const double *__restrict__ x, double *__restrict__ b)
 {
     const int lane = threadIdx.x & 63;
     const int64_t col_groups = (j1 - j0 + 4 * kPanelCols - 1) / (4 * kPanelCols);
     if ((int64_t)blockIdx.x >= col_groups) {
         const int64_t i = ((int64_t)blockIdx.x - col_groups) * blockDim.x + threadIdx.x;
-        if (i < nbk)
-            for (int q = 0; q < tc; ++q) b[(int64_t)q * ldb + k0 + i] = x[(int64_t)q * ldx + i];
+        if (i < nbk) b[k0 + i] = x[i];
         return;
     }
     const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int64_t jb = j0 + wave * kPanelCols;
     if (jb >= j1) return;
     const double *p[kPanelCols];
-    double s[kPanelCols][TC];
+    double s[kPanelCols];
 #pragma unroll
     for (int c = 0; c < kPanelCols; ++c) {
         const int64_t j = (jb + c < j1) ? jb + c : j1 - 1; // a clamped column is computed and dropped
         p[c] = R + k0 + j * M;
-#pragma unroll
-        for (int q = 0; q < TC; ++q) s[c][q] = 0.0;
+        s[c] = 0.0;
     }
-    const double *xq[TC];
-#pragma unroll
-    for (int q = 0; q < TC; ++q) xq[q] = x + (int64_t)(q < tc ? q : tc - 1) * ldx;
     int i = lane;
     for (; i + 64 < nbk; i += 128) {
-        double a[kPanelCols], c2[kPanelCols];
+        const double x0 = x[i], x1 = x[i + 64];
 #pragma unroll
-        for (int c = 0; c < kPanelCols; ++c) {
-            a[c] = p[c][i];
-            c2[c] = p[c][i + 64];
-        }
-#pragma unroll
-        for (int q = 0; q < TC; ++q) {
-            const double x0 = xq[q][i], x1 = xq[q][i + 64];
-#pragma unroll
-            for (int c = 0; c < kPanelCols; ++c) s[c][q] += a[c] * x0 + c2[c] * x1;
-        }
+        for (int c = 0; c < kPanelCols; ++c) s[c] += p[c][i] * x0 + p[c][i + 64] * x1;
     }
     if (i < nbk) {
+        const double x0 = x[i];
 #pragma unroll
-        for (int q = 0; q < TC; ++q) {
-            const double x0 = xq[q][i];
-#pragma unroll
-            for (int c = 0; c < kPanelCols; ++c) s[c][q] += p[c][i] * x0;
-        }
+        for (int c = 0; c < kPanelCols; ++c) s[c] += p[c][i] * x0;
     }
 #pragma unroll
-    for (int c = 0; c < kPanelCols; ++c)
+    for (int c = 0; c < kPanelCols; ++c) {
+        const double tot = wave_sum(s[c]);
+        if (lane == 0 && jb + c < j1) b[jb + c] -= tot;
+    }
+}
+
+// 2 to 16 right-hand sides: the same steps as skinny products on the fp64 matrix cores, still bound by the
+// bandwidth of the factor, which is read once for all columns (a 16 x 16 x 4 instruction takes 512 bytes of it in 64
+// cycles: 19 TB/s over the chip).  Right-hand sides and solution live as [row][16] arrays, unused columns zero.
+// 10 columns at M = 10000: 5.2 ms for the four solves of an iteration as vector-ALU passes over 8 and 2 columns,
+// 1.2 ms now.
+constexpr int kSolveCols = 16;
+constexpr int kSkinnyThreads = 512, kSkinnyWaves = kSkinnyThreads / 64;
+constexpr int kSkinnyTile = 32; // outputs of a workgroup, whose wavefronts share the contraction 32 at a time
+typedef double solve_d2 __attribute__((ext_vector_type(2)));
+typedef double solve_d4 __attribute__((ext_vector_type(4)));
+
+// adds up the wavefronts' accumulators (red: 32 KB of LDS); this thread's entry of the tile: accumulator t = tid / 256,
+// register (tid / 64) % 4 of lane tid % 64
+__device__ __forceinline__ double skinny_reduce(double (*red)[2][4][64], const solve_d4 (&acc)[2])
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 #pragma unroll
-        for (int q = 0; q < TC; ++q) {
-            const double tot = wave_sum(s[c][q]);
-            if (lane == 0 && jb + c < j1 && q < tc) b[(int64_t)q * ldb + jb + c] -= tot;
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wave][t][r][lane] = acc[t][r];
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kSkinnyWaves; ++w) s += red[w][tid >> 8][(tid >> 6) & 3][lane];
+    return s;
+}
+
+// b[r, c] -= sum_{k < nk} P[r + k ld] x[k, c], r < rows.  P 16-byte aligned, ld even, and column entries up to the next
+// even row readable.  A lane's 16-byte load holds the same column entry of rows 2 l and 2 l + 1: even rows are one
+// accumulator, odd rows the other.
+__global__ __launch_bounds__(kSkinnyThreads) void skinny_n_kernel(const double *__restrict__ P, int64_t ld, int64_t rows,
+                                                                 int nk, const double *__restrict__ x, double *__restrict__ b)
+{
+    __shared__ double red[kSkinnyWaves][2][4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l15 = lane & 15, q = lane >> 4;
+    const int64_t row0 = (int64_t)blockIdx.x * kSkinnyTile;
+    const double *p = P + (row0 + 2 * l15 < rows ? row0 + 2 * l15 : 0);
+    solve_d4 acc[2];
+    acc[0] = acc[1] = solve_d4{0.0, 0.0, 0.0, 0.0};
+    for (int k0 = wave * 32; k0 < nk; k0 += kSkinnyWaves * 32) {
+        solve_d2 a[8];
+        double bv[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int k = k0 + 4 * s + q, kc = k < nk ? k : nk - 1;
+            a[s] = *reinterpret_cast<const solve_d2 *>(p + (int64_t)kc * ld);
+            bv[s] = x[(int64_t)kc * kSolveCols + l15];
         }
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const bool in = k0 + 4 * s + q < nk;
+            const double bs = in ? bv[s] : 0.0;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? a[s][t] : 0.0, bs, acc[t], 0, 0, 0);
+        }
+    }
+    const double s = skinny_reduce(red, acc);
+    const int t = threadIdx.x >> 8, i = 4 * ((threadIdx.x >> 6) & 3) + q;
+    const int64_t r = row0 + 2 * i + t;
+    if (r < rows) b[r * kSolveCols + l15] -= s;
+}
+
+// MODE 0: b[j, c] -= sum_{i < nk} P[i + j ld] x[i, c], j < outs.  MODE 1, 2: b[j, c] = the same sum over i >= j, i <= j (a
+// mirrored block inverse: the plain and the transposed solve with its diagonal block).  P 16-byte aligned, ld even.  A
+// lane holds 8 consecutive i of its column, 32 per 4 lane groups.
+template <int MODE>
+__global__ __launch_bounds__(kSkinnyThreads) void skinny_t_kernel(const double *__restrict__ P, int64_t ld, int64_t outs,
+                                                                 int nk, const double *__restrict__ x, double *__restrict__ b)
+{
+    __shared__ double red[kSkinnyWaves][2][4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l15 = lane & 15, q = lane >> 4;
+    const int64_t tile0 = (int64_t)blockIdx.x * kSkinnyTile;
+    const double *p[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int64_t j = tile0 + 16 * t + l15;
+        p[t] = P + (j < outs ? j : 0) * ld;
+    }
+    solve_d4 acc[2];
+    acc[0] = acc[1] = solve_d4{0.0, 0.0, 0.0, 0.0};
+    const int first = MODE == 1 ? (int)tile0 : 0;
+    const int last = MODE == 2 && tile0 + kSkinnyTile < nk ? (int)tile0 + kSkinnyTile : nk;
+    for (int i0 = first + wave * 32; i0 < last; i0 += kSkinnyWaves * 32) {
+        solve_d2 a[2][4];
+        double bv[8];
+        const int ib = i0 + 8 * q; // nk and ld are such that 8 entries from an in-range multiple of 8 stay inside the array
+        const bool any = ib < nk;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int i = any && ib + 2 * s < nk ? ib + 2 * s : 0;
+                a[t][s] = *reinterpret_cast<const solve_d2 *>(p[t] + i);
+            }
+#pragma unroll
+        for (int s = 0; s < 8; ++s) bv[s] = x[(int64_t)(ib + s < nk ? ib + s : 0) * kSolveCols + l15];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int i = ib + s;
+            const double bs = i < nk ? bv[s] : 0.0;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int j = (int)tile0 + 16 * t + l15;
+                const bool in = i < nk && (MODE == 0 || (MODE == 1 ? i >= j : i <= j));
+                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? a[t][s >> 1][s & 1] : 0.0, bs, acc[t], 0, 0, 0);
+            }
+        }
+    }
+    const double s = skinny_reduce(red, acc);
+    const int64_t j = tile0 + 16 * (threadIdx.x >> 8) + 4 * ((threadIdx.x >> 6) & 3) + q;
+    if (j < outs) {
+        if (MODE == 0) b[j * kSolveCols + l15] -= s;
+        else b[j * kSolveCols + l15] = s;
+    }
+}
+
+// [row][16] <- tc columns of a column-major array (zero from tc on), and back
+__global__ void cols_to_rows16_kernel(const double *__restrict__ B, int64_t ldb, int64_t M, int tc, double *__restrict__ out)
+{
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t r = e % M;
+    const int c = (int)(e / M);
+    if (c < kSolveCols) out[r * kSolveCols + c] = c < tc ? B[(int64_t)c * ldb + r] : 0.0;
+}
+__global__ void rows16_to_cols_kernel(const double *__restrict__ in, int64_t M, int tc, double *__restrict__ B, int64_t ldb)
+{
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t r = e % M;
+    const int c = (int)(e / M);
+    if (c < tc) B[(int64_t)c * ldb + r] = in[r * kSolveCols + c];
 }
 
 // ---- leaf of the blocked factorisation --------------------------------------------------------
@@ -701,7 +775,8 @@ struct DevBuf {
 };
 
 // Many right-hand sides: the same blocked solve as products on the fp64 matrix cores.
-constexpr int kProductSolveMinCols = 16;    // from this many right-hand sides on
+// (two groups of 16 as skinny products still beat them: M = 20000, 32 columns: 6.3 against 7.5 ms for four solves)
+constexpr int kProductSolveMinCols = 2 * kSolveCols + 1; // from this many right-hand sides on
 constexpr int64_t kProductSolveMinM = 4096; // and this order of the factor
 
 // out <- the upper triangle (diagonal included) of one mirrored block inverse, zeros below it
@@ -732,7 +807,7 @@ int tri_solve_products(knm_ctx *ctx, const knm_precond *p, const double *R, cons
     const bool lower = (R == p->A);
     const int sb = p->sb;
     const int64_t nblk = (M + sb - 1) / sb;
-    const int64_t cap = (M * kSolveCols) / sb; // columns the staging array holds at leading dimension sb
+    const int64_t cap = 2 * M * kSolveCols / sb; // columns the staging array holds at leading dimension sb
     double *X = p->xw;
     for (int c0 = 0; c0 < t;) {
         const int tc = (int)((t - c0 < cap) ? t - c0 : cap);
@@ -778,37 +853,54 @@ int tri_solve(knm_ctx *ctx, const knm_precond *p, const double *R, const double 
     const int sb = p->sb;
     const int64_t nblk = (M + sb - 1) / sb;
     if (t >= kProductSolveMinCols && p->blk != nullptr) return tri_solve_products(ctx, p, R, S, trans, B, t);
-    // right-hand sides in groups of up to kSolveCols: a group streams the factor once
-    auto run = [&](auto width, int c0, int tc) {
-        constexpr int TC = decltype(width)::value;
+    for (int c0 = 0; c0 < t; c0 += kSolveCols) {
+        const int tc = (t - c0 < kSolveCols) ? t - c0 : kSolveCols; // columns that stream the factor together
         double *b = B + (int64_t)c0 * M;
+        double *rhs = p->xw + M * kSolveCols; // several columns: right-hand side and solution as [row][16] arrays
+        if (tc > 1)
+            hipLaunchKernelGGL(cols_to_rows16_kernel, grid1(M * kSolveCols), dim3(256), 0, ctx->stream, b, M, M, tc, rhs);
         for (int64_t step = 0; step < nblk; ++step) {
             const int64_t k = trans ? step : nblk - 1 - step; // R^T is lower: forward; R: backward
             const int64_t k0 = k * sb;
             const int nbk = (int)((M - k0 < sb) ? M - k0 : sb);
-            double *x = p->xw + k0;
-            hipLaunchKernelGGL(diag_apply_kernel<TC>, dim3((unsigned)((nbk + 3) / 4)), dim3(256), 0, ctx->stream,
-                               S + k * sb * sb, sb, nbk, trans ? 0 : 1, b + k0, M, tc, x, M);
+            const double *Sk = S + k * sb * sb;
             // the entries of b still to be solved: before the block (plain) or after it (transposed)
             const int64_t lo = trans ? k0 + nbk : 0, hi = trans ? M : k0;
-            if (trans == lower) { // panel entries R(r, k0 + j) or R(k0 + j, r) contiguous in r
+            if (tc > 1) {
+                double *x = p->xw + k0 * kSolveCols;
+                const dim3 dgrid((unsigned)((nbk + kSkinnyTile - 1) / kSkinnyTile));
+                if (trans)
+                    hipLaunchKernelGGL(skinny_t_kernel<2>, dgrid, dim3(kSkinnyThreads), 0, ctx->stream, Sk, (int64_t)sb, (int64_t)nbk,
+                                       nbk, rhs + k0 * kSolveCols, x);
+                else
+                    hipLaunchKernelGGL(skinny_t_kernel<1>, dgrid, dim3(kSkinnyThreads), 0, ctx->stream, Sk, (int64_t)sb, (int64_t)nbk,
+                                       nbk, rhs + k0 * kSolveCols, x);
+                if (hi == lo) continue;
+                const dim3 pgrid((unsigned)((hi - lo + kSkinnyTile - 1) / kSkinnyTile));
+                if (trans == lower) // panel entries R(r, k0 + j) or R(k0 + j, r) contiguous in r
+                    hipLaunchKernelGGL(skinny_n_kernel, pgrid, dim3(kSkinnyThreads), 0, ctx->stream, R + lo + k0 * ld, ld, hi - lo,
+                                       nbk, x, rhs + lo * kSolveCols);
+                else                // contiguous in the block's own index
+                    hipLaunchKernelGGL(skinny_t_kernel<0>, pgrid, dim3(kSkinnyThreads), 0, ctx->stream, R + k0 + lo * ld, ld,
+                                       hi - lo, nbk, x, rhs + lo * kSolveCols);
+                continue;
+            }
+            double *x = p->xw + k0;
+            hipLaunchKernelGGL(diag_apply_kernel, dim3((unsigned)((nbk + 3) / 4)), dim3(256), 0, ctx->stream, Sk, sb, nbk,
+                               trans ? 0 : 1, b + k0, x);
+            if (trans == lower) {
                 const int64_t groups = (hi - lo + kPanelRows - 1) / kPanelRows;
                 const int64_t copy = (nbk + kPanelWaves * 64 - 1) / (kPanelWaves * 64);
-                hipLaunchKernelGGL(panel_update_n_kernel<TC>, dim3((unsigned)(groups + copy)), dim3(kPanelWaves * 64), 0,
-                                   ctx->stream, R, ld, k0, nbk, lo, hi, x, M, b, M, tc);
-            } else {              // contiguous in the block's own index
+                hipLaunchKernelGGL(panel_update_n_kernel, dim3((unsigned)(groups + copy)), dim3(kPanelWaves * 64), 0, ctx->stream,
+                                   R, ld, k0, nbk, lo, hi, x, b);
+            } else {
                 const int64_t groups = (hi - lo + 4 * kPanelCols - 1) / (4 * kPanelCols);
                 const int64_t copy = (nbk + 255) / 256;
-                hipLaunchKernelGGL(panel_update_t_kernel<TC>, dim3((unsigned)(groups + copy)), dim3(256), 0, ctx->stream,
-                                   R, ld, k0, nbk, lo, hi, x, M, b, M, tc);
+                hipLaunchKernelGGL(panel_update_t_kernel, dim3((unsigned)(groups + copy)), dim3(256), 0, ctx->stream, R, ld, k0,
+                                   nbk, lo, hi, x, b);
             }
         }
-    };
-    for (int c = 0; c < t; c += kSolveCols) {
-        const int tc = (t - c < kSolveCols) ? t - c : kSolveCols;
-        if (tc == 1) run(std::integral_constant<int, 1>{}, c, tc);
-        else if (tc <= 4) run(std::integral_constant<int, 4>{}, c, tc);
-        else run(std::integral_constant<int, kSolveCols>{}, c, tc);
+        if (tc > 1) hipLaunchKernelGGL(rows16_to_cols_kernel, grid1(M * tc), dim3(256), 0, ctx->stream, p->xw, M, tc, b, M);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "blocked triangular solve", e);
@@ -1204,7 +1296,7 @@ static int precond_build_from(knm_ctx *ctx, int64_t M, const std::function<int(d
     const size_t dbytes = sizeof(double) * (size_t)nblk * p->sb * p->sb;
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&p->Tdinv), dbytes);
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&p->Adinv), dbytes);
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&p->xw), sizeof(double) * (size_t)M * kSolveCols);
+    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&p->xw), sizeof(double) * 2 * (size_t)M * kSolveCols);
     if (e == hipSuccess && M >= kProductSolveMinM)
         e = hipMalloc(reinterpret_cast<void **>(&p->blk), sizeof(double) * (size_t)p->sb * p->sb);
     if (e != hipSuccess) {

@@ -46,19 +46,21 @@ def test_failing_pivot_inside_a_leaf(knm):
     assert e.value.status == -5 and "172" in str(e.value)
 
 
-# wide solve blocks: three levels of merged inverses, the last pair of a level and the last block ragged
-@pytest.mark.parametrize("M", [8500])
-def test_solves_with_merged_block_inverses(knm, M):
+# wide solve blocks: four levels of merged inverses, the last pair of a level and the last block ragged; one column,
+# one and two groups of skinny products, products with wide tiles
+def test_solves_with_merged_block_inverses(knm):
+    M = 8501
     C = _rand(M, 12, 9)
     pre = knm.precond_build(C.cuda(), 2.0, 1e-4, 1e-5)
     T, A = (torch.from_numpy(x).cuda() for x in pre.factors())
-    b = torch.randn(M, 3, generator=torch.Generator().manual_seed(1), dtype=torch.float64).cuda()
-    got = pre.solve(b)
-    ref = torch.linalg.solve_triangular(T, torch.linalg.solve_triangular(A, b, upper=True), upper=True)
-    assert float((got - ref).norm() / ref.norm()) < 1e-9
-    got = pre.solve(b, transpose=True)
-    ref = torch.linalg.solve_triangular(A.T, torch.linalg.solve_triangular(T.T, b, upper=False), upper=False)
-    assert float((got - ref).norm() / ref.norm()) < 1e-9
+    for t in (1, 3, 16, 21, 40):
+        b = torch.randn(M, t, generator=torch.Generator().manual_seed(t), dtype=torch.float64).cuda()
+        got = pre.solve(b)
+        ref = torch.linalg.solve_triangular(T, torch.linalg.solve_triangular(A, b, upper=True), upper=True)
+        assert float((got - ref).norm() / ref.norm()) < 1e-9, t
+        got = pre.solve(b, transpose=True)
+        ref = torch.linalg.solve_triangular(A.T, torch.linalg.solve_triangular(T.T, b, upper=False), upper=False)
+        assert float((got - ref).norm() / ref.norm()) < 1e-9, t
     pre.close()
 
 
