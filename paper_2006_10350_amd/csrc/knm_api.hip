@@ -1,6 +1,7 @@
 // C ABI of libknm: context, workspace and the kernel-matrix-vector products.
 #include <dlfcn.h>
 
+#include <cstddef>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -82,6 +83,70 @@ int ensure(knm_ctx *ctx, float **buf, size_t *cur, size_t need)
     *buf = static_cast<float *>(p);
     *cur = need;
     return KNM_OK;
+}
+
+constexpr size_t kPoolIdleBytes = (size_t)4 << 30; // idle blocks beyond this are freed
+
+hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out)
+{
+    *out = nullptr;
+    bytes = (bytes + 255) & ~(size_t)255;
+    if (bytes == 0) bytes = 256;
+    const std::lock_guard<std::mutex> lock(ctx->pool_lock);
+    // the smallest idle block that fits without wasting more than it gives
+    knm_ctx::PoolBlock *best = nullptr;
+    for (auto &b : ctx->pool)
+        if (!b.used && b.bytes >= bytes && b.bytes <= 2 * bytes + 65536 && (best == nullptr || b.bytes < best->bytes)) best = &b;
+    if (best != nullptr) {
+        best->used = true;
+        ctx->pool_idle -= best->bytes;
+        *out = best->p;
+        return hipSuccess;
+    }
+    void *p = nullptr;
+    hipError_t e = hipMalloc(&p, bytes);
+    if (e != hipSuccess && ctx->pool_idle > 0) { // make room: the idle blocks go first
+        (void)hipGetLastError();
+        for (size_t i = 0; i < ctx->pool.size();) {
+            if (ctx->pool[i].used) {
+                ++i;
+                continue;
+            }
+            (void)hipFree(ctx->pool[i].p);
+            ctx->pool.erase(ctx->pool.begin() + (std::ptrdiff_t)i);
+        }
+        ctx->pool_idle = 0;
+        e = hipMalloc(&p, bytes);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return e;
+    }
+    ctx->pool.push_back({p, bytes, true});
+    *out = p;
+    return hipSuccess;
+}
+
+void pool_give(knm_ctx *ctx, void *p)
+{
+    const std::lock_guard<std::mutex> lock(ctx->pool_lock);
+    for (size_t i = 0; i < ctx->pool.size(); ++i) {
+        auto &b = ctx->pool[i];
+        if (b.p != p) continue;
+        b.used = false;
+        ctx->pool_idle += b.bytes;
+        break;
+    }
+    // oldest idle blocks first (hipFree waits for the device, so nothing queued still uses them)
+    for (size_t i = 0; i < ctx->pool.size() && ctx->pool_idle > kPoolIdleBytes;) {
+        if (ctx->pool[i].used) {
+            ++i;
+            continue;
+        }
+        ctx->pool_idle -= ctx->pool[i].bytes;
+        (void)hipFree(ctx->pool[i].p);
+        ctx->pool.erase(ctx->pool.begin() + (std::ptrdiff_t)i);
+    }
 }
 
 // Workspace for callers that cannot allocate (code under HIP graph capture, serving loops,
@@ -456,6 +521,7 @@ int knm_destroy(knm_ctx *ctx)
     if (ctx->vimg_buf) (void)hipFree(ctx->vimg_buf);
     if (ctx->mu_buf) (void)hipFree(ctx->mu_buf);
     if (ctx->range_count) (void)hipFree(ctx->range_count);
+    for (auto &b : ctx->pool) (void)hipFree(b.p);
     for (int i = 0; i < 5; ++i)
         if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
     extern void knm_solver_release(knm_ctx *);
@@ -520,7 +586,8 @@ size_t knm_workspace_bytes(int64_t n, int64_t M, int d, int t)
 
 size_t knm_workspace_held(const knm_ctx *ctx)
 {
-    return ctx ? ctx->w_bytes + ctx->part_bytes + ctx->pack_bytes + ctx->vimg_bytes + ctx->mu_bytes : 0;
+    if (!ctx) return 0;
+    return ctx->w_bytes + ctx->part_bytes + ctx->pack_bytes + ctx->vimg_bytes + ctx->mu_bytes + ctx->pool_idle;
 }
 
 static int check_common(knm_ctx *ctx, const void *X, int64_t n, int d, int64_t ldx, const void *C, int64_t M,

@@ -4,7 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
+#include <vector>
 
 #include "knm.h"
 
@@ -201,8 +203,16 @@ struct knm_ctx {
     bool ev_used[5] = {false, false, false, false, false};
     double fit_seconds[4] = {0.0, 0.0, 0.0, 0.0}; // last falkon_fit: preconditioner, rhs, iterations, tail
     std::string last_error;
-    // partial sums of the solver's fp64 reductions (allocated lazily by knm_solver.hip)
-    double *red_buf = nullptr;
+    hipEvent_t fit_ev[2] = {nullptr, nullptr}; // begin and end of a fit's iterations (created lazily by knm_solver.hip)
+    // device blocks of the temporaries of fits and sparse products, kept between calls (see pool_take)
+    struct PoolBlock {
+        void *p;
+        size_t bytes;
+        bool used;
+    };
+    std::vector<PoolBlock> pool;
+    size_t pool_idle = 0; // bytes of the blocks not in use
+    std::mutex pool_lock;
     // second stream for the look-ahead of the blocked factorisation (created lazily by knm_solver.hip)
     hipStream_t aux_stream = nullptr;
 };
@@ -220,6 +230,12 @@ struct TraceRange {
     bool open;
 };
 int ensure(knm_ctx *ctx, float **buf, size_t *cur, size_t need);
+// Temporaries of calls that allocate (fits, sparse products): blocks of the context's own, taken from it and given back to
+// it, because hipMalloc and hipFree cost 10 to 80 us each (2.4 ms of a 9.5 ms sparse product).  Work on a context is
+// ordered by its stream, so a block can be given back while kernels that use it are still queued.  Idle blocks of more than
+// 4 GiB in all are freed, and knm_destroy frees the rest.
+hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out);
+void pool_give(knm_ctx *ctx, void *p);
 int fail(knm_ctx *ctx, int status, const char *what, hipError_t e = hipSuccess);
 // true if (d, t) runs on the K-loop engine, false for the register-resident one
 bool use_gemm_engine(int d, int t, int cross_term, int kind);
@@ -231,4 +247,26 @@ int do_knm_v(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx, const 
 // never pass through fp32 after the merge of the chunk partials
 int do_knm_t_w(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx, const float *C, int64_t M,
                int64_t ldc, float sigma, const float *Wv, const float *wgt, int t, float *U, double *U64 = nullptr);
+
+// A temporary from the context's pool.
+struct DevBuf {
+    void *p = nullptr;
+    knm_ctx *owner = nullptr;
+    DevBuf() = default;
+    DevBuf(const DevBuf &) = delete;
+    DevBuf &operator=(const DevBuf &) = delete;
+    ~DevBuf() { free(); }
+    void free()
+    {
+        if (p) pool_give(owner, p);
+        p = nullptr;
+    }
+    int alloc(knm_ctx *ctx, size_t bytes)
+    {
+        owner = ctx;
+        const hipError_t e = pool_take(ctx, bytes, &p);
+        return e == hipSuccess ? KNM_OK : fail(ctx, KNM_ALLOC, "hipMalloc", e);
+    }
+    template <class T> T *as() { return static_cast<T *>(p); }
+};
 } // namespace knm

@@ -40,6 +40,8 @@ struct knm_precond {
     // sb x sb doubles for the solves with many right-hand sides (one block inverse with its mirror image
     // cleared); null for small M
     double *blk = nullptr;
+    // context whose pool the arrays came from (a fit's own preconditioner), null if they are the object's own
+    knm_ctx *pool = nullptr;
 };
 
 namespace {
@@ -118,16 +120,6 @@ __global__ __launch_bounds__(256) void kmm_kernel(const float *__restrict__ C, i
             if (r == c) v += jitter;
             K[r + c * ldk] = v;
         }
-}
-
-// first (1-based) index whose diagonal entry is not a positive finite number, else unchanged;
-// catches NaN/Inf pivots, which a "pivot <= 0" test inside the factorisation lets through
-__global__ void diag_check_kernel(const double *__restrict__ A, int64_t lda, int64_t M, unsigned long long *bad)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    const double v = A[i + i * lda]; // the diagonal sits at the same place in upper and lower storage
-    if (!(v > 0.0) || !(v < 1.0e300)) atomicMin(bad, (unsigned long long)(i + 1));
 }
 
 // row-major (rows x t, leading dimension t) float  <->  column-major (rows x t) double
@@ -213,9 +205,11 @@ __device__ __forceinline__ double wave_sum(double s)
 
 // x = inv(R_kk) b (lower = 1: x[c] = sum_{i >= c} S[i, c] b[i]) or x = inv(R_kk)^T b (lower = 0:
 // x[c] = sum_{i <= c} S[i, c] b[i]) for one mirrored block S of live order nbk; one wavefront
-// per entry of x, lanes along the column of S.
+// per entry of x, lanes along the column of S.  Where they are given: sum[c] = x[c] + scale add[c], x32[c] = x[c] rounded.
 __global__ __launch_bounds__(256) void diag_apply_kernel(const double *__restrict__ S, int sb, int nbk, int lower,
-                                                        const double *__restrict__ b, double *__restrict__ x)
+                                                        const double *__restrict__ b, double *__restrict__ x,
+                                                        const double *__restrict__ add, double scale,
+                                                        double *__restrict__ sum, float *__restrict__ x32)
 {
     const int lane = threadIdx.x & 63;
     const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -231,31 +225,28 @@ __global__ __launch_bounds__(256) void diag_apply_kernel(const double *__restric
     }
     if (i < hi) s0 += col[i] * b[i];
     const double s = wave_sum(s0 + s1);
-    if (lane == 0) x[c] = s;
+    if (lane == 0) {
+        x[c] = s;
+        if (sum != nullptr) sum[c] = s + scale * add[c];
+        if (x32 != nullptr) x32[c] = (float)s;
+    }
 }
 
 constexpr int kPanelWaves = 8;  // wavefronts of a panel_update_n workgroup, sharing the columns
 constexpr int kPanelRows = 64;  // rows of a panel_update_n workgroup, one per lane
 constexpr int kPanelCols = 4;   // columns of one panel_update_t wavefront
 
-// b[r] -= sum_j P[r + (k0 + j) ld] x[j] for r in [r_lo, r_hi)  (x = the solved block, nbk entries): the
-// rows above the block of an upper-storage factor in its plain solve, the rows below the block of a
-// lower-storage factor in its transposed solve.  Workgroups past the row range copy x into
-// b[k0 : k0 + nbk].
+// b[r] = src[r] - sum_j P[r + (k0 + j) ld] x[j] for r in [r_lo, r_hi)  (x = the solved block, nbk entries; src: the
+// right-hand side so far, b itself from the second block on): the rows above the block of an upper-storage factor
+// in its plain solve, the rows below the block of a lower-storage factor in its transposed solve.
 __global__ __launch_bounds__(kPanelWaves * 64) void panel_update_n_kernel(const double *__restrict__ R, int64_t M,
                                                                          int64_t k0, int nbk, int64_t r_lo,
                                                                          int64_t r_hi, const double *__restrict__ x,
-                                                                         double *__restrict__ b)
+                                                                         const double *src, double *b)
 {
     __shared__ double part[kPanelWaves][kPanelRows];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t row_groups = (r_hi - r_lo + kPanelRows - 1) / kPanelRows;
-    if ((int64_t)blockIdx.x >= row_groups) {
-        const int64_t i = ((int64_t)blockIdx.x - row_groups) * blockDim.x + threadIdx.x;
-        if (i < nbk) b[k0 + i] = x[i];
-        return;
-    }
     const int64_t r = r_lo + (int64_t)blockIdx.x * kPanelRows + lane;
     const bool live = r < r_hi;
     const double *p = R + (live ? r : r_lo) + k0 * M;
@@ -277,25 +268,19 @@ __global__ __launch_bounds__(kPanelWaves * 64) void panel_update_n_kernel(const 
     if (w == 0 && live) {
         double s = 0.0;
         for (int u = 0; u < kPanelWaves; ++u) s += part[u][lane];
-        b[r] -= s;
+        b[r] = src[r] - s;
     }
 }
 
-// b[j] -= sum_i P[(k0 + i) + j ld] x[i] for j in [j0, j1)  (x = the solved block, nbk entries): the
+// b[j] = src[j] - sum_i P[(k0 + i) + j ld] x[i] for j in [j0, j1)  (x = the solved block, nbk entries): the
 // columns right of the block of an upper-storage factor in its transposed solve, the columns left of
 // the block of a lower-storage factor in its plain solve.  One wavefront per kPanelCols columns, lanes
-// along the rows.  Workgroups past the column range copy x into b[k0 : k0 + nbk].
+// along the rows.
 __global__ __launch_bounds__(256) void panel_update_t_kernel(const double *__restrict__ R, int64_t M, int64_t k0,
                                                             int nbk, int64_t j0, int64_t j1,
-                                                            const double *__restrict__ x, double *__restrict__ b)
+                                                            const double *__restrict__ x, const double *src, double *b)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t col_groups = (j1 - j0 + 4 * kPanelCols - 1) / (4 * kPanelCols);
-    if ((int64_t)blockIdx.x >= col_groups) {
-        const int64_t i = ((int64_t)blockIdx.x - col_groups) * blockDim.x + threadIdx.x;
-        if (i < nbk) b[k0 + i] = x[i];
-        return;
-    }
     const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int64_t jb = j0 + wave * kPanelCols;
     if (jb >= j1) return;
@@ -321,7 +306,7 @@ __global__ __launch_bounds__(256) void panel_update_t_kernel(const double *__res
 #pragma unroll
     for (int c = 0; c < kPanelCols; ++c) {
         const double tot = wave_sum(s[c]);
-        if (lane == 0 && jb + c < j1) b[jb + c] -= tot;
+        if (lane == 0 && jb + c < j1) b[jb + c] = src[jb + c] - tot;
     }
 }
 
@@ -451,12 +436,14 @@ __global__ void cols_to_rows16_kernel(const double *__restrict__ B, int64_t ldb,
     const int c = (int)(e / M);
     if (c < kSolveCols) out[r * kSolveCols + c] = c < tc ? B[(int64_t)c * ldb + r] : 0.0;
 }
-__global__ void rows16_to_cols_kernel(const double *__restrict__ in, int64_t M, int tc, double *__restrict__ B, int64_t ldb)
+// (with add: plus scale add, same layout as B)
+__global__ void rows16_to_cols_kernel(const double *__restrict__ in, int64_t M, int tc, double *__restrict__ B, int64_t ldb,
+                                      const double *__restrict__ add, double scale)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t r = e % M;
     const int c = (int)(e / M);
-    if (c < tc) B[(int64_t)c * ldb + r] = in[r * kSolveCols + c];
+    if (c < tc) B[(int64_t)c * ldb + r] = in[r * kSolveCols + c] + (add != nullptr ? scale * add[(int64_t)c * ldb + r] : 0.0);
 }
 
 // ---- leaf of the blocked factorisation --------------------------------------------------------
@@ -646,82 +633,96 @@ __global__ __launch_bounds__(kLeafThreads) void potrf_trtri_leaf_kernel(double *
 inline dim3 grid1(int64_t n, int threads = 256) { return dim3((unsigned)((n + threads - 1) / threads)); }
 
 // ---- fp64 vector work of the CG driver -----------------------------------------------------
-// Sums are taken in a fixed order (256 block partials, then one block), so a fit is
-// reproducible from run to run.
-constexpr int kRedBlocks = 256;
+// Every sum is a fixed number of block partials, added up in a fixed order by each block of the kernel that
+// needs the total, so a fit is reproducible from run to run.  The scalars of CG stay on the device: an iteration takes three
+// launches for all columns and the host never waits (with the two scalars of a column read back and five launches per
+// column, 10 columns cost 50 launches and 20 synchronisations per iteration: 0.5 ms of the 4.4 ms at
+// n = 60k, M = 10k).
+constexpr int kMaxRedBlocks = 64;
+inline int red_blocks(int64_t M)
+{
+    const int64_t b = (M + 1023) / 1024;
+    return (int)(b < kMaxRedBlocks ? b : kMaxRedBlocks);
+}
 
+// sum over the 256 threads of a block, in every thread
+__device__ __forceinline__ double block_sum(double s, double *sh)
+{
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+// total of the `count` <= 64 partials of a vector, in every thread
+__device__ __forceinline__ double partials_sum(const double *__restrict__ part, int count)
+{
+    const int lane = threadIdx.x & 63;
+    return wave_sum(lane < count ? part[lane] : 0.0);
+}
+
+// part[c][block] <- this block's share of sum_i x[i, c] y[i, c] (y null: of sum_i x[i, c])
 __global__ __launch_bounds__(256) void dot_partial_kernel(const double *__restrict__ x, const double *__restrict__ y,
-                                                         int64_t n, double *__restrict__ part)
+                                                         int64_t M, double *__restrict__ part)
 {
-    __shared__ double sh[256];
+    __shared__ double sh[4];
+    const int64_t c = blockIdx.y;
     double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        s += y ? x[i] * y[i] : x[i];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < M; i += (int64_t)gridDim.x * 256)
+        s += y ? x[c * M + i] * y[c * M + i] : x[c * M + i];
+    s = block_sum(s, sh);
+    if (threadIdx.x == 0) part[c * gridDim.x + blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(256) void dot_finish_kernel(const double *__restrict__ part, int count, double *__restrict__ out)
+// out[c] <- scale times the total of the partials of column c = blockIdx.x
+__global__ __launch_bounds__(64) void dot_finish_kernel(const double *__restrict__ part, int count, double scale,
+                                                       double *__restrict__ out)
 {
-    __shared__ double sh[256];
-    sh[threadIdx.x] = ((int)threadIdx.x < count) ? part[threadIdx.x] : 0.0;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[0] = sh[0];
+    const double s = partials_sum(part + (int64_t)blockIdx.x * count, count);
+    if (threadIdx.x == 0) out[blockIdx.x] = scale * s;
 }
 
-__global__ void axpy_kernel(int64_t n, double a, const double *__restrict__ x, double *__restrict__ y)
+// a = rho / (p . q); b += a p; r -= a q; part_rr <- partials of the new r . r
+__global__ __launch_bounds__(256) void cg_step_kernel(int64_t M, const double *__restrict__ rho, const double *__restrict__ part_pq,
+                                                     const double *__restrict__ p, const double *__restrict__ q,
+                                                     double *__restrict__ b, double *__restrict__ r, double *__restrict__ part_rr)
+{
+    __shared__ double sh[4];
+    const int64_t c = blockIdx.y;
+    const double pq = partials_sum(part_pq + c * gridDim.x, gridDim.x);
+    const double a = (pq != 0.0) ? rho[c] / pq : 0.0;
+    double s = 0.0;
+    for (int64_t i = c * M + (int64_t)blockIdx.x * 256 + threadIdx.x; i < (c + 1) * M; i += (int64_t)gridDim.x * 256) {
+        b[i] += a * p[i];
+        const double v = r[i] - a * q[i];
+        r[i] = v;
+        s += v * v;
+    }
+    s = block_sum(s, sh);
+    if (threadIdx.x == 0) part_rr[c * gridDim.x + blockIdx.x] = s;
+}
+
+// rho_next = r . r; p = r + (rho_next / rho) p
+__global__ __launch_bounds__(256) void cg_direction_kernel(int64_t M, const double *__restrict__ rho, double *__restrict__ rho_next,
+                                                          const double *__restrict__ part_rr, const double *__restrict__ r,
+                                                          double *__restrict__ p)
+{
+    const int64_t c = blockIdx.y;
+    const double rn = partials_sum(part_rr + c * gridDim.x, gridDim.x);
+    const double b = (rho[c] != 0.0) ? rn / rho[c] : 0.0;
+    for (int64_t i = c * M + (int64_t)blockIdx.x * 256 + threadIdx.x; i < (c + 1) * M; i += (int64_t)gridDim.x * 256)
+        p[i] = r[i] + b * p[i];
+    if (blockIdx.x == 0 && threadIdx.x == 0) rho_next[c] = rn;
+}
+
+// y32 <- (y += x) rounded
+__global__ void add_round_kernel(int64_t n, const double *__restrict__ x, double *__restrict__ y, float *__restrict__ y32)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] += a * x[i];
+    if (i >= n) return;
+    const double v = y[i] + x[i];
+    y[i] = v;
+    y32[i] = (float)v;
 }
-
-__global__ void scal_kernel(int64_t n, double b, double *__restrict__ y)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] *= b;
-}
-
-// *out_host <- sum_i x[i] y[i] (y null: sum_i x[i]); synchronises the stream
-int vec_dot(knm_ctx *ctx, int64_t n, const double *x, const double *y, double *out_host)
-{
-    if (!ctx->red_buf) {
-        hipError_t e = hipMalloc(reinterpret_cast<void **>(&ctx->red_buf), sizeof(double) * (kRedBlocks + 1));
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            ctx->red_buf = nullptr;
-            return fail(ctx, KNM_ALLOC, "hipMalloc(reduction buffer)", e);
-        }
-    }
-    hipLaunchKernelGGL(dot_partial_kernel, dim3(kRedBlocks), dim3(256), 0, ctx->stream, x, y, n, ctx->red_buf);
-    hipLaunchKernelGGL(dot_finish_kernel, dim3(1), dim3(256), 0, ctx->stream, ctx->red_buf, kRedBlocks,
-                       ctx->red_buf + kRedBlocks);
-    hipError_t e = hipMemcpyAsync(out_host, ctx->red_buf + kRedBlocks, sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "vector reduction", e);
-    return KNM_OK;
-}
-
-int vec_axpy(knm_ctx *ctx, int64_t n, double a, const double *x, double *y)
-{
-    hipLaunchKernelGGL(axpy_kernel, grid1(n), dim3(256), 0, ctx->stream, n, a, x, y);
-    return hipGetLastError() == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "axpy launch");
-}
-
-int vec_scal(knm_ctx *ctx, int64_t n, double b, double *y)
-{
-    hipLaunchKernelGGL(scal_kernel, grid1(n), dim3(256), 0, ctx->stream, n, b, y);
-    return hipGetLastError() == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "scal launch");
-}
-
 
 // Logistic loss l(z, y) = log(1 + exp(-y z)), y = +-1 (Appendix "Logistic Falkon Algorithm",
 // Example 1a), evaluated in fp64 from fp32 predictions: first derivative g, second derivative
@@ -752,27 +753,11 @@ __global__ void newton_rhs_kernel(const float *__restrict__ u, const float *__re
     r[j] = -((double)u[j] + c * ((double)zc[j] + eps * a[j]));
 }
 
-__global__ void f64_to_f32_kernel(const double *__restrict__ a, int64_t n, float *__restrict__ out)
+__global__ void axpy_kernel(int64_t n, double a, const double *__restrict__ x, double *__restrict__ y)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = (float)a[i];
+    if (i < n) y[i] += a * x[i];
 }
-
-struct DevBuf {
-    void *p = nullptr;
-    ~DevBuf() { if (p) (void)hipFree(p); }
-    int alloc(knm_ctx *ctx, size_t bytes)
-    {
-        hipError_t e = hipMalloc(&p, bytes ? bytes : 1);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            p = nullptr;
-            return fail(ctx, KNM_ALLOC, "hipMalloc", e);
-        }
-        return KNM_OK;
-    }
-    template <class T> T *as() { return static_cast<T *>(p); }
-};
 
 // Many right-hand sides: the same blocked solve as products on the fp64 matrix cores.
 // (two groups of 16 as skinny products still beat them: M = 20000, 32 columns: 6.3 against 7.5 ms for four solves)
@@ -841,24 +826,37 @@ int tri_solve_products(knm_ctx *ctx, const knm_precond *p, const double *R, cons
     return KNM_OK;
 }
 
-// B <- op(R)^-1 B for column-major B (M x t); S = mirrored inverses of the diagonal blocks of R
-// (R = p->T, upper storage, or p->A, lower storage).  p->xw stages each solved block; solves on one
-// context are stream-ordered.  Either storage streams its panels along contiguous columns of the
-// array: what is a row update for one is a column update for the other.
-int tri_solve(knm_ctx *ctx, const knm_precond *p, const double *R, const double *S, bool trans, double *B, int t)
+// out <- op(R)^-1 in + scale add for column-major M x t arrays; S = mirrored inverses of the diagonal blocks of R
+// (R = p->T, upper storage, or p->A, lower storage); add may be null; with one column out32, where it is given, receives the
+// solution (without add) rounded.  `in` and `out` must not overlap for one column.  p->xw holds the solve's
+// intermediate vectors; solves on one context are stream-ordered.  Either storage streams its panels along contiguous columns
+// of the array: what is a row update for one is a column update for the other.
+int tri_solve(knm_ctx *ctx, const knm_precond *p, const double *R, const double *S, bool trans, const double *in, double *out, int t,
+              const double *add = nullptr, double scale = 0.0, float *out32 = nullptr)
 {
     TraceRange range(R == p->A ? (trans ? "knm solve A^-T" : "knm solve A^-1") : (trans ? "knm solve T^-T" : "knm solve T^-1"));
     const int64_t M = p->M, ld = p->ld;
     const bool lower = (R == p->A);
     const int sb = p->sb;
     const int64_t nblk = (M + sb - 1) / sb;
-    if (t >= kProductSolveMinCols && p->blk != nullptr) return tri_solve_products(ctx, p, R, S, trans, B, t);
+    if (t >= kProductSolveMinCols && p->blk != nullptr) {
+        if (in != out && hipMemcpyAsync(out, in, sizeof(double) * M * t, hipMemcpyDeviceToDevice, ctx->stream) != hipSuccess)
+            return fail(ctx, KNM_HIP_ERROR, "triangular solve: copy");
+        int st = tri_solve_products(ctx, p, R, S, trans, out, t);
+        if (!st && add != nullptr) hipLaunchKernelGGL(axpy_kernel, grid1(M * t), dim3(256), 0, ctx->stream, M * t, scale, add, out);
+        return st;
+    }
     for (int c0 = 0; c0 < t; c0 += kSolveCols) {
         const int tc = (t - c0 < kSolveCols) ? t - c0 : kSolveCols; // columns that stream the factor together
-        double *b = B + (int64_t)c0 * M;
+        const double *bin = in + (int64_t)c0 * M;
+        double *bout = out + (int64_t)c0 * M;
+        const double *badd = add != nullptr ? add + (int64_t)c0 * M : nullptr;
         double *rhs = p->xw + M * kSolveCols; // several columns: right-hand side and solution as [row][16] arrays
         if (tc > 1)
-            hipLaunchKernelGGL(cols_to_rows16_kernel, grid1(M * kSolveCols), dim3(256), 0, ctx->stream, b, M, M, tc, rhs);
+            hipLaunchKernelGGL(cols_to_rows16_kernel, grid1(M * kSolveCols), dim3(256), 0, ctx->stream, bin, M, M, tc, rhs);
+        // one column: the right-hand side so far (`in` up to the first panel update), and where the solution goes
+        double *const work = p->xw;
+        double *const sol = badd != nullptr ? p->xw + M : bout;
         for (int64_t step = 0; step < nblk; ++step) {
             const int64_t k = trans ? step : nblk - 1 - step; // R^T is lower: forward; R: backward
             const int64_t k0 = k * sb;
@@ -885,22 +883,20 @@ int tri_solve(knm_ctx *ctx, const knm_precond *p, const double *R, const double 
                                        hi - lo, nbk, x, rhs + lo * kSolveCols);
                 continue;
             }
-            double *x = p->xw + k0;
+            const double *b = step == 0 ? bin : work;
             hipLaunchKernelGGL(diag_apply_kernel, dim3((unsigned)((nbk + 3) / 4)), dim3(256), 0, ctx->stream, Sk, sb, nbk,
-                               trans ? 0 : 1, b + k0, x);
-            if (trans == lower) {
-                const int64_t groups = (hi - lo + kPanelRows - 1) / kPanelRows;
-                const int64_t copy = (nbk + kPanelWaves * 64 - 1) / (kPanelWaves * 64);
-                hipLaunchKernelGGL(panel_update_n_kernel, dim3((unsigned)(groups + copy)), dim3(kPanelWaves * 64), 0, ctx->stream,
-                                   R, ld, k0, nbk, lo, hi, x, b);
-            } else {
-                const int64_t groups = (hi - lo + 4 * kPanelCols - 1) / (4 * kPanelCols);
-                const int64_t copy = (nbk + 255) / 256;
-                hipLaunchKernelGGL(panel_update_t_kernel, dim3((unsigned)(groups + copy)), dim3(256), 0, ctx->stream, R, ld, k0,
-                                   nbk, lo, hi, x, b);
-            }
+                               trans ? 0 : 1, b + k0, sol + k0, badd != nullptr ? badd + k0 : nullptr, scale,
+                               badd != nullptr ? bout + k0 : nullptr, out32 != nullptr ? out32 + k0 : nullptr);
+            if (hi == lo) continue;
+            if (trans == lower)
+                hipLaunchKernelGGL(panel_update_n_kernel, dim3((unsigned)((hi - lo + kPanelRows - 1) / kPanelRows)),
+                                   dim3(kPanelWaves * 64), 0, ctx->stream, R, ld, k0, nbk, lo, hi, sol + k0, b, work);
+            else
+                hipLaunchKernelGGL(panel_update_t_kernel, dim3((unsigned)((hi - lo + 4 * kPanelCols - 1) / (4 * kPanelCols))),
+                                   dim3(256), 0, ctx->stream, R, ld, k0, nbk, lo, hi, sol + k0, b, work);
         }
-        if (tc > 1) hipLaunchKernelGGL(rows16_to_cols_kernel, grid1(M * tc), dim3(256), 0, ctx->stream, p->xw, M, tc, b, M);
+        if (tc > 1)
+            hipLaunchKernelGGL(rows16_to_cols_kernel, grid1(M * tc), dim3(256), 0, ctx->stream, p->xw, M, tc, bout, M, badd, scale);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "blocked triangular solve", e);
@@ -927,10 +923,12 @@ int invert_diag_blocks(knm_ctx *ctx, const knm_precond *p, const double *R, doub
 
 // Workspace of one application of the operator of Eq. 9 on column-major fp64 vectors.
 struct LinopWork {
-    DevBuf v, z32, u32, u64;
+    DevBuf v, w, c, z32, u32, u64;
     int alloc(knm_ctx *ctx, int64_t M, int t)
     {
         int st = v.alloc(ctx, sizeof(double) * M * t);
+        if (!st) st = w.alloc(ctx, sizeof(double) * M * t);
+        if (!st) st = c.alloc(ctx, sizeof(double) * M * t);
         if (!st) st = z32.alloc(ctx, sizeof(float) * M * t);
         if (!st) st = u32.alloc(ctx, sizeof(float) * M * t);
         if (!st) st = u64.alloc(ctx, sizeof(double) * M * t);
@@ -988,6 +986,7 @@ int t_w_cols(knm_ctx *ctx, const KernelOps &ops, const float *W, const float *wg
              double *cols)
 {
     if (ops.t_w64) {
+        if (t == 1) return ops.t_w64(W, wgt, t, cols); // one column: the same array either way
         int st = ops.t_w64(W, wgt, t, u64);
         if (st) return st;
         hipLaunchKernelGGL(f64_rows_to_cols, grid1(ops.M * t), dim3(256), 0, ctx->stream, u64, ops.M, t, cols, 0);
@@ -1021,30 +1020,22 @@ int linop_cols(knm_ctx *ctx, const knm_precond *p, LinopWork &wk, const KernelOp
                const double *beta, int t, double *out, const float *wgt = nullptr)
 {
     const int64_t n = ops.n, M = ops.M;
-    const size_t bytes = sizeof(double) * M * t;
-    double *v = wk.v.as<double>();
-    hipError_t e = hipMemcpyAsync(v, beta, bytes, hipMemcpyDeviceToDevice, ctx->stream);
-    if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipMemcpyAsync", e);
-    int st = tri_solve(ctx, p, p->A, p->Adinv, false, v, t); // v = A^-1 beta
+    double *v = wk.v.as<double>(), *w = wk.w.as<double>(), *c = wk.c.as<double>();
+    float *z32 = wk.z32.as<float>();
+    int st = tri_solve(ctx, p, p->A, p->Adinv, false, beta, v, t); // v = A^-1 beta
+    if (!st) st = tri_solve(ctx, p, p->T, p->Tdinv, false, v, w, t, nullptr, 0.0, t == 1 ? z32 : nullptr); // z = T^-1 v
     if (st) return st;
-    e = hipMemcpyAsync(out, v, bytes, hipMemcpyDeviceToDevice, ctx->stream);
-    if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipMemcpyAsync", e);
-    st = tri_solve(ctx, p, p->T, p->Tdinv, false, out, t); // z = T^-1 v
-    if (st) return st;
-    hipLaunchKernelGGL(f64_cols_to_f32_rows, grid1(M * t), dim3(256), 0, ctx->stream, out, M, t, wk.z32.as<float>());
+    if (t > 1) hipLaunchKernelGGL(f64_cols_to_f32_rows, grid1(M * t), dim3(256), 0, ctx->stream, w, M, t, z32);
     // c = K_nm^T (K_nm z), the O(n M) step
     st = ensure(ctx, &ctx->w_buf, &ctx->w_bytes, sizeof(float) * (size_t)n * t);
     if (st) return st;
-    st = ops.v(wk.z32.as<float>(), t, ctx->w_buf);
+    st = ops.v(z32, t, ctx->w_buf);
     if (st) return st;
-    st = t_w_cols(ctx, ops, ctx->w_buf, wgt, t, wk.u32.as<float>(), wk.u64.as<double>(), out);
+    st = t_w_cols(ctx, ops, ctx->w_buf, wgt, t, wk.u32.as<float>(), wk.u64.as<double>(), c);
     if (st) return st;
-    st = tri_solve(ctx, p, p->T, p->Tdinv, true, out, t); // T^-T c
+    st = tri_solve(ctx, p, p->T, p->Tdinv, true, c, w, t, v, lambda * (double)n); // T^-T c + lambda n v
     if (st) return st;
-    const double ln = lambda * (double)n;
-    if (vec_axpy(ctx, M * t, ln, v, out) != KNM_OK)
-        return KNM_HIP_ERROR;
-    return tri_solve(ctx, p, p->A, p->Adinv, true, out, t); // A^-T (...)
+    return tri_solve(ctx, p, p->A, p->Adinv, true, w, out, t); // A^-T (...)
 }
 
 } // namespace
@@ -1053,10 +1044,11 @@ extern "C" {
 
 void knm_solver_release(knm_ctx *ctx)
 {
-    if (ctx && ctx->red_buf) {
-        (void)hipFree(ctx->red_buf);
-        ctx->red_buf = nullptr;
-    }
+    for (int i = 0; ctx && i < 2; ++i)
+        if (ctx->fit_ev[i]) {
+            (void)hipEventDestroy(ctx->fit_ev[i]);
+            ctx->fit_ev[i] = nullptr;
+        }
     if (ctx && ctx->aux_stream) {
         (void)hipStreamDestroy(ctx->aux_stream);
         ctx->aux_stream = nullptr;
@@ -1067,11 +1059,11 @@ int precond_free(knm_precond *p)
 {
     if (!p) return KNM_INVALID_ARG;
     (void)hipSetDevice(p->device);
-    if (p->buf) (void)hipFree(p->buf);
-    if (p->Tdinv) (void)hipFree(p->Tdinv);
-    if (p->Adinv) (void)hipFree(p->Adinv);
-    if (p->xw) (void)hipFree(p->xw);
-    if (p->blk) (void)hipFree(p->blk);
+    for (double *a : {p->buf, p->Tdinv, p->Adinv, p->xw, p->blk}) {
+        if (!a) continue;
+        if (p->pool) pool_give(p->pool, a);
+        else (void)hipFree(a);
+    }
     delete p;
     return KNM_OK;
 }
@@ -1087,7 +1079,7 @@ int precond_free(knm_precond *p)
 //   the columns it writes).
 //   Step 3 (trailing update, M^3 / 3 of the flop) is one rank-k launch per block row.
 // S (as many sb x sb column-major blocks as cover M) is cleared and receives the inverses of the 128 x 128 diagonal
-// blocks at their places; `bad` is a device word; first_bad receives the 1-based index of the first failing pivot, or 0.
+// blocks at their places; `bad` is a device word that receives the least 1-based index of a failing pivot (all ones: none).
 constexpr int64_t kSubPanel = 512;
 
 // events without timing, destroyed with the set
@@ -1126,16 +1118,14 @@ static int aux_stream(knm_ctx *ctx, hipStream_t *out)
 // A[c + r ld]); every product below then has its two index roles exchanged.  A block row that straddles the
 // diagonal is stored on its own side only, because the other triangle belongs to the other factor.
 static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool lower, double *S, int sb,
-                        unsigned long long *bad, int64_t *first_bad)
+                        unsigned long long *bad)
 {
     TraceRange range(lower ? "knm Cholesky of T D T^T / M + lambda I" : "knm Cholesky of K_MM");
     int64_t b = ((M + 7) / 8 + 255) / 256 * 256;
     if (b > 4096) b = 4096;
     const int64_t nb = (M + b - 1) / b;
-    const unsigned long long none = ~0ull;
-    hipError_t e = hipMemcpyAsync(bad, &none, sizeof(none), hipMemcpyHostToDevice, ctx->stream);
-    if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipMemcpyAsync", e);
-    e = hipMemsetAsync(S, 0, sizeof(double) * (size_t)((M + sb - 1) / sb) * sb * sb, ctx->stream);
+    hipError_t e = hipMemsetAsync(bad, 0xff, sizeof(*bad), ctx->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(S, 0, sizeof(double) * (size_t)((M + sb - 1) / sb) * sb * sb, ctx->stream);
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipMemsetAsync", e);
     hipStream_t aux = nullptr;
     int st = aux_stream(ctx, &aux);
@@ -1211,12 +1201,20 @@ static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool low
                 return fail(ctx, KNM_HIP_ERROR, "hipStreamWaitEvent");
             break;
         }
-    unsigned long long got = none;
-    e = hipMemcpyAsync(&got, bad, sizeof(got), hipMemcpyDeviceToHost, ctx->stream);
+    e = hipGetLastError();
+    if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "factorisation", e);
+    return KNM_OK;
+}
+
+// The words of failing pivots of `count` factorisations (waits for the stream); pivot[k] = 0 for none.
+static int read_bad_pivots(knm_ctx *ctx, const unsigned long long *bad, int count, int64_t *pivot)
+{
+    unsigned long long got[2];
+    hipError_t e = hipMemcpyAsync(got, bad, sizeof(*got) * count, hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "factorisation", e);
-    *first_bad = (got == none) ? 0 : (int64_t)got;
+    for (int k = 0; k < count; ++k) pivot[k] = (got[k] == ~0ull) ? 0 : (int64_t)got[k];
     return KNM_OK;
 }
 
@@ -1225,51 +1223,27 @@ static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool low
 // only sums over k >= max(i, j): M^3 / 3 flop instead of the M^3 of a dense rank-M update,
 // in one launch of the rank-k kernel, which skips the vanishing part tile by tile.  The product is
 // written mirrored, into the lower storage of A beside T, and factorised there in place.
-static int build_second_factor(knm_ctx *ctx, knm_precond *p, double lambda, const double *dw,
-                               int64_t *bad_pivot)
+// Enqueued only; *bad_dev receives what chol_blocked leaves in its word.
+static int build_second_factor(knm_ctx *ctx, knm_precond *p, double lambda, const double *dw, unsigned long long *bad_dev)
 {
     const int64_t M = p->M;
-    *bad_pivot = 0;
-    DevBuf badbuf;
-    int st = badbuf.alloc(ctx, sizeof(unsigned long long));
-    if (st) return st;
     {
         TraceRange range("knm triangular product T D T^T");
         if (launch_rank_k_upper(1, M, M, 1.0 / (double)M, p->T, p->ld, dw, 1, 0.0, lambda, p->A, p->ld, ctx->stream, 1) !=
             hipSuccess)
             return fail(ctx, KNM_HIP_ERROR, "triangular product launch");
     }
-    int64_t pivot = 0;
-    st = chol_blocked(ctx, p->A, p->ld, M, true, p->Adinv, p->sb, badbuf.as<unsigned long long>(), &pivot);
-    if (st) return st;
-    if (pivot == 0) {
-        const unsigned long long none = ~0ull;
-        unsigned long long got = none;
-        hipError_t err = hipMemcpyAsync(badbuf.p, &none, sizeof(none), hipMemcpyHostToDevice, ctx->stream);
-        if (err == hipSuccess) {
-            hipLaunchKernelGGL(diag_check_kernel, grid1(M), dim3(256), 0, ctx->stream, p->A, p->ld, M,
-                               badbuf.as<unsigned long long>());
-            err = hipMemcpyAsync(&got, badbuf.p, sizeof(got), hipMemcpyDeviceToHost, ctx->stream);
-        }
-        if (err == hipSuccess) err = hipStreamSynchronize(ctx->stream);
-        if (err != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "diagonal check", err);
-        pivot = (got == none) ? 0 : (int64_t)got;
-    }
-    if (pivot != 0) {
-        *bad_pivot = pivot;
-        return fail(ctx, KNM_NOT_PD, "T D T^T / M + lambda I is not positive definite");
-    }
-    st = invert_diag_blocks(ctx, p, p->A, p->Adinv);
-    if (st) return st;
-    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "second factor"); // scratch is freed on return
-    if (hipGetLastError() != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "preconditioner kernel launch");
-    p->lambda = lambda;
-    return KNM_OK;
+    int st = chol_blocked(ctx, p->A, p->ld, M, true, p->Adinv, p->sb, bad_dev);
+    if (!st) st = invert_diag_blocks(ctx, p, p->A, p->Adinv);
+    if (!st) p->lambda = lambda;
+    return st;
 }
+static const char *const kSecondNotPd = "T D T^T / M + lambda I is not positive definite";
 
 // fill_kmm(K, ldk) writes the upper triangle of K_MM + jitter I (column-major, leading dimension ldk)
+// (pooled: the arrays come from the context's pool, for a preconditioner that does not outlive the call)
 static int precond_build_from(knm_ctx *ctx, int64_t M, const std::function<int(double *, int64_t)> &fill_kmm, double lambda,
-                              double jitter, bool second_factor, knm_precond **out, int64_t *bad_pivot_or_null)
+                              double jitter, bool second_factor, bool pooled, knm_precond **out, int64_t *bad_pivot_or_null)
 {
     if (!ctx) return KNM_INVALID_ARG;
     if (!out) return fail(ctx, KNM_INVALID_ARG, "null output");
@@ -1287,18 +1261,22 @@ static int precond_build_from(knm_ctx *ctx, int64_t M, const std::function<int(d
     p->lambda = lambda;
     p->jitter = jitter;
     p->ld = M + 2 + (M & 1); // even: every column of either factor starts 16-byte aligned
-    const size_t bytes = sizeof(double) * (size_t)p->ld * (size_t)M;
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(&p->buf), bytes);
-    p->T = p->buf;
-    p->A = p->buf ? p->buf + 2 : nullptr;
+    p->pool = pooled ? ctx : nullptr;
     p->sb = solve_block_width(M);
     const int64_t nblk = (M + p->sb - 1) / p->sb;
-    const size_t dbytes = sizeof(double) * (size_t)nblk * p->sb * p->sb;
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&p->Tdinv), dbytes);
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&p->Adinv), dbytes);
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&p->xw), sizeof(double) * 2 * (size_t)M * kSolveCols);
-    if (e == hipSuccess && M >= kProductSolveMinM)
-        e = hipMalloc(reinterpret_cast<void **>(&p->blk), sizeof(double) * (size_t)p->sb * p->sb);
+    auto take = [&](double **a, int64_t count) {
+        void *ptr = nullptr;
+        const hipError_t err = pooled ? pool_take(ctx, sizeof(double) * (size_t)count, &ptr) : hipMalloc(&ptr, sizeof(double) * (size_t)count);
+        if (err == hipSuccess) *a = static_cast<double *>(ptr);
+        return err;
+    };
+    hipError_t e = take(&p->buf, p->ld * M);
+    p->T = p->buf;
+    p->A = p->buf ? p->buf + 2 : nullptr;
+    if (e == hipSuccess) e = take(&p->Tdinv, nblk * p->sb * p->sb);
+    if (e == hipSuccess) e = take(&p->Adinv, nblk * p->sb * p->sb);
+    if (e == hipSuccess) e = take(&p->xw, 2 * M * kSolveCols);
+    if (e == hipSuccess && M >= kProductSolveMinM) e = take(&p->blk, (int64_t)p->sb * p->sb);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         precond_free(p);
@@ -1315,58 +1293,29 @@ static int precond_build_from(knm_ctx *ctx, int64_t M, const std::function<int(d
         return st;
     }
 
+    // both factors are enqueued before the host asks how the first one went (a failed pivot leaves numbers, not faults)
     DevBuf badbuf;
-    if (badbuf.alloc(ctx, sizeof(unsigned long long))) return bail(KNM_ALLOC, "hipMalloc");
-    // returns the failing pivot (1-based) of the factor in `F`, or 0
-    auto bad_diagonal = [&](const double *F, int64_t *pivot) -> hipError_t {
-        const unsigned long long none = ~0ull;
-        unsigned long long got = none;
-        hipError_t err = hipMemcpyAsync(badbuf.p, &none, sizeof(none), hipMemcpyHostToDevice, ctx->stream);
-        if (err != hipSuccess) return err;
-        hipLaunchKernelGGL(diag_check_kernel, grid1(M), dim3(256), 0, ctx->stream, F, p->ld, M,
-                           badbuf.as<unsigned long long>());
-        err = hipMemcpyAsync(&got, badbuf.p, sizeof(got), hipMemcpyDeviceToHost, ctx->stream);
-        if (err == hipSuccess) err = hipStreamSynchronize(ctx->stream);
-        *pivot = (got == none) ? 0 : (int64_t)got;
-        return err;
-    };
-
-    int64_t host_info = 0;
-    {
-        int st2 = chol_blocked(ctx, p->T, p->ld, M, false, p->Tdinv, p->sb, badbuf.as<unsigned long long>(), &host_info);
-        if (st2) {
-            precond_free(p);
-            return st2;
-        }
-    }
-    int64_t pivot = host_info;
-    if (pivot == 0 && bad_diagonal(p->T, &pivot) != hipSuccess) return bail(KNM_HIP_ERROR, "diagonal check");
-    if (pivot != 0) {
-        if (bad_pivot_or_null) *bad_pivot_or_null = pivot;
-        return bail(KNM_NOT_PD, "K_MM + jitter I is not positive definite");
-    }
-    if (hipGetLastError() != hipSuccess) return bail(KNM_HIP_ERROR, "preconditioner kernel launch");
-    st = invert_diag_blocks(ctx, p, p->T, p->Tdinv);
-    if (!st && hipStreamSynchronize(ctx->stream) != hipSuccess) st = fail(ctx, KNM_HIP_ERROR, "first factor");
+    if (badbuf.alloc(ctx, 2 * sizeof(unsigned long long))) return bail(KNM_ALLOC, "hipMalloc");
+    unsigned long long *bad = badbuf.as<unsigned long long>();
+    st = chol_blocked(ctx, p->T, p->ld, M, false, p->Tdinv, p->sb, bad);
+    if (!st) st = invert_diag_blocks(ctx, p, p->T, p->Tdinv);
+    if (!st && second_factor) st = build_second_factor(ctx, p, lambda, nullptr, bad + 1);
+    int64_t pivot[2] = {0, 0};
+    if (!st) st = read_bad_pivots(ctx, bad, second_factor ? 2 : 1, pivot);
     if (st) {
         precond_free(p);
         return st;
     }
-    if (second_factor) {
-        int64_t bad = 0;
-        st = build_second_factor(ctx, p, lambda, nullptr, &bad);
-        if (st) {
-            if (bad_pivot_or_null) *bad_pivot_or_null = -bad;
-            precond_free(p);
-            return st;
-        }
+    if (pivot[0] != 0 || pivot[1] != 0) {
+        if (bad_pivot_or_null) *bad_pivot_or_null = pivot[0] != 0 ? pivot[0] : -pivot[1];
+        return bail(KNM_NOT_PD, pivot[0] != 0 ? "K_MM + jitter I is not positive definite" : kSecondNotPd);
     }
     *out = p;
     return KNM_OK;
 }
 
 static int precond_build_impl(knm_ctx *ctx, const float *C, int64_t M, int d, int64_t ldc, float sigma, double lambda,
-                              double jitter, bool second_factor, knm_precond **out, int64_t *bad_pivot_or_null)
+                              double jitter, bool second_factor, bool pooled, knm_precond **out, int64_t *bad_pivot_or_null)
 {
     if (!ctx) return KNM_INVALID_ARG;
     if (!C || M <= 0 || d <= 0 || ldc < d || !(sigma > 0.0f))
@@ -1382,18 +1331,18 @@ static int precond_build_impl(knm_ctx *ctx, const float *C, int64_t M, int d, in
         hipLaunchKernelGGL(kmm_kernel, tg, tb, 0, ctx->stream, C, M, d, ldc, kind, scale, jitter, K, ldk);
         return hipGetLastError() == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "kmm_kernel launch");
     };
-    return precond_build_from(ctx, M, fill, lambda, jitter, second_factor, out, bad_pivot_or_null);
+    return precond_build_from(ctx, M, fill, lambda, jitter, second_factor, pooled, out, bad_pivot_or_null);
 }
 
 int precond_build(knm_ctx *ctx, const float *C, int64_t M, int d, int64_t ldc, float sigma, double lambda,
                   double jitter, knm_precond **out, int64_t *bad_pivot_or_null)
 {
-    return precond_build_impl(ctx, C, M, d, ldc, sigma, lambda, jitter, true, out, bad_pivot_or_null);
+    return precond_build_impl(ctx, C, M, d, ldc, sigma, lambda, jitter, true, false, out, bad_pivot_or_null);
 }
 
-int precond_build_csr(knm_ctx *ctx, const int64_t *c_indptr, const int64_t *c_indices, const float *c_values, int64_t M,
-                      int64_t d, float sigma, double lambda, double jitter, knm_precond **out,
-                      int64_t *bad_pivot_or_null)
+static int precond_build_csr_impl(knm_ctx *ctx, const int64_t *c_indptr, const int64_t *c_indices, const float *c_values, int64_t M,
+                      int64_t d, float sigma, double lambda, double jitter, bool second_factor, bool pooled,
+                      knm_precond **out, int64_t *bad_pivot_or_null)
 {
     if (!ctx) return KNM_INVALID_ARG;
     if (!c_indptr || M <= 0 || d <= 0 || d >= 0x7fffffffLL || !(sigma > 0.0f))
@@ -1401,7 +1350,15 @@ int precond_build_csr(knm_ctx *ctx, const int64_t *c_indptr, const int64_t *c_in
     auto fill = [=](double *K, int64_t ldk) {
         return sparse_kmm(ctx, c_indptr, c_indices, c_values, M, d, sigma, jitter, K, ldk);
     };
-    return precond_build_from(ctx, M, fill, lambda, jitter, true, out, bad_pivot_or_null);
+    return precond_build_from(ctx, M, fill, lambda, jitter, second_factor, pooled, out, bad_pivot_or_null);
+}
+
+int precond_build_csr(knm_ctx *ctx, const int64_t *c_indptr, const int64_t *c_indices, const float *c_values, int64_t M,
+                      int64_t d, float sigma, double lambda, double jitter, knm_precond **out,
+                      int64_t *bad_pivot_or_null)
+{
+    return precond_build_csr_impl(ctx, c_indptr, c_indices, c_values, M, d, sigma, lambda, jitter, true, false, out,
+                                  bad_pivot_or_null);
 }
 
 int precond_get_factors(knm_ctx *ctx, const knm_precond *p, double *T_host, double *A_host)
@@ -1514,17 +1471,18 @@ int precond_solve(knm_ctx *ctx, const knm_precond *p, int transpose, const doubl
     if (!p || !b || !out || t <= 0 || t > knm_max_t()) return fail(ctx, KNM_INVALID_ARG, "bad solve argument");
     if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipSetDevice");
     const int64_t M = p->M;
-    DevBuf bc;
+    DevBuf bc, wc;
     int st = bc.alloc(ctx, sizeof(double) * M * t);
+    if (!st) st = wc.alloc(ctx, sizeof(double) * M * t);
     if (st) return st;
-    double *v = bc.as<double>();
+    double *v = bc.as<double>(), *w = wc.as<double>();
     hipLaunchKernelGGL(f64_rows_to_cols, grid1(M * t), dim3(256), 0, ctx->stream, b, M, t, v, 0);
     if (transpose) {
-        st = tri_solve(ctx, p, p->T, p->Tdinv, true, v, t);
-        if (!st) st = tri_solve(ctx, p, p->A, p->Adinv, true, v, t);
+        st = tri_solve(ctx, p, p->T, p->Tdinv, true, v, w, t);
+        if (!st) st = tri_solve(ctx, p, p->A, p->Adinv, true, w, v, t);
     } else {
-        st = tri_solve(ctx, p, p->A, p->Adinv, false, v, t);
-        if (!st) st = tri_solve(ctx, p, p->T, p->Tdinv, false, v, t);
+        st = tri_solve(ctx, p, p->A, p->Adinv, false, v, w, t);
+        if (!st) st = tri_solve(ctx, p, p->T, p->Tdinv, false, w, v, t);
     }
     if (st) return st;
     hipLaunchKernelGGL(f64_rows_to_cols, grid1(M * t), dim3(256), 0, ctx->stream, v, M, t, out, 1);
@@ -1540,9 +1498,14 @@ int precond_reweight(knm_ctx *ctx, knm_precond *p, double lambda, const double *
     if (!p || !(lambda >= 0.0)) return fail(ctx, KNM_INVALID_ARG, "bad preconditioner argument");
     if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipSetDevice");
     int st = KNM_OK;
-    int64_t bad = 0;
-    st = build_second_factor(ctx, p, lambda, dw_or_null, &bad);
-    if (bad_pivot_or_null) *bad_pivot_or_null = -bad;
+    DevBuf badbuf;
+    st = badbuf.alloc(ctx, sizeof(unsigned long long));
+    if (st) return st;
+    int64_t pivot = 0;
+    st = build_second_factor(ctx, p, lambda, dw_or_null, badbuf.as<unsigned long long>());
+    if (!st) st = read_bad_pivots(ctx, badbuf.as<unsigned long long>(), 1, &pivot);
+    if (bad_pivot_or_null) *bad_pivot_or_null = -pivot;
+    if (!st && pivot != 0) st = fail(ctx, KNM_NOT_PD, kSecondNotPd);
     return st;
 }
 
@@ -1562,77 +1525,73 @@ static int fit_core(knm_ctx *ctx, const KernelOps &ops, knm_precond *p, const fl
     int st = KNM_OK;
 
     const int64_t len = M * t;
+    const int blocks = red_blocks(M);
+    const dim3 vgrid((unsigned)blocks, (unsigned)t), vblock(256);
     LinopWork wk;
-    DevBuf beta, r, pv, q, r32;
+    DevBuf beta, r, pv, q, scal;
     st = wk.alloc(ctx, M, t);
     if (!st) st = beta.alloc(ctx, sizeof(double) * len);
     if (!st) st = r.alloc(ctx, sizeof(double) * len);
     if (!st) st = pv.alloc(ctx, sizeof(double) * len);
     if (!st) st = q.alloc(ctx, sizeof(double) * len);
-    if (!st) st = r32.alloc(ctx, sizeof(float) * len);
+    // r . r of every iteration and column, then the partials of p . q and r . r
+    if (!st) st = scal.alloc(ctx, sizeof(double) * ((size_t)(iters + 1) * t + 2 * (size_t)blocks * t));
+    for (int i = 0; !st && i < 2; ++i)
+        if (!ctx->fit_ev[i] && hipEventCreate(&ctx->fit_ev[i]) != hipSuccess) st = fail(ctx, KNM_HIP_ERROR, "hipEventCreate");
     if (st) return st;
     double *db = beta.as<double>(), *dr = r.as<double>(), *dp = pv.as<double>(), *dq = q.as<double>();
+    double *rho = scal.as<double>(), *part_pq = rho + (size_t)(iters + 1) * t, *part_rr = part_pq + (size_t)blocks * t;
 
     // rhs = A^-T T^-T K_nm^T Y
     CrossTermScope cross(ctx);
     st = cross.begin();
     if (st) return st;
-    st = t_w_cols(ctx, ops, Y, nullptr, t, r32.as<float>(), wk.u64.as<double>(), dr);
+    st = t_w_cols(ctx, ops, Y, nullptr, t, wk.u32.as<float>(), wk.u64.as<double>(), wk.c.as<double>());
     if (st) return st;
     bool repeat = false;
     st = cross.check(&repeat);
-    if (!st && repeat) st = t_w_cols(ctx, ops, Y, nullptr, t, r32.as<float>(), wk.u64.as<double>(), dr);
+    if (!st && repeat) st = t_w_cols(ctx, ops, Y, nullptr, t, wk.u32.as<float>(), wk.u64.as<double>(), wk.c.as<double>());
     if (st) return st;
-    st = tri_solve(ctx, p, p->T, p->Tdinv, true, dr, t);
-    if (!st) st = tri_solve(ctx, p, p->A, p->Adinv, true, dr, t);
+    st = tri_solve(ctx, p, p->T, p->Tdinv, true, wk.c.as<double>(), wk.w.as<double>(), t);
+    if (!st) st = tri_solve(ctx, p, p->A, p->Adinv, true, wk.w.as<double>(), dr, t);
     if (st) return st;
     hipError_t e = hipMemsetAsync(db, 0, sizeof(double) * len, ctx->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(dp, dr, sizeof(double) * len, hipMemcpyDeviceToDevice, ctx->stream);
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "CG initialisation", e);
-
-    auto vec_ok = [&](int status) { return status == KNM_OK; };
-    std::vector<double> rho(t), pq(t);
-    for (int c = 0; c < t; ++c) {
-        if (!vec_ok(vec_dot(ctx, M, dr + c * M, dr + c * M, &rho[c])))
-            return fail(ctx, KNM_HIP_ERROR, "vector reduction");
-        if (resid_norms_or_null) resid_norms_or_null[c] = std::sqrt(rho[c]);
-    }
-    const clk::time_point t_rhs = clk::now(); // the host-pointer dot products above synchronise
+    hipLaunchKernelGGL(dot_partial_kernel, vgrid, vblock, 0, ctx->stream, dr, dr, M, part_rr);
+    hipLaunchKernelGGL(dot_finish_kernel, dim3((unsigned)t), dim3(64), 0, ctx->stream, part_rr, blocks, 1.0, rho);
+    (void)hipEventRecord(ctx->fit_ev[0], ctx->stream);
     for (int it = 0; it < iters; ++it) {
         TraceRange range("knm CG iteration");
         st = linop_cols(ctx, p, wk, ops, lambda, dp, t, dq);
         if (st) return st;
-        for (int c = 0; c < t; ++c) {
-            double *pc = dp + c * M, *qc = dq + c * M, *rc = dr + c * M, *bc = db + c * M;
-            if (!vec_ok(vec_dot(ctx, M, pc, qc, &pq[c]))) return fail(ctx, KNM_HIP_ERROR, "vector reduction");
-            const double a = (pq[c] != 0.0) ? rho[c] / pq[c] : 0.0;
-            const double ma = -a;
-            double rn = 0.0;
-            if (!vec_ok(vec_axpy(ctx, M, a, pc, bc)) ||
-                !vec_ok(vec_axpy(ctx, M, ma, qc, rc)) ||
-                !vec_ok(vec_dot(ctx, M, rc, rc, &rn)))
-                return fail(ctx, KNM_HIP_ERROR, "CG vector update");
-            const double b = (rho[c] != 0.0) ? rn / rho[c] : 0.0;
-            const double one = 1.0;
-            if (!vec_ok(vec_scal(ctx, M, b, pc)) ||
-                !vec_ok(vec_axpy(ctx, M, one, rc, pc)))
-                return fail(ctx, KNM_HIP_ERROR, "CG vector update");
-            rho[c] = rn;
-            if (resid_norms_or_null) resid_norms_or_null[(int64_t)(it + 1) * t + c] = std::sqrt(rn);
-        }
+        const double *now = rho + (size_t)it * t;
+        hipLaunchKernelGGL(dot_partial_kernel, vgrid, vblock, 0, ctx->stream, dp, dq, M, part_pq);
+        hipLaunchKernelGGL(cg_step_kernel, vgrid, vblock, 0, ctx->stream, M, now, part_pq, dp, dq, db, dr, part_rr);
+        hipLaunchKernelGGL(cg_direction_kernel, vgrid, vblock, 0, ctx->stream, M, now, rho + (size_t)(it + 1) * t, part_rr, dr, dp);
     }
     // alpha = T^-1 A^-1 beta
-    st = tri_solve(ctx, p, p->A, p->Adinv, false, db, t);
-    if (!st) st = tri_solve(ctx, p, p->T, p->Tdinv, false, db, t);
+    st = tri_solve(ctx, p, p->A, p->Adinv, false, db, wk.v.as<double>(), t);
+    if (!st) st = tri_solve(ctx, p, p->T, p->Tdinv, false, wk.v.as<double>(), wk.w.as<double>(), t, nullptr, 0.0, t == 1 ? alpha : nullptr);
     if (st) return st;
-    hipLaunchKernelGGL(f64_cols_to_f32_rows, grid1(len), dim3(256), 0, ctx->stream, db, M, t, alpha);
-    const clk::time_point t_iters = clk::now(); // each iteration ends with synchronising dot products
-    e = hipStreamSynchronize(ctx->stream); // temporaries are freed on return
+    if (t > 1) hipLaunchKernelGGL(f64_cols_to_f32_rows, grid1(len), dim3(256), 0, ctx->stream, wk.w.as<double>(), M, t, alpha);
+    (void)hipEventRecord(ctx->fit_ev[1], ctx->stream);
+    if (resid_norms_or_null)
+        e = hipMemcpyAsync(resid_norms_or_null, rho, sizeof(double) * (size_t)(iters + 1) * t, hipMemcpyDeviceToHost, ctx->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream); // the caller's arrays are written, the temporaries done with
+    if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "falkon_fit", e);
+    if (resid_norms_or_null)
+        for (int64_t i = 0; i < (int64_t)(iters + 1) * t; ++i) resid_norms_or_null[i] = std::sqrt(resid_norms_or_null[i]);
+    const clk::time_point t_end = clk::now();
+    // the iterations run asynchronously: their time is the device's, the right-hand side has what is left
+    float iter_ms = 0.0f;
+    (void)hipEventElapsedTime(&iter_ms, ctx->fit_ev[0], ctx->fit_ev[1]);
+    const double after = secs(t_precond, t_end), its = 1.0e-3 * (double)iter_ms < after ? 1.0e-3 * (double)iter_ms : after;
     ctx->fit_seconds[0] = secs(t_start, t_precond);
-    ctx->fit_seconds[1] = secs(t_precond, t_rhs);
-    ctx->fit_seconds[2] = secs(t_rhs, t_iters);
-    ctx->fit_seconds[3] = secs(t_iters, clk::now());
+    ctx->fit_seconds[1] = after - its;
+    ctx->fit_seconds[2] = its;
+    ctx->fit_seconds[3] = 0.0;
     return KNM_OK;
 }
 
@@ -1648,7 +1607,7 @@ int falkon_fit(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx, cons
     if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipSetDevice");
     const std::chrono::steady_clock::time_point t_start = std::chrono::steady_clock::now();
     knm_precond *p = nullptr;
-    int st = precond_build(ctx, C, M, d, ldc, sigma, lambda, jitter, &p, nullptr); // synchronises
+    int st = precond_build_impl(ctx, C, M, d, ldc, sigma, lambda, jitter, true, true, &p, nullptr); // synchronises
     if (st) return st;
     return fit_core(ctx, dense_ops(ctx, X, n, d, ldx, C, M, ldc, sigma), p, Y, t, lambda, iters, alpha,
                     resid_norms_or_null, t_start);
@@ -1671,7 +1630,7 @@ int falkon_fit_csr(knm_ctx *ctx, const int64_t *x_indptr, const int64_t *x_indic
     int st = sp.prepare(ctx, x_indptr, x_indices, x_values, n, c_indptr, c_indices, c_values, M, d, sigma);
     if (st) return st;
     knm_precond *p = nullptr;
-    st = precond_build_csr(ctx, c_indptr, c_indices, c_values, M, d, sigma, lambda, jitter, &p, nullptr);
+    st = precond_build_csr_impl(ctx, c_indptr, c_indices, c_values, M, d, sigma, lambda, jitter, true, true, &p, nullptr);
     if (st) return st;
     KernelOps ops;
     ops.n = n;
@@ -1727,8 +1686,12 @@ static int logfalkon_core(knm_ctx *ctx, const KernelOps &ops, const std::functio
         ~Guard() { precond_free(p); }
     } guard{p};
 
+    const int blocks = red_blocks(M), loss_blocks = kMaxRedBlocks;
+    const dim3 vgrid((unsigned)blocks), vblock(256);
+    int max_iters = 0;
+    for (int k = 0; k < n_steps; ++k) max_iters = iters[k] > max_iters ? iters[k] : max_iters;
     LinopWork wk;
-    DevBuf a64, a32, z, zc, g, dw, dm, lossv, u32, beta, r, pv, q;
+    DevBuf a64, a32, z, zc, g, dw, dm, lossv, beta, r, pv, q, scal, badbuf;
     st = wk.alloc(ctx, M, 1);
     if (!st) st = a64.alloc(ctx, sizeof(double) * M);
     if (!st) st = a32.alloc(ctx, sizeof(float) * M);
@@ -1738,19 +1701,22 @@ static int logfalkon_core(knm_ctx *ctx, const KernelOps &ops, const std::functio
     if (!st) st = dw.alloc(ctx, sizeof(float) * n);
     if (!st) st = dm.alloc(ctx, sizeof(double) * M);
     if (!st && loss_or_null) st = lossv.alloc(ctx, sizeof(double) * n);
-    if (!st) st = u32.alloc(ctx, sizeof(float) * M);
     if (!st) st = beta.alloc(ctx, sizeof(double) * M);
     if (!st) st = r.alloc(ctx, sizeof(double) * M);
     if (!st) st = pv.alloc(ctx, sizeof(double) * M);
     if (!st) st = q.alloc(ctx, sizeof(double) * M);
+    // mean losses, r . r of every iteration of a step, partials of p . q, of r . r and of the loss
+    if (!st) st = scal.alloc(ctx, sizeof(double) * ((size_t)n_steps + 1 + max_iters + 1 + 2 * blocks + loss_blocks));
+    if (!st) st = badbuf.alloc(ctx, sizeof(unsigned long long));
     if (st) return st;
     double *da = a64.as<double>(), *db = beta.as<double>(), *dr = r.as<double>(), *dp = pv.as<double>(),
            *dq = q.as<double>();
+    double *losses = scal.as<double>(), *rho = losses + n_steps + 1, *part_pq = rho + max_iters + 1, *part_rr = part_pq + blocks,
+           *part_loss = part_rr + blocks;
     hipError_t e = hipMemsetAsync(da, 0, sizeof(double) * M, ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(a32.p, 0, sizeof(float) * M, ctx->stream);
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipMemsetAsync", e);
-    auto vec_ok = [&](int status) { return status == KNM_OK; };
-    // predictions at the rows and at the centres for the current alpha, and the loss terms
+    // predictions at the rows for the current alpha and the loss terms, the mean loss to `mean_loss` (device, or null)
     auto evaluate = [&](bool derivatives, double *mean_loss) -> int {
         int s2 = ops.v(a32.as<float>(), 1, z.as<float>());
         if (s2) return s2;
@@ -1758,18 +1724,11 @@ static int logfalkon_core(knm_ctx *ctx, const KernelOps &ops, const std::functio
                            derivatives ? g.as<float>() : nullptr, derivatives ? dw.as<float>() : nullptr,
                            (double *)nullptr, mean_loss ? lossv.as<double>() : nullptr);
         if (mean_loss) {
-            // sum in pieces that fit the 32-bit BLAS interface
-            double total = 0.0;
-            for (int64_t o = 0; o < n; o += (1 << 30)) {
-                const int64_t len = (n - o < (1 << 30)) ? n - o : (1 << 30);
-                double part = 0.0;
-                if (!vec_ok(vec_dot(ctx, len, lossv.as<double>() + o, nullptr, &part)))
-                    return fail(ctx, KNM_HIP_ERROR, "loss reduction");
-                total += part;
-            }
-            *mean_loss = total / (double)n;
+            hipLaunchKernelGGL(dot_partial_kernel, dim3((unsigned)loss_blocks), dim3(256), 0, ctx->stream, lossv.as<double>(),
+                               (const double *)nullptr, n, part_loss);
+            hipLaunchKernelGGL(dot_finish_kernel, dim3(1), dim3(64), 0, ctx->stream, part_loss, loss_blocks, 1.0 / (double)n, mean_loss);
         }
-        return KNM_OK;
+        return hipGetLastError() == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "loss terms launch");
     };
 
     CrossTermScope cross(ctx);
@@ -1777,12 +1736,12 @@ static int logfalkon_core(knm_ctx *ctx, const KernelOps &ops, const std::functio
     if (st) return st;
     for (int k = 0; k < n_steps; ++k) {
         const double mu = lambdas[k];
-        st = evaluate(true, loss_or_null ? loss_or_null + k : nullptr);
+        st = evaluate(true, loss_or_null ? losses + k : nullptr);
         if (st) return st;
         if (k == 0) {
             bool repeat = false;
             st = cross.check(&repeat);
-            if (!st && repeat) st = evaluate(true, loss_or_null ? loss_or_null : nullptr);
+            if (!st && repeat) st = evaluate(true, loss_or_null ? losses : nullptr);
             if (st) return st;
         }
         // weights at the centres -> second factor of the preconditioner for this step
@@ -1790,52 +1749,46 @@ static int logfalkon_core(knm_ctx *ctx, const KernelOps &ops, const std::functio
         if (st) return st;
         hipLaunchKernelGGL(logistic_terms_kernel, grid1(M), dim3(256), 0, ctx->stream, zc.as<float>(), yC, M,
                            (float *)nullptr, (float *)nullptr, dm.as<double>(), (double *)nullptr);
-        int64_t bad = 0;
-        st = build_second_factor(ctx, p, mu, dm.as<double>(), &bad);
+        st = build_second_factor(ctx, p, mu, dm.as<double>(), badbuf.as<unsigned long long>());
         if (st) return st;
         // right-hand side  -P^T (K^T g + mu n (K_MM + eps I) alpha)
-        st = ops.t_w(g.as<float>(), nullptr, 1, u32.as<float>());
+        st = ops.t_w(g.as<float>(), nullptr, 1, wk.u32.as<float>());
         if (st) return st;
-        hipLaunchKernelGGL(newton_rhs_kernel, grid1(M), dim3(256), 0, ctx->stream, u32.as<float>(), zc.as<float>(), da,
-                           mu * (double)n, jitter, M, dr);
-        st = tri_solve(ctx, p, p->T, p->Tdinv, true, dr, 1);
-        if (!st) st = tri_solve(ctx, p, p->A, p->Adinv, true, dr, 1);
+        hipLaunchKernelGGL(newton_rhs_kernel, grid1(M), dim3(256), 0, ctx->stream, wk.u32.as<float>(), zc.as<float>(), da,
+                           mu * (double)n, jitter, M, wk.c.as<double>());
+        st = tri_solve(ctx, p, p->T, p->Tdinv, true, wk.c.as<double>(), wk.w.as<double>(), 1);
+        if (!st) st = tri_solve(ctx, p, p->A, p->Adinv, true, wk.w.as<double>(), dr, 1);
+        // (the host looks at the factorisation here, with the work up to the right-hand side already queued)
+        int64_t pivot = 0;
+        if (!st) st = read_bad_pivots(ctx, badbuf.as<unsigned long long>(), 1, &pivot);
+        if (!st && pivot != 0) st = fail(ctx, KNM_NOT_PD, kSecondNotPd);
         if (st) return st;
         e = hipMemsetAsync(db, 0, sizeof(double) * M, ctx->stream);
         if (e == hipSuccess) e = hipMemcpyAsync(dp, dr, sizeof(double) * M, hipMemcpyDeviceToDevice, ctx->stream);
         if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "CG initialisation", e);
-        double rho = 0.0;
-        if (!vec_ok(vec_dot(ctx, M, dr, dr, &rho))) return fail(ctx, KNM_HIP_ERROR, "vector reduction");
+        hipLaunchKernelGGL(dot_partial_kernel, vgrid, vblock, 0, ctx->stream, dr, dr, M, part_rr);
+        hipLaunchKernelGGL(dot_finish_kernel, dim3(1), dim3(64), 0, ctx->stream, part_rr, blocks, 1.0, rho);
         for (int it = 0; it < iters[k]; ++it) {
             st = linop_cols(ctx, p, wk, ops, mu, dp, 1, dq, dw.as<float>());
             if (st) return st;
-            double pq = 0.0, rn = 0.0;
-            if (!vec_ok(vec_dot(ctx, M, dp, dq, &pq))) return fail(ctx, KNM_HIP_ERROR, "vector reduction");
-            const double a = (pq != 0.0) ? rho / pq : 0.0, ma = -a, one = 1.0;
-            if (!vec_ok(vec_axpy(ctx, M, a, dp, db)) ||
-                !vec_ok(vec_axpy(ctx, M, ma, dq, dr)) ||
-                !vec_ok(vec_dot(ctx, M, dr, dr, &rn)))
-                return fail(ctx, KNM_HIP_ERROR, "CG vector update");
-            const double b = (rho != 0.0) ? rn / rho : 0.0;
-            if (!vec_ok(vec_scal(ctx, M, b, dp)) ||
-                !vec_ok(vec_axpy(ctx, M, one, dr, dp)))
-                return fail(ctx, KNM_HIP_ERROR, "CG vector update");
-            rho = rn;
+            hipLaunchKernelGGL(dot_partial_kernel, vgrid, vblock, 0, ctx->stream, dp, dq, M, part_pq);
+            hipLaunchKernelGGL(cg_step_kernel, vgrid, vblock, 0, ctx->stream, M, rho + it, part_pq, dp, dq, db, dr, part_rr);
+            hipLaunchKernelGGL(cg_direction_kernel, vgrid, vblock, 0, ctx->stream, M, rho + it, rho + it + 1, part_rr, dr, dp);
         }
         // alpha += T^-1 A^-1 beta
-        st = tri_solve(ctx, p, p->A, p->Adinv, false, db, 1);
-        if (!st) st = tri_solve(ctx, p, p->T, p->Tdinv, false, db, 1);
+        st = tri_solve(ctx, p, p->A, p->Adinv, false, db, wk.v.as<double>(), 1);
+        if (!st) st = tri_solve(ctx, p, p->T, p->Tdinv, false, wk.v.as<double>(), wk.w.as<double>(), 1);
         if (st) return st;
-        const double one = 1.0;
-        if (!vec_ok(vec_axpy(ctx, M, one, db, da))) return fail(ctx, KNM_HIP_ERROR, "vector update");
-        hipLaunchKernelGGL(f64_to_f32_kernel, grid1(M), dim3(256), 0, ctx->stream, da, M, a32.as<float>());
+        hipLaunchKernelGGL(add_round_kernel, grid1(M), dim3(256), 0, ctx->stream, M, wk.w.as<double>(), da, a32.as<float>());
     }
     if (loss_or_null) {
-        st = evaluate(false, loss_or_null + n_steps);
+        st = evaluate(false, losses + n_steps);
         if (st) return st;
+        e = hipMemcpyAsync(loss_or_null, losses, sizeof(double) * ((size_t)n_steps + 1), hipMemcpyDeviceToHost, ctx->stream);
     }
-    e = hipMemcpyAsync(alpha, a32.p, sizeof(float) * M, hipMemcpyDeviceToDevice, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream); // temporaries are freed on return
+    if (e == hipSuccess) e = hipMemcpyAsync(alpha, a32.p, sizeof(float) * M, hipMemcpyDeviceToDevice, ctx->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream); // the caller's arrays are written, the temporaries done with
+    if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "logfalkon_fit", e);
     return KNM_OK;
 }
@@ -1856,7 +1809,7 @@ int logfalkon_fit(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx, c
     int st = KNM_OK;
     // T depends on the centres only: built once; A is rebuilt per Newton step
     knm_precond *p = nullptr;
-    st = precond_build_impl(ctx, C, M, d, ldc, sigma, lambdas[0], jitter, false, &p, nullptr);
+    st = precond_build_impl(ctx, C, M, d, ldc, sigma, lambdas[0], jitter, false, true, &p, nullptr);
     if (st) return st;
     const KernelOps ops = dense_ops(ctx, X, n, d, ldx, C, M, ldc, sigma);
     auto centres_v = [=](const float *a, float *zc) { return do_knm_v(ctx, C, M, d, ldc, C, M, ldc, sigma, a, 1, zc); };
@@ -1882,10 +1835,7 @@ int logfalkon_fit_csr(knm_ctx *ctx, const int64_t *x_indptr, const int64_t *x_in
     if (!st) st = spc.prepare(ctx, c_indptr, c_indices, c_values, M, c_indptr, c_indices, c_values, M, d, sigma);
     if (st) return st;
     knm_precond *p = nullptr;
-    auto fill = [=](double *K, int64_t ldk) {
-        return sparse_kmm(ctx, c_indptr, c_indices, c_values, M, d, sigma, jitter, K, ldk);
-    };
-    st = precond_build_from(ctx, M, fill, lambdas[0], jitter, false, &p, nullptr);
+    st = precond_build_csr_impl(ctx, c_indptr, c_indices, c_values, M, d, sigma, lambdas[0], jitter, false, true, &p, nullptr);
     if (st) return st;
     KernelOps ops;
     ops.n = n;

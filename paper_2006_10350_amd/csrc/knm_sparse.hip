@@ -594,13 +594,6 @@ __global__ void weigh_kernel(const float *__restrict__ x, int64_t ldx, const flo
     if (r < rows) out[r] = w[r] * x[r * ldx];
 }
 
-struct DevMem {
-    void *p = nullptr;
-    ~DevMem() { if (p) (void)hipFree(p); }
-    hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 1); }
-    template <class T> T *as() { return static_cast<T *>(p); }
-};
-
 // structure check of one CSR matrix before anything indexes with the caller's numbers; *nnz_out
 // receives indptr[rows]
 int check_csr(knm_ctx *ctx, const int64_t *indptr, const int64_t *indices, int64_t rows, int64_t d, int64_t *nnz_out)
@@ -611,8 +604,8 @@ int check_csr(knm_ctx *ctx, const int64_t *indptr, const int64_t *indices, int64
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "reading the CSR size", e);
     if (nnz < 0 || nnz >= 0x7fffffffLL * 64) return fail(ctx, KNM_INVALID_ARG, "bad CSR size");
-    DevMem flag;
-    if (flag.alloc(sizeof(int)) != hipSuccess) return fail(ctx, KNM_ALLOC, "hipMalloc");
+    DevBuf flag;
+    if (flag.alloc(ctx, sizeof(int)) != hipSuccess) return fail(ctx, KNM_ALLOC, "hipMalloc");
     int bad = 0;
     e = hipMemsetAsync(flag.p, 0, sizeof(int), st);
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipMemsetAsync", e);
@@ -629,17 +622,17 @@ int check_csr(knm_ctx *ctx, const int64_t *indptr, const int64_t *indices, int64
 
 // CSC image of the centres: col_ptr (d + 1), csc_row / csc_val (nnz_c)
 struct CentreLists {
-    DevMem col_ptr, csc_row, csc_val;
+    DevBuf col_ptr, csc_row, csc_val;
     int build(knm_ctx *ctx, const int64_t *c_indptr, const int64_t *c_indices, const float *c_values, int64_t M,
               int64_t d, int64_t nnz_c)
     {
         hipStream_t st = ctx->stream;
         if (nnz_c >= 0x7fffffffLL) return fail(ctx, KNM_UNSUPPORTED, "more than 2^31 - 2 stored entries in C");
-        DevMem cursor, sums;
+        DevBuf cursor, sums;
         const int64_t scan_blocks = (d + 1 + kScanChunk - 1) / kScanChunk;
-        if (col_ptr.alloc(sizeof(int) * (d + 1)) != hipSuccess || cursor.alloc(sizeof(int) * (d + 1)) != hipSuccess ||
-            sums.alloc(sizeof(int) * scan_blocks) != hipSuccess || csc_row.alloc(sizeof(int) * nnz_c) != hipSuccess ||
-            csc_val.alloc(sizeof(float) * nnz_c) != hipSuccess) {
+        if (col_ptr.alloc(ctx, sizeof(int) * (d + 1)) != hipSuccess || cursor.alloc(ctx, sizeof(int) * (d + 1)) != hipSuccess ||
+            sums.alloc(ctx, sizeof(int) * scan_blocks) != hipSuccess || csc_row.alloc(ctx, sizeof(int) * nnz_c) != hipSuccess ||
+            csc_val.alloc(ctx, sizeof(float) * nnz_c) != hipSuccess) {
             (void)hipGetLastError();
             return fail(ctx, KNM_ALLOC, "hipMalloc(centre lists)");
         }
@@ -664,9 +657,7 @@ struct CentreLists {
                 hipLaunchKernelGGL(csc_fill_kernel, grid_for(q1 - q0), dim3(256), 0, st, c_indptr, c_indices, c_values, r0,
                                    r1, q0, q1, cursor.as<int>(), csc_row.as<int>(), csc_val.as<float>());
         }
-        e = hipStreamSynchronize(st); // cursor and sums are freed on return
-        if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "centre lists", e);
-        return KNM_OK;
+        return hipGetLastError() == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "centre lists launch");
     }
 };
 
@@ -682,14 +673,14 @@ struct SparseProducts::Impl {
     float inv2s2 = 0.0f, inv_s2 = 0.0f;
     int64_t wgs = 0;
     CentreLists lists;
-    DevMem xn, cn, xa, cb, acc, part, tmp, work_count, work_pairs, work_q0, work_len, work_val;
+    DevBuf xn, cn, xa, cb, acc, part, tmp, work_count, work_pairs, work_q0, work_len, work_val;
     // head features: dense head parts XH (n x Hn), CH (M x Hn), factors of the tail norms, per-row
     // head counts, and the vectors of the dense product (tmp_m over the centres, dense_n / tmp_n over
     // the rows)
     int Hn = 0;
     float sigma = 0.0f;
-    DevMem head_feat, head_count, XH, CH, xat, cbt, tmp_m, dense_n, dense_m, tmp_n;
-    DevMem col_base, col_scattered; // column sweep: all-pairs part and scattered terms, fp64 over the centres
+    DevBuf head_feat, head_count, XH, CH, xat, cbt, tmp_m, dense_n, dense_m, tmp_n;
+    DevBuf col_base, col_scattered; // column sweep: all-pairs part and scattered terms, fp64 over the centres
 
     int rank_one_sum(const float *ev, const float *vec, int64_t ldv, int64_t rows, double *out)
     {
@@ -717,8 +708,8 @@ struct SparseProducts::Impl {
         if (max_head <= 0 || nnz_c < min_len) return KNM_OK;
         if (max_head > kMaxHead) max_head = kMaxHead;
         const int cap = (int)(nnz_c / min_len) + 1; // no more features than this can have such lists
-        DevMem count, cand;
-        if (count.alloc(sizeof(int)) != hipSuccess || cand.alloc(sizeof(int) * 3 * (size_t)cap) != hipSuccess) {
+        DevBuf count, cand;
+        if (count.alloc(ctx, sizeof(int)) != hipSuccess || cand.alloc(ctx, sizeof(int) * 3 * (size_t)cap) != hipSuccess) {
             (void)hipGetLastError();
             return fail(ctx, KNM_ALLOC, "hipMalloc(head candidates)");
         }
@@ -755,11 +746,11 @@ struct SparseProducts::Impl {
             feats[h] = h < Hn ? cs[h].feat : 0;
             if (hl.len[h] > longest) longest = hl.len[h];
         }
-        if (head_feat.alloc(sizeof(int) * kMaxHead) != hipSuccess || CH.alloc(sizeof(float) * (size_t)M * Hn) != hipSuccess ||
-            XH.alloc(sizeof(float) * (size_t)n * Hn) != hipSuccess || xat.alloc(sizeof(float) * n) != hipSuccess ||
-            cbt.alloc(sizeof(float) * M) != hipSuccess || tmp_m.alloc(sizeof(float) * M) != hipSuccess ||
-            dense_m.alloc(sizeof(float) * M) != hipSuccess || dense_n.alloc(sizeof(float) * n) != hipSuccess ||
-            tmp_n.alloc(sizeof(float) * n) != hipSuccess) {
+        if (head_feat.alloc(ctx, sizeof(int) * kMaxHead) != hipSuccess || CH.alloc(ctx, sizeof(float) * (size_t)M * Hn) != hipSuccess ||
+            XH.alloc(ctx, sizeof(float) * (size_t)n * Hn) != hipSuccess || xat.alloc(ctx, sizeof(float) * n) != hipSuccess ||
+            cbt.alloc(ctx, sizeof(float) * M) != hipSuccess || tmp_m.alloc(ctx, sizeof(float) * M) != hipSuccess ||
+            dense_m.alloc(ctx, sizeof(float) * M) != hipSuccess || dense_n.alloc(ctx, sizeof(float) * n) != hipSuccess ||
+            tmp_n.alloc(ctx, sizeof(float) * n) != hipSuccess) {
             (void)hipGetLastError();
             return fail(ctx, KNM_ALLOC, "hipMalloc(head features)");
         }
@@ -801,11 +792,7 @@ struct SparseProducts::Impl {
 };
 
 SparseProducts::SparseProducts() : impl(new Impl()) {}
-SparseProducts::~SparseProducts()
-{
-    if (impl && impl->ctx) (void)hipStreamSynchronize(impl->ctx->stream); // kernels may still use the workspace
-    delete impl;
-}
+SparseProducts::~SparseProducts() { delete impl; }
 
 int SparseProducts::prepare(knm_ctx *ctx, const int64_t *x_indptr, const int64_t *x_indices, const float *x_values,
                             int64_t n, const int64_t *c_indptr, const int64_t *c_indices, const float *c_values,
@@ -832,11 +819,11 @@ int SparseProducts::prepare(knm_ctx *ctx, const int64_t *x_indptr, const int64_t
     s.wgs = (n + kSpWaves - 1) / kSpWaves;
     if (s.wgs > 2048) s.wgs = 2048; // 8 workgroups per CU: the sweep is bound by memory latency
     const int64_t waves = s.wgs * kSpWaves;
-    if (s.xn.alloc(sizeof(float) * n) != hipSuccess || s.cn.alloc(sizeof(float) * M) != hipSuccess ||
-        s.xa.alloc(sizeof(float) * n) != hipSuccess || s.cb.alloc(sizeof(float) * M) != hipSuccess ||
-        s.acc.alloc(sizeof(float) * waves * M) != hipSuccess || s.part.alloc(sizeof(double) * 256) != hipSuccess ||
-        s.tmp.alloc(sizeof(float) * n) != hipSuccess || s.col_base.alloc(sizeof(double) * M) != hipSuccess ||
-        s.col_scattered.alloc(sizeof(double) * M) != hipSuccess) {
+    if (s.xn.alloc(ctx, sizeof(float) * n) != hipSuccess || s.cn.alloc(ctx, sizeof(float) * M) != hipSuccess ||
+        s.xa.alloc(ctx, sizeof(float) * n) != hipSuccess || s.cb.alloc(ctx, sizeof(float) * M) != hipSuccess ||
+        s.acc.alloc(ctx, sizeof(float) * waves * M) != hipSuccess || s.part.alloc(ctx, sizeof(double) * 256) != hipSuccess ||
+        s.tmp.alloc(ctx, sizeof(float) * n) != hipSuccess || s.col_base.alloc(ctx, sizeof(double) * M) != hipSuccess ||
+        s.col_scattered.alloc(ctx, sizeof(double) * M) != hipSuccess) {
         (void)hipGetLastError();
         return fail(ctx, KNM_ALLOC, "hipMalloc(sparse workspace)");
     }
@@ -851,10 +838,10 @@ int SparseProducts::prepare(knm_ctx *ctx, const int64_t *x_indptr, const int64_t
     stat = s.choose_head(d, nnz_c, ctx->sparse_head_max, &head_min_len);
     if (stat) return stat;
     const size_t work = (size_t)(nnz_x > 0 ? nnz_x : 1);
-    if (s.work_count.alloc(sizeof(int) * n) != hipSuccess || s.head_count.alloc(sizeof(int) * n) != hipSuccess ||
-        s.work_pairs.alloc(sizeof(int) * n) != hipSuccess ||
-        s.work_q0.alloc(sizeof(int) * work) != hipSuccess || s.work_len.alloc(sizeof(int) * work) != hipSuccess ||
-        s.work_val.alloc(sizeof(float) * work) != hipSuccess) {
+    if (s.work_count.alloc(ctx, sizeof(int) * n) != hipSuccess || s.head_count.alloc(ctx, sizeof(int) * n) != hipSuccess ||
+        s.work_pairs.alloc(ctx, sizeof(int) * n) != hipSuccess ||
+        s.work_q0.alloc(ctx, sizeof(int) * work) != hipSuccess || s.work_len.alloc(ctx, sizeof(int) * work) != hipSuccess ||
+        s.work_val.alloc(ctx, sizeof(float) * work) != hipSuccess) {
         (void)hipGetLastError();
         return fail(ctx, KNM_ALLOC, "hipMalloc(sparse work list)");
     }
@@ -983,8 +970,8 @@ int sparse_kmm(knm_ctx *ctx, const int64_t *c_indptr, const int64_t *c_indices, 
     int64_t wgs = (M + kSpWaves - 1) / kSpWaves;
     if (wgs > 1024) wgs = 1024;
     const int64_t waves = wgs * kSpWaves;
-    DevMem cn, acc;
-    if (cn.alloc(sizeof(double) * M) != hipSuccess || acc.alloc(sizeof(double) * waves * M) != hipSuccess) {
+    DevBuf cn, acc;
+    if (cn.alloc(ctx, sizeof(double) * M) != hipSuccess || acc.alloc(ctx, sizeof(double) * waves * M) != hipSuccess) {
         (void)hipGetLastError();
         return fail(ctx, KNM_ALLOC, "hipMalloc(sparse K_MM workspace)");
     }
@@ -994,10 +981,8 @@ int sparse_kmm(knm_ctx *ctx, const int64_t *c_indptr, const int64_t *c_indices, 
     hipLaunchKernelGGL(sparse_kmm_kernel, dim3((unsigned)wgs), dim3(kSpThreads), 0, st, c_indptr, c_indices, c_values, M,
                        lists.col_ptr.as<int>(), lists.csc_row.as<int>(), lists.csc_val.as<float>(), cn.as<double>(),
                        1.0 / (2.0 * (double)sigma * (double)sigma), jitter, acc.as<double>(), K, ldk);
-    e = hipStreamSynchronize(st); // the workspace is freed on return
-    if (e == hipSuccess) e = hipGetLastError();
-    if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "sparse K_MM", e);
-    return KNM_OK;
+    e = hipGetLastError();
+    return e == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "sparse K_MM", e);
 }
 
 } // namespace knm
