@@ -1,6 +1,7 @@
 // C ABI of libknm: context, workspace and the kernel-matrix-vector products.
 #include <dlfcn.h>
 
+#include <cmath>
 #include <cstddef>
 #include <cstdio>
 #include <cstdlib>
@@ -184,31 +185,111 @@ bool use_gemm_engine(int d, int t, int cross_term, int kind)
     return t > 1 || d > (cross_term == KNM_CROSS_F16X3 ? f16_max_d() : small_max_d());
 }
 
-// Chunking of the stream dimension.  More chunks = more workgroups (needed when there
-// are few fixed blocks) and shorter fp32 running sums; each chunk costs one partial
+// Chunking of the stream dimension.  More chunks = more workgroups and shorter fp32 running sums; each chunk costs one partial
 // vector that the merge pass adds up in fp64.
+struct ChunkGrid {
+    int64_t stage, per_block, blocks, stages; // points per stage and per fixed block, fixed blocks, stages in all
+    int64_t min_chunks;
+};
+static ChunkGrid chunk_grid(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind)
+{
+    ChunkGrid g;
+    const bool gemm = use_gemm_engine(d, t, cross_term, kind);
+    g.stage = gemm ? gemm_stage_points() : (cross_term == KNM_CROSS_F16X3 ? f16_stage_points(d, kind) : stage_points());
+    g.per_block = gemm ? gemm_fixed_per_block() : fixed_per_block(d);
+    g.blocks = (nF + g.per_block - 1) / g.per_block;
+    g.stages = (nS + g.stage - 1) / g.stage;
+    const int64_t max_len = (int64_t)1 << 18; // bound the length of a per-lane fp32 running sum
+    g.min_chunks = (nS + max_len - 1) / max_len;
+    return g;
+}
+
+// Chunks of at least 2048 points, 4096 workgroups where the stream is long enough: fewer partials than choose_chunks, for
+// calls whose workspace is limited.
+static int64_t choose_chunks_compact(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind, int64_t *chunk_len)
+{
+    const bool gemm = use_gemm_engine(d, t, cross_term, kind);
+    const ChunkGrid g = chunk_grid(nF, nS, d, t, cross_term, kind);
+    const int64_t min_len = gemm ? 16 * g.stage : 2048;
+    int64_t chunks = (4096 + g.blocks - 1) / g.blocks;
+    if (gemm && chunks < 16) chunks = 16;
+    const int64_t max_chunks_by_len = (nS + min_len - 1) / min_len;
+    if (chunks > max_chunks_by_len) chunks = max_chunks_by_len;
+    if (chunks < g.min_chunks) chunks = g.min_chunks;
+    int64_t len = (nS + chunks - 1) / chunks;
+    len = (len + g.stage - 1) / g.stage * g.stage;
+    *chunk_len = len;
+    return (nS + len - 1) / len;
+}
+
+// The number of chunks is the one with the least estimated time among those that make about 1, 2, ... 16 rounds of the workgroups
+// the chip holds at once (and the smallest numbers): rounds x stages x time of a stage, a round in which at most half of
+// the places are taken counting for less because its workgroups have a CU to themselves; the start and end of a
+// workgroup; and the merge pass.  What counts is that the last round is nearly full: n = 60k, d = 784, M = 10k,
+// 10 columns ran 1175 workgroups of 16 tiles on 512 places, three rounds for the work of 2.3.
 int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind, int64_t *chunk_len)
 {
     const bool gemm = use_gemm_engine(d, t, cross_term, kind);
-    const int64_t stage = gemm ? gemm_stage_points()
-                               : (cross_term == KNM_CROSS_F16X3 ? f16_stage_points(d, kind) : stage_points());
-    const int64_t per_block = gemm ? gemm_fixed_per_block() : fixed_per_block(d);
-    const int64_t blocks = (nF + per_block - 1) / per_block;
-    const int64_t target_wgs = 4096;       // several waves of workgroups over 256 CUs
-    const int64_t min_len = gemm ? 16 * stage : 2048; // amortise the per-workgroup prologue/epilogue
-    const int64_t max_len = (int64_t)1 << 18; // bound the length of a per-lane fp32 running sum
-    int64_t chunks = (target_wgs + blocks - 1) / blocks;
-    if (gemm && chunks < 16) chunks = 16;  // the K-loop engine tiles (fixed blocks x chunks) over each XCD's L2
-    const int64_t max_chunks_by_len = (nS + min_len - 1) / min_len;
-    if (chunks > max_chunks_by_len) chunks = max_chunks_by_len;
-    const int64_t min_chunks_by_len = (nS + max_len - 1) / max_len;
-    if (chunks < min_chunks_by_len) chunks = min_chunks_by_len;
-    if (chunks < 1) chunks = 1;
-    int64_t len = (nS + chunks - 1) / chunks;
-    len = (len + stage - 1) / stage * stage;
-    chunks = (nS + len - 1) / len;
-    *chunk_len = len;
-    return chunks;
+    const bool f16 = cross_term == KNM_CROSS_F16X3;
+    const ChunkGrid g = chunk_grid(nF, nS, d, t, cross_term, kind);
+    // workgroups per CU and microseconds of a stage (K-loop engines: of a tile) of one of them on a full chip, from the rates of
+    // the engines (ps per kernel entry) on large problems
+    int per_cu = 2;
+    double stage_us, wg_us = 4.0;
+    if (gemm) {
+        const double kc = (double)((d + 15) / 16);
+        const int tl = f16 && t > gemm_f16_max_t(kind) ? gemm_f16_max_t(kind) : (!f16 && t > gemm_max_t() ? gemm_max_t() : t);
+        double cycles; // per tile and SIMD
+        if (f16) {
+            per_cu = gemm_f16_workgroups_per_cu(d, tl, kind);
+            const bool mc = gemm_f16_matrix_reduction(d, tl);
+            cycles = 256.0 + 900.0 * kc + (mc ? 3600.0 + 48.0 * 32.0 * ((tl + 31) / 32) : 128.0 * (14.0 + 4.0 * tl));
+        } else {
+            cycles = 4200.0 * kc + 128.0 * (14.0 + 4.0 * tl);
+        }
+        if (kind != KNM_KERNEL_GAUSSIAN) cycles += 128.0 * 16.0;
+        stage_us = per_cu * cycles / 2100.0;
+    } else {
+        if (f16) per_cu = f16_workgroups_per_cu(d, kind);
+        const double ps = (f16 ? (d <= 12 ? 0.106 : d <= 28 ? 0.167 : 0.22) : 0.12 + 0.019 * d) * (kind == KNM_KERNEL_GAUSSIAN ? 1.0 : 1.6);
+        stage_us = 1.0e-6 * ps * (double)(g.stage * g.per_block) * 256.0 * per_cu;
+    }
+    const double slots = 256.0 * per_cu;
+    // partials of more than 48 MB only where the compact rule has them too: the allocation-free call, whose scratch is
+    // 64 MB, then cuts the stream the same way
+    int64_t compact_len = 0;
+    int64_t most = choose_chunks_compact(nF, nS, d, t, cross_term, kind, &compact_len);
+    const int64_t by_bytes = (int64_t)(((size_t)48 << 20) / (sizeof(float) * (size_t)nF * t));
+    if (by_bytes > most) most = by_bytes;
+    double best = 0.0;
+    int64_t best_chunks = 0;
+    auto consider = [&](int64_t chunks) {
+        if (chunks > g.stages) chunks = g.stages;
+        if (chunks > most) chunks = most;
+        if (chunks < g.min_chunks) chunks = g.min_chunks;
+        const int64_t len = (g.stages + chunks - 1) / chunks; // stages per chunk
+        chunks = (g.stages + len - 1) / len;
+        if (chunks == best_chunks || chunks > 65535) return;
+        const double w = (double)(g.blocks * chunks);
+        const double rounds = floor(w / slots), rest = w - rounds * slots;
+        const double load = rounds + (rest == 0.0 ? 0.0 : per_cu > 1 && rest <= 256.0 ? 0.6 : 1.0);
+        double us = load * ((double)len * stage_us) + (rounds + (rest > 0.0 ? 1.0 : 0.0)) * wg_us;
+        // few chunks share less of the fixed points' image in an XCD's L2 (see PatchMap)
+        if (gemm && chunks < 8 && w > 256.0) us *= 1.0 + 0.5 / (double)chunks;
+        if (chunks > 1) us += 3.0 + 1.0e-6 * (double)chunks * (double)nF * (double)t * 4.0 / 3.0;
+        if (best_chunks == 0 || us < best) {
+            best = us;
+            best_chunks = chunks;
+        }
+    };
+    consider(1);
+    if ((double)g.blocks < 32.0 * slots) {
+        for (int k = 2; k <= 16; ++k) consider(k);
+        for (int k = 1; k <= 16; ++k) consider((int64_t)((double)k * slots / (double)g.blocks));
+    }
+    int64_t len = (g.stages + best_chunks - 1) / best_chunks;
+    *chunk_len = len * g.stage;
+    return (g.stages + len - 1) / len;
 }
 
 static bool bad_geom(const void *X, int64_t n, int d, int64_t ldx, const void *C, int64_t M, int64_t ldc,
@@ -217,63 +298,167 @@ static bool bad_geom(const void *X, int64_t n, int d, int64_t ldx, const void *C
     return !X || !C || n <= 0 || M <= 0 || d <= 0 || t <= 0 || ldx < d || ldc < d || !(sigma > 0.0f);
 }
 
-// mu[k] = mean of feature k over `rows` rows of P taken `stride` rows apart (a sample spread over the
-// whole set, so that data stored in some order still gives a representative centre): the common shift
-// of a sweep's two point sets.  One workgroup per 32 features, 32 row lanes per feature with four
-// loads in flight each, fp64 sums in a fixed order.
-constexpr int kMeanRowLanes = 32;
-constexpr int64_t kMeanSample = 16384; // rows of the sample at most
-__global__ __launch_bounds__(32 * kMeanRowLanes) void column_mean_kernel(const float *__restrict__ P, int64_t rows,
-                                                                        int64_t stride, int64_t ld, int d,
-                                                                        float *__restrict__ mu)
+// Common shift of a sweep's two point sets: mu[k] = mean of feature k over `rows` rows of P taken `stride` rows apart (a sample
+// spread over the whole set, so that data stored in some order still gives a representative centre; it only has to
+// be near the middle of the data).  It is kept only where it pays: if the mean itself is within sigma of the origin
+// (|mu|^2 / 2 sigma^2 <= 0.5) the norm terms are small anyway, and mu is set to zero, which leaves the
+// points exactly as they are (data with many exact zeros keeps them: the matrix cores draw less
+// power on such operands, and the sweep runs measurably faster).
+// Workgroup (x, y): features [x << fbits, ...), 256 >> fbits row lanes over row group y; fp64 partials, which the last
+// workgroup to finish (`done` counts and wraps to zero) adds up in a fixed order.  One launch of about 5 us; with one
+// workgroup per 32 features and a second launch for the decision it took 40 us, which is the whole time of a small sweep.
+constexpr int64_t kMeanSample = 4096; // rows of the sample at most
+constexpr int kMeanGroups = 64;       // row groups at most
+__global__ __launch_bounds__(256) void column_shift_kernel(const float *__restrict__ P, int rows, int64_t stride, int64_t ld, int d,
+                                                          float inv2s2, int fbits, double *__restrict__ part, unsigned *__restrict__ done,
+                                                          float *__restrict__ mu)
 {
-    __shared__ double part[kMeanRowLanes][32];
-    const int f = threadIdx.x & 31, rl = threadIdx.x >> 5;
-    const int k = blockIdx.x * 32 + f;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    __shared__ double sh[256];
+    __shared__ bool last;
+    const int tid = threadIdx.x;
+    const int f = tid & ((1 << fbits) - 1), rl = tid >> fbits, lanes = 256 >> fbits;
+    const int k = (blockIdx.x << fbits) + f;
+    const int groups = gridDim.y;
+    const int per = (rows + groups - 1) / groups;
+    const int r1 = (int)(blockIdx.y + 1) * per < rows ? (int)(blockIdx.y + 1) * per : rows;
+    double s = 0.0;
     if (k < d) {
         const float *col = P + k;
         const int64_t step = stride * ld;
-        int64_t r = rl;
-        for (; r + 3 * kMeanRowLanes < rows; r += 4 * kMeanRowLanes) {
-            const float a0 = col[r * step], a1 = col[(r + kMeanRowLanes) * step];
-            const float a2 = col[(r + 2 * kMeanRowLanes) * step], a3 = col[(r + 3 * kMeanRowLanes) * step];
-            s0 += (double)a0;
-            s1 += (double)a1;
-            s2 += (double)a2;
-            s3 += (double)a3;
+        int r = (int)blockIdx.y * per + rl;
+        for (; r + 3 * lanes < r1; r += 4 * lanes) {
+            const float a0 = col[r * step], a1 = col[(r + lanes) * step];
+            const float a2 = col[(r + 2 * lanes) * step], a3 = col[(r + 3 * lanes) * step];
+            s += ((double)a0 + (double)a1) + ((double)a2 + (double)a3);
         }
-        for (; r < rows; r += kMeanRowLanes) s0 += (double)col[r * step];
+        for (; r < r1; r += lanes) s += (double)col[r * step];
     }
-    part[rl][f] = (s0 + s1) + (s2 + s3);
+    sh[tid] = s;
     __syncthreads();
     if (rl == 0 && k < d) {
-        double total = 0.0;
-        for (int i = 0; i < kMeanRowLanes; ++i) total += part[i][f];
-        const float m = (float)(total / (double)rows);
-        mu[k] = (m == m && fabsf(m) < 3.0e38f) ? m : 0.0f; // a NaN or Inf in the data must not spread to every point
+        for (int i = 1; i < lanes; ++i) s += sh[(i << fbits) + f];
+        part[(int64_t)blockIdx.y * d + k] = s;
     }
-}
-
-// Keeps the shift only where it pays: if the mean itself is within sigma of the origin
-// (|mu|^2 / 2 sigma^2 <= 0.5) the norm terms are small anyway, and mu is set to zero, which leaves the
-// points exactly as they are (data with many exact zeros keeps them: the matrix cores draw less
-// power on such operands, and the sweep runs measurably faster).  One workgroup.
-__global__ __launch_bounds__(256) void shift_decide_kernel(float *__restrict__ mu, int d, float inv2s2)
-{
-    __shared__ float part[256];
-    float s = 0.0f;
-    for (int k = threadIdx.x; k < d; k += 256) s = fmaf(mu[k], mu[k], s);
-    part[threadIdx.x] = s;
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) last = atomicInc(done, gridDim.x * gridDim.y - 1) == gridDim.x * gridDim.y - 1;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    double sq = 0.0;
+    for (int c = tid; c < d; c += 256) {
+        double total = 0.0;
+        for (int y = 0; y < groups; ++y) total += part[(int64_t)y * d + c];
+        const float m = (float)(total / (double)rows);
+        const float v = (m == m && fabsf(m) < 3.0e38f) ? m : 0.0f; // a NaN or Inf in the data must not spread to every point
+        mu[c] = v;
+        sq += (double)v * (double)v;
+    }
+    sh[tid] = sq;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+        if (tid < w) sh[tid] += sh[tid + w];
         __syncthreads();
     }
-    const bool keep = part[0] * inv2s2 > 0.5f;
+    const bool keep = sh[0] * (double)inv2s2 > 0.5;
     if (!keep)
-        for (int k = threadIdx.x; k < d; k += 256) mu[k] = 0.0f;
-    if (threadIdx.x == 0) mu[d] = keep ? 1.0f : 0.0f; // lets the hot loops skip the loads of an all-zero shift
+        for (int c = tid; c < d; c += 256) mu[c] = 0.0f;
+    if (tid == 0) mu[d] = keep ? 1.0f : 0.0f; // lets the hot loops skip the loads of an all-zero shift
+}
+// mu_buf: the shift and its flag, then (8-byte aligned) the partials
+static int mean_groups(int64_t rows, int d)
+{
+    int64_t g = (rows + 63) / 64;
+    if (g > kMeanGroups) g = kMeanGroups;
+    if (g * d > 65536) g = 65536 / d > 0 ? 65536 / d : 1;
+    return (int)g;
+}
+static size_t mu_offset(int d) { return (sizeof(float) * ((size_t)d + 1) + 7) & ~(size_t)7; }
+static size_t mu_bytes_wanted(int64_t rows, int d)
+{
+    return mu_offset(d) + sizeof(double) * (size_t)mean_groups(rows < kMeanSample ? rows : kMeanSample, d) * d;
+}
+static int column_shift(knm_ctx *ctx, const float *P, int64_t rows, int64_t ld, int d, float sigma, float *mu)
+{
+    const int64_t stride = (rows + kMeanSample - 1) / kMeanSample; // every stride-th row, spread over the set
+    const int sample = (int)((rows + stride - 1) / stride);
+    const int fbits = d <= 8 ? 3 : d <= 16 ? 4 : 5;
+    double *part = reinterpret_cast<double *>(reinterpret_cast<char *>(mu) + mu_offset(d));
+    hipLaunchKernelGGL(column_shift_kernel, dim3((unsigned)((d + (1 << fbits) - 1) >> fbits), (unsigned)mean_groups(sample, d)), dim3(256),
+                       0, ctx->stream, P, sample, stride, ld, d, 1.0f / (2.0f * sigma * sigma), fbits, part, ctx->range_count + 32, mu);
+    return hipGetLastError() == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "column_shift_kernel launch");
+}
+
+SweepShare::SweepShare(knm_ctx *c, const float *X, int64_t n_, int64_t ldx, const float *C, int64_t M, int64_t ldc, int d_, float sigma_,
+                       int t_, bool pooled_)
+    : ctx(c), P{X, C}, n{n_, M}, ld{ldx, ldc}, d(d_), sigma(sigma_), t(t_), pooled(pooled_)
+{
+}
+SweepShare::~SweepShare()
+{
+    if (pooled)
+        for (void *p : img)
+            if (p) pool_give(ctx, p);
+    if (ctx->mu_owner == this) ctx->mu_owner = nullptr;
+}
+
+// Points the kept image of set k must have room for: as fixed points whole fixed blocks, as stream points whole chunks.
+static int64_t share_rows(const int64_t (&n)[2], int k, int d, int t, int cross_term, int kind)
+{
+    int64_t len = 0;
+    const int64_t chunks = choose_chunks(n[k ^ 1], n[k], d, t, cross_term, kind, &len);
+    const int64_t fixed = (n[k] + gemm_fixed_per_block() - 1) / gemm_fixed_per_block() * gemm_fixed_per_block();
+    return chunks * len > fixed ? chunks * len : fixed;
+}
+constexpr size_t kShareCap = (size_t)8 << 30; // bytes of the kept images of a pair at most (unless the caller set a cap)
+
+// Bytes of both images of a product's point sets on the K-loop split-fp16 engine, 0 if they are not kept
+static size_t product_image_bytes(const int64_t (&n)[2], int d, int t, int kind, size_t limit)
+{
+    if (!use_gemm_engine(d, t, KNM_CROSS_F16X3, kind)) return 0;
+    const size_t pp = gemm_f16_pack_bytes_per_point(d);
+    const size_t bytes = pp * (size_t)(share_rows(n, 0, d, t, KNM_CROSS_F16X3, kind) + share_rows(n, 1, d, t, KNM_CROSS_F16X3, kind));
+    return bytes <= (limit ? limit : kShareCap) ? bytes : 0;
+}
+
+// Decides, at the first sweep of a scope (and again if the arithmetic changed), whether images are kept, and finds room for
+// them: a fit's in blocks of the pool, a product's in the context's image workspace behind the head.
+static int share_images(knm_ctx *ctx, SweepShare *sh)
+{
+    if (sh->decided && sh->cross_term == ctx->cross_term && sh->kind == ctx->kernel_kind) return KNM_OK;
+    for (int k = 0; k < 2; ++k) {
+        if (sh->img[k] && sh->pooled) pool_give(ctx, sh->img[k]);
+        sh->img[k] = nullptr;
+        sh->rows[k] = sh->ready[k] = 0;
+    }
+    sh->decided = true;
+    sh->cross_term = ctx->cross_term;
+    sh->kind = ctx->kernel_kind;
+    if (ctx->cross_term != KNM_CROSS_F16X3 || ctx->static_mode) return KNM_OK;
+    const bool gemm = use_gemm_engine(sh->d, sh->t, ctx->cross_term, ctx->kernel_kind);
+    if (!gemm && (!sh->pooled || sh->d > f16_max_d())) return KNM_OK;
+    const size_t pp = gemm ? gemm_f16_pack_bytes_per_point(sh->d) : f16_pack_bytes_per_point(sh->d);
+    const int64_t r0 = share_rows(sh->n, 0, sh->d, sh->t, ctx->cross_term, ctx->kernel_kind);
+    const int64_t r1 = share_rows(sh->n, 1, sh->d, sh->t, ctx->cross_term, ctx->kernel_kind);
+    if (pp * (size_t)(r0 + r1) > (ctx->pack_limit ? ctx->pack_limit : kShareCap)) return KNM_OK;
+    if (sh->pooled) {
+        for (int k = 0; k < 2; ++k)
+            if (pool_take(ctx, pp * (size_t)(k == 0 ? r0 : r1), &sh->img[k]) != hipSuccess) {
+                // no room: the sweeps pack slab by slab
+                if (sh->img[0]) pool_give(ctx, sh->img[0]);
+                sh->img[0] = sh->img[1] = nullptr;
+                return KNM_OK;
+            }
+    } else {
+        const size_t head = gemm_f16_head_bytes();
+        int st = ensure(ctx, &ctx->pack_buf, &ctx->pack_bytes, head + pp * (size_t)(r0 + r1));
+        if (st) return st;
+        sh->img[0] = reinterpret_cast<char *>(ctx->pack_buf) + head;
+        sh->img[1] = static_cast<char *>(sh->img[0]) + pp * (size_t)r0;
+    }
+    sh->rows[0] = r0;
+    sh->rows[1] = r1;
+    return KNM_OK;
 }
 
 // Bytes of the packed-operand workspace one sweep asks for in the split-fp16 modes (0 in the
@@ -309,7 +494,16 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
                  hipEvent_t after_sweep)
 {
     int64_t chunk_len = 0;
-    const int64_t chunks = choose_chunks(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
+    int64_t chunks = choose_chunks(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
+    if (ctx->static_mode) {
+        // where these partials and the least operand images do not fit the scratch together: fewer chunks
+        const bool packs = ctx->cross_term == KNM_CROSS_F16X3;
+        const size_t least = !packs ? 0
+                             : use_gemm_engine(d, t, ctx->cross_term, ctx->kernel_kind) ? gemm_f16_min_pack_bytes(nF, chunks * chunk_len, chunk_len, d)
+                                                                                       : f16_pack_bytes_per_point(d) * (size_t)chunk_len;
+        if (sizeof(float) * (size_t)chunks * nF * t + mu_bytes_wanted(kMeanSample, d) + least + 1024 > kStaticScratchBytes)
+            chunks = choose_chunks_compact(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
+    }
     if (chunks > 65535) return fail(ctx, KNM_UNSUPPORTED, "too many stream chunks");
     const bool gemm = use_gemm_engine(d, t, ctx->cross_term, ctx->kernel_kind);
     if (gemm && ctx->cross_term == KNM_CROSS_F32 && (!gemm_leading_dimension_ok(ldf) || !gemm_leading_dimension_ok(lds)))
@@ -323,19 +517,32 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
                          (part_is_64 ? sizeof(double) : sizeof(float)) * (size_t)chunks * nF * t, &part);
         if (st) return st;
     }
-    // common shift: feature means of (a strided sample of at most 16384 rows of) the smaller point set
+    // common shift of the two sets, from the smaller one of them (or of the pair they belong to)
+    SweepShare *sh = ctx->static_mode ? nullptr : ctx->share;
+    const int set_f = sh ? sh->which(F, nF, ldf) : -1, set_s = sh ? sh->which(S, nS, lds) : -1;
+    const bool shared = set_f >= 0 && set_s >= 0 && sh->d == d && sh->sigma == sigma;
     float *mu = nullptr;
     {
-        int st = acquire(ctx, &ctx->mu_buf, &ctx->mu_bytes, sizeof(float) * ((size_t)d + 1), &mu); // + the "shifted" flag
-        if (st) return st;
         const bool from_f = nF <= nS;
-        const int64_t rows = from_f ? nF : nS;
-        const int64_t stride = (rows + kMeanSample - 1) / kMeanSample; // every stride-th row, spread over the set
-        hipLaunchKernelGGL(column_mean_kernel, dim3((unsigned)((d + 31) / 32)), dim3(32 * kMeanRowLanes), 0, ctx->stream,
-                           from_f ? F : S, (rows + stride - 1) / stride, stride, from_f ? ldf : lds, d, mu);
-        hipLaunchKernelGGL(shift_decide_kernel, dim3(1), dim3(256), 0, ctx->stream, mu, d,
-                           1.0f / (2.0f * sigma * sigma));
-        if (hipGetLastError() != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "column_mean_kernel launch");
+        const float *P = from_f ? F : S;
+        int64_t rows = from_f ? nF : nS, ld = from_f ? ldf : lds;
+        if (shared) {
+            const int k = sh->n[1] <= sh->n[0] ? 1 : 0;
+            P = sh->P[k];
+            rows = sh->n[k];
+            ld = sh->ld[k];
+        }
+        int st = acquire(ctx, &ctx->mu_buf, &ctx->mu_bytes, mu_bytes_wanted(rows, d), &mu);
+        if (st) return st;
+        if (!shared || ctx->mu_owner != sh) {
+            st = column_shift(ctx, P, rows, ld, d, sigma, mu);
+            if (st) return st;
+            if (!ctx->static_mode) ctx->mu_owner = shared ? sh : nullptr;
+        }
+    }
+    if (shared) {
+        int st = share_images(ctx, sh);
+        if (st) return st;
     }
     // columns per launch
     int group = 1;
@@ -392,9 +599,22 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
         };
         float *pack = nullptr;
         const size_t mark_used = ctx->static_used;
+        const int64_t f_rows = (nF + gemm_fixed_per_block() - 1) / gemm_fixed_per_block() * gemm_fixed_per_block();
+        const int64_t s_rows = chunks * chunk_len;
+        const bool kept = shared && sh->img[0] != nullptr && sh->rows[set_s] >= s_rows && (!gemm || sh->rows[set_f] >= f_rows);
+        if (kept) {
+            a.simg = sh->img[set_s];
+            a.simg_ready = sh->ready[set_s] >= s_rows;
+            if (!a.simg_ready) sh->ready[set_s] = s_rows;
+            if (gemm) {
+                a.fimg = sh->img[set_f];
+                a.fimg_ready = sh->ready[set_f] >= f_rows;
+                if (!a.fimg_ready) sh->ready[set_f] = f_rows;
+            }
+        }
         if (gemm && ctx->cross_term == KNM_CROSS_F16X3) {
-            size_t want = 0;
-            int st = pack_room(&want);
+            size_t want = gemm_f16_head_bytes();
+            int st = kept ? KNM_OK : pack_room(&want);
             if (!st) st = acquire(ctx, &ctx->pack_buf, &ctx->pack_bytes, want, &pack);
             if (st) return st;
             // the vectors as a packed image, when the matrix-core reduction runs and the image is of moderate
@@ -410,8 +630,11 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
             e = launch_sweep_gemm(a, ctx->stream);
         } else if (f16) {
             size_t want = 0;
-            int st = pack_room(&want);
-            if (!st) st = acquire(ctx, &ctx->pack_buf, &ctx->pack_bytes, want, &pack);
+            int st = KNM_OK;
+            if (!kept) {
+                st = pack_room(&want);
+                if (!st) st = acquire(ctx, &ctx->pack_buf, &ctx->pack_bytes, want, &pack);
+            }
             if (st) return st;
             e = launch_sweep_f16(a, pack, want, ctx->stream);
         } else {
@@ -556,6 +779,7 @@ size_t knm_workspace_bytes(int64_t n, int64_t M, int d, int t)
     // the largest needs over the arithmetic modes and kernel functions (they may cut the stream
     // differently): chunk partials, and the packed operands of the split-fp16 modes
     size_t part = 0, pack = 0, vimg = 0;
+    const int64_t sets[2] = {n, M};
     for (int mode = 0; mode < 4; ++mode) {
         const int cross = mode & 1, kind = mode >> 1;
         const int64_t c1 = choose_chunks(n, M, d, t, cross, kind, &len);
@@ -572,6 +796,8 @@ size_t knm_workspace_bytes(int64_t n, int64_t M, int d, int t)
             const size_t k2 = packs ? pack_bytes_wanted(M, d, t, kind, 0, c2, l2) : 0;
             if (k1 > pack) pack = k1;
             if (k2 > pack) pack = k2;
+            const size_t both = product_image_bytes(sets, d, t, kind, 0);
+            if (both > 0 && both + gemm_f16_head_bytes() > pack) pack = both + gemm_f16_head_bytes();
             if (use_gemm_engine(d, t, cross, kind)) {
                 // packed vector image of the widest launch (matrix-core reduction), for either sweep
                 const int wide = t < gemm_f16_max_t(kind) ? t : gemm_f16_max_t(kind);
@@ -581,7 +807,7 @@ size_t knm_workspace_bytes(int64_t n, int64_t M, int d, int t)
             }
         }
     }
-    return bytes + part + pack + vimg + sizeof(float) * ((size_t)d + 1);
+    return bytes + part + pack + vimg + mu_bytes_wanted(kMeanSample, d);
 }
 
 size_t knm_workspace_held(const knm_ctx *ctx)
@@ -626,6 +852,8 @@ static int prod_impl(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx
         W = ctx->w_buf;
     }
     begin_timing(ctx);
+    SweepShare share(ctx, X, n, ldx, C, M, ldc, d, sigma, t, false);
+    const ShareScope scope(share);
     st = do_knm_v(ctx, X, n, d, ldx, C, M, ldc, sigma, V, t, W);
     if (st) return st;
     mark(ctx, 1);

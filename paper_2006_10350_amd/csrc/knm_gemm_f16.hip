@@ -211,12 +211,54 @@ __device__ __forceinline__ float column_scale(uint32_t bits, bool inverse)
 // consecutive in that order.  They are therefore numbered so that each XCD works through
 // "patches" of pf fixed blocks x pc chunks: the pf fixed-block images, which every
 // workgroup re-reads for each of its stream tiles, stay in that XCD's L2, and a stream tile
-// fetched by one workgroup is reused by the pf - 1 others on the same chunk.
+// fetched by one workgroup is reused by the pf - 1 others on the same chunk.  The chunks are taken in groups of pc (the last one
+// narrower).  In each, 8 patches at a time go to the 8 XCDs, and the fixed blocks that are left when fewer
+// than 8 whole patches remain are split evenly over them: every XCD gets the same number of workgroups to within
+// one per group (whole patches dealt out left some XCDs with a fifth more than others at 235 fixed blocks x 5 chunks).
 struct PatchMap {
-    int pf, pc;          // patch shape
-    int64_t n_fblocks;   // fixed blocks of this launch
-    int64_t n_chunks;    // stream chunks of this launch
-    int64_t n_patch_f;   // ceil(n_fblocks / pf)
+    int pc;                  // chunks of a group
+    int64_t n_fblocks;       // fixed blocks of this launch
+    int64_t full_groups;     // groups of pc chunks; slots_full places per XCD each
+    int64_t slots_full, slots_last;
+    int pc_last;             // chunks of the last group (0: none)
+    int pf, pf_last;         // fixed blocks of a patch
+    static int64_t slots(int64_t n_f, int pf, int pc)
+    {
+        const int64_t whole = n_f / (8 * pf);
+        return whole * pf * pc + ((n_f - whole * 8 * pf) * pc + 7) / 8;
+    }
+    // false: no work for this workgroup
+    __device__ bool find(int64_t block, int64_t &f, int64_t &c) const
+    {
+        const int xcd = (int)(block & 7);
+        int64_t slot = block >> 3;
+        int64_t group = full_groups;
+        int gc = pc_last, gf = pf_last;
+        if (slot < full_groups * slots_full) {
+            group = slot / slots_full;
+            slot -= group * slots_full;
+            gc = pc;
+            gf = pf;
+        } else {
+            slot -= full_groups * slots_full;
+            if (slot >= slots_last) return false;
+        }
+        const int per_patch = gf * gc;
+        const int64_t whole = n_fblocks / (8 * gf);
+        if (slot < whole * per_patch) {
+            const int within = (int)(slot % per_patch);
+            f = ((slot / per_patch) * 8 + xcd) * gf + within % gf;
+            c = group * pc + within / gf;
+            return true;
+        }
+        slot -= whole * per_patch;
+        const int64_t rest = (n_fblocks - whole * 8 * gf) * gc, share = (rest + 7) / 8;
+        const int64_t i = xcd * share + slot;
+        if (i >= rest) return false;
+        f = whole * 8 * gf + i / gc;
+        c = group * pc + i % gc;
+        return true;
+    }
 };
 
 // Fimg: image of the fixed points [fixed_row0, fixed_row0 + 256 n_fblocks);
@@ -235,13 +277,8 @@ __global__ __launch_bounds__(kThreads, workgroups_per_cu(MV, TP, KIND, VI)) void
                                                                      PatchMap pm, const uint32_t *__restrict__ colmax)
 {
     static_assert(MV || !VI, "the packed vector image belongs to the matrix-core reduction");
-    const int per_patch = pm.pf * pm.pc;
-    const int64_t slot = (int64_t)blockIdx.x >> 3;
-    const int64_t patch = (slot / per_patch) * 8 + (blockIdx.x & 7);
-    const int within = (int)(slot % per_patch);
-    const int64_t fblk = (patch % pm.n_patch_f) * pm.pf + within % pm.pf;
-    const int64_t cblk = (patch / pm.n_patch_f) * pm.pc + within / pm.pf;
-    if (fblk >= pm.n_fblocks || cblk >= pm.n_chunks) return; // whole workgroup, before any barrier
+    int64_t fblk, cblk;
+    if (!pm.find(blockIdx.x, fblk, cblk)) return; // whole workgroup, before any barrier
 
     // Ring of operand stages (24 KB each) in dynamic LDS, filled by loads that write LDS directly, and
     // behind it the vector rows of a tile: fp32 [stream point][column], or for MV split halves in
@@ -859,14 +896,15 @@ void launch_tp(const SweepArgs &a, const f16x8 *Fimg, const f16x8 *Simg, int64_t
                int64_t chunk0, int64_t chunks, int n_kc, const uint32_t *colmax, hipStream_t stream)
 {
     PatchMap pm;
+    pm.pc = kPatch / kPatchF;
     pm.pf = kPatchF;
-    pm.pc = kPatch / pm.pf;
     pm.n_fblocks = f_blocks;
-    pm.n_chunks = chunks;
-    pm.n_patch_f = (f_blocks + pm.pf - 1) / pm.pf;
-    const int64_t n_patch_c = (chunks + pm.pc - 1) / pm.pc;
-    const int64_t patches = (pm.n_patch_f * n_patch_c + 7) / 8 * 8;
-    const dim3 grid((unsigned)(patches * kPatch));
+    pm.full_groups = chunks / pm.pc;
+    pm.pc_last = (int)(chunks % pm.pc);
+    pm.pf_last = pm.pc_last > 0 ? kPatch / pm.pc_last : 1; // as many workgroups per patch
+    pm.slots_full = PatchMap::slots(f_blocks, pm.pf, pm.pc);
+    pm.slots_last = pm.pc_last > 0 ? PatchMap::slots(f_blocks, pm.pf_last, pm.pc_last) : 0;
+    const dim3 grid((unsigned)(8 * (pm.full_groups * pm.slots_full + pm.slots_last)));
     // dynamic LDS: the ring of stages and the vector rows of a tile (more than the 64 KB a kernel gets
     // without asking)
     constexpr int kVecUnits = MV ? (TP / 2) * 4 * 2 * 2 * 64 : (kStream * TP * 4 + 15) / 16;
@@ -918,6 +956,12 @@ static bool reduce_on_matrix_cores(int d, int t)
     const int n_kc = (d + kChunk - 1) / kChunk;
     return t > 16 || (t >= kMvMinT && 4 * (3 + t) >= 3 * n_kc + 1);
 }
+bool gemm_f16_matrix_reduction(int d, int t) { return reduce_on_matrix_cores(d, t); }
+int gemm_f16_workgroups_per_cu(int d, int t, int kind)
+{
+    const bool mv = reduce_on_matrix_cores(d, t);
+    return workgroups_per_cu(mv, mv ? (t <= 32 ? 2 : t <= 64 ? 4 : t <= 128 ? 8 : 10) : 2, kind, true);
+}
 static int column_groups(int t) { return t <= 32 ? 1 : (t <= 64 ? 2 : (t <= 128 ? 4 : 5)); }
 
 size_t gemm_f16_vector_image_bytes(int d, int t, int64_t nS_padded)
@@ -954,12 +998,13 @@ hipError_t launch_sweep_gemm_f16(const SweepArgs &a, void *pack_buf, size_t pack
     const int64_t nFp = (a.nF + kFixed - 1) / kFixed * kFixed;
     const int64_t nSp = a.n_chunks * a.chunk_len;
     const size_t bytesF = (size_t)nFp * pp, bytesS = (size_t)nSp * pp;
-    if (pack_bytes < gemm_f16_min_pack_bytes(a.nF, nSp, a.chunk_len, a.d)) return hipErrorInvalidValue;
+    const bool kept = a.fimg != nullptr && a.simg != nullptr; // whole images of the caller's
+    if (pack_bytes < (kept ? kHeadBytes : gemm_f16_min_pack_bytes(a.nF, nSp, a.chunk_len, a.d))) return hipErrorInvalidValue;
 
     // slab sizes: the smaller operand is packed whole, the other in slabs that fill the rest
     const size_t room = pack_bytes - kHeadBytes;
     int64_t f_slab = nFp, s_slab = a.n_chunks; // fixed rows / stream chunks per slab
-    if (bytesF + bytesS > room) {
+    if (!kept && bytesF + bytesS > room) {
         if (bytesF <= bytesS) s_slab = (int64_t)((room - bytesF) / ((size_t)a.chunk_len * pp));
         else f_slab = (int64_t)((room - bytesS) / ((size_t)kFixed * pp)) * kFixed;
     }
@@ -968,6 +1013,10 @@ hipError_t launch_sweep_gemm_f16(const SweepArgs &a, void *pack_buf, size_t pack
     f16x8 *Fimg = reinterpret_cast<f16x8 *>(static_cast<char *>(pack_buf) + kHeadBytes);
     const int64_t f_rows_max = f_slab < nFp ? f_slab : nFp;
     f16x8 *Simg = Fimg + (size_t)f_rows_max * pp / sizeof(f16x8);
+    if (kept) {
+        Fimg = static_cast<f16x8 *>(a.fimg);
+        Simg = static_cast<f16x8 *>(a.simg);
+    }
     const bool mv = reduce_on_matrix_cores(a.d, a.t);
     if (mv) {
         // largest magnitude of every vector column: the power-of-two scale into the fp16 range
@@ -996,11 +1045,12 @@ hipError_t launch_sweep_gemm_f16(const SweepArgs &a, void *pack_buf, size_t pack
 
     for (int64_t f0 = 0; f0 < nFp; f0 += f_slab) {
         const int64_t f_rows = (nFp - f0 < f_slab) ? nFp - f0 : f_slab;
-        hipError_t e = pack_points(a.F, a.nF, a.ldf, a.mu, a.d, a.sigma, f0, f_rows, n_kc, Fimg, a.range_count, stream);
+        hipError_t e = hipSuccess;
+        if (!kept || !a.fimg_ready) e = pack_points(a.F, a.nF, a.ldf, a.mu, a.d, a.sigma, f0, f_rows, n_kc, Fimg, a.range_count, stream);
         if (e != hipSuccess) return e;
         for (int64_t c0 = 0; c0 < a.n_chunks; c0 += s_slab) {
             const int64_t nc = (a.n_chunks - c0 < s_slab) ? a.n_chunks - c0 : s_slab;
-            if (f0 == 0 || s_slab < a.n_chunks) { // a whole stream image is built once
+            if (kept ? !a.simg_ready : (f0 == 0 || s_slab < a.n_chunks)) { // a whole stream image is built once
                 e = pack_points(a.S, a.nS, a.lds, a.mu, a.d, a.sigma, c0 * a.chunk_len, nc * a.chunk_len, n_kc, Simg, a.range_count, stream);
                 if (e != hipSuccess) return e;
             }

@@ -52,6 +52,41 @@ struct SweepArgs {
     // vectors converted once per sweep into the layout of the LDS stage; null = every workgroup converts
     // the rows of its tiles itself
     void *vimg = nullptr;
+    // split-fp16 engines: packed images of all stream (and, K-loop engine, all fixed) points kept by the caller for several
+    // sweeps (SweepShare); an image that is not ready yet is packed by the sweep.  null: images live in the workspace
+    // the launcher is given, slab by slab if need be
+    void *fimg = nullptr, *simg = nullptr;
+    bool fimg_ready = false, simg_ready = false;
+};
+
+// What the sweeps of one pair of point sets have in common: the shift and the packed images, computed by the first sweep that
+// needs them.  A product shares them between its two sweeps, a fit over all its iterations.
+struct SweepShare {
+    ::knm_ctx *ctx;
+    const float *P[2]; // the sets (X and C)
+    int64_t n[2], ld[2];
+    int d;
+    float sigma;
+    int t;                       // columns of the sweeps
+    // a fit's or sparse product's: images of both engines kept in blocks of the pool; else (a product) those of the K-loop engine, whose
+    // two sweeps need both of them, in the context's image workspace
+    bool pooled;
+    int cross_term = -1, kind = -1; // what the images were packed for
+    bool decided = false;        // whether images are kept has been decided
+    void *img[2] = {nullptr, nullptr};
+    int64_t rows[2] = {0, 0};    // points an image has room for
+    int64_t ready[2] = {0, 0};   // points packed so far
+    SweepShare(::knm_ctx *ctx, const float *X, int64_t n, int64_t ldx, const float *C, int64_t M, int64_t ldc, int d, float sigma, int t,
+               bool pooled);
+    ~SweepShare();
+    SweepShare(const SweepShare &) = delete;
+    SweepShare &operator=(const SweepShare &) = delete;
+    int which(const float *Q, int64_t m, int64_t l) const
+    {
+        for (int k = 0; k < 2; ++k)
+            if (P[k] == Q && n[k] == m && ld[k] == l) return k;
+        return -1;
+    }
 };
 
 // ---- kernels of r = |x - c| (Laplacian, Matern) on the K-loop engines ---------------------
@@ -106,6 +141,7 @@ int64_t f16_stage_points(int d, int kind); // stream points staged per LDS buffe
 size_t f16_pack_bytes_per_point(int d);
 // pack_buf: device workspace for the packed stream image, at least one chunk's worth
 hipError_t launch_sweep_f16(const SweepArgs &a, void *pack_buf, size_t pack_bytes, hipStream_t stream);
+int f16_workgroups_per_cu(int d, int kind);
 // K-loop engine (knm_gemm.hip): any d, up to gemm_max_t() columns per launch
 int gemm_max_t();
 bool gemm_leading_dimension_ok(int64_t ld); // leading dimensions the fp32 K-loop engine can index
@@ -120,6 +156,8 @@ int gemm_f16_max_t(int kind); // columns per launch at most
 int gemm_f16_group_t(int d, int t_left, int kind, bool with_vector_image); // columns the next launch should take
 // bytes of the packed vector image of a launch with t columns over nS_padded stream points (0: no such image)
 size_t gemm_f16_vector_image_bytes(int d, int t, int64_t nS_padded);
+int gemm_f16_workgroups_per_cu(int d, int t, int kind); // of a launch with t columns and the packed vector image
+bool gemm_f16_matrix_reduction(int d, int t);           // the reduction against t columns runs on the matrix cores
 size_t gemm_f16_min_pack_bytes(int64_t nF, int64_t nS_padded, int64_t chunk_len, int d);
 hipError_t launch_sweep_gemm_f16(const SweepArgs &a, void *pack_buf, size_t pack_bytes, hipStream_t stream);
 // out[j * ldo] = sum over chunks of part[chunk * chunk_stride + j * ldp], summed in fp64 in a fixed
@@ -211,6 +249,8 @@ struct knm_ctx {
         bool used;
     };
     std::vector<PoolBlock> pool;
+    knm::SweepShare *share = nullptr; // of the product or fit whose sweeps are being enqueued
+    const knm::SweepShare *mu_owner = nullptr; // mu_buf holds the shift of this pair of sets
     size_t pool_idle = 0; // bytes of the blocks not in use
     std::mutex pool_lock;
     // second stream for the look-ahead of the blocked factorisation (created lazily by knm_solver.hip)
@@ -237,6 +277,15 @@ int ensure(knm_ctx *ctx, float **buf, size_t *cur, size_t need);
 hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out);
 void pool_give(knm_ctx *ctx, void *p);
 int fail(knm_ctx *ctx, int status, const char *what, hipError_t e = hipSuccess);
+// The sweeps enqueued until it goes out of scope belong to the pair of point sets (see SweepShare).
+struct ShareScope {
+    knm_ctx *ctx;
+    SweepShare *before;
+    explicit ShareScope(SweepShare &s) : ctx(s.ctx), before(s.ctx->share) { ctx->share = &s; }
+    ~ShareScope() { ctx->share = before; }
+    ShareScope(const ShareScope &) = delete;
+    ShareScope &operator=(const ShareScope &) = delete;
+};
 // true if (d, t) runs on the K-loop engine, false for the register-resident one
 bool use_gemm_engine(int d, int t, int cross_term, int kind);
 // number of stream chunks for a sweep over nS stream points against nF fixed points

@@ -1421,6 +1421,8 @@ int falkon_linop_weighted(knm_ctx *ctx, const knm_precond *p, const float *X, in
     if (!st) st = oc.alloc(ctx, sizeof(double) * M * t);
     if (st) return st;
     hipLaunchKernelGGL(f64_rows_to_cols, grid1(M * t), dim3(256), 0, ctx->stream, beta, M, t, bc.as<double>(), 0);
+    SweepShare share(ctx, X, n, ldx, C, M, ldc, d, sigma, t, false);
+    const ShareScope scope(share);
     st = linop_cols(ctx, p, wk, dense_ops(ctx, X, n, d, ldx, C, M, ldc, sigma), lambda, bc.as<double>(), t, oc.as<double>(),
                     dw_or_null);
     if (st) return st;
@@ -1609,6 +1611,8 @@ int falkon_fit(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx, cons
     knm_precond *p = nullptr;
     int st = precond_build_impl(ctx, C, M, d, ldc, sigma, lambda, jitter, true, true, &p, nullptr); // synchronises
     if (st) return st;
+    SweepShare share(ctx, X, n, ldx, C, M, ldc, d, sigma, t, true);
+    const ShareScope scope(share);
     return fit_core(ctx, dense_ops(ctx, X, n, d, ldx, C, M, ldc, sigma), p, Y, t, lambda, iters, alpha,
                     resid_norms_or_null, t_start);
 }
@@ -1811,6 +1815,8 @@ int logfalkon_fit(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx, c
     knm_precond *p = nullptr;
     st = precond_build_impl(ctx, C, M, d, ldc, sigma, lambdas[0], jitter, false, true, &p, nullptr);
     if (st) return st;
+    SweepShare share(ctx, X, n, ldx, C, M, ldc, d, sigma, 1, true);
+    const ShareScope scope(share);
     const KernelOps ops = dense_ops(ctx, X, n, d, ldx, C, M, ldc, sigma);
     auto centres_v = [=](const float *a, float *zc) { return do_knm_v(ctx, C, M, d, ldc, C, M, ldc, sigma, a, 1, zc); };
     return logfalkon_core(ctx, ops, centres_v, p, y, yC, lambdas, iters, n_steps, jitter, alpha, loss_or_null);

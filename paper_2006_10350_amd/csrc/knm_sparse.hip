@@ -30,6 +30,8 @@
 // rank-one term.
 #include <algorithm>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <vector>
 
 #include "knm_internal.h"
@@ -680,6 +682,7 @@ struct SparseProducts::Impl {
     int Hn = 0;
     float sigma = 0.0f;
     DevBuf head_feat, head_count, XH, CH, xat, cbt, tmp_m, dense_n, dense_m, tmp_n;
+    std::unique_ptr<SweepShare> share; // of the dense head product
     DevBuf col_base, col_scattered; // column sweep: all-pairs part and scattered terms, fp64 over the centres
 
     int rank_one_sum(const float *ev, const float *vec, int64_t ldv, int64_t rows, double *out)
@@ -876,6 +879,9 @@ int SparseProducts::prepare(knm_ctx *ctx, const int64_t *x_indptr, const int64_t
             if (stat) return stat;
         }
     }
+    if (s.Hn > 0)
+        s.share.reset(new (std::nothrow) SweepShare(ctx, s.XH.as<float>(), n, s.Hn, s.CH.as<float>(), M, s.Hn, s.Hn, sigma, 1, true));
+    if (s.Hn > 0 && !s.share) return fail(ctx, KNM_ALLOC, "host allocation");
     hipError_t e = hipMemsetAsync(s.acc.p, 0, sizeof(float) * waves * M, st);
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipMemsetAsync", e);
     return KNM_OK;
@@ -891,6 +897,7 @@ int SparseProducts::v(const float *V, int t, float *W)
             // all pairs: a^T_i sum_j k(x^H_i, c^H_j) b^T_j v_j on the dense engine
             hipLaunchKernelGGL(scale_kernel, grid_for(s.M), dim3(256), 0, s.ctx->stream, s.cbt.as<float>(), V + c, (int64_t)t,
                                s.M, s.tmp_m.as<float>(), (int64_t)1);
+            const ShareScope scope(*s.share);
             int stat = do_knm_v(s.ctx, s.XH.as<float>(), s.n, s.Hn, s.Hn, s.CH.as<float>(), s.M, s.Hn, s.sigma,
                                 s.tmp_m.as<float>(), 1, s.dense_n.as<float>());
             if (stat) return stat;
@@ -926,6 +933,7 @@ int SparseProducts::t_w(const float *W, const float *wgt, int t, float *U)
             // all pairs: b^T_j sum_i k(x^H_i, c^H_j) a^T_i w_i on the dense engine
             hipLaunchKernelGGL(scale_kernel, grid_for(s.n), dim3(256), 0, st, s.xat.as<float>(), w, ldw, s.n,
                                s.tmp_n.as<float>(), (int64_t)1);
+            const ShareScope scope(*s.share);
             int stat = do_knm_t_w(s.ctx, s.XH.as<float>(), s.n, s.Hn, s.Hn, s.CH.as<float>(), s.M, s.Hn, s.sigma,
                                   s.tmp_n.as<float>(), nullptr, 1, s.dense_m.as<float>());
             if (stat) return stat;

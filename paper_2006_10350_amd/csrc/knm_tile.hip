@@ -29,6 +29,8 @@
 // This makes a lane's slots pairs of adjacent features, which keeps the global loads
 // and LDS accesses 8 or 16 bytes wide.
 
+#include <type_traits>
+
 #include "knm_internal.h"
 #include "knm_operands.h"
 
@@ -276,15 +278,32 @@ __global__ __launch_bounds__(kThreads, (KS <= 15 ? 3 : 1)) void gauss_sweep_kern
         }
 }
 
-template <typename TI, typename TO>
-__global__ void merge_kernel(const TI *__restrict__ part, int64_t n_chunks, int64_t chunk_stride, int64_t ldp,
-                             TO *__restrict__ out, int64_t ldo, int64_t count)
+// out[j] = sum of the chunk partials of entry j in fp64.  A wavefront takes 64 entries and every SLICES-th chunk, and the sums of
+// the workgroup's wavefronts are added in their order: one thread per entry read 147 partials one after the other
+// (36 us for 5000 entries, 8 us in 8 slices).
+template <typename TI, typename TO, int SLICES>
+__global__ __launch_bounds__(64 * SLICES) void merge_kernel(const TI *__restrict__ part, int64_t n_chunks, int64_t chunk_stride,
+                                                           int64_t ldp, TO *__restrict__ out, int64_t ldo, int64_t count)
 {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= count) return;
+    __shared__ double sh[SLICES][64];
+    const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
+    const int64_t j = (int64_t)blockIdx.x * 64 + lane;
+    const TI *p = part + (j < count ? j : 0) * ldp;
     double s = 0.0;
-    for (int64_t c = 0; c < n_chunks; ++c) s += (double)part[c * chunk_stride + j * ldp];
-    out[j * ldo] = (TO)s;
+    int64_t c = slice;
+    for (; c + 3 * SLICES < n_chunks; c += 4 * SLICES) {
+        const TI a0 = p[c * chunk_stride], a1 = p[(c + SLICES) * chunk_stride];
+        const TI a2 = p[(c + 2 * SLICES) * chunk_stride], a3 = p[(c + 3 * SLICES) * chunk_stride];
+        s += ((double)a0 + (double)a1) + ((double)a2 + (double)a3);
+    }
+    for (; c < n_chunks; c += SLICES) s += (double)p[c * chunk_stride];
+    if constexpr (SLICES > 1) {
+        sh[slice][lane] = s;
+        __syncthreads();
+        if (slice != 0) return;
+        for (int k = 1; k < SLICES; ++k) s += sh[k][lane];
+    }
+    if (j < count) out[j * ldo] = (TO)s;
 }
 
 constexpr int kR = 2;
@@ -335,15 +354,19 @@ hipError_t launch_merge(const float *part, const double *part64, int64_t n_chunk
                         float *out, double *out64, int64_t ldo, int64_t count, hipStream_t stream)
 {
     if ((part == nullptr) == (part64 == nullptr) || (out == nullptr) == (out64 == nullptr)) return hipErrorInvalidValue;
-    const dim3 threads(256), blocks((unsigned)((count + 255) / 256));
-    if (part64 != nullptr && out64 != nullptr)
-        hipLaunchKernelGGL((merge_kernel<double, double>), blocks, threads, 0, stream, part64, n_chunks, chunk_stride, ldp, out64, ldo, count);
-    else if (part64 != nullptr)
-        hipLaunchKernelGGL((merge_kernel<double, float>), blocks, threads, 0, stream, part64, n_chunks, chunk_stride, ldp, out, ldo, count);
-    else if (out64 != nullptr)
-        hipLaunchKernelGGL((merge_kernel<float, double>), blocks, threads, 0, stream, part, n_chunks, chunk_stride, ldp, out64, ldo, count);
-    else
-        hipLaunchKernelGGL((merge_kernel<float, float>), blocks, threads, 0, stream, part, n_chunks, chunk_stride, ldp, out, ldo, count);
+    const dim3 blocks((unsigned)((count + 63) / 64));
+    auto launch = [&](auto *in, auto *to) {
+        using TI = std::remove_const_t<std::remove_pointer_t<decltype(in)>>;
+        using TO = std::remove_pointer_t<decltype(to)>;
+        if (n_chunks >= 8)
+            hipLaunchKernelGGL((merge_kernel<TI, TO, 8>), blocks, dim3(512), 0, stream, in, n_chunks, chunk_stride, ldp, to, ldo, count);
+        else
+            hipLaunchKernelGGL((merge_kernel<TI, TO, 1>), blocks, dim3(64), 0, stream, in, n_chunks, chunk_stride, ldp, to, ldo, count);
+    };
+    if (part64 != nullptr && out64 != nullptr) launch(part64, out64);
+    else if (part64 != nullptr) launch(part64, out);
+    else if (out64 != nullptr) launch(part, out64);
+    else launch(part, out);
     return hipGetLastError();
 }
 

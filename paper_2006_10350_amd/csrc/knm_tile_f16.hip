@@ -561,16 +561,17 @@ hipError_t launch_nu(const SweepArgs &a, void *pack_buf, size_t pack_bytes, hipS
     const int64_t per_block = (int64_t)kWaves * 64;
     const int64_t blocks = (a.nF + per_block - 1) / per_block;
     // slab = whole chunks whose packed image fits the workspace
-    int64_t slab_chunks = (int64_t)(pack_bytes / bytes_per_point) / a.chunk_len;
+    int64_t slab_chunks = a.simg != nullptr ? a.n_chunks : (int64_t)(pack_bytes / bytes_per_point) / a.chunk_len;
     if (slab_chunks < 1) return hipErrorInvalidValue;
     const bool a16 = (a.d % 4 == 0) && (a.lds % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.S) & 15) == 0);
     const bool a8 = (a.d % 2 == 0) && (a.lds % 2 == 0) && ((reinterpret_cast<uintptr_t>(a.S) & 7) == 0);
-    f16x8 *packed = static_cast<f16x8 *>(pack_buf);
+    f16x8 *packed = static_cast<f16x8 *>(a.simg != nullptr ? a.simg : pack_buf);
     for (int64_t c0 = 0; c0 < a.n_chunks; c0 += slab_chunks) {
         const int64_t nc = (a.n_chunks - c0 < slab_chunks) ? a.n_chunks - c0 : slab_chunks;
         const int64_t row0 = c0 * a.chunk_len, rows = nc * a.chunk_len;
         const dim3 pgrid((unsigned)((rows + kThreads / 2 - 1) / (kThreads / 2)));
-        if (a16)
+        if (a.simg != nullptr && a.simg_ready) { // packed by an earlier sweep
+        } else if (a16)
             hipLaunchKernelGGL((pack_stream_kernel<NU, 4>), pgrid, dim3(kThreads), 0, stream, a.S, a.nS, a.lds, a.mu, a.d,
                                a.sigma, row0, rows, packed, a.range_count);
         else if (a8)
@@ -593,6 +594,7 @@ hipError_t launch_nu(const SweepArgs &a, void *pack_buf, size_t pack_bytes, hipS
 
 int f16_max_d() { return 44; } // 6 units of 8 features; larger images exceed 64 KB of static LDS
 int64_t f16_stage_points(int d, int kind) { return stage_of(d <= 12 ? 2 : (d <= 28 ? 4 : 6), kind); }
+int f16_workgroups_per_cu(int d, int kind) { return d <= 12 && kind == KNM_KERNEL_GAUSSIAN ? 3 : 2; } // by registers
 int f16_radial_max_d() { return 28; } // the kernels of r need more registers per entry: 4 units
 
 // bytes of packed image per stream point for this d
