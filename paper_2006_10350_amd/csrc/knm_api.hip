@@ -223,10 +223,13 @@ static int64_t choose_chunks_compact(int64_t nF, int64_t nS, int d, int t, int c
 }
 
 // The number of chunks is the one with the least estimated time among those that make about 1, 2, ... 16 rounds of the workgroups
-// the chip holds at once (and the smallest numbers): rounds x stages x time of a stage, a round in which at most half of
-// the places are taken counting for less because its workgroups have a CU to themselves; the start and end of a
-// workgroup; and the merge pass.  What counts is that the last round is nearly full: n = 60k, d = 784, M = 10k,
-// 10 columns ran 1175 workgroups of 16 tiles on 512 places, three rounds for the work of 2.3.
+// the chip holds at once, the smallest numbers and multiples of 8.  The estimate: rounds x stages x time of a stage, where a last round that
+// takes at most half of the places counts half because its workgroups have a CU to themselves, and part of a round more because
+// workgroups do not end together (measured: 79 blocks, 2.0 rounds 3.75 ms, 4.0 3.47, 4.9 3.27, 6.0 3.37, 6.9 3.27); the start
+// and end of a workgroup; partials written and merged; and for the K-loop engine what the sharing of operands in an XCD's L2 loses
+// (see PatchMap) with fewer than 8 chunks (d = 784: 4 chunks 32 % slower), in a last group of fewer than 8 (18 %), and in
+// long chunks, along which workgroups drift apart (2 % per doubling).  n = 60k, d = 784, M = 10k, 10 columns ran
+// 1175 workgroups of 16 tiles on 512 places: 2.48 ms per sweep, 2.0 ms cut finer.
 int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind, int64_t *chunk_len)
 {
     const bool gemm = use_gemm_engine(d, t, cross_term, kind);
@@ -235,7 +238,7 @@ int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int 
     // workgroups per CU and microseconds of a stage (K-loop engines: of a tile) of one of them on a full chip, from the rates of
     // the engines (ps per kernel entry) on large problems
     int per_cu = 2;
-    double stage_us, wg_us = 4.0;
+    double stage_us, wg_us = 5.0, uneven = 0.2;
     if (gemm) {
         const double kc = (double)((d + 15) / 16);
         const int tl = f16 && t > gemm_f16_max_t(kind) ? gemm_f16_max_t(kind) : (!f16 && t > gemm_max_t() ? gemm_max_t() : t);
@@ -249,6 +252,8 @@ int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int 
         }
         if (kind != KNM_KERNEL_GAUSSIAN) cycles += 128.0 * 16.0;
         stage_us = per_cu * cycles / 2100.0;
+        wg_us = per_cu > 1 ? 6.0 : 8.0;
+        uneven = 0.4;
     } else {
         if (f16) per_cu = f16_workgroups_per_cu(d, kind);
         const double ps = (f16 ? (d <= 12 ? 0.106 : d <= 28 ? 0.167 : 0.22) : 0.12 + 0.019 * d) * (kind == KNM_KERNEL_GAUSSIAN ? 1.0 : 1.6);
@@ -272,11 +277,14 @@ int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int 
         if (chunks == best_chunks || chunks > 65535) return;
         const double w = (double)(g.blocks * chunks);
         const double rounds = floor(w / slots), rest = w - rounds * slots;
-        const double load = rounds + (rest == 0.0 ? 0.0 : per_cu > 1 && rest <= 256.0 ? 0.6 : 1.0);
+        const double load = rounds + uneven + (rest == 0.0 ? 0.0 : per_cu > 1 && rest <= 256.0 ? 0.5 : 1.0);
         double us = load * ((double)len * stage_us) + (rounds + (rest > 0.0 ? 1.0 : 0.0)) * wg_us;
-        // few chunks share less of the fixed points' image in an XCD's L2 (see PatchMap)
-        if (gemm && chunks < 8 && w > 256.0) us *= 1.0 + 0.5 / (double)chunks;
-        if (chunks > 1) us += 3.0 + 1.0e-6 * (double)chunks * (double)nF * (double)t * 4.0 / 3.0;
+        if (gemm && w > 256.0) {
+            double loss = chunks < 8 ? 0.55 - 0.055 * (double)chunks : 0.18 * (double)(chunks % 8) / (double)chunks;
+            if (len > 64) loss += 0.02 * log2((double)len / 64.0);
+            us *= 1.0 + loss * (d < 784 ? (double)d / 784.0 : 1.0);
+        }
+        if (chunks > 1) us += 3.0 + 1.0e-6 * (double)chunks * (double)nF * (double)t * 4.0 / 2.0;
         if (best_chunks == 0 || us < best) {
             best = us;
             best_chunks = chunks;
@@ -286,6 +294,8 @@ int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int 
     if ((double)g.blocks < 32.0 * slots) {
         for (int k = 2; k <= 16; ++k) consider(k);
         for (int k = 1; k <= 16; ++k) consider((int64_t)((double)k * slots / (double)g.blocks));
+        if (gemm)
+            for (int k = 24; k <= 128; k += 8) consider(k);
     }
     int64_t len = (g.stages + best_chunks - 1) / best_chunks;
     *chunk_len = len * g.stage;
