@@ -66,6 +66,37 @@ int fail(knm_ctx *ctx, int status, const char *what, hipError_t e)
     return status;
 }
 
+// hipMalloc that frees the idle blocks of the pool when there is no room (the pool's lock is held)
+static hipError_t alloc_locked(knm_ctx *ctx, size_t bytes, void **out)
+{
+    *out = nullptr;
+    hipError_t e = hipMalloc(out, bytes);
+    if (e != hipSuccess && ctx->pool_idle > 0) {
+        (void)hipGetLastError();
+        for (size_t i = 0; i < ctx->pool.size();) {
+            if (ctx->pool[i].used) {
+                ++i;
+                continue;
+            }
+            (void)hipFree(ctx->pool[i].p);
+            ctx->pool.erase(ctx->pool.begin() + (std::ptrdiff_t)i);
+        }
+        ctx->pool_idle = 0;
+        e = hipMalloc(out, bytes);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *out = nullptr;
+    }
+    return e;
+}
+
+hipError_t device_alloc(knm_ctx *ctx, size_t bytes, void **out)
+{
+    const std::lock_guard<std::mutex> lock(ctx->pool_lock);
+    return alloc_locked(ctx, bytes, out);
+}
+
 int ensure(knm_ctx *ctx, float **buf, size_t *cur, size_t need)
 {
     if (*cur >= need) return KNM_OK;
@@ -76,9 +107,8 @@ int ensure(knm_ctx *ctx, float **buf, size_t *cur, size_t need)
         if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipFree(workspace)", e);
     }
     void *p = nullptr;
-    hipError_t e = hipMalloc(&p, need);
+    hipError_t e = device_alloc(ctx, need, &p);
     if (e != hipSuccess) {
-        (void)hipGetLastError();
         return fail(ctx, KNM_ALLOC, "hipMalloc(workspace)", e);
     }
     *buf = static_cast<float *>(p);
@@ -105,25 +135,14 @@ hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out)
         return hipSuccess;
     }
     void *p = nullptr;
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess && ctx->pool_idle > 0) { // make room: the idle blocks go first
-        (void)hipGetLastError();
-        for (size_t i = 0; i < ctx->pool.size();) {
-            if (ctx->pool[i].used) {
-                ++i;
-                continue;
-            }
-            (void)hipFree(ctx->pool[i].p);
-            ctx->pool.erase(ctx->pool.begin() + (std::ptrdiff_t)i);
-        }
-        ctx->pool_idle = 0;
-        e = hipMalloc(&p, bytes);
+    const hipError_t e = alloc_locked(ctx, bytes, &p);
+    if (e != hipSuccess) return e;
+    try {
+        ctx->pool.push_back({p, bytes, true});
+    } catch (const std::bad_alloc &) { // the entry points are C: nothing may be thrown through them
+        (void)hipFree(p);
+        return hipErrorOutOfMemory;
     }
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return e;
-    }
-    ctx->pool.push_back({p, bytes, true});
     *out = p;
     return hipSuccess;
 }
@@ -297,6 +316,7 @@ int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int 
         if (gemm)
             for (int k = 24; k <= 128; k += 8) consider(k);
     }
+    if (best_chunks == 0) best_chunks = g.min_chunks; // more than 65535 chunks: the sweep refuses them
     int64_t len = (g.stages + best_chunks - 1) / best_chunks;
     *chunk_len = len * g.stage;
     return (g.stages + len - 1) / len;

@@ -1219,6 +1219,14 @@ static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool low
     hipStream_t aux = nullptr;
     int st = aux_stream(ctx, &aux);
     if (st) return st;
+    // on an early return the arrays may go back to the pool, whose blocks are ordered by the context's stream only
+    struct AuxJoin {
+        hipStream_t s;
+        ~AuxJoin()
+        {
+            if (s) (void)hipStreamSynchronize(s);
+        }
+    } join{aux};
     EventSet ev_rows, ev_rest;
     if (!ev_rows.create(nb) || !ev_rest.create(nb)) return fail(ctx, KNM_HIP_ERROR, "hipEventCreate");
     std::vector<char> have_rest(nb, 0);
@@ -1290,6 +1298,7 @@ static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool low
                 return fail(ctx, KNM_HIP_ERROR, "hipStreamWaitEvent");
             break;
         }
+    join.s = nullptr; // ordered before whatever follows on the context's stream
     e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "factorisation", e);
     return KNM_OK;
@@ -1355,7 +1364,8 @@ static int precond_build_from(knm_ctx *ctx, int64_t M, const std::function<int(d
     const int64_t nblk = (M + p->sb - 1) / p->sb;
     auto take = [&](double **a, int64_t count) {
         void *ptr = nullptr;
-        const hipError_t err = pooled ? pool_take(ctx, sizeof(double) * (size_t)count, &ptr) : hipMalloc(&ptr, sizeof(double) * (size_t)count);
+        const size_t bytes = sizeof(double) * (size_t)count;
+        const hipError_t err = pooled ? pool_take(ctx, bytes, &ptr) : device_alloc(ctx, bytes, &ptr);
         if (err == hipSuccess) *a = static_cast<double *>(ptr);
         return err;
     };

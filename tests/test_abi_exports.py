@@ -56,3 +56,14 @@ def test_no_cpu_fallback_without_gpu():
         pytest.skip("GPU present")
     with pytest.raises(RuntimeError):
         pkg.Context()
+
+
+def test_workspace_of_streams_beyond_the_chunk_limit():
+    # more than 65535 chunks of 2^18 points: the products refuse such a call, the size query still answers
+    import paper_2006_10350_amd as pkg
+
+    lib = pkg.load_library()
+    n = 20_000_000_000
+    for M, d, t in ((1000, 1, 1), (1000, 50, 4)):
+        assert lib.knm_workspace_bytes(n, M, d, t) >= n * t * 4
+        assert lib.knm_workspace_bytes(M, n, d, t) >= M * t * 4
