@@ -201,11 +201,14 @@ __device__ __forceinline__ double wave_sum(double s)
     return s;
 }
 
+typedef double solve_d2 __attribute__((ext_vector_type(2)));
+
 // One right-hand side: the three kernels below, bound by the bandwidth of the factor.
 
 // x = inv(R_kk) b (lower = 1: x[c] = sum_{i >= c} S[i, c] b[i]) or x = inv(R_kk)^T b (lower = 0:
 // x[c] = sum_{i <= c} S[i, c] b[i]) for one mirrored block S of live order nbk; one wavefront
-// per entry of x, lanes along the column of S.  Where they are given: sum[c] = x[c] + scale add[c], x32[c] = x[c] rounded.
+// per entry of x, lanes along the column of S, 1024 entries of it in flight (with two 8-byte loads per lane in flight a block of
+// 2048 took 10.9 us).  sb even, S 16-byte aligned.  Where they are given: sum[c] = x[c] + scale add[c], x32[c] = x[c] rounded.
 __global__ __launch_bounds__(256) void diag_apply_kernel(const double *__restrict__ S, int sb, int nbk, int lower,
                                                         const double *__restrict__ b, double *__restrict__ x,
                                                         const double *__restrict__ add, double scale,
@@ -217,13 +220,25 @@ __global__ __launch_bounds__(256) void diag_apply_kernel(const double *__restric
     const double *col = S + (int64_t)c * sb;
     const int lo = lower ? c : 0;
     const int hi = lower ? nbk : c + 1;
+    constexpr int kFlight = 8;
     double s0 = 0.0, s1 = 0.0;
-    int i = lo + lane;
-    for (; i + 64 < hi; i += 128) {
-        s0 += col[i] * b[i];
-        s1 += col[i + 64] * b[i + 64];
+    for (int i0 = (lo & ~1) + 2 * lane; i0 < hi; i0 += 128 * kFlight) {
+        solve_d2 a[kFlight];
+        double b0[kFlight], b1[kFlight];
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) { // (an entry outside the range is taken from the column's first pair and dropped)
+            const int i = i0 + 128 * u, ia = i < hi ? i : 0;
+            a[u] = *reinterpret_cast<const solve_d2 *>(col + ia);
+            b0[u] = b[ia];
+            b1[u] = b[ia + 1 < nbk ? ia + 1 : 0];
+        }
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) {
+            const int i = i0 + 128 * u;
+            if (i >= lo && i < hi) s0 = fma(a[u][0], b0[u], s0);
+            if (i + 1 < hi) s1 = fma(a[u][1], b1[u], s1);
+        }
     }
-    if (i < hi) s0 += col[i] * b[i];
     const double s = wave_sum(s0 + s1);
     if (lane == 0) {
         x[c] = s;
@@ -232,13 +247,16 @@ __global__ __launch_bounds__(256) void diag_apply_kernel(const double *__restric
     }
 }
 
-constexpr int kPanelWaves = 8;  // wavefronts of a panel_update_n workgroup, sharing the columns
-constexpr int kPanelRows = 64;  // rows of a panel_update_n workgroup, one per lane
+constexpr int kPanelWaves = 16; // wavefronts of a panel_update_n workgroup, sharing the columns
+constexpr int kPanelRows = 32;  // rows of a panel_update_n workgroup, two per lane
 constexpr int kPanelCols = 4;   // columns of one panel_update_t wavefront
 
 // b[r] = src[r] - sum_j P[r + (k0 + j) ld] x[j] for r in [r_lo, r_hi)  (x = the solved block, nbk entries; src: the
 // right-hand side so far, b itself from the second block on): the rows above the block of an upper-storage factor
-// in its plain solve, the rows below the block of a lower-storage factor in its transposed solve.
+// in its plain solve, the rows below the block of a lower-storage factor in its transposed solve.  ld and r_lo even, R 16-byte
+// aligned, column entries up to the next even row readable.  16 lanes take 32 rows of a column, the four lane groups of 16
+// wavefronts 64 columns at a time, eight loads in flight each: with 64 rows per workgroup of 8 wavefronts an update of 3000 rows
+// had 46 workgroups.
 __global__ __launch_bounds__(kPanelWaves * 64) void panel_update_n_kernel(const double *__restrict__ R, int64_t M,
                                                                          int64_t k0, int nbk, int64_t r_lo,
                                                                          int64_t r_hi, const double *__restrict__ x,
@@ -247,28 +265,42 @@ __global__ __launch_bounds__(kPanelWaves * 64) void panel_update_n_kernel(const 
     __shared__ double part[kPanelWaves][kPanelRows];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t r = r_lo + (int64_t)blockIdx.x * kPanelRows + lane;
-    const bool live = r < r_hi;
-    const double *p = R + (live ? r : r_lo) + k0 * M;
+    const int l15 = lane & 15, q = lane >> 4;
+    const int64_t r = r_lo + (int64_t)blockIdx.x * kPanelRows + 2 * l15;
+    const double *p = R + (r < r_hi ? r : r_lo) + k0 * M;
+    constexpr int kStep = 4 * kPanelWaves;
     double s0 = 0.0, s1 = 0.0;
-    int j = w;
-    for (; j + 7 * kPanelWaves < nbk; j += 8 * kPanelWaves) {
-        double a[8];
+    for (int j0 = 4 * w + q; j0 < nbk; j0 += 8 * kStep) {
+        solve_d2 a[8];
+        double xv[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) a[u] = p[(int64_t)(j + u * kPanelWaves) * M];
-#pragma unroll
-        for (int u = 0; u < 8; u += 2) {
-            s0 += a[u] * x[j + u * kPanelWaves];
-            s1 += a[u + 1] * x[j + (u + 1) * kPanelWaves];
+        for (int u = 0; u < 8; ++u) {
+            const int j = j0 + u * kStep, jc = j < nbk ? j : j0;
+            a[u] = *reinterpret_cast<const solve_d2 *>(p + (int64_t)jc * M);
+            xv[u] = x[jc];
         }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (j0 + u * kStep < nbk) {
+                s0 = fma(a[u][0], xv[u], s0);
+                s1 = fma(a[u][1], xv[u], s1);
+            }
     }
-    for (; j < nbk; j += kPanelWaves) s0 += p[(int64_t)j * M] * x[j];
-    part[w][lane] = s0 + s1;
+    s0 += __shfl_xor(s0, 32);
+    s1 += __shfl_xor(s1, 32);
+    s0 += __shfl_xor(s0, 16);
+    s1 += __shfl_xor(s1, 16);
+    if (q == 0) {
+        part[w][2 * l15] = s0;
+        part[w][2 * l15 + 1] = s1;
+    }
     __syncthreads();
-    if (w == 0 && live) {
+    const int64_t row = r_lo + (int64_t)blockIdx.x * kPanelRows + threadIdx.x;
+    if (threadIdx.x < kPanelRows && row < r_hi) {
         double s = 0.0;
-        for (int u = 0; u < kPanelWaves; ++u) s += part[u][lane];
-        b[r] = src[r] - s;
+#pragma unroll
+        for (int u = 0; u < kPanelWaves; ++u) s += part[u][threadIdx.x];
+        b[row] = src[row] - s;
     }
 }
 
@@ -314,49 +346,55 @@ __global__ __launch_bounds__(256) void panel_update_t_kernel(const double *__res
 // bandwidth of the factor, which is read once for all columns (a 16 x 16 x 4 instruction takes 512 bytes of it in 64
 // cycles: 19 TB/s over the chip).  Right-hand sides and solution live as [row][16] arrays, unused columns zero.
 // 10 columns at M = 10000: 5.2 ms for the four solves of an iteration as vector-ALU passes over 8 and 2 columns,
-// 1.2 ms now.
+// 1.07 ms with 32 outputs and 8 wavefronts per workgroup (62 to 250 workgroups of a panel, 64 of a diagonal block), 0.83 ms now.
 constexpr int kSolveCols = 16;
-constexpr int kSkinnyThreads = 512, kSkinnyWaves = kSkinnyThreads / 64;
-constexpr int kSkinnyTile = 32; // outputs of a workgroup, whose wavefronts share the contraction 32 at a time
-typedef double solve_d2 __attribute__((ext_vector_type(2)));
+constexpr int kSkinnyThreads = 1024, kSkinnyWaves = kSkinnyThreads / 64;
 typedef double solve_d4 __attribute__((ext_vector_type(4)));
+// Outputs of a workgroup, whose 16 wavefronts share the contraction 32 at a time: 16 NT.  A product of at most 2048
+// outputs (a diagonal block) is 128 workgroups with NT = 1.
+constexpr int64_t kSkinnyNarrowUpTo = 2048;
 
-// adds up the wavefronts' accumulators (red: 32 KB of LDS); this thread's entry of the tile: accumulator t = tid / 256,
+// adds up the wavefronts' accumulators; this thread's entry of the tile (threads below 256 NT): accumulator t = tid / 256,
 // register (tid / 64) % 4 of lane tid % 64
-__device__ __forceinline__ double skinny_reduce(double (*red)[2][4][64], const solve_d4 (&acc)[2])
+template <int NT> __device__ __forceinline__ double skinny_reduce(double (*red)[NT][4][64], const solve_d4 (&acc)[NT])
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) red[wave][t][r][lane] = acc[t][r];
     __syncthreads();
     double s = 0.0;
+    if (tid < 256 * NT) {
 #pragma unroll
-    for (int w = 0; w < kSkinnyWaves; ++w) s += red[w][tid >> 8][(tid >> 6) & 3][lane];
+        for (int w = 0; w < kSkinnyWaves; ++w) s += red[w][tid >> 8][(tid >> 6) & 3][lane];
+    }
     return s;
 }
 
 // b[r, c] -= sum_{k < nk} P[r + k ld] x[k, c], r < rows.  P 16-byte aligned, ld even, and column entries up to the next
-// even row readable.  A lane's 16-byte load holds the same column entry of rows 2 l and 2 l + 1: even rows are one
-// accumulator, odd rows the other.
+// even row readable.  A lane's load of NT entries holds the same column entry of rows NT l ... NT l + NT - 1: accumulator t
+// has rows t mod NT.
+template <int NT>
 __global__ __launch_bounds__(kSkinnyThreads) void skinny_n_kernel(const double *__restrict__ P, int64_t ld, int64_t rows,
                                                                  int nk, const double *__restrict__ x, double *__restrict__ b)
 {
-    __shared__ double red[kSkinnyWaves][2][4][64];
+    typedef double row_t __attribute__((ext_vector_type(NT)));
+    __shared__ double red[kSkinnyWaves][NT][4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l15 = lane & 15, q = lane >> 4;
-    const int64_t row0 = (int64_t)blockIdx.x * kSkinnyTile;
-    const double *p = P + (row0 + 2 * l15 < rows ? row0 + 2 * l15 : 0);
-    solve_d4 acc[2];
-    acc[0] = acc[1] = solve_d4{0.0, 0.0, 0.0, 0.0};
+    const int64_t row0 = (int64_t)blockIdx.x * (16 * NT);
+    const double *p = P + (row0 + NT * l15 < rows ? row0 + NT * l15 : 0);
+    solve_d4 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = solve_d4{0.0, 0.0, 0.0, 0.0};
     for (int k0 = wave * 32; k0 < nk; k0 += kSkinnyWaves * 32) {
-        solve_d2 a[8];
+        row_t a[8];
         double bv[8];
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int k = k0 + 4 * s + q, kc = k < nk ? k : nk - 1;
-            a[s] = *reinterpret_cast<const solve_d2 *>(p + (int64_t)kc * ld);
+            a[s] = *reinterpret_cast<const row_t *>(p + (int64_t)kc * ld);
             bv[s] = x[(int64_t)kc * kSolveCols + l15];
         }
 #pragma unroll
@@ -364,43 +402,43 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_n_kernel(const double *
             const bool in = k0 + 4 * s + q < nk;
             const double bs = in ? bv[s] : 0.0;
 #pragma unroll
-            for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? a[s][t] : 0.0, bs, acc[t], 0, 0, 0);
+            for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? a[s][t] : 0.0, bs, acc[t], 0, 0, 0);
         }
     }
-    const double s = skinny_reduce(red, acc);
+    const double s = skinny_reduce<NT>(red, acc);
     const int t = threadIdx.x >> 8, i = 4 * ((threadIdx.x >> 6) & 3) + q;
-    const int64_t r = row0 + 2 * i + t;
-    if (r < rows) b[r * kSolveCols + l15] -= s;
+    const int64_t r = row0 + NT * i + t;
+    if (t < NT && r < rows) b[r * kSolveCols + l15] -= s;
 }
 
 // MODE 0: b[j, c] -= sum_{i < nk} P[i + j ld] x[i, c], j < outs.  MODE 1, 2: b[j, c] = the same sum over i >= j, i <= j (a
 // mirrored block inverse: the plain and the transposed solve with its diagonal block).  P 16-byte aligned, ld even.  A
 // lane holds 8 consecutive i of its column, 32 per 4 lane groups.
-template <int MODE>
+template <int MODE, int NT>
 __global__ __launch_bounds__(kSkinnyThreads) void skinny_t_kernel(const double *__restrict__ P, int64_t ld, int64_t outs,
                                                                  int nk, const double *__restrict__ x, double *__restrict__ b)
 {
-    __shared__ double red[kSkinnyWaves][2][4][64];
+    __shared__ double red[kSkinnyWaves][NT][4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l15 = lane & 15, q = lane >> 4;
-    const int64_t tile0 = (int64_t)blockIdx.x * kSkinnyTile;
-    const double *p[2];
+    const int64_t tile0 = (int64_t)blockIdx.x * (16 * NT);
+    const double *p[NT];
+    solve_d4 acc[NT];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < NT; ++t) {
         const int64_t j = tile0 + 16 * t + l15;
         p[t] = P + (j < outs ? j : 0) * ld;
+        acc[t] = solve_d4{0.0, 0.0, 0.0, 0.0};
     }
-    solve_d4 acc[2];
-    acc[0] = acc[1] = solve_d4{0.0, 0.0, 0.0, 0.0};
-    const int first = MODE == 1 ? (int)tile0 : 0;
-    const int last = MODE == 2 && tile0 + kSkinnyTile < nk ? (int)tile0 + kSkinnyTile : nk;
+    const int first = MODE == 1 ? (int)tile0 & ~31 : 0;
+    const int last = MODE == 2 && tile0 + 16 * NT < nk ? (int)tile0 + 16 * NT : nk;
     for (int i0 = first + wave * 32; i0 < last; i0 += kSkinnyWaves * 32) {
-        solve_d2 a[2][4];
+        solve_d2 a[NT][4];
         double bv[8];
         const int ib = i0 + 8 * q; // nk and ld are such that 8 entries from an in-range multiple of 8 stay inside the array
         const bool any = ib < nk;
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const int i = any && ib + 2 * s < nk ? ib + 2 * s : 0;
@@ -413,16 +451,17 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_t_kernel(const double *
             const int i = ib + s;
             const double bs = i < nk ? bv[s] : 0.0;
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < NT; ++t) {
                 const int j = (int)tile0 + 16 * t + l15;
                 const bool in = i < nk && (MODE == 0 || (MODE == 1 ? i >= j : i <= j));
                 acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? a[t][s >> 1][s & 1] : 0.0, bs, acc[t], 0, 0, 0);
             }
         }
     }
-    const double s = skinny_reduce(red, acc);
-    const int64_t j = tile0 + 16 * (threadIdx.x >> 8) + 4 * ((threadIdx.x >> 6) & 3) + q;
-    if (j < outs) {
+    const double s = skinny_reduce<NT>(red, acc);
+    const int t = threadIdx.x >> 8;
+    const int64_t j = tile0 + 16 * t + 4 * ((threadIdx.x >> 6) & 3) + q;
+    if (t < NT && j < outs) {
         if (MODE == 0) b[j * kSolveCols + l15] -= s;
         else b[j * kSolveCols + l15] = s;
     }
@@ -955,21 +994,23 @@ int tri_solve(knm_ctx *ctx, const knm_precond *p, const double *R, const double 
             const int64_t lo = trans ? k0 + nbk : 0, hi = trans ? M : k0;
             if (tc > 1) {
                 double *x = p->xw + k0 * kSolveCols;
-                const dim3 dgrid((unsigned)((nbk + kSkinnyTile - 1) / kSkinnyTile));
-                if (trans)
-                    hipLaunchKernelGGL(skinny_t_kernel<2>, dgrid, dim3(kSkinnyThreads), 0, ctx->stream, Sk, (int64_t)sb, (int64_t)nbk,
-                                       nbk, rhs + k0 * kSolveCols, x);
-                else
-                    hipLaunchKernelGGL(skinny_t_kernel<1>, dgrid, dim3(kSkinnyThreads), 0, ctx->stream, Sk, (int64_t)sb, (int64_t)nbk,
-                                       nbk, rhs + k0 * kSolveCols, x);
+                // the diagonal block, then the panel of the entries still to be solved
+                auto diagonal = [&](auto kernel) {
+                    hipLaunchKernelGGL(kernel, dim3((unsigned)((nbk + 15) / 16)), dim3(kSkinnyThreads), 0, ctx->stream, Sk, (int64_t)sb,
+                                       (int64_t)nbk, nbk, rhs + k0 * kSolveCols, x);
+                };
+                if (trans) diagonal(skinny_t_kernel<2, 1>);
+                else diagonal(skinny_t_kernel<1, 1>);
                 if (hi == lo) continue;
-                const dim3 pgrid((unsigned)((hi - lo + kSkinnyTile - 1) / kSkinnyTile));
+                const bool narrow = hi - lo <= kSkinnyNarrowUpTo;
+                const dim3 pgrid((unsigned)(narrow ? (hi - lo + 15) / 16 : (hi - lo + 31) / 32));
+                auto panel = [&](auto kernel, const double *P) {
+                    hipLaunchKernelGGL(kernel, pgrid, dim3(kSkinnyThreads), 0, ctx->stream, P, ld, hi - lo, nbk, x, rhs + lo * kSolveCols);
+                };
                 if (trans == lower) // panel entries R(r, k0 + j) or R(k0 + j, r) contiguous in r
-                    hipLaunchKernelGGL(skinny_n_kernel, pgrid, dim3(kSkinnyThreads), 0, ctx->stream, R + lo + k0 * ld, ld, hi - lo,
-                                       nbk, x, rhs + lo * kSolveCols);
+                    narrow ? panel(skinny_n_kernel<1>, R + lo + k0 * ld) : panel(skinny_n_kernel<2>, R + lo + k0 * ld);
                 else                // contiguous in the block's own index
-                    hipLaunchKernelGGL(skinny_t_kernel<0>, pgrid, dim3(kSkinnyThreads), 0, ctx->stream, R + k0 + lo * ld, ld,
-                                       hi - lo, nbk, x, rhs + lo * kSolveCols);
+                    narrow ? panel(skinny_t_kernel<0, 1>, R + k0 + lo * ld) : panel(skinny_t_kernel<0, 2>, R + k0 + lo * ld);
                 continue;
             }
             const double *b = step == 0 ? bin : work;
