@@ -285,6 +285,33 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
 #pragma unroll
         for (int nn = 0; nn < kMJ; ++nn) acc[m][nn] = d4{0.0, 0.0, 0.0, 0.0};
 
+    // C[4 r + l / 16][l % 16] of a 16 x 16 block is entry r of lane l of its accumulator.  The small tiles, whose products take
+    // no longer than a miss, read their part of C before them
+    constexpr bool kEarlyC = !SYM && TI * TJ <= 64 * 64;
+    auto entry = [&](int m, int nn, int r, double *&dst) { // false: not stored
+        const int64_t j = j0 + wj + nn * 16 + (lane & 15);
+        const int64_t i = i0 + wi + m * 16 + (lane >> 4) + 4 * r;
+        if (j >= a.nj || i >= a.n || (SYM && i > j)) return false;
+        if (!SYM && ((a.part == 1 && i > j) || (a.part == 2 && i < j))) return false;
+        dst = a.trans_c ? a.C + j + i * a.ldc : a.C + i + j * a.ldc;
+        return true;
+    };
+    double old[kEarlyC ? kMI : 1][kEarlyC ? kMJ : 1][4];
+    auto read_c = [&]() {
+        if constexpr (kEarlyC) {
+#pragma unroll
+            for (int m = 0; m < kMI; ++m)
+#pragma unroll
+                for (int nn = 0; nn < kMJ; ++nn)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        double *dst = nullptr;
+                        old[m][nn][r] = a.beta != 0.0 && entry(m, nn, r, dst) ? *dst : 0.0;
+                    }
+        }
+    };
+
+    if (stages <= 0) read_c();
     if (stages > 0) {
         Fetch<FA, TI, VEC, kTK> fa;
         Fetch<FB, TJ, VEC, kTK> fb;
@@ -342,6 +369,7 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
         fetch();
         commit(0, lds);
         if (stages > 1) fetch();
+        read_c();
         __syncthreads();
         read_ops(lds, 0, av[0], bv[0]);
         // Per stage: the operands of a k-step are read while the products of the one before
@@ -376,26 +404,20 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
         }
     }
 
-    // accumulator entry r of lane l is C[4 r + l / 16][l % 16] of its 16 x 16 block
 #pragma unroll
     for (int m = 0; m < kMI; ++m)
 #pragma unroll
-        for (int nn = 0; nn < kMJ; ++nn) {
-            const int64_t j = j0 + wj + nn * 16 + (lane & 15);
-            const int64_t ib = i0 + wi + m * 16 + (lane >> 4);
-            if (j >= a.nj) continue;
+        for (int nn = 0; nn < kMJ; ++nn)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int64_t i = ib + 4 * r;
-                if ((SYM && i > j) || i >= a.n) continue;
-                if (!SYM && ((a.part == 1 && i > j) || (a.part == 2 && i < j))) continue;
-                double *dst = a.trans_c ? a.C + j + i * a.ldc : a.C + i + j * a.ldc;
+                double *dst = nullptr;
+                if (!entry(m, nn, r, dst)) continue;
                 double v = a.alpha * acc[m][nn][r];
-                if (a.beta != 0.0) v += a.beta * *dst;
-                if (SYM && i == j) v += a.shift;
+                if constexpr (kEarlyC) v += a.beta * old[m][nn][r];
+                else if (a.beta != 0.0) v += a.beta * *dst;
+                if (SYM && i0 + wi + m * 16 + (lane >> 4) + 4 * r == j0 + wj + nn * 16 + (lane & 15)) v += a.shift;
                 *dst = v;
             }
-        }
 }
 
 // A thread's byte offsets inside a stage must fit the 32-bit buffer offset.
@@ -405,11 +427,17 @@ bool stage_offsets_fit(int form_nt, int64_t ld, int rows, int depth)
     return span * 8 < 0xffffffffLL;
 }
 
-// 64 x 64 tiles below this many 128 x 128 ones (two waves of the two workgroups a CU holds): the few wide tiles of a small
+// Small tiles below this many 128 x 128 ones (two waves of the two workgroups a CU holds): the few wide tiles of a small
 // product leave compute units idle and each is a chain of four times the matrix instructions (33 us for a product over
 // k = 128 against 9 us).  From 256 to 2048 the fits take the same time; without small tiles M = 5000 takes 68 ms per
 // logistic fit instead of 56, M = 20000 371 ms per fit instead of 355.
 constexpr int64_t kSmallTilesBelow = 1024;
+
+// Of those products, 32 x 32 tiles where 64 x 64 ones are few or short (t64: their number): a wavefront's 4 products per k are a chain of
+// 256 cycles, which 32 x 32 tiles cut to a quarter.  128 rows, k = 384: 1200 columns 22.3 us against 10.6, 5000 23.1 against
+// 18.0, 18000 60.1 against 49.4; 512 rows, k = 512: 2500 columns 43.3 against 33.3, 8700 109.8 against 103.7.  Long products of many
+// tiles read the operands once less: 1280 rows, k = 1280: 8700 columns 546 against 565, 5000 325 against 343, 2500 182 against 180.
+bool smallest_tiles(int64_t t64, int64_t K) { return t64 <= 640 || K <= 512; }
 
 // Patch of tiles that the workgroups of one XCD take together: 8 x 8, smaller where there would be fewer than four
 // per XCD (all XCDs busy counts for more than shared rows of the operands)
@@ -515,7 +543,7 @@ hipError_t launch_gemm_f64(int a_nt, int64_t ni, int64_t nj, int64_t K, double a
     int TI = 128, TJ = 128;
     if (big < kSmallTilesBelow) {
         // in place: a tile must hold all of the entries that are computed from the operand rows it overwrites
-        if (!in_place) TI = TJ = 64;
+        if (!in_place) TI = TJ = smallest_tiles(((ni + 63) / 64) * ((nj + 63) / 64), K) ? 32 : 64;
         else if (a_nt) TI = 32;
         else TJ = 32;
     }
@@ -536,6 +564,7 @@ hipError_t launch_gemm_f64(int a_nt, int64_t ni, int64_t nj, int64_t K, double a
         constexpr int FA = decltype(fa)::value, FB = decltype(fb)::value, V = decltype(vec)::value;
         if (TI == 128 && TJ == 128) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false>), grid, block, 0, stream, a);
         else if (TI == 64) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 64, 64>), grid, block, 0, stream, a);
+        else if (TI == 32 && TJ == 32) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 32, 32>), grid, block, 0, stream, a);
         else if constexpr (FA == 1 && FB == 0) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 32, 128>), grid, block, 0, stream, a);
         else if constexpr (FA == 0 && FB == 0) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 128, 32>), grid, block, 0, stream, a);
     };
@@ -567,7 +596,8 @@ hipError_t launch_merge_inverses(const double *R, int64_t ld, int lower, int64_t
     for (int h = 128; h < sb; h *= 2) {
         a.merge_h = h;
         a.merge_pairs = (sb + 2 * h - 1) / (2 * h);
-        const int tiles = h / 64;
+        const bool smallest = smallest_tiles((int64_t)(h / 64) * (h / 64) * blocks * a.merge_pairs, h);
+        const int tiles = h / (smallest ? 32 : 64);
         a.patch_i = a.patch_j = 1;
         a.n_patch_i = tiles;
         a.n_patches = (int64_t)tiles * tiles;
@@ -578,15 +608,23 @@ hipError_t launch_merge_inverses(const double *R, int64_t ld, int lower, int64_t
         a.A = R;
         a.lda = ld;
         a.ldb = sb;
-        if (lower && vec2) hipLaunchKernelGGL((rank_k_upper_kernel<0, 0, false, 2, false, 64, 64>), grid, dim3(kThreads), 0, stream, a);
-        else if (lower) hipLaunchKernelGGL((rank_k_upper_kernel<0, 0, false, 1, false, 64, 64>), grid, dim3(kThreads), 0, stream, a);
-        else if (vec2) hipLaunchKernelGGL((rank_k_upper_kernel<1, 0, false, 2, false, 64, 64>), grid, dim3(kThreads), 0, stream, a);
-        else hipLaunchKernelGGL((rank_k_upper_kernel<1, 0, false, 1, false, 64, 64>), grid, dim3(kThreads), 0, stream, a);
+        auto launch = [&](auto fa, auto fb, auto vec) {
+            constexpr int FA = decltype(fa)::value, FB = decltype(fb)::value, V = decltype(vec)::value;
+            if (smallest) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 32, 32>), grid, dim3(kThreads), 0, stream, a);
+            else hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 64, 64>), grid, dim3(kThreads), 0, stream, a);
+        };
+        constexpr std::integral_constant<int, 0> tn{};
+        constexpr std::integral_constant<int, 1> nt{}, one{};
+        constexpr std::integral_constant<int, 2> two{};
+        if (lower && vec2) launch(tn, tn, two);
+        else if (lower) launch(tn, tn, one);
+        else if (vec2) launch(nt, tn, two);
+        else launch(nt, tn, one);
         a.merge = 2;
         a.alpha = -1.0;
         a.trans_c = 0;
         a.lda = sb;
-        hipLaunchKernelGGL((rank_k_upper_kernel<1, 1, false, 2, false, 64, 64>), grid, dim3(kThreads), 0, stream, a);
+        launch(nt, nt, two);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -79,3 +79,24 @@ def test_products_with_wide_tiles(knm, a_nt):
     C = torch.zeros(nj, ni, dtype=torch.float64, device="cuda")
     knm.block_product((a[:ni].T if a_nt else a[:ni]).contiguous(), a[:nj].contiguous(), C, a_nt=a_nt)
     assert float((C.T - a[:ni] @ a[:nj].T).abs().max()) < 1e-12 * k
+
+
+# 32 x 32 tiles with remainders in every direction, the last short product and the first that takes 64 x 64 tiles, also with
+# operands that only allow 8-byte loads (odd leading dimensions); C is read (beta) and, with NaNs in it, not read (beta = 0)
+@pytest.mark.parametrize("a_nt", [False, True])
+@pytest.mark.parametrize("ni,nj,k", [(1, 1, 1), (33, 31, 7), (32, 64, 32), (95, 161, 33), (64, 65, 513), (1650, 1700, 512), (1650, 1700, 514),
+                                     (1651, 1701, 513)])
+def test_products_with_small_tiles(knm, ni, nj, k, a_nt):
+    g = torch.Generator(device="cuda").manual_seed(ni + nj + k)
+    a = torch.randn(ni, k, generator=g, device="cuda", dtype=torch.float64)
+    b = torch.randn(nj, k, generator=g, device="cuda", dtype=torch.float64)
+    C0 = torch.randn(nj, ni, generator=g, device="cuda", dtype=torch.float64)
+    ref = a @ b.T
+    A = (a.T if a_nt else a).contiguous()  # column-major ni x k or k x ni
+    C = C0.clone()
+    knm.block_product(A, b, C, alpha=-1.0, beta=1.0, a_nt=a_nt)
+    # k + 1 roundings of partial sums of products that reach about 4 each at most a few times over: far below 1e-13 (k + 10)
+    assert float((C.T - (C0.T - ref)).abs().max()) < 1e-13 * (k + 10)
+    C = torch.full_like(C0, float("nan"))
+    knm.block_product(A, b, C, alpha=1.0, beta=0.0, a_nt=a_nt)
+    assert float((C.T - ref).abs().max()) < 1e-13 * (k + 10)
