@@ -58,8 +58,9 @@ constexpr int kXcds = 8;
 // the 16 k of one column, which the k-contiguous form writes at once, over 16 bank pairs.
 template <int TI, int TJ> struct Tile {
     // contraction depth of a stage: the small tiles have a quarter of the products per k, so they take twice the
-    // depth to cover the latency of the loads and the barrier
-    static constexpr int kTK = TI * TJ >= 128 * 128 ? 16 : 32;
+    // depth to cover the latency of the loads and the barrier; 64 x 64 ones, taken where there are many, do that with four
+    // workgroups per CU instead of two (1280 rows, k = 1280, 5000 columns: 348 -> 320 us; symmetric, 5000 rows, k = 640: 393 -> 364)
+    static constexpr int kTK = TI * TJ >= 128 * 128 || (TI == 64 && TJ == 64) ? 16 : 32;
     static constexpr int kSA = TI + 16, kSB = TJ + 16;
     static constexpr int kStageDoubles = kTK * (kSA + kSB);
 };
@@ -433,11 +434,11 @@ bool stage_offsets_fit(int form_nt, int64_t ld, int rows, int depth)
 // logistic fit instead of 56, M = 20000 371 ms per fit instead of 355.
 constexpr int64_t kSmallTilesBelow = 1024;
 
-// Of those products, 32 x 32 tiles where 64 x 64 ones are few or short (t64: their number): a wavefront's 4 products per k are a chain of
-// 256 cycles, which 32 x 32 tiles cut to a quarter.  128 rows, k = 384: 1200 columns 22.3 us against 10.6, 5000 23.1 against
-// 18.0, 18000 60.1 against 49.4; 512 rows, k = 512: 2500 columns 43.3 against 33.3, 8700 109.8 against 103.7.  Long products of many
-// tiles read the operands once less: 1280 rows, k = 1280: 8700 columns 546 against 565, 5000 325 against 343, 2500 182 against 180.
-bool smallest_tiles(int64_t t64, int64_t K) { return t64 <= 640 || K <= 512; }
+// Of those products, 32 x 32 tiles where 64 x 64 ones are few (t64: their number), and up to a few more where they are short: a
+// wavefront's 4 products per k are a chain of 256 cycles, which 32 x 32 tiles cut to a quarter.  Microseconds with 64 x 64 and 32 x 32: 128 rows,
+// k = 384: 1200 columns 22.3 and 10.6, 5000 23.1 and 18.0; 512 rows, k = 2048: 2500 columns (320 tiles) 142 and 112, 3500 (440) 143 and 157;
+// 512 rows, k = 512: 2500 columns 44.5 and 34.3, 5000 (632) 62.9 and 62.6, 8700 (1088) 98.9 and 114.7.
+bool smallest_tiles(int64_t t64, int64_t K) { return t64 <= 400 || (K <= 512 && t64 <= 640); }
 
 // Patch of tiles that the workgroups of one XCD take together: 8 x 8, smaller where there would be fewer than four
 // per XCD (all XCDs busy counts for more than shared rows of the operands)

@@ -81,11 +81,11 @@ def test_products_with_wide_tiles(knm, a_nt):
     assert float((C.T - a[:ni] @ a[:nj].T).abs().max()) < 1e-12 * k
 
 
-# 32 x 32 tiles with remainders in every direction, the last short product and the first that takes 64 x 64 tiles, also with
+# 32 x 32 tiles with remainders in every direction, the last products that take them and the first that take 64 x 64 ones, also with
 # operands that only allow 8-byte loads (odd leading dimensions); C is read (beta) and, with NaNs in it, not read (beta = 0)
 @pytest.mark.parametrize("a_nt", [False, True])
-@pytest.mark.parametrize("ni,nj,k", [(1, 1, 1), (33, 31, 7), (32, 64, 32), (95, 161, 33), (64, 65, 513), (1650, 1700, 512), (1650, 1700, 514),
-                                     (1651, 1701, 513)])
+@pytest.mark.parametrize("ni,nj,k", [(1, 1, 1), (33, 31, 7), (32, 64, 32), (95, 161, 33), (64, 65, 513), (1278, 1264, 514), (1650, 1500, 512),
+                                     (1650, 1500, 514), (1651, 1701, 33)])
 def test_products_with_small_tiles(knm, ni, nj, k, a_nt):
     g = torch.Generator(device="cuda").manual_seed(ni + nj + k)
     a = torch.randn(ni, k, generator=g, device="cuda", dtype=torch.float64)
