@@ -50,7 +50,7 @@ namespace {
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
 
-constexpr int kThreads = 256; // 2 x 2 wavefronts, each a quarter of the tile
+constexpr int kThreads = 256; // four wavefronts, each a quarter of the tile
 constexpr int kXcds = 8;
 // Tile of TI x TJ entries of C.  LDS image of an operand tile: element (k, i) at k * stride + i, for the k-contiguous form at
 // k * stride + (i ^ (k % 16)).  The strides are 16 mod 32 doubles, so the four 16-lane groups of an
@@ -61,7 +61,8 @@ template <int TI, int TJ> struct Tile {
     // depth to cover the latency of the loads and the barrier; 64 x 64 ones, taken where there are many, do that with four
     // workgroups per CU instead of two (1280 rows, k = 1280, 5000 columns: 348 -> 320 us; symmetric, 5000 rows, k = 640: 393 -> 364)
     static constexpr int kTK = TI * TJ >= 128 * 128 || (TI == 64 && TJ == 64) ? 16 : 32;
-    static constexpr int kSA = TI + 16, kSB = TJ + 16;
+    static constexpr int kSA = TI == 16 ? 16 : TI + 16, kSB = TJ == 16 ? 16 : TJ + 16;
+    static constexpr int kWI = TI == 16 ? 1 : TJ == 16 ? 4 : 2, kWJ = 4 / kWI; // wavefronts along i and j
     static constexpr int kStageDoubles = kTK * (kSA + kSB);
 };
 
@@ -217,7 +218,8 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
 {
     constexpr int kTK = Tile<TI, TJ>::kTK, kSA = Tile<TI, TJ>::kSA, kSB = Tile<TI, TJ>::kSB;
     constexpr int kStageDoubles = Tile<TI, TJ>::kStageDoubles;
-    constexpr int kMI = TI / 32, kMJ = TJ / 32; // 16 x 16 accumulators of a wavefront
+    constexpr int kWI = Tile<TI, TJ>::kWI, kWJ = Tile<TI, TJ>::kWJ;
+    constexpr int kMI = TI / 16 / kWI, kMJ = TJ / 16 / kWJ; // 16 x 16 accumulators of a wavefront
     __shared__ double lds[2 * kStageDoubles];
     if (!SYM && a.merge != 0) {
         // pair (off, off + h) of block k of the inverses: A, B, C and the sizes from the arrays' bases
@@ -273,7 +275,7 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int wi = (wave % 2) * (TI / 2), wj = (wave / 2) * (TJ / 2);
+    const int wi = (wave % kWI) * (TI / kWI), wj = (wave / kWI) * (TJ / kWJ);
     // (triangular factors of the merges: W22 ends at its column's diagonal, W11 starts at its row's)
     if (!SYM && a.merge == 1 && a.K > j0 + TJ) a.K = j0 + TJ;
     const int64_t kbeg = (SYM && a.tri) ? j0 : (!SYM && a.merge == 2) ? i0 : 0; // a multiple of kTK
@@ -440,6 +442,10 @@ constexpr int64_t kSmallTilesBelow = 1024;
 // 512 rows, k = 512: 2500 columns 44.5 and 34.3, 5000 (632) 62.9 and 62.6, 8700 (1088) 98.9 and 114.7.
 bool smallest_tiles(int64_t t64, int64_t K) { return t64 <= 400 || (K <= 512 && t64 <= 640); }
 
+// In-place products (128 rows, k = 128) of up to this many columns take 16 at a time, longer ones 32: two workgroups per CU hold 8192, and
+// with 16 a wavefront's chain of matrix instructions is half as long (preconditioner at M = 1000 0.99 -> 0.94 ms, M = 5000 6.87 -> 6.69 ms).
+constexpr int64_t kNarrowUpTo = 8192;
+
 // Patch of tiles that the workgroups of one XCD take together: 8 x 8, smaller where there would be fewer than four
 // per XCD (all XCDs busy counts for more than shared rows of the operands)
 void choose_patch(int64_t tiles_i, int64_t tiles_j, int *patch_i, int *patch_j)
@@ -545,8 +551,7 @@ hipError_t launch_gemm_f64(int a_nt, int64_t ni, int64_t nj, int64_t K, double a
     if (big < kSmallTilesBelow) {
         // in place: a tile must hold all of the entries that are computed from the operand rows it overwrites
         if (!in_place) TI = TJ = smallest_tiles(((ni + 63) / 64) * ((nj + 63) / 64), K) ? 32 : 64;
-        else if (a_nt) TI = 32;
-        else TJ = 32;
+        else (a_nt ? TI : TJ) = (a_nt ? ni : nj) <= kNarrowUpTo ? 16 : 32;
     }
     if (in_place && (a_nt ? nj > 128 : ni > 128)) return hipErrorInvalidValue;
     const int64_t tiles_i = (ni + TI - 1) / TI, tiles_j = (nj + TJ - 1) / TJ;
@@ -566,8 +571,13 @@ hipError_t launch_gemm_f64(int a_nt, int64_t ni, int64_t nj, int64_t K, double a
         if (TI == 128 && TJ == 128) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false>), grid, block, 0, stream, a);
         else if (TI == 64) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 64, 64>), grid, block, 0, stream, a);
         else if (TI == 32 && TJ == 32) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 32, 32>), grid, block, 0, stream, a);
-        else if constexpr (FA == 1 && FB == 0) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 32, 128>), grid, block, 0, stream, a);
-        else if constexpr (FA == 0 && FB == 0) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 128, 32>), grid, block, 0, stream, a);
+        else if constexpr (FA == 1 && FB == 0) {
+            if (TI == 16) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 16, 128>), grid, block, 0, stream, a);
+            else hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 32, 128>), grid, block, 0, stream, a);
+        } else if constexpr (FA == 0 && FB == 0) {
+            if (TJ == 16) hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 128, 16>), grid, block, 0, stream, a);
+            else hipLaunchKernelGGL((rank_k_upper_kernel<FA, FB, false, V, false, 128, 32>), grid, block, 0, stream, a);
+        }
     };
     auto with_forms = [&](auto vec) {
         constexpr std::integral_constant<int, 0> tn{};
