@@ -100,3 +100,32 @@ def test_products_with_small_tiles(knm, ni, nj, k, a_nt):
     C = torch.full_like(C0, float("nan"))
     knm.block_product(A, b, C, alpha=1.0, beta=0.0, a_nt=a_nt)
     assert float((C.T - ref).abs().max()) < 1e-13 * (k + 10)
+
+
+# the rows' passes of sparse inputs take 16 lanes per row and walk on beyond 262144 rows: norms of rows longer than the lanes and
+# of the last row, and a repeated feature found at either side of a lane group's end and in the last row
+@pytest.mark.parametrize("rows,at", [(3, 15), (3, 16), (3, 32), (3, 39), (262150, 7)])
+def test_csr_rows_longer_than_their_lanes(knm, rows, at):
+    length = 40 if rows < 10 else 8
+    d = 64
+    ids = torch.arange(length).repeat(rows) + 1
+    val = torch.rand(rows * length, generator=torch.Generator().manual_seed(rows + at)) + 0.5
+    ptr = torch.arange(rows + 1) * length
+
+    def csr(i):
+        return torch.sparse_csr_tensor(ptr.cuda(), i.cuda(), val.cuda(), size=(rows, d), check_invariants=False)
+
+    c_rows = 2
+    C = torch.sparse_csr_tensor(ptr[:c_rows + 1].cuda(), ids[:c_rows * length].cuda(), val[:c_rows * length].cuda(), size=(c_rows, d),
+                                check_invariants=False)
+    V = torch.ones(c_rows, 1, device="cuda")
+    _, W = knm.knm_prod_csr(csr(ids), C, 4.0, V, return_w=True)
+    X64 = torch.zeros(rows, d, dtype=torch.float64)
+    X64[:, 1:length + 1] = val.double().reshape(rows, length)
+    K = torch.exp(-torch.cdist(X64[-3:], X64[:c_rows]) ** 2 / 32.0)
+    assert float((W[-3:].cpu().double() - K.sum(1, keepdim=True)).abs().max()) < 1e-5
+    bad = ids.clone()
+    bad[(rows - 1) * length + at] = bad[(rows - 1) * length + at - 1]
+    with pytest.raises(knm.KnmError) as e:
+        knm.knm_prod_csr(csr(bad), C, 4.0, V)
+    assert e.value.status == -1
