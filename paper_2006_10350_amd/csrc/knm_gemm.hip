@@ -103,7 +103,8 @@ __global__ __launch_bounds__(kThreads, 2) void gauss_gemm_kernel(SweepArgs a)
     // Two levels of summation: the terms of one tile (64 per lane and fixed point) in fp32 from zero,
     // the tile sums into fp64 running sums, so that the rounding of a long sum of same-sign terms
     // does not grow with the chunk (with 16 columns the registers hold only the fp32 sums, which
-    // then run through the chunk).
+    // then run through the chunk).  Where the result is asked for in fp64 (a solver's K^T w, whose rounding T^-T amplifies) the
+    // fp32 sums of the Gaussian kernel cover 8 terms.
     constexpr bool kWide = TP <= 12;
     float sum[2][TP];
     double wide[2][kWide ? TP : 1];
@@ -114,6 +115,17 @@ __global__ __launch_bounds__(kThreads, 2) void gauss_gemm_kernel(SweepArgs a)
             sum[fb][c] = 0.0f;
             if constexpr (kWide) wide[fb][c] = 0.0;
         }
+    auto widen = [&]() {
+        if constexpr (kWide) {
+#pragma unroll
+            for (int fb = 0; fb < 2; ++fb)
+#pragma unroll
+                for (int c = 0; c < TP; ++c) {
+                    wide[fb][c] += (double)sum[fb][c];
+                    sum[fb][c] = 0.0f;
+                }
+        }
+    };
 
     for (int tile = 0; tile < n_tiles; ++tile) {
         const int64_t stream0 = chunk_begin + (int64_t)tile * kStream;
@@ -301,6 +313,8 @@ __global__ __launch_bounds__(kThreads, 2) void gauss_gemm_kernel(SweepArgs a)
 #pragma unroll
                     for (int c = 0; c < TP; ++c) sum[fb][c] = fmaf(p, vr[c], sum[fb][c]);
                 }
+                if constexpr (kWide && KIND == KNM_KERNEL_GAUSSIAN)
+                    if (r % 8 == 7 && a.out64 != nullptr) widen();
             }
         if constexpr (KIND != KNM_KERNEL_GAUSSIAN) {
             if (__builtin_amdgcn_ballot_w64(any_near) != 0) {
@@ -332,15 +346,7 @@ __global__ __launch_bounds__(kThreads, 2) void gauss_gemm_kernel(SweepArgs a)
                 }
             }
         }
-        if constexpr (kWide) {
-#pragma unroll
-            for (int fb = 0; fb < 2; ++fb)
-#pragma unroll
-                for (int c = 0; c < TP; ++c) {
-                    wide[fb][c] += (double)sum[fb][c];
-                    sum[fb][c] = 0.0f;
-                }
-        }
+        widen();
         __syncthreads(); // aug / vimg / img are rewritten by the next tile
     }
 

@@ -69,6 +69,8 @@ constexpr int workgroups_per_cu(bool mv, int tp, int kind, bool vi)
 {
     return !mv || tp == 2 || (tp == 4 && kind == KNM_KERNEL_GAUSSIAN && vi) ? 2 : 1;
 }
+// columns up to which the vector-ALU reduction keeps fp64 running sums beside the fp32 sums of a tile
+constexpr int wide_columns(int kind) { return kind == KNM_KERNEL_GAUSSIAN ? 12 : 10; }
 // Stages in the LDS ring: 3 (two stages of loads in flight) where the rings and vector rows of the workgroups
 // of a CU fit its 160 KB, 2 for the matrix-core reduction at two workgroups per CU with its 16 KB of vector
 // halves per group
@@ -270,7 +272,8 @@ struct PatchMap {
 // colmax[c] = bits of max |vec[:, c]|.
 // VI (with MV): the vector halves of a tile come from the packed image a.vimg (pack_vectors_kernel) by
 // direct-to-LDS loads instead of being converted by the workgroup.
-template <int TP, bool MV, int KIND, bool VI = false>
+// FINE: the fp32 sums of the vector-ALU reduction cover kFineTerms terms instead of a tile's 64 (see there).
+template <int TP, bool MV, int KIND, bool VI = false, bool FINE = false>
 __global__ __launch_bounds__(kThreads, workgroups_per_cu(MV, TP, KIND, VI)) void gauss_gemm_f16_kernel(SweepArgs a, const f16x8 *__restrict__ Fimg,
                                                                      const f16x8 *__restrict__ Simg,
                                                                      int64_t fixed_row0, int64_t chunk0, int n_kc,
@@ -319,7 +322,14 @@ __global__ __launch_bounds__(kThreads, workgroups_per_cu(MV, TP, KIND, VI)) void
     // long sum of same-sign terms does not grow with the length of the chunk (a plain fp32 running sum
     // over some thousand terms loses 2-3 digits of what the solver's T^-T amplifies).  With more than 12
     // columns (10 for the kernels of r) the registers do not hold a second set of sums and the fp32 sums run through the chunk.
-    constexpr bool kWide = !MV && TP <= (KIND == KNM_KERNEL_GAUSSIAN ? 12 : 10);
+    // FINE (results asked for in fp64: a solver's K^T w): T^-T amplifies the rounding of these sums some 1e5 times, far
+    // beyond that of the kernel values, v or w, which average out over the rows.  Coefficients of a fit with n = 60k, d = 784,
+    // M = 10k, 10 columns, against the same iterations in 64 bits, eight seeds: 4.0e-3 to 8.1e-3 (3.1e-2 where one class has 97 %
+    // of the rows) with sums of 64 terms, 1.2e-3 to 2.3e-3 (7.9e-3) with 16, 7.0e-4 to 1.3e-3 (4.1e-3) with 8, for
+    // 0.7 % of the fit's time.  (The kernels of r have no such instantiation: it spills 90 to 660 registers.)
+    constexpr bool kWide = !MV && TP <= wide_columns(KIND);
+    static_assert(kWide || !FINE, "FINE shortens the sums of the vector-ALU reduction");
+    constexpr int kFineTerms = 8;
     float sum[2][TP];
     double wide[2][kWide ? TP : 1];
 #pragma unroll
@@ -329,6 +339,17 @@ __global__ __launch_bounds__(kThreads, workgroups_per_cu(MV, TP, KIND, VI)) void
             sum[fb][c] = 0.0f;
             if constexpr (kWide) wide[fb][c] = 0.0;
         }
+    auto widen = [&]() {
+        if constexpr (kWide) {
+#pragma unroll
+            for (int fb = 0; fb < 2; ++fb)
+#pragma unroll
+                for (int c = 0; c < TP; ++c) {
+                    wide[fb][c] += (double)sum[fb][c];
+                    sum[fb][c] = 0.0f;
+                }
+        }
+    };
     // MV: output tile [column][fixed point] of each fixed block, and this thread's column scale
     f32x16 dacc[G][2];
     float vscale[G];
@@ -741,6 +762,8 @@ __global__ __launch_bounds__(kThreads, workgroups_per_cu(MV, TP, KIND, VI)) void
 #pragma unroll
                     for (int c = 0; c < TP; ++c) sum[fb][c] = fmaf(p, vr[cur][c], sum[fb][c]);
                 }
+                if constexpr (FINE)
+                    if (it % kFineTerms == kFineTerms - 1 && it + 1 < 64) widen();
             }
             if constexpr (KIND != KNM_KERNEL_GAUSSIAN) {
                 if (__builtin_amdgcn_ballot_w64(any_near) != 0) {
@@ -757,15 +780,7 @@ __global__ __launch_bounds__(kThreads, workgroups_per_cu(MV, TP, KIND, VI)) void
                     }
                 }
             }
-            if constexpr (kWide) {
-#pragma unroll
-                for (int fb = 0; fb < 2; ++fb)
-#pragma unroll
-                    for (int c = 0; c < TP; ++c) {
-                        wide[fb][c] += (double)sum[fb][c];
-                        sum[fb][c] = 0.0f;
-                    }
-            }
+            widen();
         }
     }
 
@@ -914,7 +929,9 @@ void launch_tp(const SweepArgs &a, const f16x8 *Fimg, const f16x8 *Simg, int64_t
         // (which the dispatcher gives at most 128 columns at a time) have no such instantiation
         if constexpr (MV && TP == 10 && decltype(kind)::value != KNM_KERNEL_GAUSSIAN) return;
         else {
-        auto *const kernel = gauss_gemm_f16_kernel<TP, MV, decltype(kind)::value, VI>;
+        auto *kernel = gauss_gemm_f16_kernel<TP, MV, decltype(kind)::value, VI>;
+        if constexpr (!MV && TP <= wide_columns(decltype(kind)::value) && decltype(kind)::value == KNM_KERNEL_GAUSSIAN)
+            if (a.out64 != nullptr) kernel = gauss_gemm_f16_kernel<TP, MV, decltype(kind)::value, VI, true>;
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds_bytes) != hipSuccess)
             return;
