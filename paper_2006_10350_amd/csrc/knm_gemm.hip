@@ -70,6 +70,8 @@ __device__ __forceinline__ float acc_read(const float &x)
     return p;
 }
 
+constexpr int kWideColumns = 12; // columns up to which fp64 running sums are kept beside the fp32 sums of a tile
+
 // TP: number of vector columns, padded to a multiple of 4.  VW: 4 if rows can be read
 // with aligned 16-byte loads, else 1.
 template <int TP, int VW, int KIND>
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(kThreads, 2) void gauss_gemm_kernel(SweepArgs a)
     // does not grow with the chunk (with 16 columns the registers hold only the fp32 sums, which
     // then run through the chunk).  Where the result is asked for in fp64 (a solver's K^T w, whose rounding T^-T amplifies) the
     // fp32 sums of the Gaussian kernel cover 8 terms.
-    constexpr bool kWide = TP <= 12;
+    constexpr bool kWide = TP <= kWideColumns;
     float sum[2][TP];
     double wide[2][kWide ? TP : 1];
 #pragma unroll
@@ -397,6 +399,7 @@ hipError_t launch_tp(const SweepArgs &a, hipStream_t stream)
 } // namespace
 
 int gemm_max_t() { return 16; }
+bool gemm_fp32_sums(int t) { return t > kWideColumns; }
 // the stagers form row offsets within a block of 256 fixed + 128 stream points in 32 bits
 bool gemm_leading_dimension_ok(int64_t ld) { return ld <= (int64_t)0x7fffffff / 384; }
 int64_t gemm_stage_points() { return kStream; }

@@ -974,6 +974,7 @@ static bool reduce_on_matrix_cores(int d, int t)
     return t > 16 || (t >= kMvMinT && 4 * (3 + t) >= 3 * n_kc + 1);
 }
 bool gemm_f16_matrix_reduction(int d, int t) { return reduce_on_matrix_cores(d, t); }
+bool gemm_f16_fp32_sums(int d, int t, int kind) { return reduce_on_matrix_cores(d, t) || t > wide_columns(kind); }
 int gemm_f16_workgroups_per_cu(int d, int t, int kind)
 {
     const bool mv = reduce_on_matrix_cores(d, t);

@@ -158,6 +158,9 @@ int gemm_f16_group_t(int d, int t_left, int kind, bool with_vector_image); // co
 size_t gemm_f16_vector_image_bytes(int d, int t, int64_t nS_padded);
 int gemm_f16_workgroups_per_cu(int d, int t, int kind); // of a launch with t columns and the packed vector image
 bool gemm_f16_matrix_reduction(int d, int t);           // the reduction against t columns runs on the matrix cores
+// sums over the stream points run through a chunk in fp32 (else those of a tile are added in fp64)
+bool gemm_f16_fp32_sums(int d, int t, int kind);
+bool gemm_fp32_sums(int t);
 size_t gemm_f16_min_pack_bytes(int64_t nF, int64_t nS_padded, int64_t chunk_len, int d);
 hipError_t launch_sweep_gemm_f16(const SweepArgs &a, void *pack_buf, size_t pack_bytes, hipStream_t stream);
 // out[j * ldo] = sum over chunks of part[chunk * chunk_stride + j * ldp], summed in fp64 in a fixed
