@@ -340,9 +340,11 @@ static bool bad_geom(const void *X, int64_t n, int d, int64_t ldx, const void *C
 // points exactly as they are (data with many exact zeros keeps them: the matrix cores draw less
 // power on such operands, and the sweep runs measurably faster).
 // Workgroup (x, y): features [x << fbits, ...), 256 >> fbits row lanes over row group y; fp64 partials, which the last
-// workgroup to finish (`done` counts and wraps to zero) adds up in a fixed order.  One launch of about 5 us; with one
-// workgroup per 32 features and a second launch for the decision it took 40 us, which is the whole time of a small sweep.
-constexpr int64_t kMeanSample = 4096; // rows of the sample at most
+// workgroup to finish (`done` counts and wraps to zero) adds up in a fixed order.  Bound by the latency of its loads: 5 us for
+// 1000 rows of 8 features, 9 us for 10000, 11 us for 16384 of 28, 40 us for 10000 of 784 (two launches and one
+// workgroup per 32 features before: 4, 16, 46 and 30 us; the partials' sum without loads in flight and up to 1600 workgroups
+// at the counter: 161 us for the last).
+constexpr int64_t kMeanSample = 16384; // rows of the sample at most
 constexpr int kMeanGroups = 64;       // row groups at most
 __global__ __launch_bounds__(256) void column_shift_kernel(const float *__restrict__ P, int rows, int64_t stride, int64_t ld, int d,
                                                           float inv2s2, int fbits, double *__restrict__ part, unsigned *__restrict__ done,
@@ -383,6 +385,7 @@ __global__ __launch_bounds__(256) void column_shift_kernel(const float *__restri
     double sq = 0.0;
     for (int c = tid; c < d; c += 256) {
         double total = 0.0;
+#pragma unroll 16
         for (int y = 0; y < groups; ++y) total += part[(int64_t)y * d + c];
         const float m = (float)(total / (double)rows);
         const float v = (m == m && fabsf(m) < 3.0e38f) ? m : 0.0f; // a NaN or Inf in the data must not spread to every point
@@ -401,12 +404,15 @@ __global__ __launch_bounds__(256) void column_shift_kernel(const float *__restri
     if (tid == 0) mu[d] = keep ? 1.0f : 0.0f; // lets the hot loops skip the loads of an all-zero shift
 }
 // mu_buf: the shift and its flag, then (8-byte aligned) the partials
+static int mean_feature_bits(int d) { return d <= 8 ? 3 : d <= 16 ? 4 : 5; }
+static int mean_feature_groups(int d) { return (d + (1 << mean_feature_bits(d)) - 1) >> mean_feature_bits(d); }
 static int mean_groups(int64_t rows, int d)
 {
     int64_t g = (rows + 63) / 64;
     if (g > kMeanGroups) g = kMeanGroups;
-    if (g * d > 65536) g = 65536 / d > 0 ? 65536 / d : 1;
-    return (int)g;
+    // at most 256 workgroups: each pays for a fence and a turn at the counter
+    const int most = 256 / mean_feature_groups(d);
+    return g > most ? (most > 0 ? most : 1) : (int)g;
 }
 static size_t mu_offset(int d) { return (sizeof(float) * ((size_t)d + 1) + 7) & ~(size_t)7; }
 static size_t mu_bytes_wanted(int64_t rows, int d)
@@ -417,10 +423,9 @@ static int column_shift(knm_ctx *ctx, const float *P, int64_t rows, int64_t ld, 
 {
     const int64_t stride = (rows + kMeanSample - 1) / kMeanSample; // every stride-th row, spread over the set
     const int sample = (int)((rows + stride - 1) / stride);
-    const int fbits = d <= 8 ? 3 : d <= 16 ? 4 : 5;
     double *part = reinterpret_cast<double *>(reinterpret_cast<char *>(mu) + mu_offset(d));
-    hipLaunchKernelGGL(column_shift_kernel, dim3((unsigned)((d + (1 << fbits) - 1) >> fbits), (unsigned)mean_groups(sample, d)), dim3(256),
-                       0, ctx->stream, P, sample, stride, ld, d, 1.0f / (2.0f * sigma * sigma), fbits, part, ctx->range_count + 32, mu);
+    hipLaunchKernelGGL(column_shift_kernel, dim3((unsigned)mean_feature_groups(d), (unsigned)mean_groups(sample, d)), dim3(256),
+                       0, ctx->stream, P, sample, stride, ld, d, 1.0f / (2.0f * sigma * sigma), mean_feature_bits(d), part, ctx->range_count + 32, mu);
     return hipGetLastError() == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "column_shift_kernel launch");
 }
 

@@ -218,6 +218,25 @@ def test_large_norm_close_pairs(knm, cross):
     assert rel_l2(W2, oracle.knm_v(X2.numpy(), C.numpy(), sigma, V.numpy())) < TIGHT
 
 
+def test_shift_of_rows_in_a_regular_order(knm, cross):
+    """Every fourth centre far from the others: the shift has to come from all of 16384 rows, as it does when the same rows are
+    stored in random order.  (A sample of every fourth row finds the far ones only: 12 to 21 times the error in W.)"""
+    M, d, sigma = 16384, 8, 1.0
+    g = torch.Generator().manual_seed(77)
+    C = 11.0 + 0.5 * torch.randn(M, d, generator=g)
+    C[::4] -= 11.0
+    V = torch.rand(M, 1, generator=g)
+    X = 11.0 + 0.5 * torch.randn(20000, d, generator=g)
+    rows = torch.arange(0, 20000, 401)
+    ref = oracle.knm_v(X[rows].numpy(), C.numpy(), sigma, V.numpy())
+    errors = []
+    for order in (torch.arange(M), torch.randperm(M, generator=g)):
+        W = knm.knm_v(X.cuda(), C[order].cuda(), sigma, V[order].cuda())[rows.cuda()].cpu().numpy()
+        errors.append(rel_l2(W, ref))
+    print(f"in order {errors[0]:.2e}, at random {errors[1]:.2e}", flush=True)
+    assert errors[0] < 2.0 * errors[1]
+
+
 def test_split_half_range_limits(knm):
     """The split-fp16 cross term saturates instead of producing Inf/NaN, and huge norms
     (far outliers) still give exact zeros against ordinary points."""
