@@ -74,6 +74,7 @@ SIGNATURES = {
     "knm_set_kernel": (_int, [_vp, _int]),
     "knm_set_sparse_head_limit": (_int, [_vp, _int]),
     "knm_workspace_held": (ctypes.c_size_t, [_vp]),
+    "knm_release_workspace": (_int, [_vp]),
     "knm_set_pack_limit": (_int, [_vp, ctypes.c_size_t]),
     "knm_set_timing": (_int, [_vp, _int]),
     "knm_range_exceeded": (_int, [_vp, ctypes.POINTER(_i64), _int]),
@@ -191,6 +192,10 @@ class Context:
     def workspace_held(self) -> int:
         """Device bytes of workspace this context holds now."""
         return int(load_library().knm_workspace_held(self._h))
+
+    def release_workspace(self) -> None:
+        """Give the context's workspace back to the device (waits for its stream)."""
+        self.check(load_library().knm_release_workspace(self._h))
 
     def set_sparse_head_limit(self, max_features: int):
         """Sparse inputs: how many of the most frequent features may be handled densely (0: none)."""

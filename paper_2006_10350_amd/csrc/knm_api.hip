@@ -8,6 +8,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <utility>
 
 #include "knm_internal.h"
 
@@ -66,22 +67,44 @@ int fail(knm_ctx *ctx, int status, const char *what, hipError_t e)
     return status;
 }
 
-// hipMalloc that frees the idle blocks of the pool when there is no room (the pool's lock is held)
+// frees the idle blocks of the pool (its lock is held; hipFree waits for the device)
+static void free_idle_locked(knm_ctx *ctx)
+{
+    for (size_t i = 0; i < ctx->pool.size();) {
+        if (ctx->pool[i].used) {
+            ++i;
+            continue;
+        }
+        (void)hipFree(ctx->pool[i].p);
+        ctx->pool.erase(ctx->pool.begin() + (std::ptrdiff_t)i);
+    }
+    ctx->pool_idle = 0;
+}
+
+// hipMalloc that gives up the idle blocks of the pool, and then the kept images of the fit that is running (its sweeps pack slab
+// by slab from there on), when there is no room (the pool's lock is held)
 static hipError_t alloc_locked(knm_ctx *ctx, size_t bytes, void **out)
 {
     *out = nullptr;
     hipError_t e = hipMalloc(out, bytes);
     if (e != hipSuccess && ctx->pool_idle > 0) {
         (void)hipGetLastError();
-        for (size_t i = 0; i < ctx->pool.size();) {
-            if (ctx->pool[i].used) {
-                ++i;
-                continue;
-            }
-            (void)hipFree(ctx->pool[i].p);
-            ctx->pool.erase(ctx->pool.begin() + (std::ptrdiff_t)i);
+        free_idle_locked(ctx);
+        e = hipMalloc(out, bytes);
+    }
+    SweepShare *sh = ctx->share;
+    if (e != hipSuccess && sh != nullptr && sh->pooled && sh->rows[0] > 0) {
+        (void)hipGetLastError();
+        for (int k = 0; k < 2; ++k) {
+            for (auto &b : ctx->pool)
+                if (b.p == sh->img[k]) {
+                    b.used = false;
+                    ctx->pool_idle += b.bytes;
+                }
+            sh->img[k] = nullptr;
+            sh->rows[k] = sh->ready[k] = 0;
         }
-        ctx->pool_idle = 0;
+        free_idle_locked(ctx);
         e = hipMalloc(out, bytes);
     }
     if (e != hipSuccess) {
@@ -641,8 +664,8 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
         const size_t mark_used = ctx->static_used;
         const int64_t f_rows = (nF + gemm_fixed_per_block() - 1) / gemm_fixed_per_block() * gemm_fixed_per_block();
         const int64_t s_rows = chunks * chunk_len;
-        const bool kept = shared && sh->img[0] != nullptr && sh->rows[set_s] >= s_rows && (!gemm || sh->rows[set_f] >= f_rows);
-        if (kept) {
+        bool kept = shared && sh->img[0] != nullptr && sh->rows[set_s] >= s_rows && (!gemm || sh->rows[set_f] >= f_rows);
+        auto use_images = [&] {
             a.simg = sh->img[set_s];
             a.simg_ready = sh->ready[set_s] >= s_rows;
             if (!a.simg_ready) sh->ready[set_s] = s_rows;
@@ -651,7 +674,7 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
                 a.fimg_ready = sh->ready[set_f] >= f_rows;
                 if (!a.fimg_ready) sh->ready[set_f] = f_rows;
             }
-        }
+        };
         if (gemm && ctx->cross_term == KNM_CROSS_F16X3) {
             size_t want = gemm_f16_head_bytes();
             int st = kept ? KNM_OK : pack_room(&want);
@@ -665,6 +688,13 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
                 if (st) return st;
                 a.vimg = ctx->vimg_buf;
             }
+            if (kept && sh->img[0] == nullptr) { // given up for one of these two
+                kept = false;
+                st = pack_room(&want);
+                if (!st) st = acquire(ctx, &ctx->pack_buf, &ctx->pack_bytes, want, &pack);
+                if (st) return st;
+            }
+            if (kept) use_images();
             e = launch_sweep_gemm_f16(a, pack, want, ctx->stream);
         } else if (gemm) {
             e = launch_sweep_gemm(a, ctx->stream);
@@ -676,6 +706,7 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
                 if (!st) st = acquire(ctx, &ctx->pack_buf, &ctx->pack_bytes, want, &pack);
             }
             if (st) return st;
+            if (kept) use_images();
             e = launch_sweep_f16(a, pack, want, ctx->stream);
         } else {
             e = launch_sweep(a, ctx->stream);
@@ -854,6 +885,25 @@ size_t knm_workspace_held(const knm_ctx *ctx)
 {
     if (!ctx) return 0;
     return ctx->w_bytes + ctx->part_bytes + ctx->pack_bytes + ctx->vimg_bytes + ctx->mu_bytes + ctx->pool_idle;
+}
+
+int knm_release_workspace(knm_ctx *ctx)
+{
+    if (!ctx) return KNM_INVALID_ARG;
+    if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipSetDevice");
+    hipError_t e = hipStreamSynchronize(ctx->stream);
+    if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "knm_release_workspace", e);
+    for (auto held : {std::make_pair(&ctx->w_buf, &ctx->w_bytes), std::make_pair(&ctx->part_buf, &ctx->part_bytes),
+                      std::make_pair(&ctx->pack_buf, &ctx->pack_bytes), std::make_pair(&ctx->vimg_buf, &ctx->vimg_bytes),
+                      std::make_pair(&ctx->mu_buf, &ctx->mu_bytes)}) {
+        const hipError_t freed = *held.first ? hipFree(*held.first) : hipSuccess;
+        if (e == hipSuccess) e = freed;
+        *held.first = nullptr;
+        *held.second = 0;
+    }
+    const std::lock_guard<std::mutex> lock(ctx->pool_lock);
+    free_idle_locked(ctx);
+    return e == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "knm_release_workspace", e);
 }
 
 static int check_common(knm_ctx *ctx, const void *X, int64_t n, int d, int64_t ldx, const void *C, int64_t M,

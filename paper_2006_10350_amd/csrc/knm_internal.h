@@ -277,7 +277,8 @@ int ensure(knm_ctx *ctx, float **buf, size_t *cur, size_t need);
 // it, because hipMalloc and hipFree cost 10 to 80 us each (2.4 ms of a 9.5 ms sparse product).  Work on a context is
 // ordered by its stream, so a block can be given back while kernels that use it are still queued.  Idle blocks of more than
 // 4 GiB in all are freed, and knm_destroy frees the rest.
-hipError_t device_alloc(knm_ctx *ctx, size_t bytes, void **out); // hipMalloc, with the idle blocks given up if there is no room
+// hipMalloc, with the idle blocks and then the running fit's images given up if there is no room
+hipError_t device_alloc(knm_ctx *ctx, size_t bytes, void **out);
 hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out);
 void pool_give(knm_ctx *ctx, void *p);
 int fail(knm_ctx *ctx, int status, const char *what, hipError_t e = hipSuccess);

@@ -1,0 +1,96 @@
+"""What the library does when device memory runs out in the middle of a call, and that its workspace can be had back: on the
+host, with a HIP runtime that only counts memory (fake_hip.c)."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB = os.path.join(os.path.dirname(HERE), "paper_2006_10350_amd", "libknm.so")
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("hip") / "libfakehip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-Wl,-soname,libfakehip.so", "-o", out, os.path.join(HERE, "fake_hip.c")], check=True)
+    return out
+
+
+def _run(shim, body):
+    """In a process of its own: the fake runtime must come before the real one."""
+    head = f"""
+        import ctypes as c
+        hip = c.CDLL({shim!r}, mode=c.RTLD_GLOBAL)
+        lib = c.CDLL({LIB!r})
+        hip.fake_set_budget.argtypes = [c.c_size_t]
+        hip.fake_live.restype = hip.fake_peak.restype = lib.knm_workspace_held.restype = c.c_size_t
+        lib.knm_workspace_held.argtypes = lib.knm_release_workspace.argtypes = lib.knm_destroy.argtypes = [c.c_void_p]
+        P, L, I, F, D = c.c_void_p, c.c_int64, c.c_int, c.c_float, c.c_double
+        lib.falkon_fit.argtypes = [P, P, L, I, L, P, I, P, L, L, F, D, D, I, P, P]
+        ctx = P()
+        assert lib.knm_create(c.byref(ctx), 0, None) == 0
+        created = hip.fake_live()
+        x, cen, y, alpha = (P(0x7f0000000000 + (i << 36)) for i in range(4))  # never read: kernels do not run
+
+        def fit(n, d, M, t):
+            return lib.falkon_fit(ctx, x, n, d, d, y, t, cen, M, d, 1.0, 1e-6, 1e-6, 3, alpha, None)
+        """
+    r = subprocess.run([sys.executable, "-c", textwrap.dedent(head) + textwrap.dedent(body)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_images_are_given_up_when_a_fit_needs_the_room(shim):
+    # 40M rows of 28 features: 5.1 GB of kept images, taken at the first sweep; W and the partials come after them.  Sweeps that
+    # pack slab by slab get by with 2 GiB.
+    _run(shim, """
+        n, d, M, t = 40_000_000, 28, 1000, 1
+        assert fit(n, d, M, t) == 0
+        peak = hip.fake_peak()
+        assert peak > 128 * n
+        lib.knm_destroy(ctx)
+        assert hip.fake_live() == 0
+        for budget in (peak - 1, peak - (64 << 20), 128 * n, 3 << 30):
+            ctx = P()
+            assert lib.knm_create(c.byref(ctx), 0, None) == 0
+            hip.fake_set_budget(budget)
+            assert fit(n, d, M, t) == 0, (budget, peak)
+            assert hip.fake_peak() <= budget
+            lib.knm_destroy(ctx)
+            assert hip.fake_live() == 0
+            hip.fake_set_budget(1 << 50)
+        """)
+
+
+def test_a_fit_without_room_fails_and_leaves_nothing(shim):
+    _run(shim, """
+        for n, d, M, t in ((40_000_000, 28, 1000, 1), (2_000_000, 300, 2000, 20)):
+            hip.fake_set_budget(1 << 50)
+            assert fit(n, d, M, t) == 0
+            peak = hip.fake_peak()
+            refused = 0
+            for part in range(1, 40):  # budgets that end at every stage of the call
+                hip.fake_set_budget(peak * part // 40)
+                lib.knm_release_workspace(ctx)
+                assert hip.fake_live() == created
+                st = fit(n, d, M, t)
+                assert st in (0, -3)
+                refused += st != 0
+                assert hip.fake_live() == created + lib.knm_workspace_held(ctx)
+            assert 0 < refused < 39
+            hip.fake_set_budget(1 << 50)
+            assert fit(n, d, M, t) == 0  # the context is as good as new
+        """)
+
+
+def test_workspace_can_be_had_back(shim):
+    _run(shim, """
+        assert fit(1_000_000, 28, 5000, 1) == 0 and fit(100_000, 300, 3000, 20) == 0
+        held = lib.knm_workspace_held(ctx)
+        assert held > 1 << 28 and hip.fake_live() == created + held
+        assert lib.knm_release_workspace(ctx) == 0
+        assert lib.knm_workspace_held(ctx) == 0 and hip.fake_live() == created
+        assert fit(100_000, 300, 3000, 20) == 0
+        assert lib.knm_release_workspace(None) == -1
+        """)
