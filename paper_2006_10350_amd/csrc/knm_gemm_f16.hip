@@ -47,6 +47,7 @@
 
 #include "knm_internal.h"
 #include "knm_operands.h"
+#include "knm_patch_map.h"
 
 namespace knm {
 namespace {
@@ -207,61 +208,6 @@ __device__ __forceinline__ float column_scale(uint32_t bits, bool inverse)
     const int shift = 13 - (e - 127);
     return ldexpf(1.0f, inverse ? -shift : shift);
 }
-
-// Workgroup -> (fixed block, stream chunk).  Workgroups are dealt round-robin to the 8 XCDs
-// (each with its own L2) in launch order, and the ones resident together on an XCD are
-// consecutive in that order.  They are therefore numbered so that each XCD works through
-// "patches" of pf fixed blocks x pc chunks: the pf fixed-block images, which every
-// workgroup re-reads for each of its stream tiles, stay in that XCD's L2, and a stream tile
-// fetched by one workgroup is reused by the pf - 1 others on the same chunk.  The chunks are taken in groups of pc (the last one
-// narrower).  In each, 8 patches at a time go to the 8 XCDs, and the fixed blocks that are left when fewer
-// than 8 whole patches remain are split evenly over them: every XCD gets the same number of workgroups to within
-// one per group (whole patches dealt out left some XCDs with a fifth more than others at 235 fixed blocks x 5 chunks).
-struct PatchMap {
-    int pc;                  // chunks of a group
-    int64_t n_fblocks;       // fixed blocks of this launch
-    int64_t full_groups;     // groups of pc chunks; slots_full places per XCD each
-    int64_t slots_full, slots_last;
-    int pc_last;             // chunks of the last group (0: none)
-    int pf, pf_last;         // fixed blocks of a patch
-    static int64_t slots(int64_t n_f, int pf, int pc)
-    {
-        const int64_t whole = n_f / (8 * pf);
-        return whole * pf * pc + ((n_f - whole * 8 * pf) * pc + 7) / 8;
-    }
-    // false: no work for this workgroup
-    __device__ bool find(int64_t block, int64_t &f, int64_t &c) const
-    {
-        const int xcd = (int)(block & 7);
-        int64_t slot = block >> 3;
-        int64_t group = full_groups;
-        int gc = pc_last, gf = pf_last;
-        if (slot < full_groups * slots_full) {
-            group = slot / slots_full;
-            slot -= group * slots_full;
-            gc = pc;
-            gf = pf;
-        } else {
-            slot -= full_groups * slots_full;
-            if (slot >= slots_last) return false;
-        }
-        const int per_patch = gf * gc;
-        const int64_t whole = n_fblocks / (8 * gf);
-        if (slot < whole * per_patch) {
-            const int within = (int)(slot % per_patch);
-            f = ((slot / per_patch) * 8 + xcd) * gf + within % gf;
-            c = group * pc + within / gf;
-            return true;
-        }
-        slot -= whole * per_patch;
-        const int64_t rest = (n_fblocks - whole * 8 * gf) * gc, share = (rest + 7) / 8;
-        const int64_t i = xcd * share + slot;
-        if (i >= rest) return false;
-        f = whole * 8 * gf + i / gc;
-        c = group * pc + i % gc;
-        return true;
-    }
-};
 
 // Fimg: image of the fixed points [fixed_row0, fixed_row0 + 256 n_fblocks);
 // Simg: image of the stream chunks [chunk0, chunk0 + n_chunks).
@@ -900,9 +846,6 @@ hipError_t pack_points(const float *P, int64_t nP, int64_t ld, const float *mu, 
     return hipGetLastError();
 }
 
-constexpr int kPatch = 64;  // workgroups per patch = resident workgroups per XCD (32 CUs x 2)
-constexpr int kPatchF = 8;  // fixed blocks per patch (measured: 2..8 within 4 % of each other, 64 is 25 % slower)
-
 constexpr int kMvMinT = 8;    // columns from which the reduction against the vectors may run on the matrix cores
 constexpr size_t kHeadBytes = 1024; // head of the workspace: per-column magnitude words for that path (up to 256 columns)
 
@@ -910,16 +853,8 @@ template <int TP, bool MV, bool VI = false>
 void launch_tp(const SweepArgs &a, const f16x8 *Fimg, const f16x8 *Simg, int64_t fixed_row0, int64_t f_blocks,
                int64_t chunk0, int64_t chunks, int n_kc, const uint32_t *colmax, hipStream_t stream)
 {
-    PatchMap pm;
-    pm.pc = kPatch / kPatchF;
-    pm.pf = kPatchF;
-    pm.n_fblocks = f_blocks;
-    pm.full_groups = chunks / pm.pc;
-    pm.pc_last = (int)(chunks % pm.pc);
-    pm.pf_last = pm.pc_last > 0 ? kPatch / pm.pc_last : 1; // as many workgroups per patch
-    pm.slots_full = PatchMap::slots(f_blocks, pm.pf, pm.pc);
-    pm.slots_last = pm.pc_last > 0 ? PatchMap::slots(f_blocks, pm.pf_last, pm.pc_last) : 0;
-    const dim3 grid((unsigned)(8 * (pm.full_groups * pm.slots_full + pm.slots_last)));
+    const PatchMap pm = PatchMap::make(f_blocks, chunks);
+    const dim3 grid((unsigned)pm.workgroups());
     // dynamic LDS: the ring of stages and the vector rows of a tile (more than the 64 KB a kernel gets
     // without asking)
     constexpr int kVecUnits = MV ? (TP / 2) * 4 * 2 * 2 * 64 : (kStream * TP * 4 + 15) / 16;

@@ -1,7 +1,9 @@
-"""How a sweep's stream is cut into chunks (host code of the library, no GPU needed)."""
+"""How a sweep's stream is cut into chunks, and which workgroup takes which of them (host code, no GPU needed)."""
 import ctypes
 import itertools
+import os
 import random
+import subprocess
 
 import pytest
 
@@ -69,3 +71,43 @@ def test_chunks_cover_the_stream_within_their_bounds(plan):
             assert length <= compact, shape
         if 4 * chunks * nF * t > 48 << 20:
             assert chunks <= max(-(-nS // compact), 1), shape
+
+
+def test_every_workgroup_pair_is_taken_once(tmp_path):
+    """The numbering of the K-loop engine's workgroups over the XCDs: every (fixed block, chunk) once, none outside."""
+    import paper_2006_10350_amd as pkg
+
+    csrc = os.path.join(os.path.dirname(pkg.LIB_PATH), "csrc")
+    (tmp_path / "map.cpp").write_text("""
+        #include "knm_patch_map.h"
+        #include <cstdio>
+        #include <vector>
+        int main()
+        {
+            for (int64_t blocks = 1; blocks <= 700; blocks += blocks < 140 ? 1 : 37)
+                for (int64_t chunks = 1; chunks <= 70; ++chunks) {
+                    const knm::PatchMap pm = knm::PatchMap::make(blocks, chunks);
+                    std::vector<int> seen((size_t)(blocks * chunks), 0);
+                    int64_t per_xcd[8] = {0};
+                    for (int64_t wg = 0; wg < pm.workgroups(); ++wg) {
+                        int64_t f, c;
+                        if (!pm.find(wg, f, c)) continue;
+                        if (f < 0 || f >= blocks || c < 0 || c >= chunks || seen[(size_t)(f * chunks + c)]++) return 1;
+                        ++per_xcd[wg & 7];
+                    }
+                    int64_t most = 0, total = 0;
+                    for (int64_t n : per_xcd) {
+                        most = n > most ? n : most;
+                        total += n;
+                    }
+                    if (total != blocks * chunks) return 2;
+                    // no XCD more than one above the even share per group of 8 chunks
+                    if (8 * most > total + 8 * ((chunks + 7) / 8)) return 3;
+                }
+            return 0;
+        }
+        """)
+    exe = str(tmp_path / "map")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-D__HIP_PLATFORM_AMD__", "-I", csrc, "-I", "/opt/rocm/include", "-o", exe,
+                    str(tmp_path / "map.cpp")], check=True)
+    assert subprocess.run([exe], timeout=100).returncode == 0
