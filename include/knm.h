@@ -84,7 +84,8 @@ int knm_prod(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx,
              const float *V, int t, float *W_or_null, float *U);
 
 /* knm_prod for callers that cannot allocate device memory: code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc.  Same arguments and result as knm_prod, except that
+ * serving loops, harnesses that forbid hipMalloc.  Same arguments and result as knm_prod (up to the last bits where the
+ * array below holds fewer partials than knm_prod would make), except that
  * W (n x t) must be given.  The call allocates nothing: the chunk partials, the common shift and the
  * converted operands of the split-fp16 engines live in a static device array of
  * knm_static_scratch_bytes() bytes (64 MiB) that every GPU the library runs on holds until the process

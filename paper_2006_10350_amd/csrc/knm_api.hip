@@ -274,7 +274,8 @@ static int64_t choose_chunks_compact(int64_t nF, int64_t nS, int d, int t, int c
 // at d = 50, 100, 200, 440 and 784, 1 and 10 columns, 60k x 10k, 300k x 3k and 15k x 15k points, both sweeps: within 2 % in 59 of
 // 60, 4.7 % in one.  n = 60k, d = 784, M = 10k, 10 columns ran
 // 1175 workgroups of 16 tiles on 512 places: 2.48 ms per sweep, 2.0 ms cut finer.
-int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind, int64_t *chunk_len)
+// (any_length: the choice by time alone, whatever the length of fp32 sums)
+static int64_t choose_chunks_by_time(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind, bool any_length, int64_t *chunk_len)
 {
     const bool gemm = use_gemm_engine(d, t, cross_term, kind);
     const bool f16 = cross_term == KNM_CROSS_F16X3;
@@ -312,7 +313,7 @@ int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int 
     // matrix-core reduction cut into 1 chunk in place of 16 the error of W against 64 bits went from 2.7e-7 to 3.1e-5
     // (n = 4.6M, M = 90k, 19 columns, v >= 0), and from 2.5e-7 to 4.4e-7 in U at n = 120k, M = 20k, 144 columns
     const bool fp32_sums = !gemm || (f16 ? gemm_f16_fp32_sums(d, t, kind) : gemm_fp32_sums(t));
-    const int64_t least = fp32_sums && most > g.min_chunks ? most : g.min_chunks;
+    const int64_t least = fp32_sums && !any_length && most > g.min_chunks ? most : g.min_chunks;
     const int64_t by_bytes = (int64_t)(((size_t)48 << 20) / (sizeof(float) * (size_t)nF * t));
     if (by_bytes > most) most = by_bytes;
     double best = 0.0;
@@ -350,6 +351,11 @@ int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int 
     int64_t len = (g.stages + best_chunks - 1) / best_chunks;
     *chunk_len = len * g.stage;
     return (g.stages + len - 1) / len;
+}
+
+int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind, int64_t *chunk_len)
+{
+    return choose_chunks_by_time(nF, nS, d, t, cross_term, kind, false, chunk_len);
 }
 
 static bool bad_geom(const void *X, int64_t n, int d, int64_t ldx, const void *C, int64_t M, int64_t ldc,
@@ -562,12 +568,16 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
     int64_t chunks = choose_chunks(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
     if (ctx->static_mode) {
         // where these partials and the least operand images do not fit the scratch together: fewer chunks
-        const bool packs = ctx->cross_term == KNM_CROSS_F16X3;
-        const size_t least = !packs ? 0
-                             : use_gemm_engine(d, t, ctx->cross_term, ctx->kernel_kind) ? gemm_f16_min_pack_bytes(nF, chunks * chunk_len, chunk_len, d)
-                                                                                       : f16_pack_bytes_per_point(d) * (size_t)chunk_len;
-        if (sizeof(float) * (size_t)chunks * nF * t + mu_bytes_wanted(kMeanSample, d) + least + 1024 > kStaticScratchBytes)
-            chunks = choose_chunks_compact(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
+        auto fits = [&] {
+            const bool packs = ctx->cross_term == KNM_CROSS_F16X3;
+            const size_t least = !packs ? 0
+                                 : use_gemm_engine(d, t, ctx->cross_term, ctx->kernel_kind) ? gemm_f16_min_pack_bytes(nF, chunks * chunk_len, chunk_len, d)
+                                                                                           : f16_pack_bytes_per_point(d) * (size_t)chunk_len;
+            return sizeof(float) * (size_t)chunks * nF * t + mu_bytes_wanted(kMeanSample, d) + least + 1024 <= kStaticScratchBytes;
+        };
+        if (!fits()) chunks = choose_chunks_compact(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
+        if (!fits()) chunks = choose_chunks_by_time(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, true, &chunk_len);
+        if (!fits()) chunks = choose_chunks_compact(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len); // refused below
     }
     if (chunks > 65535) return fail(ctx, KNM_UNSUPPORTED, "too many stream chunks");
     const bool gemm = use_gemm_engine(d, t, ctx->cross_term, ctx->kernel_kind);

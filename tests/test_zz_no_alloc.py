@@ -59,6 +59,20 @@ def test_static_scratch_product_in_slabs(knm):
     assert rel_l2(W[rows.cuda()].cpu().numpy(), Wo) < 1e-4
 
 
+# partials that only fit when the stream is cut into fewer chunks than the ordinary call's (whose fp32 sums are shorter): taken all the same
+@pytest.mark.parametrize("n,M,d,t", [(57669, 27426, 9, 20), (103711, 2292, 17, 144)])
+def test_static_scratch_product_with_fewer_partials(knm, n, M, d, t):
+    g = torch.Generator().manual_seed(n)
+    X = torch.randn(n, d, generator=g).cuda()
+    V = torch.randn(M, t, generator=g).cuda()
+    W = torch.empty(n, t, device="cuda")
+    U = torch.empty(M, t, device="cuda")
+    knm.knm_prod_static(X, X[:M].contiguous(), 3.0, V, W, U)
+    U_ref, W_ref = knm.knm_prod(X, X[:M].contiguous(), 3.0, V, return_w=True)
+    # fp32 sums of up to 5000 terms on both sides
+    assert rel_l2(W.cpu(), W_ref.cpu()) < 5e-6 and rel_l2(U.cpu(), U_ref.cpu()) < 5e-6
+
+
 def test_static_scratch_rejects_what_does_not_fit(knm):
     # 64 MiB hold the partials of chunks x M x t floats only up to a point
     n, M, d, t = 300000, 60000, 8, 16
