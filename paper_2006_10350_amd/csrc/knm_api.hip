@@ -646,7 +646,7 @@ static int keep_values(knm_ctx *ctx, SweepShare *sh, int f, int s, bool column_s
 {
     const bool f16 = sh->cross_term == KNM_CROSS_F16X3;
     const bool ready = !f16 || (sh->img[0] != nullptr && sh->rows[f] >= kept_rows(sh->n[f]) && sh->rows[s] >= kept_rows(sh->n[s]));
-    if (sh->keep_decided || sh->uses == 0 || (f == s && sh->P[0] != sh->P[1])) return KNM_OK;
+    if (sh->keep_decided || sh->uses == 0 || !sh->pair(f, s)) return KNM_OK;
     sh->keep_decided = true;
     const size_t bytes = kept_bytes(sh->n[f], sh->n[s]);
     if (bytes > kKeepCap || !ready || !keeping_pays(sh->n[f], sh->n[s], sh->d, sh->t, sh->cross_term, sh->kind, sh->uses)) return KNM_OK;
@@ -655,6 +655,8 @@ static int keep_values(knm_ctx *ctx, SweepShare *sh, int f, int s, bool column_s
     if (pool_take(ctx, bytes, &p, true) != hipSuccess) return KNM_OK; // no room: the sweeps form the values
     sh->keep = p;
     sh->keep_columns = column_sweep;
+    sh->keep_n[0] = sh->n[f];
+    sh->keep_n[1] = sh->n[s];
     return form_values(ctx, sh, f, s, mu, static_cast<float *>(p));
 }
 
@@ -762,9 +764,9 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
         int st = share_images(ctx, sh);
         if (!st) st = keep_values(ctx, sh, set_f, set_s, column_sweep, mu);
         if (st) return st;
-        if (sh->keep && (set_f != set_s || sh->P[0] == sh->P[1])) {
-            const bool over_stream = column_sweep == sh->keep_columns;
-            const int64_t kF = over_stream ? nF : nS, kS = over_stream ? nS : nF;
+        const bool over_stream = column_sweep == sh->keep_columns;
+        const int64_t kF = over_stream ? nF : nS, kS = over_stream ? nS : nF;
+        if (sh->keep && sh->pair(set_f, set_s) && kF == sh->keep_n[0] && kS == sh->keep_n[1]) {
             const int parts = kept_chunks(kF, kS, over_stream, t);
             st = acquire(ctx, &ctx->part_buf, &ctx->part_bytes, sizeof(double) * (size_t)parts * nF * t, &part);
             if (st) return st;

@@ -137,6 +137,7 @@ struct SweepShare {
     bool keep_decided = false;
     void *keep = nullptr;
     bool keep_columns = false;
+    int64_t keep_n[2] = {0, 0};  // fixed and stream points they were formed for
     float *slab = nullptr;       // a product's: the row sweep leaves its values here (KeptRowsArgs)
     SweepShare(::knm_ctx *ctx, const float *X, int64_t n, int64_t ldx, const float *C, int64_t M, int64_t ldc, int d, float sigma, int t,
                bool pooled);
@@ -149,6 +150,10 @@ struct SweepShare {
             if (P[k] == Q && n[k] == m && ld[k] == l) return k;
         return -1;
     }
+    // Whether a sweep of set f against set s is one over the pair's kernel values, or its transpose.  A set against itself (k(C, C) in a
+    // logistic fit) is, only where the two sets are one and the same: with the base pointer alone in common (every tenth row of X
+    // as the centres, or X the first rows of C) the values are others.
+    bool pair(int f, int s) const { return f != s || (P[0] == P[1] && n[0] == n[1] && ld[0] == ld[1]); }
 };
 
 // ---- kernels of r = |x - c| (Laplacian, Matern) on the K-loop engines ---------------------

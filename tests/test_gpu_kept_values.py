@@ -91,3 +91,25 @@ def test_logistic_fit_from_kept_values(knm, n, M):
     pred = knm.falkon_predict(Xt.cuda(), Cd, sigma, alpha).cpu().numpy()
     assert rel_l2(pred, oracle.falkon_predict(Xt.numpy(), C.numpy(), sigma, ao)) < 1e-3
     assert np.allclose(loss, lo, rtol=1e-4, atol=1e-6)
+
+
+# centres that are views of the rows, or rows that are a view of the centres: the result of copies of them, to the last bit, from kept values
+@pytest.mark.parametrize("cross", ["f16x3", "f32"])
+@pytest.mark.parametrize("which", ["every tenth row", "first rows", "rows among the centres"])
+def test_logistic_fit_of_views_from_kept_values(knm, which, cross):
+    d, sigma = 500, 0.5 * math.sqrt(500)
+    P = _rand(3000, d, 21)
+    z = torch.where(P[:, :1] + 0.5 * P[:, 1:2] * P[:, 2:3] > 0, 1.0, -1.0).cuda()
+    P = P.cuda()
+    X, y, C, yC = {"every tenth row": (P, z, P[::10], z[::10].contiguous()), "first rows": (P, z, P[:300], z[:300]),
+                   "rows among the centres": (P[:300], z[:300], P[:1000], z[:1000])}[which]
+    fits = []
+    for copied in (True, False):
+        ctx = knm.Context()
+        ctx.set_cross_term(cross)
+        fits.append(knm.logfalkon_fit(X.clone() if copied else X, y, C.clone() if copied else C, yC, sigma, [1e-2, 1e-3], [4, 5], 1e-6, ctx=ctx))
+    assert torch.equal(*fits)
+    ao = oracle.logfalkon_fit(X.cpu().numpy(), y.cpu().numpy(), C.cpu().numpy(), yC.cpu().numpy(), sigma, [1e-2, 1e-3], [4, 5], 1e-6)
+    Xt = _rand(200, d, 9)
+    pred = knm.falkon_predict(Xt.cuda(), C, sigma, fits[0]).cpu().numpy()
+    assert rel_l2(pred, oracle.falkon_predict(Xt.numpy(), C.cpu().numpy(), sigma, ao)) < 1e-3
