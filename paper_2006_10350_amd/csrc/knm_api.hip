@@ -487,7 +487,8 @@ static int column_shift(knm_ctx *ctx, const float *P, int64_t rows, int64_t ld, 
 
 SweepShare::SweepShare(knm_ctx *c, const float *X, int64_t n_, int64_t ldx, const float *C, int64_t M, int64_t ldc, int d_, float sigma_,
                        int t_, bool pooled_)
-    : ctx(c), P{X, C}, n{n_, M}, ld{ldx, ldc}, d(d_), sigma(sigma_), t(t_), pooled(pooled_)
+    : ctx(c), P{X, C}, n{n_, M}, ld{ldx, ldc}, d(d_), sigma(sigma_), t(t_), shift_P(M <= n_ ? C : X), shift_n(M <= n_ ? M : n_),
+      shift_ld(M <= n_ ? ldc : ldx), pooled(pooled_)
 {
     // (an unregistered block is only one that is not given up)
     if (pooled) (void)(spare_add(ctx, 0, &keep) && spare_add(ctx, 1, &img[0]) && spare_add(ctx, 1, &img[1]));
@@ -747,10 +748,9 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
         const float *P = from_f ? F : S;
         int64_t rows = from_f ? nF : nS, ld = from_f ? ldf : lds;
         if (shared) {
-            const int k = sh->n[1] <= sh->n[0] ? 1 : 0;
-            P = sh->P[k];
-            rows = sh->n[k];
-            ld = sh->ld[k];
+            P = sh->shift_P;
+            rows = sh->shift_n;
+            ld = sh->shift_ld;
         }
         int st = acquire(ctx, &ctx->mu_buf, &ctx->mu_bytes, mu_bytes_wanted(rows, d), &mu);
         if (st) return st;
@@ -1162,7 +1162,8 @@ static int prod_kept(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx
     if (chunks > 65535 || !values.take(kept_bytes(rows, M)) || !part.take(sizeof(float) * (size_t)chunks * M * t) || !state.take(2 * state_bytes) ||
         (dw != nullptr && !weighted.take(sizeof(float) * (size_t)rows * t)))
         return KNM_OK;
-    SweepShare share(ctx, X, rows, ldx, C, M, ldc, d, sigma, t, false);
+    SweepShare share(ctx, X, n, ldx, C, M, ldc, d, sigma, t, false); // (the shift is that of the whole pair, for all slabs)
+    share.n[0] = rows;
     share.slab = static_cast<float *>(values.p);
     const ShareScope scope(share);
     k.values = share.slab;

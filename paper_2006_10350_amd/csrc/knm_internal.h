@@ -123,6 +123,9 @@ struct SweepShare {
     int d;
     float sigma;
     int t;                       // columns of the sweeps
+    // the smaller set, as a whole: the common shift is that of its rows, also where P[0] goes through X in slabs
+    const float *shift_P;
+    int64_t shift_n, shift_ld;
     // a fit's or sparse product's: images of both engines kept in blocks of the pool; else (a product) those of the K-loop engine, whose
     // two sweeps need both of them, in the context's image workspace
     bool pooled;

@@ -52,6 +52,24 @@ def test_product_in_slabs(knm, t):
     assert float((W - v).norm() / v.norm()) < 1e-6
 
 
+# slabs with fewer rows than there are centres, the first of them far from everything else: the common shift is the whole pair's (that of the
+# first slab left an error of 4e-3 in W and another U than knm_t_y's)
+def test_product_in_slabs_of_sorted_rows(knm):
+    n, M, d, sigma = 40000, 36000, 400, 16.0
+    g = torch.Generator(device="cuda").manual_seed(2)
+    X = torch.randn(n, d, generator=g, device="cuda")
+    X[:16384] += 100.0 * sigma / math.sqrt(d)
+    C, V, ctx = torch.randn(M, d, generator=g, device="cuda"), torch.randn(M, 2, generator=g, device="cuda"), knm.Context()
+    C[::2] = X[-18000:]
+    U, W = knm.knm_prod(X, C, sigma, V, return_w=True, ctx=ctx)
+    assert ctx.workspace_held() > 16384 * M * 4  # a slab of values
+    assert torch.equal(U, knm.knm_t_y(X, C, sigma, W, ctx=ctx))
+    some = np.r_[0:16384:128, 16384:n:128]
+    ref, other = (oracle.knm_v(X[some].cpu().numpy(), C.cpu().numpy(), sigma, v.cpu().numpy()) for v in (V, V.abs()))
+    assert rel_l2(W[some].cpu().numpy(), ref) < 1e-6
+    assert np.abs(W[some].cpu().numpy() - ref).max() < 1e-6 * other.max()
+
+
 # fits: one and two groups of columns, kernels of r (every centre coincides with a row), the fp32 engine; sizes at the edges of the 32 x 32 blocks,
 # the fixed blocks (256) and the tiles (128), one of them the smallest there is.  Predictions carry what the products' rounding (3e-7)
 # becomes through T^-1 at this jitter, and no more than those of sweeps that form the values each time (1e-5)
