@@ -603,7 +603,11 @@ static bool keeping_pays(int64_t n, int64_t M, int d, int t, int cross_term, int
 // columns: d = 200 0.97 and - (matrix-core reduction), 250 1.07 and -, 300 1.15 and 1.21, 400 1.28 and 1.35, 784 1.56 and 1.62 (n = 300k, M =
 // 20k); d = 784 1.24 and 1.28 at n = 5000, M = 500.  1 column at d = 240, 260, 300: 30000 x 3000 0.96, 0.98 and 1.05, 100k x 1500 1.07, 1.00 and
 // 1.05, five other sizes from 3000 x 800 to 150k x 9000 1.05 to 1.17: the line lies at d = 260 (4 columns 240, 10 columns 234).  Slabs of 16 GiB were no faster than of 4.
+// The more centres, the fewer rows has a slab, and each reads all centres again: 400k centres (2560 rows) 1.04, 1.07, 1.11 and 1.18 at d = 260,
+// 280, 300 and 340 with 1 column, 1M centres (1024 rows) 1.00, 1.03, 1.04 and 1.12, 1.53 at d = 784; 4M centres (256 rows) 0.94 at d = 270,
+// 1.14 at 400 and 0.74 at 784, where the centres' image is not kept either.
 constexpr size_t kKeepSlabCap = (size_t)4 << 30; // bytes of a slab at most
+constexpr int64_t kKeepSlabRows = 1024;          // rows of a slab at least, where there are several
 static int64_t product_keep_rows(int64_t n, int64_t M, int d, int t, int cross_term, int kind)
 {
     if (cross_term != KNM_CROSS_F16X3 || kind != KNM_KERNEL_GAUSSIAN || t > kept_rows_max_t() || !use_gemm_engine(d, t, cross_term, kind) ||
@@ -613,6 +617,7 @@ static int64_t product_keep_rows(int64_t n, int64_t M, int d, int t, int cross_t
     if (kept_bytes(n, M) > kKeepSlabCap) {
         rows = (int64_t)(kKeepSlabCap / kept_bytes(256, M)) * 256;
         if (rows >= 16384) rows = rows / 16384 * 16384; // 64 fixed blocks x 8 chunks fill the chip
+        if (rows < kKeepSlabRows) return 0;
     }
     return rows;
 }

@@ -803,7 +803,9 @@ __global__ __launch_bounds__(256) void pair_rows_kernel(SparseArgs a)
 }
 // A workgroup has a range of `width` centres in LDS, one fp64 sum each (20480 fill the 160 KB), and adds up the pairs of its share of the rows
 // there; the workgroups' sums are merged.  (fp64 atomics in device memory took
-// 0.605 ms for 200k rows against 20000 centres, 0.046 ms this way.)
+// 0.605 ms for 200k rows against 20000 centres, 0.046 ms this way.)  Every range of centres reads all pairs; products with walks and with
+// pairs, rows of 100 entries: 100k x 30000 (2 ranges) 3.04 and 2.46 ms, 100k x 60000 (3) 7.04 and 5.27, 200k x 100k (5) 20.5 and 14.4, 200k x
+// 200k (10) 44.9 and 30.7, 330k x 327k (16) 123 and 83, 20000 x 327k (16) 20.4 and 14.9.
 constexpr int kPairThreads = 1024;
 constexpr int kPairWidth = 20480;
 __global__ __launch_bounds__(kPairThreads) void pair_columns_kernel(SparseArgs a, int width, double *__restrict__ part)

@@ -10,7 +10,7 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(os.path.dirname(HERE), "paper_2006_10350_amd", "libknm.so")
 
-# the sums over kept values by their first arguments: values, points of the two sides (KeptArgs)
+# the sums over a fit's kept values by their first arguments: values, points of the two sides (KeptArgs); how many sums over a product's slabs
 RECORD = """
 #include <stddef.h>
 #include <stdint.h>
@@ -21,7 +21,10 @@ static const void *functions[kFunctions];
 static int known, reads;
 static int64_t sizes[kLaunches][2];
 static const void *values[kLaunches];
+static const void *slab_sums[64];
+static int slab_kinds, slabs;
 int kept_reads(void) { return reads; }
+int kept_slabs(void) { return slabs; }
 int64_t kept_size(int launch, int side) { return sizes[launch][side]; }
 int kept_blocks(void) /* different blocks of values */
 {
@@ -38,10 +41,12 @@ void __hipRegisterFunction(void **modules, const void *host, char *device, const
 {
     (void)modules; (void)device; (void)limit; (void)tid; (void)bid; (void)block; (void)grid; (void)size;
     if (strstr(name, "kept_over_") && known < kFunctions) functions[known++] = host;
+    if (strstr(name, "kept_rows_kernel") && slab_kinds < 64) slab_sums[slab_kinds++] = host;
 }
 int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, void *stream)
 {
     (void)grid; (void)block; (void)lds; (void)stream;
+    for (int i = 0; i < slab_kinds; ++i) slabs += slab_sums[i] == f;
     for (int i = 0; i < known; ++i)
         if (functions[i] == f && reads < kLaunches) {
             memcpy(&values[reads], args[0], 8);
@@ -93,6 +98,30 @@ def test_logistic_fit_reads_the_values_of_its_pair(shims, n, M, step, shared, cr
         # in each of two Newton steps a sweep by rows, one by columns and two for each iteration; and one of k(C, C)
         own = {shared} and {n} == {M} and {step} == 1
         assert len(reads) == 2 * 2 + 2 * 9 + (2 if own else 0)
+        """
+    r = subprocess.run([sys.executable, "-c", textwrap.dedent(body)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+# slabs of 4 GiB of values: one, three, many of the fewest rows (1024), fewer rows than that (two sweeps); few features, many columns and
+# the other arithmetic (two sweeps)
+@pytest.mark.parametrize("n,M,d,t,cross,slabs", [(40000, 20000, 784, 10, 1, 1), (40000, 50000, 784, 1, 1, 3), (20480, 1 << 20, 300, 1, 1, 20),
+                                                 (20480, (1 << 20) + 128, 300, 1, 1, 0), (1000, 3 << 20, 300, 1, 1, 0), (256, 3 << 20, 300, 1, 1, 1),
+                                                 (40000, 20000, 200, 1, 1, 0), (40000, 20000, 784, 13, 1, 0), (40000, 20000, 784, 1, 0, 0)])
+def test_slabs_of_a_product(shims, n, M, d, t, cross, slabs):
+    body = f"""
+        import ctypes as c
+        rec, hip = (c.CDLL(s, mode=c.RTLD_GLOBAL) for s in {shims!r})
+        lib = c.CDLL({LIB!r})
+        P, L, I, F = c.c_void_p, c.c_int64, c.c_int, c.c_float
+        lib.knm_prod.argtypes = [P, P, L, I, L, P, L, L, F, P, I, P, P]
+        ctx = P()
+        assert lib.knm_create(c.byref(ctx), 0, None) == 0
+        assert lib.knm_set_cross_term(ctx, {cross}) == 0
+        x, cen, v, u = (P(0x7f0000000000 + (i << 40)) for i in range(4))  # never read: kernels do not run
+        for k in (1, 2):
+            assert lib.knm_prod(ctx, x, {n}, {d}, {d}, cen, {M}, {d}, 1.0, v, {t}, None, u) == 0
+            assert rec.kept_slabs() == k * {slabs}, rec.kept_slabs()
         """
     r = subprocess.run([sys.executable, "-c", textwrap.dedent(body)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
