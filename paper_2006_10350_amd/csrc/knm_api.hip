@@ -163,6 +163,14 @@ int ensure(knm_ctx *ctx, float **buf, size_t *cur, size_t need)
     return KNM_OK;
 }
 
+static size_t pool_bytes(knm_ctx *ctx, const void *p)
+{
+    const std::lock_guard<std::mutex> lock(ctx->pool_lock);
+    for (const auto &b : ctx->pool)
+        if (b.p == p) return b.bytes;
+    return 0;
+}
+
 constexpr size_t kPoolIdleBytes = (size_t)16 << 30; // idle blocks beyond this are freed (30 ms per GiB once a process has gone through the
                                                     // card's memory: what a fit keeps has to fit)
 
@@ -215,6 +223,17 @@ void pool_give(knm_ctx *ctx, void *p)
         (void)hipFree(ctx->pool[i].p);
         ctx->pool.erase(ctx->pool.begin() + (std::ptrdiff_t)i);
     }
+}
+
+void pool_drop(knm_ctx *ctx, void *p)
+{
+    const std::lock_guard<std::mutex> lock(ctx->pool_lock);
+    for (size_t i = 0; i < ctx->pool.size(); ++i)
+        if (ctx->pool[i].p == p) {
+            (void)hipFree(p);
+            ctx->pool.erase(ctx->pool.begin() + (std::ptrdiff_t)i);
+            return;
+        }
 }
 
 // Workspace for callers that cannot allocate (code under HIP graph capture, serving loops,
@@ -666,6 +685,47 @@ static int keep_values(knm_ctx *ctx, SweepShare *sh, int f, int s, bool column_s
     return form_values(ctx, sh, f, s, mu, static_cast<float *>(p));
 }
 
+static void drop_slab(knm_ctx *ctx)
+{
+    if (ctx->slab == nullptr) return;
+    spare_remove(ctx, 0, &ctx->slab);
+    pool_drop(ctx, ctx->slab);
+    ctx->slab = nullptr;
+}
+
+// The context's slab for as long as a product uses it: `bytes` of it, or none.  A call on a stream that is being captured takes what is
+// there and allocates nothing, and what it took stays until the context outgrows it or its workspace is released, as the other buffers of a
+// captured product do.
+struct SlabUse {
+    knm_ctx *ctx;
+    void *p = nullptr;
+    SlabUse(knm_ctx *c, size_t bytes) : ctx(c)
+    {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        const hipError_t e = hipStreamIsCapturing(ctx->stream, &status);
+        if (e != hipSuccess) (void)hipGetLastError(); // (the null stream beside one that is captured)
+        const bool capturing = e != hipSuccess || status != hipStreamCaptureStatusNone;
+        if (ctx->slab == nullptr || ctx->slab_bytes < bytes) {
+            if (capturing) return;
+            drop_slab(ctx);
+            bytes = (bytes + 255) & ~(size_t)255;
+            if (pool_take(ctx, bytes, &ctx->slab, true) != hipSuccess) return;
+            ctx->slab_bytes = pool_bytes(ctx, ctx->slab);
+            ctx->slab_captured = false;
+        }
+        spare_remove(ctx, 0, &ctx->slab);
+        ctx->slab_captured |= capturing;
+        p = ctx->slab;
+    }
+    ~SlabUse()
+    {
+        // (an unregistered block is only one that is not given up)
+        if (p != nullptr && !ctx->slab_captured) (void)spare_add(ctx, 0, &ctx->slab);
+    }
+    SlabUse(const SlabUse &) = delete;
+    SlabUse &operator=(const SlabUse &) = delete;
+};
+
 // The sums over kept values `keep` of nF fixed and nS stream points, `part` holding kept_chunks() partials of n_out x t.
 static int kept_partials(knm_ctx *ctx, const float *keep, int64_t nF, int64_t nS, bool over_stream, const float *vec, const float *wgt,
                          int t, double *part, int chunks)
@@ -1076,7 +1136,7 @@ size_t knm_workspace_bytes(int64_t n, int64_t M, int d, int t)
 size_t knm_workspace_held(const knm_ctx *ctx)
 {
     if (!ctx) return 0;
-    return ctx->w_bytes + ctx->part_bytes + ctx->pack_bytes + ctx->vimg_bytes + ctx->mu_bytes + ctx->pool_idle;
+    return ctx->w_bytes + ctx->part_bytes + ctx->pack_bytes + ctx->vimg_bytes + ctx->mu_bytes + ctx->pool_idle + (ctx->slab ? ctx->slab_bytes : 0);
 }
 
 int knm_release_workspace(knm_ctx *ctx)
@@ -1093,6 +1153,7 @@ int knm_release_workspace(knm_ctx *ctx)
         *held.first = nullptr;
         *held.second = 0;
     }
+    drop_slab(ctx);
     const std::lock_guard<std::mutex> lock(ctx->pool_lock);
     free_idle_locked(ctx);
     return e == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "knm_release_workspace", e);
@@ -1154,29 +1215,28 @@ static int prod_kept(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx
     *done = false;
     KeptRowsArgs k{};
     const int64_t chunks = choose_chunks(M, n, d, t, ctx->cross_term, ctx->kernel_kind, &k.chunk_len);
-    struct Block {
-        knm_ctx *ctx;
-        void *p = nullptr;
-        ~Block()
-        {
-            if (p) pool_give(ctx, p);
-        }
-        bool take(size_t bytes) { return pool_take(ctx, bytes, &p, true) == hipSuccess; }
-    } values{ctx}, part{ctx}, state{ctx}, weighted{ctx};
-    const size_t state_bytes = sizeof(double) * 2 * (size_t)M * t;
-    if (chunks > 65535 || !values.take(kept_bytes(rows, M)) || !part.take(sizeof(float) * (size_t)chunks * M * t) || !state.take(2 * state_bytes) ||
-        (dw != nullptr && !weighted.take(sizeof(float) * (size_t)rows * t)))
-        return KNM_OK;
+    if (chunks > 65535) return KNM_OK;
+    // values, chunk partials, running sums, weighted rows
+    const size_t pieces[4] = {kept_bytes(rows, M), sizeof(float) * (size_t)chunks * M * t, sizeof(double) * 4 * (size_t)M * t,
+                              dw != nullptr ? sizeof(float) * (size_t)rows * t : 0};
+    size_t at[4], bytes = 0;
+    for (int i = 0; i < 4; ++i) {
+        at[i] = bytes;
+        bytes += (pieces[i] + 255) & ~(size_t)255;
+    }
+    const SlabUse slab(ctx, bytes);
+    if (slab.p == nullptr) return KNM_OK;
+    auto piece = [&](int i) { return static_cast<void *>(static_cast<char *>(slab.p) + at[i]); };
     SweepShare share(ctx, X, n, ldx, C, M, ldc, d, sigma, t, false); // (the shift is that of the whole pair, for all slabs)
     share.n[0] = rows;
-    share.slab = static_cast<float *>(values.p);
+    share.slab = static_cast<float *>(piece(0));
     const ShareScope scope(share);
     k.values = share.slab;
     k.n = n;
     k.nS = M;
     k.t = t;
-    k.part = static_cast<float *>(part.p);
-    double *s_in = static_cast<double *>(state.p), *s_out = s_in + 2 * (size_t)M * t;
+    k.part = static_cast<float *>(piece(1));
+    double *s_in = static_cast<double *>(piece(2)), *s_out = s_in + 2 * (size_t)M * t;
     for (k.row0 = 0; k.row0 < n; k.row0 += rows, std::swap(s_in, s_out)) {
         k.rows = n - k.row0 < rows ? n - k.row0 : rows;
         share.P[0] = X + k.row0 * ldx;
@@ -1191,9 +1251,10 @@ static int prod_kept(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx
         k.vec = Wb;
         if (dw != nullptr) {
             const int64_t count = k.rows * t;
-            k.vec = static_cast<float *>(weighted.p);
+            float *const weighted = static_cast<float *>(piece(3));
+            k.vec = weighted;
             hipLaunchKernelGGL(weigh_rows_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, ctx->stream, Wb, dw + k.row0, count, t,
-                               static_cast<float *>(weighted.p));
+                               weighted);
         }
         k.state_in = s_in;
         k.state_out = s_out;

@@ -333,7 +333,12 @@ struct knm_ctx {
     knm::SweepShare *share = nullptr; // of the product or fit whose sweeps are being enqueued
     const knm::SweepShare *mu_owner = nullptr; // mu_buf holds the shift of this pair of sets
     size_t pool_idle = 0; // bytes of the blocks not in use
-    // blocks in use that the calls under way can do without: where their owners keep the pointers.  When something else finds no
+    // a product's kept kernel values and sums over them (prod_kept), in a block of the pool that stays in use between calls, so that it is
+    // where a captured product writes; spare while no product runs, unless one was captured
+    void *slab = nullptr;
+    size_t slab_bytes = 0;
+    bool slab_captured = false;
+    // blocks in use that can be done without: where their owners keep the pointers.  When something else finds no
     // room, those of [0] (kernel values, pair lists) and then of [1] (images) go back and the pointers become null
     std::vector<void **> spare[2];
     std::mutex pool_lock;
@@ -362,6 +367,7 @@ int ensure(knm_ctx *ctx, float **buf, size_t *cur, size_t need);
 hipError_t device_alloc(knm_ctx *ctx, size_t bytes, void **out);
 // (optional: without giving up spare blocks)
 hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out, bool optional = false);
+void pool_drop(knm_ctx *ctx, void *p); // back to the device
 void pool_give(knm_ctx *ctx, void *p);
 bool spare_add(knm_ctx *ctx, int phase, void **p); // false: no host memory for it
 void spare_remove(knm_ctx *ctx, int phase, void **p);

@@ -82,6 +82,11 @@ int hipStreamDestroy(void *s) { (void)s; return 0; }
 int hipStreamSynchronize(void *s) { (void)s; return 0; }
 int hipStreamWaitEvent(void *s, void *e, unsigned f) { (void)s; (void)e; (void)f; return 0; }
 int hipFuncSetAttribute(const void *f, int a, int v) { (void)f; (void)a; (void)v; return 0; }
+/* streams are not captured unless a test says so */
+static int capturing;
+void fake_set_capturing(int on) { capturing = on; }
+int hipStreamIsCapturing(void *s, int *status) { (void)s; *status = capturing; return 0; }
+int fake_inside(const void *p, size_t bytes) { return inside(p, bytes); }
 int hipLaunchKernel(void) { ++launches; return 0; }
 int __hipPushCallConfiguration(void) { return 0; }
 int __hipPopCallConfiguration(void) { return 0; }

@@ -1,4 +1,5 @@
 """Products and fits that form kernel values once and read them again, against the oracle."""
+import contextlib
 import math
 
 import numpy as np
@@ -22,7 +23,7 @@ def _rand(n, d, seed):
 # products: the sums over kept rows are those of knm_t_y's sweep to the last bit.  Edges of the 32 x 32 blocks, fixed blocks (256) and tiles
 # (128), of 64 centres and of the columns (12), one row, one centre; chunks that end in a slab
 @pytest.mark.parametrize("n,M,d,t", [(1, 1, 700, 1), (33, 127, 700, 2), (255, 257, 300, 12), (256, 128, 401, 7), (1000, 511, 784, 10), (2049, 31, 305, 9),
-                                     (1537, 1025, 784, 1), (40001, 300, 320, 3)])
+                                     (1537, 1025, 784, 1), (40001, 300, 320, 3), (255, 257, 330, 12)])
 def test_products_from_kept_values(knm, n, M, d, t):
     X = _rand(n, d, n + d).cuda()
     C = torch.cat([X[: max(1, M // 2)], _rand(M, d, M).cuda()])[:M].contiguous()  # coincident pairs
@@ -50,6 +51,39 @@ def test_product_in_slabs(knm, t):
     assert torch.equal(U, knm.knm_t_y(X, C, 16.0, W, ctx=ctx))
     v = knm.knm_v(X, C, 16.0, V, ctx=ctx)
     assert float((W - v).norm() / v.norm()) < 1e-6
+
+
+# a captured product that keeps a slab: fits and larger workspaces in between do not take it away, and every replay is the eager result
+def test_product_with_a_slab_replays_in_a_graph(knm):
+    n, M, d, t, sigma = 3000, 700, 784, 10, 21.0
+    X, C, V, w = _rand(n, d, 70).cuda(), _rand(M, d, 71).cuda(), _rand(M, t, 72).cuda(), torch.rand(n, generator=torch.Generator().manual_seed(4)).cuda()
+    U, Z, Y = torch.empty(M, t, device="cuda"), torch.empty(M, t, device="cuda"), _rand(4000, 2, 73).cuda()
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        ctx = knm.Context()  # bound to the side stream
+        for graph in (None, torch.cuda.CUDAGraph()):  # an eager call allocates the workspace
+            with contextlib.ExitStack() as stack:
+                if graph is not None:
+                    stack.enter_context(torch.cuda.graph(graph, stream=side))
+                knm.knm_prod(X, C, sigma, V, out=U, ctx=ctx)
+                Z.copy_(knm.knm_prod_weighted(X, C, sigma, w, V, ctx=ctx))
+            side.synchronize()
+    F = _rand(4000, 300, 74).cuda()
+    for rep in range(4):
+        print(f"replay {rep}", flush=True)
+        X.copy_(_rand(n, d, 80 + rep).cuda())
+        V.copy_(_rand(M, t, 90 + rep).cuda())
+        U.fill_(float("nan"))
+        Z.fill_(float("nan"))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            knm.falkon_fit(F, Y, F[: 100 * (rep + 1)], 13.0, 1e-4, 3, 1e-6, ctx=ctx)
+            graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(U, knm.knm_prod(X, C, sigma, V)) and torch.equal(Z, knm.knm_prod_weighted(X, C, sigma, w, V)), rep
+    del graph
+    ctx.close()
 
 
 # slabs with fewer rows than there are centres, the first of them far from everything else: the common shift is the whole pair's (that of the

@@ -25,6 +25,8 @@ static const void *slab_sums[64];
 static int slab_kinds, slabs;
 int kept_reads(void) { return reads; }
 int kept_slabs(void) { return slabs; }
+static const void *slab;
+const void *kept_slab(void) { return slab; } /* values of the last sum over a slab */
 int64_t kept_size(int launch, int side) { return sizes[launch][side]; }
 int kept_blocks(void) /* different blocks of values */
 {
@@ -46,7 +48,11 @@ void __hipRegisterFunction(void **modules, const void *host, char *device, const
 int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, void *stream)
 {
     (void)grid; (void)block; (void)lds; (void)stream;
-    for (int i = 0; i < slab_kinds; ++i) slabs += slab_sums[i] == f;
+    for (int i = 0; i < slab_kinds; ++i)
+        if (slab_sums[i] == f) {
+            ++slabs;
+            memcpy(&slab, args[0], 8);
+        }
     for (int i = 0; i < known; ++i)
         if (functions[i] == f && reads < kLaunches) {
             memcpy(&values[reads], args[0], 8);
@@ -55,6 +61,40 @@ int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t ld
     return 0;
 }
 """
+
+HEAD = """
+import ctypes as c
+rec, hip = (c.CDLL(s, mode=c.RTLD_GLOBAL) for s in {shims!r})
+lib = c.CDLL({lib!r})
+P, L, I, F, D, Z = c.c_void_p, c.c_int64, c.c_int, c.c_float, c.c_double, c.c_size_t
+rec.kept_size.restype = c.c_int64
+rec.kept_slab.restype = P
+hip.fake_set_budget.argtypes = [Z]
+hip.fake_inside.argtypes = [P, Z]
+hip.fake_live.restype = hip.fake_peak.restype = lib.knm_workspace_held.restype = Z
+lib.knm_workspace_held.argtypes = lib.knm_release_workspace.argtypes = lib.knm_destroy.argtypes = [P]
+lib.logfalkon_fit.argtypes = [P, P, L, I, L, P, P, L, L, P, F, P, P, I, D, P, P]
+lib.falkon_fit.argtypes = [P, P, L, I, L, P, I, P, L, L, F, D, D, I, P, P]
+lib.knm_prod.argtypes = [P, P, L, I, L, P, L, L, F, P, I, P, P]
+ctx = P()
+assert lib.knm_create(c.byref(ctx), 0, None) == 0
+created = hip.fake_live()
+x, cen, y, yc, alpha, v, u = (P(0x7f0000000000 + (i << 40)) for i in range(7))  # never read: kernels do not run
+
+
+def prod(n, M, d, t):
+    return lib.knm_prod(ctx, x, n, d, d, cen, M, d, 1.0, v, t, None, u)
+
+
+def fit(n, d, M, t):
+    return lib.falkon_fit(ctx, x, n, d, d, y, t, cen, M, d, 1.0, 1e-6, 1e-6, 3, alpha, None)
+"""
+
+
+def _run(shims, body):
+    """In a process of its own: the fake runtime must come before the real one."""
+    r = subprocess.run([sys.executable, "-c", HEAD.format(shims=shims, lib=LIB) + textwrap.dedent(body)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
 
 
 @pytest.fixture(scope="module")
@@ -75,17 +115,8 @@ def shims(tmp_path_factory):
 @pytest.mark.parametrize("cross", [0, 1])
 def test_logistic_fit_reads_the_values_of_its_pair(shims, n, M, step, shared, cross):
     d = 500
-    body = f"""
-        import ctypes as c
-        rec, hip = (c.CDLL(s, mode=c.RTLD_GLOBAL) for s in {shims!r})
-        lib = c.CDLL({LIB!r})
-        rec.kept_size.restype = c.c_int64
-        P, L, I, F, D = c.c_void_p, c.c_int64, c.c_int, c.c_float, c.c_double
-        lib.logfalkon_fit.argtypes = [P, P, L, I, L, P, P, L, L, P, F, P, P, I, D, P, P]
-        ctx = P()
-        assert lib.knm_create(c.byref(ctx), 0, None) == 0
+    _run(shims, f"""
         assert lib.knm_set_cross_term(ctx, {cross}) == 0
-        x, cen, y, yc, alpha = (P(0x7f0000000000 + (i << 36)) for i in range(5))  # never read: kernels do not run
         if {shared}:
             cen = x
         lambdas, iters = (c.c_double * 2)(1e-2, 1e-3), (c.c_int * 2)(4, 5)
@@ -98,9 +129,7 @@ def test_logistic_fit_reads_the_values_of_its_pair(shims, n, M, step, shared, cr
         # in each of two Newton steps a sweep by rows, one by columns and two for each iteration; and one of k(C, C)
         own = {shared} and {n} == {M} and {step} == 1
         assert len(reads) == 2 * 2 + 2 * 9 + (2 if own else 0)
-        """
-    r = subprocess.run([sys.executable, "-c", textwrap.dedent(body)], capture_output=True, text=True, timeout=120)
-    assert r.returncode == 0, r.stdout + r.stderr
+        """)
 
 
 # slabs of 4 GiB of values: one, three, many of the fewest rows (1024), fewer rows than that (two sweeps); few features, many columns and
@@ -109,19 +138,74 @@ def test_logistic_fit_reads_the_values_of_its_pair(shims, n, M, step, shared, cr
                                                  (20480, (1 << 20) + 128, 300, 1, 1, 0), (1000, 3 << 20, 300, 1, 1, 0), (256, 3 << 20, 300, 1, 1, 1),
                                                  (40000, 20000, 200, 1, 1, 0), (40000, 20000, 784, 13, 1, 0), (40000, 20000, 784, 1, 0, 0)])
 def test_slabs_of_a_product(shims, n, M, d, t, cross, slabs):
-    body = f"""
-        import ctypes as c
-        rec, hip = (c.CDLL(s, mode=c.RTLD_GLOBAL) for s in {shims!r})
-        lib = c.CDLL({LIB!r})
-        P, L, I, F = c.c_void_p, c.c_int64, c.c_int, c.c_float
-        lib.knm_prod.argtypes = [P, P, L, I, L, P, L, L, F, P, I, P, P]
-        ctx = P()
-        assert lib.knm_create(c.byref(ctx), 0, None) == 0
+    _run(shims, f"""
         assert lib.knm_set_cross_term(ctx, {cross}) == 0
-        x, cen, v, u = (P(0x7f0000000000 + (i << 40)) for i in range(4))  # never read: kernels do not run
         for k in (1, 2):
-            assert lib.knm_prod(ctx, x, {n}, {d}, {d}, cen, {M}, {d}, 1.0, v, {t}, None, u) == 0
+            assert prod({n}, {M}, {d}, {t}) == 0
             assert rec.kept_slabs() == k * {slabs}, rec.kept_slabs()
-        """
-    r = subprocess.run([sys.executable, "-c", textwrap.dedent(body)], capture_output=True, text=True, timeout=120)
-    assert r.returncode == 0, r.stdout + r.stderr
+        """)
+
+
+# The shapes of the GPU tests that are to go by kept values do
+@pytest.mark.parametrize("n,M,d,t,cross,kind", [(1100, 130, 400, 1, 1, 0), (900, 257, 784, 20, 1, 0), (256, 128, 700, 16, 1, 0), (1537, 33, 705, 17, 1, 0),
+                                                (1, 1, 700, 1, 1, 0), (700, 100, 300, 3, 1, 1), (513, 255, 301, 9, 1, 3), (1025, 128, 90, 2, 0, 0),
+                                                (257, 31, 91, 32, 0, 1)])
+def test_fits_that_read_kept_values(shims, n, M, d, t, cross, kind):
+    _run(shims, f"""
+        assert lib.knm_set_cross_term(ctx, {cross}) == 0 and lib.knm_set_kernel(ctx, {kind}) == 0
+        assert lib.falkon_fit(ctx, x, {n}, {d}, {d}, y, {t}, cen, {M}, {d}, 1.0, 1e-4, 1e-6, 8, alpha, None) == 0
+        assert rec.kept_reads() == 2 * 8 + 1 and rec.kept_blocks() == 1, rec.kept_reads()
+        """)
+
+
+@pytest.mark.parametrize("n,M,d,t", [(1, 1, 700, 1), (33, 127, 700, 2), (255, 257, 330, 12), (256, 128, 401, 7), (1000, 511, 784, 10), (2049, 31, 305, 9),
+                                     (1537, 1025, 784, 1), (40001, 300, 320, 3), (55003, 25000, 400, 10), (40000, 36000, 400, 2)])
+def test_products_that_keep_slabs(shims, n, M, d, t):
+    _run(shims, f"""
+        assert prod({n}, {M}, {d}, {t}) == 0
+        assert rec.kept_slabs() > 0
+        """)
+
+
+# A captured product holds pointers into its slab: no other call frees that or moves it, and none is allocated while the stream is captured
+def test_slab_of_a_captured_product_stays(shims):
+    _run(shims, """
+        n, M, d, t = 40000, 20000, 784, 10
+        hip.fake_set_capturing(1)
+        lib.knm_prod(ctx, x, n, 784, d, cen, M, d, 1.0, v, t, None, u)
+        assert rec.kept_slabs() == 0  # two sweeps: nothing to take it from
+        hip.fake_set_capturing(0)
+        assert prod(n, M, d, t) == 0 and rec.kept_slabs() == 1
+        slab, held = rec.kept_slab(), lib.knm_workspace_held(ctx)
+        hip.fake_set_capturing(1)
+        assert prod(n, M, d, t) == 0 and rec.kept_slabs() == 2 and rec.kept_slab() == slab
+        assert lib.knm_workspace_held(ctx) == held and hip.fake_live() == created + held
+        hip.fake_set_capturing(0)
+        assert fit(1_000_000, 400, 2000, 10) == 0 and fit(5_000_000, 300, 3000, 1) == 0  # idle blocks of 16 GiB and more
+        assert hip.fake_inside(slab, 4 * n * M)
+        hip.fake_set_budget(hip.fake_live() + (1 << 20))
+        assert fit(3_000_000, 784, 3000, 12) in (0, -3)
+        hip.fake_set_budget(1 << 50)
+        assert hip.fake_inside(slab, 4 * n * M)
+        assert prod(n // 2, M // 2, d, t) == 0 and rec.kept_slab() == slab
+        assert lib.knm_release_workspace(ctx) == 0 and hip.fake_live() == created
+        """)
+
+
+# One that was not is given up when a fit finds no room, and comes back with the next product
+def test_slab_is_given_up_when_a_fit_needs_the_room(shims):
+    _run(shims, """
+        assert fit(3_000_000, 28, 3000, 1) == 0
+        need = hip.fake_peak()
+        lib.knm_release_workspace(ctx)
+        assert prod(40000, 20000, 784, 10) == 0 and rec.kept_slabs() == 1
+        slab = rec.kept_slab()
+        hip.fake_set_budget(need + (1 << 30))
+        assert fit(3_000_000, 28, 3000, 1) == 0
+        assert not hip.fake_inside(slab, 1 << 30)
+        hip.fake_set_budget(1 << 50)
+        assert prod(40000, 20000, 784, 10) == 0 and rec.kept_slabs() == 2
+        assert hip.fake_live() == created + lib.knm_workspace_held(ctx)
+        lib.knm_destroy(ctx)
+        assert hip.fake_live() == 0
+        """)
