@@ -171,10 +171,21 @@ static size_t pool_bytes(knm_ctx *ctx, const void *p)
     return 0;
 }
 
-constexpr size_t kPoolIdleBytes = (size_t)16 << 30; // idle blocks beyond this are freed (30 ms per GiB once a process has gone through the
-                                                    // card's memory: what a fit keeps has to fit)
+// Idle blocks beyond this are freed (30 ms per GiB once a process has gone through the card's memory: what a fit keeps has to fit), and
+// beyond the second number where the card is nearly full
+constexpr size_t kPoolIdleBytes = (size_t)16 << 30, kPoolIdleFull = (size_t)4 << 30;
 
-hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out, bool optional)
+// Whether a sixteenth of the card (18 GB) is left beside `bytes` more: kernel values, pair lists and slabs are for speed alone and leave that to
+// the rest of the program, whose own allocator sees none of the idle blocks.
+static bool leaves_room(size_t bytes)
+{
+    size_t free = 0, total = 0;
+    if (hipMemGetInfo(&free, &total) == hipSuccess) return free >= bytes && free - bytes >= total / 16;
+    (void)hipGetLastError();
+    return false;
+}
+
+hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out, PoolUse use)
 {
     *out = nullptr;
     bytes = (bytes + 255) & ~(size_t)255;
@@ -190,8 +201,9 @@ hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out, bool optional)
         *out = best->p;
         return hipSuccess;
     }
+    if (use == PoolUse::kForSpeed && !leaves_room(bytes)) return hipErrorOutOfMemory;
     void *p = nullptr;
-    const hipError_t e = alloc_locked(ctx, bytes, &p, optional);
+    const hipError_t e = alloc_locked(ctx, bytes, &p, use != PoolUse::kNeeded);
     if (e != hipSuccess) return e;
     try {
         ctx->pool.push_back({p, bytes, true});
@@ -214,11 +226,13 @@ void pool_give(knm_ctx *ctx, void *p)
         break;
     }
     // oldest idle blocks first (hipFree waits for the device, so nothing queued still uses them)
-    for (size_t i = 0; i < ctx->pool.size() && ctx->pool_idle > kPoolIdleBytes;) {
+    auto too_many = [&] { return ctx->pool_idle > kPoolIdleBytes || (ctx->pool_idle > kPoolIdleFull && !leaves_room(0)); };
+    for (size_t i = 0; i < ctx->pool.size();) {
         if (ctx->pool[i].used) {
             ++i;
             continue;
         }
+        if (!too_many()) break;
         ctx->pool_idle -= ctx->pool[i].bytes;
         (void)hipFree(ctx->pool[i].p);
         ctx->pool.erase(ctx->pool.begin() + (std::ptrdiff_t)i);
@@ -567,7 +581,7 @@ static int share_images(knm_ctx *ctx, SweepShare *sh)
     if (pp * (size_t)(r0 + r1) > (ctx->pack_limit ? ctx->pack_limit : kShareCap)) return KNM_OK;
     if (sh->pooled) {
         for (int k = 0; k < 2; ++k)
-            if (pool_take(ctx, pp * (size_t)(k == 0 ? r0 : r1), &sh->img[k], true) != hipSuccess) {
+            if (pool_take(ctx, pp * (size_t)(k == 0 ? r0 : r1), &sh->img[k], PoolUse::kOptional) != hipSuccess) {
                 // no room: the sweeps pack slab by slab
                 if (sh->img[0]) pool_give(ctx, sh->img[0]);
                 sh->img[0] = sh->img[1] = nullptr;
@@ -677,7 +691,7 @@ static int keep_values(knm_ctx *ctx, SweepShare *sh, int f, int s, bool column_s
     if (bytes > kKeepCap || !ready || !keeping_pays(sh->n[f], sh->n[s], sh->d, sh->t, sh->cross_term, sh->kind, sh->uses)) return KNM_OK;
     if (!f16 && (!gemm_leading_dimension_ok(sh->ld[f]) || !gemm_leading_dimension_ok(sh->ld[s]))) return KNM_OK;
     void *p = nullptr;
-    if (pool_take(ctx, bytes, &p, true) != hipSuccess) return KNM_OK; // no room: the sweeps form the values
+    if (pool_take(ctx, bytes, &p, PoolUse::kForSpeed) != hipSuccess) return KNM_OK; // no room: the sweeps form the values
     sh->keep = p;
     sh->keep_columns = column_sweep;
     sh->keep_n[0] = sh->n[f];
@@ -709,7 +723,7 @@ struct SlabUse {
             if (capturing) return;
             drop_slab(ctx);
             bytes = (bytes + 255) & ~(size_t)255;
-            if (pool_take(ctx, bytes, &ctx->slab, true) != hipSuccess) return;
+            if (pool_take(ctx, bytes, &ctx->slab, PoolUse::kForSpeed) != hipSuccess) return;
             ctx->slab_bytes = pool_bytes(ctx, ctx->slab);
             ctx->slab_captured = false;
         }

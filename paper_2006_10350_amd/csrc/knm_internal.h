@@ -362,11 +362,12 @@ int ensure(knm_ctx *ctx, float **buf, size_t *cur, size_t need);
 // Temporaries of calls that allocate (fits, sparse products): blocks of the context's own, taken from it and given back to
 // it, because hipMalloc and hipFree cost 10 to 80 us each (2.4 ms of a 9.5 ms sparse product), and far more for large blocks.  Work on a context is
 // ordered by its stream, so a block can be given back while kernels that use it are still queued.  Idle blocks of more than
-// 16 GiB in all are freed, and knm_destroy frees the rest.
+// 16 GiB in all are freed (4 GiB where a sixteenth of the card is not free), and knm_destroy frees the rest.
 // hipMalloc, with the idle blocks and then the spare ones (knm_ctx::spare) given up if there is no room
 hipError_t device_alloc(knm_ctx *ctx, size_t bytes, void **out);
-// (optional: without giving up spare blocks)
-hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out, bool optional = false);
+// (kOptional: without giving up spare blocks; kForSpeed: and only where the card has room to spare)
+enum class PoolUse { kNeeded, kOptional, kForSpeed };
+hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out, PoolUse use = PoolUse::kNeeded);
 void pool_drop(knm_ctx *ctx, void *p); // back to the device
 void pool_give(knm_ctx *ctx, void *p);
 bool spare_add(knm_ctx *ctx, int phase, void **p); // false: no host memory for it

@@ -1137,7 +1137,7 @@ struct SparseProducts::Impl {
         if (sums.alloc(ctx, sizeof(int) * (size_t)blocks) != hipSuccess ||
             pair_count.alloc(ctx, sizeof(int) * (size_t)n) != hipSuccess ||
             pair_part.alloc(ctx, sizeof(double) * (size_t)pair_wgs * (size_t)M) != hipSuccess ||
-            pool_take(ctx, sizeof(SparsePair) * (size_t)total, &p, true) != hipSuccess) {
+            pool_take(ctx, sizeof(SparsePair) * (size_t)total, &p, PoolUse::kForSpeed) != hipSuccess) {
             (void)hipGetLastError();
             return KNM_OK; // no room: every sweep walks
         }

@@ -69,7 +69,7 @@ lib = c.CDLL({lib!r})
 P, L, I, F, D, Z = c.c_void_p, c.c_int64, c.c_int, c.c_float, c.c_double, c.c_size_t
 rec.kept_size.restype = c.c_int64
 rec.kept_slab.restype = P
-hip.fake_set_budget.argtypes = [Z]
+hip.fake_set_budget.argtypes = hip.fake_set_total.argtypes = [Z]
 hip.fake_inside.argtypes = [P, Z]
 hip.fake_live.restype = hip.fake_peak.restype = lib.knm_workspace_held.restype = Z
 lib.knm_workspace_held.argtypes = lib.knm_release_workspace.argtypes = lib.knm_destroy.argtypes = [P]
@@ -208,4 +208,31 @@ def test_slab_is_given_up_when_a_fit_needs_the_room(shims):
         assert hip.fake_live() == created + lib.knm_workspace_held(ctx)
         lib.knm_destroy(ctx)
         assert hip.fake_live() == 0
+        """)
+
+
+# What is for speed alone (a fit's values, a slab) leaves a sixteenth of the card to the rest of the program, and beyond 4 GiB of idle blocks
+# so does the pool
+def test_kept_values_leave_room(shims):
+    _run(shims, """
+        card = 288 << 30
+        hip.fake_set_total(card)
+        for n, d, M, t in ((500_000, 400, 3000, 10), (1_000_000, 400, 2000, 1)):
+            hip.fake_set_budget(card)
+            reads, slabs = rec.kept_reads(), rec.kept_slabs()
+            assert fit(n, d, M, t) == 0 and rec.kept_reads() == reads + 7
+            assert prod(n, M, d, t) == 0 and rec.kept_slabs() > slabs
+            assert lib.knm_workspace_held(ctx) > 5 << 30
+            lib.knm_release_workspace(ctx)
+            hip.fake_set_budget(card // 16 + (3 << 30))  # the rest is others'
+            reads, slabs = rec.kept_reads(), rec.kept_slabs()
+            assert fit(n, d, M, t) == 0 and rec.kept_reads() == reads
+            assert lib.knm_workspace_held(ctx) < 5 << 30
+            assert prod(n, M, d, t) == 0 and rec.kept_slabs() == slabs
+            lib.knm_release_workspace(ctx)
+            hip.fake_set_budget(card)
+            assert fit(n, d, M, t) == 0 and lib.knm_workspace_held(ctx) > 5 << 30
+            hip.fake_set_budget(hip.fake_live() + (1 << 30))
+            assert fit(n, d, M, t) == 0 and lib.knm_workspace_held(ctx) < 5 << 30
+            lib.knm_release_workspace(ctx)
         """)
