@@ -1195,7 +1195,7 @@ static int small_knm_v(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t l
         part = reinterpret_cast<double *>(ctx->part_buf);
     }
     hipError_t e = launch_direct(X, n, ldx, C, M, ldc, d, engine_sigma(sigma, ctx->kernel_kind), ctx->kernel_kind, V, t, W, part,
-                                 ctx->cross_term == KNM_CROSS_F16X3 ? ctx->range_count : nullptr, ctx->stream);
+                                 ctx->cross_term == KNM_CROSS_F16X3 ? ctx->range_count : nullptr, 1.0f / (2.0f * sigma * sigma), ctx->stream);
     if (e == hipSuccess && part != nullptr) e = launch_merge(nullptr, part, chunks, n * t, 1, W, nullptr, 1, n * t, ctx->stream);
     return e == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "launch_direct", e);
 }

@@ -27,7 +27,56 @@ struct DirectArgs {
     float *out;   // n x t
     double *part; // chunks x n x t, or null
     unsigned int *range_count; // as SweepArgs has it, or null
+    float inv2s2;              // of the caller's sigma
 };
+constexpr int kSample = 16384; // rows that the engines' common shift is the mean of, at most
+
+// A program that asks knm_range_exceeded hears of the points that the split-fp16 engines could not take, though nothing is clamped here.  The
+// engines measure from their common shift, the mean of the smaller set, which this path does not have; it looks at the distances at
+// hand, from the first centre and from the first row, and only a workgroup that sees one of more than a third of the range forms the shift and
+// measures its points from there.  (If no distance is that large, each set lies within two thirds of the range of itself and
+// the whole range of the other set's mean.)
+template <int R> __device__ __forceinline__ void count_out_of_range(const DirectArgs &a, int64_t row0, int64_t j0, int64_t j1)
+{
+    __shared__ double sums[kThreads];
+    __shared__ float mu[kMaxD];
+    __shared__ bool shifted;
+    const int tid = threadIdx.x;
+    const bool rows = a.n <= a.M; // the smaller set
+    const float *const P = rows ? a.X : a.C;
+    const int64_t count = rows ? a.n : a.M, ld = rows ? a.ldx : a.ldc;
+    const int64_t stride = (count + kSample - 1) / kSample;
+    const int sample = (int)((count + stride - 1) / stride);
+    const int bits = a.d <= 1 ? 0 : 32 - __clz(a.d - 1);
+    const int f = tid & ((1 << bits) - 1);
+    double s = 0.0;
+    if (f < a.d)
+        for (int r = tid >> bits; r < sample; r += kThreads >> bits) s += (double)P[r * stride * ld + f];
+    sums[tid] = s;
+    __syncthreads();
+    if (tid < a.d) {
+        for (int k = tid + (1 << bits); k < kThreads; k += 1 << bits) s += sums[k];
+        const float m = (float)(s / (double)sample);
+        mu[tid] = (m == m && fabsf(m) < 3.0e38f) ? m : 0.0f;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double sq = 0.0;
+        for (int k = 0; k < a.d; ++k) sq += (double)mu[k] * (double)mu[k];
+        shifted = sq * (double)a.inv2s2 > 0.5;
+    }
+    __syncthreads();
+    auto check = [&](const float *p) {
+        float q = 0.0f;
+        for (int k = 0; k < a.d; ++k) {
+            const float diff = p[k] - (shifted ? mu[k] : 0.0f);
+            q = fmaf(diff, diff, q);
+        }
+        if (!(a.s2 * q <= kNormMax)) atomicAdd(a.range_count, 1u);
+    };
+    if (tid < R && row0 + tid < a.n) check(a.X + (row0 + tid) * a.ldx);
+    for (int64_t j = j0 + tid; j < (row0 == 0 ? j1 : 1); j += kThreads) check(a.C + j * a.ldc);
+}
 
 // R rows, TP columns; VW = 4: the rows of both sets can be read 16 bytes at a time
 template <int KIND, int R, int TP, int VW>
@@ -35,9 +84,11 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(DirectArgs a)
 {
     __shared__ __attribute__((aligned(16))) float xs[kMaxD / 4][R][4];
     __shared__ float red[kThreads / 64][R * TP];
+    __shared__ int far;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t row0 = (int64_t)blockIdx.x * R;
     const int d4 = (a.d + 3) / 4;
+    if (tid == 0) far = 0;
     for (int k = tid; k < d4 * 4 * R; k += kThreads) {
         const int r = k / (d4 * 4), f = k % (d4 * 4);
         const bool in = row0 + r < a.n && f < a.d;
@@ -80,12 +131,10 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(DirectArgs a)
                 }
             }
         }
-        // Nothing is clamped here, but a program that asks knm_range_exceeded hears of the points that the split-fp16 engines could not
-        // take: rows that far from the first centre, centres that far from the first row
         if (a.range_count != nullptr && (j == 0 || row0 == 0)) {
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                if (!(a.s2 * q[r] <= kNormMax) && row0 + r < a.n && (j == 0 || r == 0)) atomicAdd(a.range_count, 1u);
+                if (!(a.s2 * q[r] <= kNormMax / 9.0f) && row0 + r < a.n && (j == 0 || r == 0)) far = 1;
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -117,6 +166,7 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(DirectArgs a)
             else a.out[row * a.t + c] = (float)s;
         }
     }
+    if (far != 0) count_out_of_range<R>(a, row0, j0, j1);
 }
 
 int columns(int t) { return t == 1 ? 1 : t == 2 ? 2 : t <= 4 ? 4 : t <= 8 ? 8 : 16; }
@@ -151,7 +201,7 @@ bool direct_pays(int64_t n, int64_t M, int d, int t, bool wide)
 bool direct_wide(const float *C, int64_t ldc, int d) { return d % 4 == 0 && ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0; }
 
 hipError_t launch_direct(const float *X, int64_t n, int64_t ldx, const float *C, int64_t M, int64_t ldc, int d, float sigma, int kind,
-                         const float *V, int t, float *out, double *part, unsigned int *range_count, hipStream_t stream)
+                         const float *V, int t, float *out, double *part, unsigned int *range_count, float inv2s2, hipStream_t stream)
 {
     if (n <= 0 || M <= 0 || d <= 0 || d > kMaxD || t <= 0 || t > 16 || kind < KNM_KERNEL_GAUSSIAN || kind > KNM_KERNEL_MATERN52) return hipErrorInvalidValue;
     const int chunks = direct_chunks(n, M, t);
@@ -166,6 +216,7 @@ hipError_t launch_direct(const float *X, int64_t n, int64_t ldx, const float *C,
     a.out = out;
     a.part = part;
     a.range_count = range_count;
+    a.inv2s2 = inv2s2;
     const int64_t groups = (n + rows(t) - 1) / rows(t);
     if (groups > 0x7fffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)groups, (unsigned)chunks);

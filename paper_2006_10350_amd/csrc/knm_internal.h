@@ -244,7 +244,7 @@ bool direct_wide(const float *C, int64_t ldc, int d); // rows of C can be read 1
 bool direct_pays(int64_t n, int64_t M, int d, int t, bool wide);
 int direct_chunks(int64_t n, int64_t M, int t);
 hipError_t launch_direct(const float *X, int64_t n, int64_t ldx, const float *C, int64_t M, int64_t ldc, int d, float sigma, int kind,
-                         const float *V, int t, float *out, double *part, unsigned int *range_count, hipStream_t stream);
+                         const float *V, int t, float *out, double *part, unsigned int *range_count, float inv2s2, hipStream_t stream);
 
 // fp64 rank-k update of the upper triangle of C on the matrix cores (knm_dsyrk.hip):
 //   C[i, j] = alpha sum_{k < K} w[k] a(i, k) a(j, k) + beta C[i, j] + shift [i == j],  i <= j < n,

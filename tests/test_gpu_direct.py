@@ -56,3 +56,49 @@ def test_small_predictions_report_the_range(knm, where, index):
     ctx.set_cross_term("f32")
     knm.knm_v(X.cuda(), C.cuda(), 1.0, V.cuda(), ctx=ctx)
     assert ctx.range_exceeded() == 0
+
+
+# what is reported is what the engines report (knm_prod's row sweep packs the same points): outliers in the first row, the first centre, both or
+# neither, on either side of 1705 sigma from the smaller set's mean; sets far from the origin, from each other and spread
+# out; points in range but more than that apart.  Nothing lies within a tenth of the line
+@pytest.mark.parametrize("n,M", [(100, 300), (300, 100), (40, 4200), (1, 600), (1, 1)])
+@pytest.mark.parametrize("name", ["opposite outliers in range", "first points out together", "one beyond", "one far row", "sets far from the origin",
+                                  "sets apart", "sets a little apart", "spread out", "spread beyond", "a NaN"])
+def test_small_predictions_report_what_the_engines_would(knm, n, M, name):
+    if name == "a NaN" and M == 1:
+        pytest.skip("the engines' shift is that of the row")
+    d, ctx = 6, knm.Context()
+    X, C, V = _rand(n, d, n), _rand(M, d, M + 1), _rand(M, 1, 3)
+    if name == "opposite outliers in range":
+        X[n // 2, 1] += 1500.0
+        C[0, 1] -= 1500.0 if n > 1 else 0.0
+    elif name == "first points out together":
+        X[0] += 1000.0
+        C[0] += 1000.0
+    elif name == "one beyond":
+        C[M // 3, 2] += 1900.0 if M > 1 else 0.0
+    elif name == "one far row":
+        X[n - 1, 2] += 1500.0
+    elif name == "sets far from the origin":
+        X += 1.0e5
+        C += 1.0e5
+    elif name == "sets apart":
+        X[:, 0] += 2000.0
+    elif name == "sets a little apart":
+        X[:, 0] += 1200.0
+        C[:, 0] -= 200.0
+    elif name == "spread out":
+        X[:, 0] = torch.linspace(-1400.0, 1400.0, n) if n > 1 else X[:, 0]
+        C[:, 0] = torch.linspace(1400.0, -1400.0, M) if M > 1 and n > 1 else C[:, 0]
+    elif name == "spread beyond":
+        X[:, 0] = torch.linspace(-2100.0, 2100.0, n)
+        C[:, 0] = torch.linspace(2100.0, -2100.0, M)
+    else:
+        X[n // 2, 3] = float("nan")
+    X, C, V = X.cuda(), C.cuda(), V.cuda()
+    knm.knm_prod(X, C, 1.0, V, ctx=ctx)
+    engines = ctx.range_exceeded()
+    knm.knm_v(X, C, 1.0, V, ctx=ctx)
+    small = ctx.range_exceeded()
+    print(name, engines, small)
+    assert (small > 0) == (engines > 0)
