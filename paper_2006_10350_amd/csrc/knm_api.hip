@@ -1207,7 +1207,7 @@ int knm_v(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx, const flo
     if (st) return st;
     if (!V || !W) return fail(ctx, KNM_INVALID_ARG, "null vector");
     begin_timing(ctx);
-    if (direct_pays(n, M, d, t, direct_wide(C, ldc, d))) st = small_knm_v(ctx, X, n, d, ldx, C, M, ldc, sigma, V, t, W);
+    if (direct_takes(sigma) && direct_pays(n, M, d, t, direct_wide(C, ldc, d))) st = small_knm_v(ctx, X, n, d, ldx, C, M, ldc, sigma, V, t, W);
     else st = do_knm_v(ctx, X, n, d, ldx, C, M, ldc, sigma, V, t, W);
     mark(ctx, 1);
     mark(ctx, 4);

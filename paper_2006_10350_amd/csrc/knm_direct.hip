@@ -198,6 +198,8 @@ bool direct_pays(int64_t n, int64_t M, int d, int t, bool wide)
     const double ps = (0.03 + 0.0003 * d) * (wide ? 1.0 : 2.0) * (t <= 2 ? 1.0 : t <= 4 ? 1.3 : t <= 8 ? 2.5 : 5.0);
     return 5.0 + (direct_chunks(n, M, t) > 1 ? 4.0 : 0.0) + values * ops * ps < 0.95 * (20.0 + 0.2 * values);
 }
+// (squares of differences and of sigma have to stay within fp32; the engines scale before they square)
+bool direct_takes(float sigma) { return sigma >= 1.0e-15f && sigma <= 1.0e15f; }
 bool direct_wide(const float *C, int64_t ldc, int d) { return d % 4 == 0 && ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0; }
 
 hipError_t launch_direct(const float *X, int64_t n, int64_t ldx, const float *C, int64_t M, int64_t ldc, int d, float sigma, int kind,

@@ -240,6 +240,7 @@ hipError_t launch_merge(const float *part, const double *part64, int64_t n_chunk
 
 // small predictions in one launch (knm_direct.hip): d <= 128, t <= 16; sigma as the engines take it.  With direct_chunks() > 1 the result
 // is in partials of n x t each, to be merged
+bool direct_takes(float sigma); // of the caller
 bool direct_wide(const float *C, int64_t ldc, int d); // rows of C can be read 16 bytes at a time
 bool direct_pays(int64_t n, int64_t M, int d, int t, bool wide);
 int direct_chunks(int64_t n, int64_t M, int t);

@@ -102,3 +102,12 @@ def test_small_predictions_report_what_the_engines_would(knm, n, M, name):
     small = ctx.range_exceeded()
     print(name, engines, small)
     assert (small > 0) == (engines > 0)
+
+
+# units in which squares leave fp32: sigma and the features times a power of two give the same result
+@pytest.mark.parametrize("power", [-80, -66, -50, 50, 66, 80])
+def test_small_predictions_in_any_unit(knm, power):
+    X, C, V, unit = _rand(100, 8, 1).cuda(), _rand(300, 8, 2).cuda(), _rand(300, 2, 3).cuda(), 2.0 ** power
+    W = knm.knm_v(X, C, 2.0, V)
+    other = knm.knm_v(X * unit, C * unit, 2.0 * unit, V)
+    assert float((other - W).norm() / W.norm()) < 2e-6
