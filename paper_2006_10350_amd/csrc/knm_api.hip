@@ -744,22 +744,18 @@ struct SlabUse {
 static int kept_partials(knm_ctx *ctx, const float *keep, int64_t nF, int64_t nS, bool over_stream, const float *vec, const float *wgt,
                          int t, double *part, int chunks)
 {
-    for (int c = 0; c < t; c += kept_max_t()) {
-        KeptArgs k{};
-        k.values = keep;
-        k.nF = nF;
-        k.nS = nS;
-        k.over_stream = over_stream;
-        k.vec = vec + c;
-        k.ldv = k.ldp = t;
-        k.t = t - c < kept_max_t() ? t - c : kept_max_t();
-        k.wgt = wgt;
-        k.part = part + c;
-        k.chunks = chunks;
-        const hipError_t e = launch_kept_sum(k, ctx->stream);
-        if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "launch_kept_sum", e);
-    }
-    return KNM_OK;
+    KeptArgs k{};
+    k.values = keep;
+    k.nF = nF;
+    k.nS = nS;
+    k.over_stream = over_stream;
+    k.vec = vec;
+    k.t = t;
+    k.wgt = wgt;
+    k.part = part;
+    k.chunks = chunks;
+    const hipError_t e = launch_kept_sum(k, ctx->stream);
+    return e == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "launch_kept_sum", e);
 }
 
 // Bytes of the packed-operand workspace one sweep asks for in the split-fp16 modes (0 in the
@@ -845,7 +841,7 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
         if (st) return st;
         const bool over_stream = column_sweep == sh->keep_columns;
         const int64_t kF = over_stream ? nF : nS, kS = over_stream ? nS : nF;
-        if (sh->keep && sh->pair(set_f, set_s) && kF == sh->keep_n[0] && kS == sh->keep_n[1]) {
+        if (sh->keep && sh->pair(set_f, set_s) && kF == sh->keep_n[0] && kS == sh->keep_n[1] && t <= kept_max_t()) {
             const int parts = kept_chunks(kF, kS, over_stream, t);
             st = acquire(ctx, &ctx->part_buf, &ctx->part_bytes, sizeof(double) * (size_t)parts * nF * t, &part);
             if (st) return st;

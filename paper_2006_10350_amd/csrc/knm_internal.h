@@ -83,12 +83,10 @@ struct KeptArgs {
     const float *values;
     int64_t nF, nS;          // points of the two sides
     bool over_stream;        // the sum runs over the stream points (result over the fixed ones), else the other way round
-    const float *vec;        // vec[i * ldv + c] of the points summed over
-    int64_t ldv;
+    const float *vec;        // vec[i * t + c] of the points summed over
     int t;                   // columns, at most kept_max_t()
     const float *wgt;        // per point summed over, or null
-    double *part;            // part[chunk * n_out * ldp + i * ldp + c]
-    int64_t ldp;
+    double *part;            // part[chunk * n_out * t + i * t + c]
     int chunks;              // from kept_chunks()
 };
 int kept_max_t();

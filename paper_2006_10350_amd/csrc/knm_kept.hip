@@ -33,12 +33,12 @@ template <int G, int STEP, bool WGT> struct Entries {
     {
         left = a.n_in - r0 >= 16 ? 16 : (int)(a.n_in - r0);
         const int64_t r0c = left > 0 ? r0 : 0;
-        const float *const vec = a.k.vec + r0c * a.k.ldv;
+        const float *const vec = a.k.vec + r0c * a.k.t;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int r = STEP * e + at < left ? STEP * e + at : 0;
 #pragma unroll
-            for (int g = 0; g < G; ++g) v[e][g] = vec[r * (int)a.k.ldv + col[g]];
+            for (int g = 0; g < G; ++g) v[e][g] = vec[r * a.k.t + col[g]];
             if constexpr (WGT) w[e] = a.k.wgt[r0c + r];
         }
     }
@@ -51,7 +51,7 @@ template <int G, int STEP, bool WGT> struct Entries {
 __device__ __forceinline__ void store_sum(const SumArgs &a, int64_t i, int c, double v)
 {
     if (i >= a.n_out || c >= a.k.t) return;
-    a.k.part[((int64_t)blockIdx.y * a.n_out + i) * a.k.ldp + c] = v;
+    a.k.part[((int64_t)blockIdx.y * a.n_out + i) * a.k.t + c] = v;
 }
 
 // (the wavefront's number in the grid's first dimension, as a scalar)

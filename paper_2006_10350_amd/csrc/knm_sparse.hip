@@ -277,25 +277,20 @@ __global__ __launch_bounds__(256) void scan_sums_kernel(int *__restrict__ sums, 
     }
 }
 
-// (and, unless it is null, a copy of the result)
-__global__ void scan_add_kernel(int *__restrict__ out, int *__restrict__ copy, int64_t len, const int *__restrict__ sums)
+__global__ void scan_add_kernel(int *__restrict__ out, int64_t len, const int *__restrict__ sums)
 {
     const int64_t i = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x); // kScanChunk is a multiple of 4
     if (i >= len) return;
     const int add = sums[i / kScanChunk];
-    if (i + 4 <= len) {
+    if (i + 3 < len) {
         int4 x = *reinterpret_cast<const int4 *>(out + i);
         x.x += add;
         x.y += add;
         x.z += add;
         x.w += add;
         *reinterpret_cast<int4 *>(out + i) = x;
-        if (copy != nullptr) *reinterpret_cast<int4 *>(copy + i) = x;
     } else {
-        for (int64_t k = i; k < len; ++k) {
-            out[k] += add;
-            if (copy != nullptr) copy[k] = out[k];
-        }
+        for (int64_t k = i; k < len; ++k) out[k] += add;
     }
 }
 
@@ -969,8 +964,7 @@ struct CentreLists {
         hipLaunchKernelGGL(scan_local_kernel, dim3((unsigned)fill_blocks), dim3(256), 0, st, col_ptr.as<int>(), features + 1,
                            col_ptr.as<int>(), sums.as<int>());
         hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(256), 0, st, sums.as<int>(), fill_blocks);
-        hipLaunchKernelGGL(scan_add_kernel, grid_for(features / 4 + 1), dim3(256), 0, st, col_ptr.as<int>(), (int *)nullptr,
-                           features + 1, sums.as<int>());
+        hipLaunchKernelGGL(scan_add_kernel, grid_for(features / 4 + 1), dim3(256), 0, st, col_ptr.as<int>(), features + 1, sums.as<int>());
         if (nnz_c > 0)
             hipLaunchKernelGGL(csc_fill_kernel, grid_for(nnz_c), dim3(256), 0, st, number.as<int>(), place.as<int>(), row.as<int>(),
                                c_values, nnz_c, col_ptr.as<int>(), csc_row.as<int>(), csc_val.as<float>());
@@ -1146,7 +1140,7 @@ struct SparseProducts::Impl {
         int *off = pair_off.as<int>();
         hipLaunchKernelGGL(scan_local_kernel, dim3((unsigned)blocks), dim3(256), 0, st, off, n, off, sums.as<int>());
         hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(256), 0, st, sums.as<int>(), blocks);
-        hipLaunchKernelGGL(scan_add_kernel, grid_for((n + 3) / 4), dim3(256), 0, st, off, off, n, sums.as<int>());
+        hipLaunchKernelGGL(scan_add_kernel, grid_for((n + 3) / 4), dim3(256), 0, st, off, n, sums.as<int>());
         hipLaunchKernelGGL(sparse_sweep_kernel<kFormPairs>, dim3((unsigned)wgs), dim3(kSpThreads), 0, st, args());
         return hipGetLastError() == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "pair lists launch");
     }
