@@ -218,6 +218,20 @@ def engine_of(w, cross: str, kernel: str):
     return name, k_loop, f16
 
 
+def forms_values_once(w, cross: str, kernel: str) -> bool:
+    """Whether the library's product takes X in slabs whose kernel values it keeps from K v to K^T w (same rule as the library): at
+    most 12 columns on the vector ALU of the split-fp16 K-loop engine, from about 230 features (many columns) or 260 (one) on, and
+    slabs of 4 GiB that have 1024 rows where there are several."""
+    _, k_loop, f16 = engine_of(w, cross, kernel)
+    matrix_reduction = w.t > 16 or (w.t >= 8 and 4 * (3 + w.t) >= 3 * ((w.d + 15) // 16) + 1)
+    if not (k_loop and f16) or kernel != "gaussian" or w.t > 12 or matrix_reduction:
+        return False
+    if 0.14 + 0.0045 * w.d + (0.15 if w.t > 5 else 0.03 * w.t) < 1.34:
+        return False
+    rows = (4 << 30) // (256 * 4 * ((w.M + 127) // 128 * 128)) * 256
+    return rows >= 1024 or (w.n + 255) // 256 * 256 <= rows
+
+
 def product_leg(knm, synth, torch, ctx, w, steps: int, warmup: int, cross: str, kernel: str, inputs=None, probe=None):
     """Times `steps` full products K_nm^T (K_nm v) on workload w; returns the metrics of the leg."""
     inp = inputs or synth.make_inputs(w, device="cuda", with_targets=False)
@@ -248,7 +262,11 @@ def product_leg(knm, synth, torch, ctx, w, steps: int, warmup: int, cross: str, 
     kernel_name, k_loop, f16 = engine_of(w, cross, kernel)
     # columns per launch of the K-loop engines (split-fp16: with its packed vector image)
     group = (160 if kernel == "gaussian" else 128) if (k_loop and f16) else 16
-    launches = 2 * ((w.t + group - 1) // group if k_loop else 1) * steps
+    # A product that forms every value once is priced as a whole: its row sweeps of slabs and its sums over the kept values
+    # (kept_rows_kernel) stand for one launch
+    once = forms_values_once(w, cross, kernel)
+    sweeps = 1 if once else 2
+    launches = sweeps * ((w.t + group - 1) // group if k_loop else 1) * steps
     avg_launch_ms = (sum(row_ms) + sum(col_ms)) / launches
     # Algorithmic contraction work of one launch (one sweep): every kernel entry once, 2 d flop each.
     # Padded or augmented contraction slots, the 2 t reduction flop and the exp are not counted.
@@ -258,7 +276,8 @@ def product_leg(knm, synth, torch, ctx, w, steps: int, warmup: int, cross: str, 
     traffic, mfma_insts = counters(w.name + ("" if f16 else "_f32")) if default else (None, None)
     roofline = {
         "bound": "mfma",
-        "kernel": kernel_name,
+        "kernel": kernel_name + (" + kept_rows_kernel" if once else ""),
+        "values_formed": "once, in slabs" if once else "in each sweep",
         # the contraction's own dtype: f16 matrix cores (three split products per feature pair,
         # fp32 accumulate) in the default mode, fp32 matrix cores otherwise
         "contraction_dtype": "f16" if f16 else "f32",
@@ -268,8 +287,9 @@ def product_leg(knm, synth, torch, ctx, w, steps: int, warmup: int, cross: str, 
         "frac": tflops / (PEAK_FP16_MFMA_TFLOPS if f16 else PEAK_FP32_MFMA_TFLOPS),
         "traffic": traffic,
         "avg_launch_ms": avg_launch_ms,
-        "row_sweep_ms": sum(row_ms) / len(row_ms),
-        "col_sweep_ms": sum(col_ms) / len(col_ms),
+        # (in slabs the two alternate; the library's events tell only the last slab's sums from what comes before them)
+        "row_sweep_ms": None if once else sum(row_ms) / len(row_ms),
+        "col_sweep_ms": None if once else sum(col_ms) / len(col_ms),
         "merge_ms": sum(merge_ms) / len(merge_ms),
         "flop_per_launch": flop_per_launch,
         # the same launch priced against the fp32 matrix peak (what the 2 d flop per entry would cost there)
@@ -299,10 +319,10 @@ def product_leg(knm, synth, torch, ctx, w, steps: int, warmup: int, cross: str, 
         "steps": steps, "warmup": warmup,
         "s_per_product": s_per_product,
         "g_entries_per_s": entries / s_per_product / 1e9,
-        "g_entry_evaluations_per_s": 2.0 * entries / s_per_product / 1e9,
+        "g_entry_evaluations_per_s": sweeps * entries / s_per_product / 1e9,
         "cross_term": "f16x3" if f16 else "f32",
-        # fractions of the fp32 matrix peak: the method's two evaluations of every entry, and one
-        "fp32_mfma_frac_two_sweeps": 2.0 * entries * 2.0 * w.d / s_per_product / 1e12 / PEAK_FP32_MFMA_TFLOPS,
+        # fractions of the fp32 matrix peak: the method's two evaluations of every entry (where there are two), and one
+        "fp32_mfma_frac_two_sweeps": None if once else 2.0 * entries * 2.0 * w.d / s_per_product / 1e12 / PEAK_FP32_MFMA_TFLOPS,
         "fp32_mfma_frac_single_eval": entries * 2.0 * w.d / s_per_product / 1e12 / PEAK_FP32_MFMA_TFLOPS,
         "roofline": roofline,
         "_tensors": (X, C, v, U),

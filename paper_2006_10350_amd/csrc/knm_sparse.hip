@@ -55,7 +55,7 @@ constexpr int kHashMaxPairs = 320; // a row with at most this many pair updates 
 // by all of them, up to this many (8 bytes each); beyond it, and where there is no room, every sweep walks.  A walk adds
 // into its accumulators at random, which is what it waits for; a reader streams.  200k rows of 100 entries against 20000
 // centres: 1.19 ms by rows and 1.25 ms by columns walked; 1.16 ms to form the pairs, 0.075 ms and 0.046 ms
-// read, so that two sweeps already gain (a product 5.72 -> 4.55 ms).  A fit of 20 sweeps at 50k rows: 50.2 -> 41.3 ms.
+// read, so that two sweeps already gain (a product 5.72 -> 4.55 ms).  A fit of 21 sweeps, 100k rows and 10000 centres: 50.2 -> 41.3 ms.
 constexpr unsigned long long kMaxPairs = (unsigned long long)1 << 29;
 constexpr int kSide = 2;            // entries of X per lane that are looked up side by side
 constexpr int kMaxHead = 128;       // features treated densely, at most (one dense row of X^H and C^H each)

@@ -167,6 +167,25 @@ def test_products_that_keep_slabs(shims, n, M, d, t):
         """)
 
 
+# bench.py prices a product by whether it forms its values once: its rule is the library's
+def test_the_benchmarks_rule_for_slabs(shims):
+    shapes = [(n, d, M, t, cross, kind) for n, M in ((2_000_000, 50_000), (30_000, 3000), (20_480, 1 << 20), (20_480, (1 << 20) + 128), (1000, 3 << 20),
+                                                     (256, 3 << 20))
+              for d in (28, 233, 234, 239, 240, 260, 261, 304, 305, 784) for t in (1, 4, 6, 8, 10, 12, 13, 40) for cross, kind in ((1, 0), (0, 0), (1, 1))]
+    _run(shims, f"""
+        import os, sys, types
+        sys.path.insert(0, {os.path.dirname(HERE)!r})
+        import bench
+        for n, d, M, t, cross, kind in {shapes!r}:
+            assert lib.knm_set_cross_term(ctx, cross) == 0 and lib.knm_set_kernel(ctx, kind) == 0
+            before = rec.kept_slabs()
+            assert prod(n, M, d, t) == 0
+            w = types.SimpleNamespace(n=n, d=d, M=M, t=t)
+            once = bench.forms_values_once(w, "f16x3" if cross else "f32", "laplacian" if kind else "gaussian")
+            assert once == (rec.kept_slabs() > before), (n, d, M, t, cross, kind, once)
+        """)
+
+
 # A captured product holds pointers into its slab: no other call frees that or moves it, and none is allocated while the stream is captured
 def test_slab_of_a_captured_product_stays(shims):
     _run(shims, """
