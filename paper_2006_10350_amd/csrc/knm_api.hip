@@ -1,6 +1,7 @@
 // C ABI of libknm: context, workspace and the kernel-matrix-vector products.
 #include <dlfcn.h>
 
+#include <chrono>
 #include <cmath>
 #include <cstddef>
 #include <cstdio>
@@ -225,8 +226,17 @@ void pool_give(knm_ctx *ctx, void *p)
         ctx->pool_idle += b.bytes;
         break;
     }
+    // (how full the card is is asked at most every 50 ms: a call gives some 25 blocks back, and the answer takes 5 to 50 us)
+    auto full = [&] {
+        const auto now = std::chrono::steady_clock::now();
+        if (now - ctx->room_asked > std::chrono::milliseconds(50)) {
+            ctx->room_asked = now;
+            ctx->room_left = leaves_room(0);
+        }
+        return !ctx->room_left;
+    };
     // oldest idle blocks first (hipFree waits for the device, so nothing queued still uses them)
-    auto too_many = [&] { return ctx->pool_idle > kPoolIdleBytes || (ctx->pool_idle > kPoolIdleFull && !leaves_room(0)); };
+    auto too_many = [&] { return ctx->pool_idle > kPoolIdleBytes || (ctx->pool_idle > kPoolIdleFull && full()); };
     for (size_t i = 0; i < ctx->pool.size();) {
         if (ctx->pool[i].used) {
             ++i;

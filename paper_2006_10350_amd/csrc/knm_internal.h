@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <chrono>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -332,6 +333,8 @@ struct knm_ctx {
     knm::SweepShare *share = nullptr; // of the product or fit whose sweeps are being enqueued
     const knm::SweepShare *mu_owner = nullptr; // mu_buf holds the shift of this pair of sets
     size_t pool_idle = 0; // bytes of the blocks not in use
+    std::chrono::steady_clock::time_point room_asked{}; // when the card was last found to have room_left
+    bool room_left = true;
     // a product's kept kernel values and sums over them (prod_kept), in a block of the pool that stays in use between calls, so that it is
     // where a captured product writes; spare while no product runs, unless one was captured
     void *slab = nullptr;

@@ -234,24 +234,28 @@ def test_slab_is_given_up_when_a_fit_needs_the_room(shims):
 # so does the pool
 def test_kept_values_leave_room(shims):
     _run(shims, """
+        import time
+        def others_leave(bytes):
+            hip.fake_set_budget(bytes)
+            time.sleep(0.06)  # the pool asks that often
         card = 288 << 30
         hip.fake_set_total(card)
         for n, d, M, t in ((500_000, 400, 3000, 10), (1_000_000, 400, 2000, 1)):
-            hip.fake_set_budget(card)
+            others_leave(card)
             reads, slabs = rec.kept_reads(), rec.kept_slabs()
             assert fit(n, d, M, t) == 0 and rec.kept_reads() == reads + 7
             assert prod(n, M, d, t) == 0 and rec.kept_slabs() > slabs
             assert lib.knm_workspace_held(ctx) > 5 << 30
             lib.knm_release_workspace(ctx)
-            hip.fake_set_budget(card // 16 + (3 << 30))  # the rest is others'
+            others_leave(card // 16 + (3 << 30))  # the rest is others'
             reads, slabs = rec.kept_reads(), rec.kept_slabs()
             assert fit(n, d, M, t) == 0 and rec.kept_reads() == reads
             assert lib.knm_workspace_held(ctx) < 5 << 30
             assert prod(n, M, d, t) == 0 and rec.kept_slabs() == slabs
             lib.knm_release_workspace(ctx)
-            hip.fake_set_budget(card)
+            others_leave(card)
             assert fit(n, d, M, t) == 0 and lib.knm_workspace_held(ctx) > 5 << 30
-            hip.fake_set_budget(hip.fake_live() + (1 << 30))
+            others_leave(hip.fake_live() + (1 << 30))
             assert fit(n, d, M, t) == 0 and lib.knm_workspace_held(ctx) < 5 << 30
             lib.knm_release_workspace(ctx)
         """)
