@@ -84,7 +84,8 @@ int knm_v(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx,
 
 /* U[M x t] = K_nm^T (K_nm V), the product evaluated once per conjugate-gradient
  * iteration (Section 3.1, "Blockwise K_nm-vector product"); K_nm is never formed as a whole (from about 230 features on the
- * kernel values of a slab of rows, up to 4 GiB, are kept from K V to their share of K^T).
+ * kernel values of a slab of rows, up to 4 GiB, are kept from K V to their share of K^T; where there is no room for one, the values are formed
+ * twice, and the last bits of W differ).
  * If W_or_null is not NULL it also receives W[n x t] = K_nm V. */
 int knm_prod(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx,
              const float *C, int64_t M, int64_t ldc, float sigma,
@@ -92,7 +93,8 @@ int knm_prod(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx,
 
 /* knm_prod for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments and result as knm_prod (up to the last bits where the
- * array below holds fewer partials than knm_prod would make), except that
+ * array below holds fewer partials than knm_prod would make, and where knm_prod keeps kernel values, which rounds W in another order: up to
+ * 12 columns and from about 230 features on), except that
  * W (n x t) must be given.  The call allocates nothing: the chunk partials, the common shift and the
  * converted operands of the split-fp16 engines live in a static device array of
  * knm_static_scratch_bytes() bytes (64 MiB) that every GPU the library runs on holds until the process
@@ -334,7 +336,7 @@ int knm_set_pack_limit(knm_ctx *ctx, size_t bytes);
  * point about 1700 sigma from the bulk of the data); beyond that, and for features that are not finite,
  * the conversion clamps, and the kernel values of such a point are wrong wherever they are not zero
  * anyway.  Every clamped conversion of a point is counted on the device (a knm_v small enough to be evaluated from
- * differences clamps nothing, and counts such points all the same).  knm_range_exceeded waits for
+ * differences clamps nothing, but counts the points that the conversion would have clamped).  knm_range_exceeded waits for
  * the stream, writes the count since the last reset to the HOST pointer (several sweeps may convert
  * the same point, so only zero or non-zero is meaningful: 0 means no operand was clamped), and
  * clears it if reset != 0.  The product entry points do not synchronise and therefore cannot report
