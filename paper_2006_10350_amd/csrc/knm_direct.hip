@@ -32,10 +32,10 @@ struct DirectArgs {
 constexpr int kSample = 16384; // rows that the engines' common shift is the mean of, at most
 
 // A program that asks knm_range_exceeded hears of the points that the split-fp16 engines could not take, though nothing is clamped here.  The
-// engines measure from their common shift, the mean of the smaller set, which this path does not have; it looks at the distances at
-// hand, from the first centre and from the first row, and only a workgroup that sees one of more than a third of the range forms the shift and
-// measures its points from there.  (If no distance is that large, each set lies within two thirds of the range of itself and
-// the whole range of the other set's mean.)
+// engines measure from their common shift, the mean of the smaller set (nothing, where that is less than one sigma), which this path does not
+// have.  A point more than the range from the shift is at least that far from some point of the smaller set, and every point of the other set is
+// more than a third of the range from one of the two.  So a workgroup that sees such a distance, between any of its rows and
+// centres, forms the shift and measures its own points and the whole smaller set from there; usual data never gets there.
 template <int R> __device__ __forceinline__ void count_out_of_range(const DirectArgs &a, int64_t row0, int64_t j0, int64_t j1)
 {
     __shared__ double sums[kThreads];
@@ -66,16 +66,21 @@ template <int R> __device__ __forceinline__ void count_out_of_range(const Direct
         shifted = sq * (double)a.inv2s2 > 0.5;
     }
     __syncthreads();
-    auto check = [&](const float *p) {
-        float q = 0.0f;
-        for (int k = 0; k < a.d; ++k) {
-            const float diff = p[k] - (shifted ? mu[k] : 0.0f);
-            q = fmaf(diff, diff, q);
+    bool beyond = false;
+    auto check = [&](const float *points, int64_t ldp, int64_t begin, int64_t end) {
+        for (int64_t i = begin + tid; i < end; i += kThreads) {
+            float q = 0.0f;
+            for (int k = 0; k < a.d; ++k) {
+                const float diff = points[i * ldp + k] - (shifted ? mu[k] : 0.0f);
+                q = fmaf(diff, diff, q);
+            }
+            beyond |= !(a.s2 * q <= kNormMax);
         }
-        if (!(a.s2 * q <= kNormMax)) atomicAdd(a.range_count, 1u);
     };
-    if (tid < R && row0 + tid < a.n) check(a.X + (row0 + tid) * a.ldx);
-    for (int64_t j = j0 + tid; j < (row0 == 0 ? j1 : 1); j += kThreads) check(a.C + j * a.ldc);
+    check(P, ld, 0, count);
+    if (rows) check(a.C, a.ldc, j0, j1);
+    else check(a.X, a.ldx, row0, row0 + R < a.n ? row0 + R : a.n);
+    if (__syncthreads_or(beyond) && tid == 0) atomicAdd(a.range_count, 1u);
 }
 
 // R rows, TP columns; VW = 4: the rows of both sets can be read 16 bytes at a time
@@ -84,16 +89,14 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(DirectArgs a)
 {
     __shared__ __attribute__((aligned(16))) float xs[kMaxD / 4][R][4];
     __shared__ float red[kThreads / 64][R * TP];
-    __shared__ int far;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t row0 = (int64_t)blockIdx.x * R;
     const int d4 = (a.d + 3) / 4;
-    if (tid == 0) far = 0;
     for (int k = tid; k < d4 * 4 * R; k += kThreads) {
         const int r = k / (d4 * 4), f = k % (d4 * 4);
-        const bool in = row0 + r < a.n && f < a.d;
-        const float v = a.X[in ? (row0 + r) * a.ldx + f : 0];
-        xs[f >> 2][r][f & 3] = in ? v : 0.0f; // (features past the last are zero on both sides)
+        const int64_t row = row0 + r < a.n ? row0 + r : a.n - 1; // (a row that does not exist repeats the last one and is not stored)
+        const float v = a.X[f < a.d ? row * a.ldx + f : 0];
+        xs[f >> 2][r][f & 3] = f < a.d ? v : 0.0f; // (features past the last are zero on both sides)
     }
     __syncthreads();
     const int64_t j0 = (int64_t)blockIdx.y * a.chunk, j1 = j0 + a.chunk < a.M ? j0 + a.chunk : a.M;
@@ -102,6 +105,7 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(DirectArgs a)
     for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int c = 0; c < TP; ++c) sum[r][c] = 0.0f;
+    unsigned farthest = 0; // bits of the largest q: squares order like their bit patterns, and a NaN lies above all of them
     for (int64_t j = j0 + tid; j < j1; j += kThreads) {
         const float *cj = a.C + j * a.ldc;
         float v[TP], q[R];
@@ -131,11 +135,8 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(DirectArgs a)
                 }
             }
         }
-        if (a.range_count != nullptr && (j == 0 || row0 == 0)) {
 #pragma unroll
-            for (int r = 0; r < R; ++r)
-                if (!(a.s2 * q[r] <= kNormMax / 9.0f) && row0 + r < a.n && (j == 0 || r == 0)) far = 1;
-        }
+        for (int r = 0; r < R; ++r) farthest = max(farthest, __float_as_uint(q[r]));
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             float p;
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(DirectArgs a)
             else a.out[row * a.t + c] = (float)s;
         }
     }
-    if (far != 0) count_out_of_range<R>(a, row0, j0, j1);
+    if (a.range_count != nullptr && __syncthreads_or(!(a.s2 * __uint_as_float(farthest) <= kNormMax / 9.0f))) count_out_of_range<R>(a, row0, j0, j1);
 }
 
 int columns(int t) { return t == 1 ? 1 : t == 2 ? 2 : t <= 4 ? 4 : t <= 8 ? 8 : 16; }

@@ -63,7 +63,8 @@ def test_small_predictions_report_the_range(knm, where, index):
 # out; points in range but more than that apart.  Nothing lies within a tenth of the line
 @pytest.mark.parametrize("n,M", [(100, 300), (300, 100), (40, 4200), (1, 600), (1, 1)])
 @pytest.mark.parametrize("name", ["opposite outliers in range", "first points out together", "one beyond", "one far row", "sets far from the origin",
-                                  "sets apart", "sets a little apart", "spread out", "spread beyond", "a NaN"])
+                                  "sets apart", "sets a little apart", "spread out", "spread beyond", "rows beyond beside the first centre",
+                                  "centres beyond beside the first rows", "a NaN"])
 def test_small_predictions_report_what_the_engines_would(knm, n, M, name):
     if name == "a NaN" and M == 1:
         pytest.skip("the engines' shift is that of the row")
@@ -93,6 +94,12 @@ def test_small_predictions_report_what_the_engines_would(knm, n, M, name):
     elif name == "spread beyond":
         X[:, 0] = torch.linspace(-2100.0, 2100.0, n)
         C[:, 0] = torch.linspace(2100.0, -2100.0, M)
+    elif name == "rows beyond beside the first centre":  # which is in range, and less than a third of it away
+        X[-4:, 1] += 2090.0
+        C[0, 1] += 1535.0
+    elif name == "centres beyond beside the first rows":  # all of a workgroup's, where there are 4200
+        X[:4, 1] += 1535.0
+        C[-104:, 1] += 2090.0
     else:
         X[n // 2, 3] = float("nan")
     X, C, V = X.cuda(), C.cuda(), V.cuda()
