@@ -5,6 +5,7 @@
 // limit and no second evaluation of near pairs.  A thread has one centre at a time and R rows, whose features come from LDS as
 // broadcasts; it adds at most kCentresPerThread terms in fp32, a workgroup's threads are added in fp32 over a wavefront and in
 // fp64 beyond it, and so are the parts of a row that is split over several workgroups (launch_merge).
+#include <limits>
 #include <type_traits>
 
 #include "knm_internal.h"
@@ -28,6 +29,7 @@ struct DirectArgs {
     double *part; // chunks x n x t, or null
     unsigned int *range_count; // as SweepArgs has it, or null
     float inv2s2;              // of the caller's sigma
+    float most;                // exponents are no larger, nor a NaN where this is none
 };
 constexpr int kSample = 16384; // rows that the engines' common shift is the mean of, at most
 
@@ -139,9 +141,10 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(DirectArgs a)
         for (int r = 0; r < R; ++r) farthest = max(farthest, __float_as_uint(q[r]));
 #pragma unroll
         for (int r = 0; r < R; ++r) {
+            const float x = fminf(a.s2 * q[r], a.most);
             float p;
-            if constexpr (KIND == KNM_KERNEL_GAUSSIAN) p = __builtin_amdgcn_exp2f(-a.s2 * q[r]);
-            else p = radial_from_exponent<KIND>(-a.s2 * q[r]);
+            if constexpr (KIND == KNM_KERNEL_GAUSSIAN) p = __builtin_amdgcn_exp2f(-x);
+            else p = radial_from_exponent<KIND>(-x);
 #pragma unroll
             for (int c = 0; c < TP; ++c) sum[r][c] = fmaf(p, v[c], sum[r][c]);
         }
@@ -220,6 +223,10 @@ hipError_t launch_direct(const float *X, int64_t n, int64_t ldx, const float *C,
     a.part = part;
     a.range_count = range_count;
     a.inv2s2 = inv2s2;
+    // 2^-1e30 and 2^-1e15 are 0: a point with a feature that is not finite or too large to square has the value 0, as with the engines, which
+    // clamp it, and does not make a NaN of every other point's result (a Matern kernel's 0 times infinity).  Where nothing is clamped, kernels
+    // of r carry a NaN on.
+    a.most = kind == KNM_KERNEL_GAUSSIAN || range_count != nullptr ? 1.0e30f : std::numeric_limits<float>::quiet_NaN();
     const int64_t groups = (n + rows(t) - 1) / rows(t);
     if (groups > 0x7fffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)groups, (unsigned)chunks);

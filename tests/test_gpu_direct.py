@@ -118,3 +118,33 @@ def test_small_predictions_in_any_unit(knm, power):
     W = knm.knm_v(X, C, 2.0, V)
     other = knm.knm_v(X * unit, C * unit, 2.0 * unit, V)
     assert float((other - W).norm() / W.norm()) < 2e-6
+
+
+# a point that is not finite, or too far for its square to be, has the value 0 in the split-fp16 mode and for the Gaussian kernel: its row is 0, and the other
+# rows are what they are without it.  Kernels of r in the fp32 mode carry a NaN on
+@pytest.mark.parametrize("cross", ["f16x3", "f32"])
+@pytest.mark.parametrize("kernel", ["gaussian", "laplacian", "matern32", "matern52"])
+@pytest.mark.parametrize("n,M,d,t", [(100, 300, 6, 1), (100, 300, 8, 3), (5, 4200, 8, 1)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), -float("inf"), 1e25, 1e18])
+def test_small_predictions_with_a_point_that_is_not_finite(knm, n, M, d, t, value, kernel, cross):
+    ctx = knm.Context()
+    ctx.set_kernel(kernel)
+    ctx.set_cross_term(cross)
+    X, C, V, sigma = _rand(n, d, 1), _rand(M, d, 2), _rand(M, t, 3), 1.5
+    far_row, far_centre, without = X.clone(), C.clone(), V.clone()
+    far_row[n // 2, 2] = far_centre[M // 3, 2] = value
+    without[M // 3] = 0.0
+    row, centre, both = (knm.knm_v(x.cuda(), c.cuda(), sigma, V.cuda(), ctx=ctx).cpu().numpy().astype(np.float64)
+                         for x, c in ((far_row, C), (X, far_centre), (far_row, far_centre)))
+    with oracle.kernel(kernel):
+        ref, other, scale = (oracle.knm_v(X.numpy(), C.numpy(), sigma, v.numpy()) for v in (V, without, V.abs()))
+    rest = np.arange(n) != n // 2
+    if cross == "f32" and kernel != "gaussian" and not abs(value) < 1e20:
+        if value != value:
+            assert np.isnan(row[n // 2]).all() and np.isnan(centre).all()
+        assert np.max(np.abs(row - ref)[rest] / scale[rest]) < 2e-6
+        return
+    assert (row[n // 2] == 0.0).all() and np.max(np.abs(row - ref)[rest] / scale[rest]) < 2e-6
+    assert np.max(np.abs(centre - other) / scale) < 2e-6
+    if value != value:
+        assert (both[n // 2] == 0.0).all() and np.max(np.abs(both - other)[rest] / scale[rest]) < 2e-6
