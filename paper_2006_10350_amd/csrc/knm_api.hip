@@ -642,10 +642,13 @@ static bool keeping_pays(int64_t n, int64_t M, int d, int t, int cross_term, int
 
 // Rows of X whose kernel values a product keeps from its row sweep to its sums over the columns, 0 if it forms them twice: where a second
 // sweep (estimated as in keeping_pays) takes longer than storing the values beside the first (0.2 ps per value) and reading them
-// (0.8), and its sums are those of the vector ALU, which kept_rows_kernel repeats to the last bit.  Products as fast as by two sweeps, 1 and 10
-// columns: d = 200 0.97 and - (matrix-core reduction), 250 1.07 and -, 300 1.15 and 1.21, 400 1.28 and 1.35, 784 1.56 and 1.62 (n = 300k, M =
-// 20k); d = 784 1.24 and 1.28 at n = 5000, M = 500.  1 column at d = 240, 260, 300: 30000 x 3000 0.96, 0.98 and 1.05, 100k x 1500 1.07, 1.00 and
-// 1.05, five other sizes from 3000 x 800 to 150k x 9000 1.05 to 1.17: the line lies at d = 260 (4 columns 240, 10 columns 234).  Slabs of 16 GiB were no faster than of 4.
+// (0.8), and its sums are those of the vector ALU, which kept_rows_kernel repeats to the last bit.  The line lies at d = 260 with 1 column, 240
+// with 4, 234 with 6 to 12.  Products as fast as by two sweeps, 1 column at d = 262, normal rows and rows of which four fifths are zeros (whose two
+// sweeps take a fifth less, at a higher clock): 5000 x 500 1.14 and 1.15, 36099 x 2443 1.13 and 1.02, 100k x 1500 1.15 and 1.03, 50000 x 8000
+// 1.27 and 1.10, 300k x 20k 1.27 and 1.13; 4 columns at d = 244 1.18, 1.14 and 1.03, 1.27 and 1.25, 1.23 and 1.11, 1.25 and 1.09; 8 columns
+// at d = 236 1.20, 1.20 and 1.16, 1.29 and 1.20, 1.23 and 1.12, 1.26 and 1.12; d = 784 1.3 to 1.6.  (While values went through the caches as
+// other data do, and pushed the operands out, 1 column at d = 262 was 0.96 to 1.10 and, on rows of zeros, 0.84 to 0.93 times as fast.)
+// Slabs of 16 GiB were no faster than of 4.
 // The more centres, the fewer rows has a slab, and each reads all centres again: 400k centres (2560 rows) 1.04, 1.07, 1.11 and 1.18 at d = 260,
 // 280, 300 and 340 with 1 column, 1M centres (1024 rows) 1.00, 1.03, 1.04 and 1.12, 1.53 at d = 784; 4M centres (256 rows) 0.94 at d = 270,
 // 1.14 at 400 and 0.74 at 784, where the centres' image is not kept either.

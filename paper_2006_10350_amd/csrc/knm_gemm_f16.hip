@@ -624,7 +624,9 @@ __global__ __launch_bounds__(kThreads, workgroups_per_cu(MV, TP, KIND, VI)) void
             if (j >= chunk_end) return 0.0f;
             return radial_from_exponent<KIND>(exact_exponent(frow[fb], a.S + j * a.lds, a.d, s2));
         };
-        // KEEP: a quad of registers is 4 consecutive stream rows of a fixed point, one unit of the block
+        // KEEP: a quad of registers is 4 consecutive stream rows of a fixed point, one unit of the block.  KEEP 2: stored past the caches, where
+        // the values push out the operands that the workgroups share (with kept_rows_kernel's loads, products of 36099 x 2443, 1 column: d = 262
+        // 335 -> 297 us, 784 572 -> 551)
         float *const kept = KEEP ? a.keep + (((fixed0 >> 5) + wave * 2) * a.keep_s32 + (stream0 >> 5)) * (int64_t)kKeptBlock +
                                        kept_unit(lane & 31, h) * 4
                                  : nullptr;
@@ -798,7 +800,8 @@ __global__ __launch_bounds__(kThreads, workgroups_per_cu(MV, TP, KIND, VI)) void
                     if constexpr (KEEP == 2) {
                         quad[fb][it & 3] = p;
                         if ((it & 3) == 3)
-                            *reinterpret_cast<f32x4 *>(kept + (fb * a.keep_s32 + (it >> 4)) * (int64_t)kKeptBlock + ((it & 15) >> 2) * 32) = quad[fb];
+                            __builtin_nontemporal_store(quad[fb], reinterpret_cast<f32x4 *>(kept + (fb * a.keep_s32 + (it >> 4)) * (int64_t)kKeptBlock +
+                                                                                            ((it & 15) >> 2) * 32));
                     }
 #pragma unroll
                     for (int c = 0; c < TP; ++c) sum[fb][c] = fmaf(p, vr[cur][c], sum[fb][c]);

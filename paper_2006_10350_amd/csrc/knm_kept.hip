@@ -182,7 +182,8 @@ __global__ __launch_bounds__(kThreads, workgroups_per_cu(G)) void kept_over_fixe
 // and product e is that of centres 4 i + e.  A workgroup is two groups of centres and both halves, over the part of one
 // chunk that lies in the slab: the order of a chunk's sums is fixed, so the chunks and the centres are all there is to share
 // out, and a wavefront has a whole tile (16 KB) on its way.  Bound by the bandwidth of the values: 16384 x 50000 of them, 10 columns, in
-// 0.63 ms, 5.2 TB/s (on the vector ALU, one lane per centre, with the vector entries from scalar loads 1.3 to 1.6 ms: they came from the L2).
+// 0.53 ms, 6.2 TB/s (0.63 with loads that leave the values in the caches; on the vector ALU, one lane per centre, with the vector entries from
+// scalar loads 1.3 to 1.6 ms: they came from the L2).
 __global__ __launch_bounds__(kThreads, 2) void kept_rows_kernel(KeptRowsArgs a, int64_t n_s32, int64_t chunk0)
 {
     __shared__ double other[2][16][64];
@@ -222,7 +223,8 @@ __global__ __launch_bounds__(kThreads, 2) void kept_rows_kernel(KeptRowsArgs a, 
             for (int i = 0; i < 4; ++i) {
                 const int r = 32 * b + 8 * i + 4 * h + q;
                 // (a block of 32 rows that begins past the end does not exist)
-                kv[4 * b + i] = *reinterpret_cast<const f32x4 *>((32 * b < left ? p : base + ((row - a.row0) >> 5) * n_s32 * kKeptBlock) + i * 256 + at);
+                kv[4 * b + i] = __builtin_nontemporal_load(
+                    reinterpret_cast<const f32x4 *>((32 * b < left ? p : base + ((row - a.row0) >> 5) * n_s32 * kKeptBlock) + i * 256 + at));
                 w[4 * b + i] = a.vec[(row - a.row0 + (r < left ? r : 0)) * a.t + col];
             }
         };
