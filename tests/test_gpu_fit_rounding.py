@@ -55,13 +55,14 @@ def _fit64(X, Y, C, sigma, round_u=False):
     return solve(T, solve(A, b))
 
 
-# K-loop engines, several columns and one; classes as skewed as one-hot targets get.  If every entry of K^T w is rounded to fp32
-# the coefficients move by E (measured here).  The engines add the terms of an entry in fp32 sums of 8 and those in fp64: n terms of
+# Several columns and one; classes as skewed as one-hot targets get; kernel values kept for all sweeps, whose sums are all fp64, and formed by
+# every sweep of the K-loop engine (the images that the values are formed from do not fit the cap).  If every entry of K^T w is rounded to fp32
+# the coefficients move by E (measured here).  The engine adds the terms of an entry in fp32 sums of 8 and those in fp64: n terms of
 # size m give an rms error of m eps sqrt(n 8^2 / 3) against an entry of n m, eps that of one rounding, i.e. sqrt(64 / (3 n)) of a rounding of
 # the entry, and so of E.  Sums of 64 terms would give sqrt(64^2 / (3 n)), eight times as much; the bound is 2.5 times the first.  The
 # kernel values' own rounding (a few 1e-7 of random sign, averaged over the n rows) moves the coefficients by some 1e-4 times more.
-@pytest.mark.parametrize("cross,t", [("f16x3", 10), ("f16x3", 1), ("f32", 3)])
-def test_coefficients_against_the_same_iterations_in_64_bits(knm, cross, t):
+@pytest.mark.parametrize("cross,t,kept", [("f16x3", 10, True), ("f16x3", 1, True), ("f32", 3, True), ("f16x3", 10, False), ("f16x3", 1, False)])
+def test_coefficients_against_the_same_iterations_in_64_bits(knm, cross, t, kept):
     n, d, M = 20000, 784, 2000
     g = torch.Generator(device="cuda").manual_seed(5)
     X = _image_rows(n, d, g)
@@ -71,11 +72,14 @@ def test_coefficients_against_the_same_iterations_in_64_bits(knm, cross, t):
     Y = torch.nn.functional.one_hot(torch.multinomial(share, n, replacement=True, generator=g), 10).float()[:, :t].contiguous()
     ctx = knm.Context()
     ctx.set_cross_term(cross)
+    if not kept:
+        ctx.set_pack_limit(16 << 20)
     alpha = knm.falkon_fit(X, Y, C, sigma, LAMBDA, ITERS, JITTER, ctx=ctx)
+    assert (ctx.workspace_held() > 4 * n * M) == kept, ctx.workspace_held()  # the block of the values stays with the context
     exact = _fit64(X, Y, C, sigma)
     rounded = float((_fit64(X, Y, C, sigma, round_u=True) - exact).norm() / exact.norm())
     error = float((alpha.double() - exact).norm() / exact.norm())
-    print(f"\n  {cross}, t = {t}: K^T w rounded to fp32 moves the coefficients by {rounded:.2e}, the fit is {error:.2e} off")
+    print(f"\n  {cross}, t = {t}, {'kept' if kept else 'formed'}: K^T w rounded to fp32 moves the coefficients by {rounded:.2e}, the fit is {error:.2e} off")
     assert error < 2.5 * math.sqrt(64.0 / (3.0 * n)) * rounded + 1e-3
 
 
