@@ -92,7 +92,7 @@ def test_products_match_oracle(knm, cross, n, M, d, t, sigma):
     assert rel_l2(U.cpu().numpy(), Uo) < TIGHT
     assert rel_l2(W2.cpu().numpy(), Wo) < TIGHT
     # element by element as well: no single output may hide behind the norm of the others
-    for got, ref in ((W, oracle.knm_v(Xn, Cn, sigma, V.numpy())), (R, oracle.knm_t_y(Xn, Cn, sigma, Y.numpy())),
+    for got, ref in ((W, oracle.knm_v(Xn, Cn, sigma, V.numpy())), (W2.cpu().numpy(), Wo), (R, oracle.knm_t_y(Xn, Cn, sigma, Y.numpy())),
                      (U.cpu().numpy(), Uo)):
         ref = np.asarray(ref).reshape(got.shape)
         assert np.max(np.abs(got - ref)) < TOL * np.max(np.abs(ref))
@@ -101,6 +101,16 @@ def test_products_match_oracle(knm, cross, n, M, d, t, sigma):
     # without the W output the library uses its own workspace: same result bit for bit
     U2 = knm.knm_prod(Xd, Cd, sigma, Vd)
     assert torch.equal(U2, U)
+
+
+# W by knm_v, which takes calls as small as these in one launch from differences, and by the row sweep of a product, which is the engines'
+BY = pytest.mark.parametrize("by", ["knm_v", "knm_prod"])
+
+
+def _row_sums(knm, by, X, C, sigma, V):
+    if by == "knm_v":
+        return knm.knm_v(X.cuda(), C.cuda(), sigma, V.cuda()).cpu().numpy()
+    return knm.knm_prod(X.cuda(), C.cuda(), sigma, V.cuda(), return_w=True)[1].cpu().numpy()
 
 
 @pytest.mark.parametrize("kind", ["ones", "unit"])
@@ -112,7 +122,8 @@ def test_special_vectors(knm, cross, kind):
     assert rel_l2(U, oracle.knm_prod(X.numpy(), C.numpy(), sigma, v.numpy())) < TIGHT
 
 
-def test_columns_of_very_different_scale(knm):
+@BY
+def test_columns_of_very_different_scale(knm, by):
     """Matrix-core reduction: every vector column is scaled by its own power of two into the fp16
     range, so columns of magnitude 1e-6 and 1e5, an all-zero column and a column dominated by one
     entry must each keep the product accuracy."""
@@ -125,7 +136,7 @@ def test_columns_of_very_different_scale(knm):
     V[:, 5] = 1.0
     V[:, 6] *= 1e-30           # near the bottom of the fp32 range
     knm.default_context().set_cross_term("f16x3")
-    W = knm.knm_v(X.cuda(), C.cuda(), sigma, V.cuda()).cpu().numpy()
+    W = _row_sums(knm, by, X, C, sigma, V)
     Wo = oracle.knm_v(X.numpy(), C.numpy(), sigma, V.numpy())
     assert np.array_equal(W[:, 3], np.zeros(n, dtype=np.float32))
     for c in range(t):
@@ -177,7 +188,8 @@ def test_strided_unaligned_points_on_the_k_loop_engine(knm, cross, d, t):
     assert rel_l2(U.cpu().numpy(), ref) < TIGHT
 
 
-def test_degenerate_sizes(knm, cross):
+@BY
+def test_degenerate_sizes(knm, cross, by):
     sigma = 1.0
     X, C = _rand(1, 3, 14), _rand(1, 3, 15)
     v = torch.tensor([[2.0]])
@@ -186,18 +198,18 @@ def test_degenerate_sizes(knm, cross):
     assert U.ravel()[0] == pytest.approx(2.0 * k * k, rel=1e-5)
     # identical points: kernel exactly 1 on the diagonal, never above
     P = _rand(200, 28, 16, scale=3.0).cuda()
-    W = knm.knm_v(P, P, 0.5, torch.ones(200, 1).cuda())  # small sigma: off-diagonal underflows to 0
-    Wn = W.cpu().numpy()
+    Wn = _row_sums(knm, by, P, P, 0.5, torch.ones(200, 1))  # small sigma: off-diagonal underflows to 0
     assert np.all(np.isfinite(Wn)) and Wn.max() <= 1.0 and Wn.min() >= 0.0
     assert np.allclose(Wn, 1.0, atol=2e-3)
     # far-apart points: exact zeros, no NaN / Inf
     far = torch.zeros(64, 4)
     far[:, 0] = 1.0e4
-    W = knm.knm_v(far.cuda(), torch.zeros(64, 4).cuda(), 1.0, torch.ones(64, 1).cuda()).cpu().numpy()
+    W = _row_sums(knm, by, far, torch.zeros(64, 4), 1.0, torch.ones(64, 1))
     assert np.array_equal(W, np.zeros_like(W))
 
 
-def test_large_norm_close_pairs(knm, cross):
+@BY
+def test_large_norm_close_pairs(knm, cross, by):
     """Data far from the origin (|x|^2 ~ 1000 sigma^2) with small mutual distances: the norm expansion
     alone would keep only ~1e-4 of the exponent; the engines expand around the centres' mean, so the
     accuracy is that of centred data.  A second case moves single points far away from that mean."""
@@ -205,7 +217,7 @@ def test_large_norm_close_pairs(knm, cross):
     X = 11.0 + 0.5 * _rand(n, d, 18)
     C = 11.0 + 0.5 * _rand(M, d, 19)
     V = torch.ones(M, 1)
-    W = knm.knm_v(X.cuda(), C.cuda(), sigma, V.cuda()).cpu().numpy()
+    W = _row_sums(knm, by, X, C, sigma, V)
     err = rel_l2(W, oracle.knm_v(X.numpy(), C.numpy(), sigma, V.numpy()))
     print(f"offset data: {err:.2e}", flush=True)
     assert err < TIGHT
@@ -214,7 +226,7 @@ def test_large_norm_close_pairs(knm, cross):
     # outliers in the data (not among the centres): their rows are far from everything, the rest is unaffected
     X2 = X.clone()
     X2[::97] += 40.0
-    W2 = knm.knm_v(X2.cuda(), C.cuda(), sigma, V.cuda()).cpu().numpy()
+    W2 = _row_sums(knm, by, X2, C, sigma, V)
     assert rel_l2(W2, oracle.knm_v(X2.numpy(), C.numpy(), sigma, V.numpy())) < TIGHT
 
 
@@ -237,7 +249,8 @@ def test_shift_of_rows_in_a_regular_order(knm, cross):
     assert errors[0] < 2.0 * errors[1]
 
 
-def test_split_half_range_limits(knm):
+@BY
+def test_split_half_range_limits(knm, by):
     """The split-fp16 cross term saturates instead of producing Inf/NaN, and huge norms
     (far outliers) still give exact zeros against ordinary points."""
     ctx = knm.default_context()
@@ -249,7 +262,7 @@ def test_split_half_range_limits(knm):
         X[11, 0] = 2.0e5      # beyond fp16: saturates
         C[5] = X[7]           # an outlier centre equal to an outlier row
         V = torch.ones(M, 1)
-        W = knm.knm_v(X.cuda(), C.cuda(), sigma, V.cuda()).cpu().numpy()
+        W = _row_sums(knm, by, X, C, sigma, V)
         Wo = oracle.knm_v(X.numpy(), C.numpy(), sigma, V.numpy())
         assert np.all(np.isfinite(W))
         keep = np.ones(n, dtype=bool)
@@ -263,7 +276,7 @@ def test_split_half_range_limits(knm):
         assert ctx.range_exceeded() >= 1
         assert ctx.range_exceeded() == 0  # the query resets the count
         X[11, 0] = 1.0
-        knm.knm_v(X.cuda(), C.cuda(), sigma, V.cuda())
+        _row_sums(knm, by, X, C, sigma, V)
         assert ctx.range_exceeded() == 0
     finally:
         ctx.set_cross_term("f16x3")
@@ -406,8 +419,9 @@ def test_workspace_held_stays_within_the_announced_bound(knm, n, M, d, t):
             ctx.close()
 
 
+@BY
 @pytest.mark.parametrize("t", [9, 20])
-def test_matrix_core_reduction_keeps_small_kernel_values(knm, t):
+def test_matrix_core_reduction_keeps_small_kernel_values(knm, t, by):
     """Data and centres in two clusters far apart: the kernel values lie around and below fp16's
     normal range (6e-5), most of them by orders of magnitude.  With 8 or more columns the kernel values go through
     fp16 halves, which must still resolve them relative to themselves."""
@@ -417,6 +431,6 @@ def test_matrix_core_reduction_keeps_small_kernel_values(knm, t):
     for sigma in (3.1, 2.7):  # kernel values up to 5e-4 and up to 5e-5 (median 1e-7 and 1e-9)
         assert oracle.kernel_matrix(X.numpy(), C.numpy(), sigma).max() < 1e-3
         Wo = oracle.knm_v(X.numpy(), C.numpy(), sigma, V.numpy())
-        W = knm.knm_v(X.cuda(), C.cuda(), sigma, V.cuda()).cpu().numpy()
+        W = _row_sums(knm, by, X, C, sigma, V)
         print(f"sigma {sigma}: |W| {np.linalg.norm(Wo):.2e} error {rel_l2(W, Wo):.2e}", flush=True)
         assert rel_l2(W, Wo) < TOL

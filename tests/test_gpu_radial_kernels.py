@@ -100,7 +100,9 @@ def test_radial_weighted_product(knm, lap):
     assert rel_l2(U, oracle.knm_prod_weighted(X.numpy(), C.numpy(), sigma, dw.numpy(), V.numpy())) < TOL
 
 
-def test_radial_large_norms_and_near_duplicates(knm, lap):
+# (knm_v takes a call as small as this in one launch from differences; the row sweep of a product is the engines')
+@pytest.mark.parametrize("by", ["knm_v", "knm_prod"])
+def test_radial_large_norms_and_near_duplicates(knm, lap, by):
     """Points far from the origin (the norm expansion cancels seven digits), centres that are data
     rows, and centres that are data rows moved by 1e-3: the pairs below the refinement threshold
     are taken from differences, the others keep the accuracy of the expansion (the bar of the
@@ -110,7 +112,10 @@ def test_radial_large_norms_and_near_duplicates(knm, lap):
     C = _centres(X, M, 19)
     C[::2] += 1e-3 * _rand(M // 2, d, 20)
     V = torch.ones(M, 1)
-    W = knm.knm_v(X.cuda(), C.cuda(), sigma, V.cuda()).cpu().numpy()
+    if by == "knm_v":
+        W = knm.knm_v(X.cuda(), C.cuda(), sigma, V.cuda()).cpu().numpy()
+    else:
+        W = knm.knm_prod(X.cuda(), C.cuda(), sigma, V.cuda(), return_w=True)[1].cpu().numpy()
     Wo = oracle.knm_v(X.numpy(), C.numpy(), sigma, V.numpy())
     err = rel_l2(W, Wo)
     print(f"large norms: {err:.2e}", flush=True)
