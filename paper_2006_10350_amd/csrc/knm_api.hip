@@ -1116,7 +1116,7 @@ size_t knm_workspace_bytes(int64_t n, int64_t M, int d, int t)
     // differently): chunk partials, and the packed operands of the split-fp16 modes
     size_t part = 0, pack = 0, vimg = 0, keep = 0;
     const int64_t sets[2] = {n, M};
-    if (direct_pays(n, M, d, t, true)) part = sizeof(double) * (size_t)direct_chunks(n, M, t) * n * t; // of a small K V
+    if (direct_pays(n, M, d, t, true, KNM_CROSS_F16X3) || direct_pays(n, M, d, t, true, KNM_CROSS_F32)) part = sizeof(double) * (size_t)direct_chunks(n, M, t) * n * t; // of a small K V
     for (int mode = 0; mode < 4; ++mode) {
         const int cross = mode & 1, kind = mode >> 1;
         const int64_t c1 = choose_chunks(n, M, d, t, cross, kind, &len);
@@ -1216,7 +1216,7 @@ int knm_v(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx, const flo
     if (st) return st;
     if (!V || !W) return fail(ctx, KNM_INVALID_ARG, "null vector");
     begin_timing(ctx);
-    if (direct_takes(sigma) && direct_pays(n, M, d, t, direct_wide(C, ldc, d))) st = small_knm_v(ctx, X, n, d, ldx, C, M, ldc, sigma, V, t, W);
+    if (direct_takes(sigma) && direct_pays(n, M, d, t, direct_wide(C, ldc, d), ctx->cross_term)) st = small_knm_v(ctx, X, n, d, ldx, C, M, ldc, sigma, V, t, W);
     else st = do_knm_v(ctx, X, n, d, ldx, C, M, ldc, sigma, V, t, W);
     mark(ctx, 1);
     mark(ctx, 4);

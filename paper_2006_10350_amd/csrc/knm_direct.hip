@@ -190,17 +190,30 @@ int direct_chunks(int64_t n, int64_t M, int t)
     return (int)((M + len - 1) / len);
 }
 
-// Where this launch (and the merge of a split row) takes less time than the four or more of the engines.  Estimates in us, fitted at d = 4
-// to 128, n = 1 to 20000, M = 300 to 50000: here 5 + 0.03 to 0.07 ps per value and operation (twice that where rows cannot be
-// read 16 bytes at a time, more where several columns leave fewer rows per workgroup), the engines 20 + 0.2 ps per value.  Measured, 1 column:
-// n = 200, M = 1000, d = 8 21.4 -> 9.1 (launches from Python, about 9 at least), n = 5000, M = 300, d = 17 25.8 -> 10.6, n = 1000, M =
-// 4000, d = 28 25.6 -> 20.3, beyond the line n = 1000, M = 4000, d = 44 27.4 -> 33.4.
-bool direct_pays(int64_t n, int64_t M, int d, int t, bool wide)
+// Where this launch (and the merge of a split row) takes less time than the four or more of the engines.  Estimates in us, fitted at d = 2
+// to 128, t = 1 to 16, n = 1 to 1000000, M = 1 to 50000, four kernels and both cross terms (1625 shapes).  What the differences of the values
+// take: 5 + 0.03 to 0.07 ps per value and operation (twice that where rows cannot be read 16 bytes at a time, more where several columns leave
+// fewer rows per workgroup), the engines 20 + 0.2 ps per value.  What a workgroup takes, however few its centres are: one pass after
+// the other over 256 of them, each a chain of loads, and 1 ns per group of rows with 1 column, 3.6 from 3 on, for the sums over its threads (16
+// sums of 6 steps through LDS).  The engines: 28 and more with 8 columns (the column maxima, and one workgroup per 128 rows of few), in the
+// fp32 mode more with many features.  Measured from Python (9 us at least), engines and this launch: n = 200, M = 1000, d = 8, 1 column 21.4
+// and 9.1, n = 1000, M = 4000, d = 28 25.6 and 20.3, n = 20000, M = 1000, d = 8 25.1 and 16.8, n = 5000, M = 300, d = 8, 8 columns 31.9
+// and 19.3; beyond the line n = 1000, M = 4000, d = 44 27.4 and 33.4, n = 20000, M = 300, d = 8, 3 columns 22.3 and 27.6, n = 100000, M = 100, d =
+// 8 22.3 and 34.7, n = 1000000, M = 1, d = 8 82.5 and 315, with 16 columns 142 and 4290.
+bool direct_pays(int64_t n, int64_t M, int d, int t, bool wide, int cross_term)
 {
     if (d > kMaxD || t > 16 || n > 1000000 || M > 1000000) return false;
     const double values = 1.0e-6 * (double)n * (double)M, ops = 2.0 * d + 8.0 + 2.0 * t;
     const double ps = (0.03 + 0.0003 * d) * (wide ? 1.0 : 2.0) * (t <= 2 ? 1.0 : t <= 4 ? 1.3 : t <= 8 ? 2.5 : 5.0);
-    return 5.0 + (direct_chunks(n, M, t) > 1 ? 4.0 : 0.0) + values * ops * ps < 0.95 * (20.0 + 0.2 * values);
+    const int chunks = direct_chunks(n, M, t), sums = rows(t) * columns(t), quads = (d + 3) / 4;
+    const double least = 5.0 + (chunks > 1 ? 4.0 : 0.0);
+    const double groups = (double)((n + rows(t) - 1) / rows(t)) * (double)chunks;
+    const double passes = (double)(((M + chunks - 1) / chunks + kThreads - 1) / kThreads);
+    const double pass = (columns(t) > 4 ? 0.05 * (columns(t) - 4) : 0.0) +
+                        (sums <= 4 ? 0.02 : sums <= 8 ? 0.13 : 0.15) * (t > 4 ? 0.5 : 1.0) * (wide ? 1.0 : 3.0) * quads;
+    const double workgroups = passes * pass + 1.0e-3 * groups * (0.2 + 0.21 * sums + 0.005 * quads) + (columns(t) == 16 ? 8.0 * values : 0.0);
+    const double engines = cross_term != KNM_CROSS_F16X3 ? 20.0 + 0.12 * d : t >= 8 ? 28.0 + 0.011 * (double)(M < 4000 ? M : 4000) : 20.0;
+    return least + values * ops * ps < 0.95 * (20.0 + 0.2 * values) && least + workgroups < 0.95 * (engines + 0.2 * values);
 }
 // (squares of differences and of sigma have to stay within fp32; the engines scale before they square)
 bool direct_takes(float sigma) { return sigma >= 1.0e-15f && sigma <= 1.0e15f; }

@@ -241,7 +241,7 @@ hipError_t launch_merge(const float *part, const double *part64, int64_t n_chunk
 // is in partials of n x t each, to be merged
 bool direct_takes(float sigma); // of the caller
 bool direct_wide(const float *C, int64_t ldc, int d); // rows of C can be read 16 bytes at a time
-bool direct_pays(int64_t n, int64_t M, int d, int t, bool wide);
+bool direct_pays(int64_t n, int64_t M, int d, int t, bool wide, int cross_term);
 int direct_chunks(int64_t n, int64_t M, int t);
 hipError_t launch_direct(const float *X, int64_t n, int64_t ldx, const float *C, int64_t M, int64_t ldc, int d, float sigma, int kind,
                          const float *V, int t, float *out, double *part, unsigned int *range_count, float inv2s2, hipStream_t stream);

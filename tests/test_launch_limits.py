@@ -61,3 +61,30 @@ def test_products_of_many_outputs(shims, n, d, M, t):
         """
     r = subprocess.run([sys.executable, "-c", textwrap.dedent(body)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+# A small prediction is one launch (two where its rows are split), but not one of hundreds of thousands of workgroups with next to nothing
+# to do each: few centres or many columns against many rows, which took up to 30 times as long as the engines
+@pytest.mark.parametrize("n,M,d,t,cross,launches", [(200, 1000, 8, 1, 1, 1), (1, 50_001, 5, 1, 1, 2), (20_000, 1000, 8, 1, 1, 1), (5000, 300, 8, 8, 1, 1),
+                                                    (20_000, 10, 8, 1, 0, 1), (100_000, 100, 8, 1, 1, None), (20_000, 300, 8, 3, 1, None),
+                                                    (60_000, 30, 12, 5, 1, None), (10_000, 20, 4, 16, 0, None), (1_000_000, 1, 8, 16, 1, None),
+                                                    (1_000_000, 10, 2, 3, 1, None), (1_000_000, 1, 2, 1, 0, None)])
+def test_small_predictions_have_few_workgroups(shims, n, M, d, t, cross, launches):
+    body = f"""
+        import ctypes as c
+        check, hip = (c.CDLL(s, mode=c.RTLD_GLOBAL) for s in {shims!r})
+        lib = c.CDLL({LIB!r})
+        P, L, I, F = c.c_void_p, c.c_int64, c.c_int, c.c_float
+        lib.knm_v.argtypes = [P, P, L, I, L, P, L, L, F, P, I, P]
+        lib.knm_set_cross_term.argtypes = [P, I]
+        check.checked_launches.restype = c.c_long
+        ctx = P()
+        assert lib.knm_create(c.byref(ctx), 0, None) == 0 and lib.knm_set_cross_term(ctx, {cross}) == 0
+        x, cen, v, u = (P(0x7f0000000000 + (i << 40)) for i in range(4))  # never read: kernels do not run
+        before = check.checked_launches()
+        assert lib.knm_v(ctx, x, {n}, {d}, {d}, cen, {M}, {d}, 1.0, v, {t}, u) == 0
+        count = check.checked_launches() - before
+        assert count == {launches} if {launches} else count > 1, count  # (shift and sweep at least; no rows are split here)
+        """
+    r = subprocess.run([sys.executable, "-c", textwrap.dedent(body)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
