@@ -427,6 +427,10 @@ __global__ void scale_kernel(const float *__restrict__ e, const float *__restric
     if (r < rows) out[r * ldo] = e[r] * x[r * ldx];
 }
 
+// The number of pairs is added up in several words, a cache line each: one atomic per wavefront on a single word made the work list of
+// 17223 rows of 13 entries 103 us, 7 without
+constexpr int kTotals = 15, kTotalStride = 16;
+
 // Work list of X (see SparseArgs): one wavefront per row looks every entry's feature up in the
 // centre lists once, so that the sweeps stream (start, length, value) instead of reading the
 // list pointers at random for every entry, pass and sweep; entries whose feature occurs in no
@@ -442,12 +446,13 @@ __global__ __launch_bounds__(kSpThreads) void build_work_kernel(const int64_t *_
                                                                int *__restrict__ work_q0, int *__restrict__ work_len,
                                                                float *__restrict__ work_val, float *__restrict__ XH,
                                                                int64_t M, int *__restrict__ pair_cap,
-                                                               unsigned long long *__restrict__ pair_total)
+                                                               unsigned long long *__restrict__ pair_totals)
 {
     const int lane = threadIdx.x & 63;
     const int64_t wave = (int64_t)blockIdx.x * kSpWaves + (threadIdx.x >> 6);
     const int64_t waves = (int64_t)gridDim.x * kSpWaves;
     __shared__ int heads_of[kMaxHead];
+    __shared__ unsigned long long totals[kSpWaves];
     if ((int)threadIdx.x < Hn) heads_of[threadIdx.x] = head_feat[threadIdx.x];
     __syncthreads();
     const unsigned long long below = (1ull << lane) - 1ull;
@@ -538,7 +543,14 @@ __global__ __launch_bounds__(kSpThreads) void build_work_kernel(const int64_t *_
         }
         total += (unsigned long long)(pairs < M ? pairs : M);
     }
-    if (lane == 0 && total > 0) atomicAdd(pair_total, total);
+    if (pair_totals == nullptr) return; // (the same for all)
+    if (lane == 0) totals[threadIdx.x >> 6] = total;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        total = 0;
+        for (int w = 0; w < kSpWaves; ++w) total += totals[w];
+        if (total > 0) atomicAdd(pair_totals + blockIdx.x % kTotals * kTotalStride, total);
+    }
 }
 
 // A pair of points that share a tail feature: the centre and K_ij - KH_ij
@@ -1200,21 +1212,22 @@ int SparseProducts::prepare(knm_ctx *ctx, const int64_t *x_indptr, const int64_t
         (void)hipGetLastError();
         return fail(ctx, KNM_ALLOC, "hipMalloc(sparse work list)");
     }
-    // two words of the partial sums' room: largest head norm term, number of pairs
+    // in the partial sums' room: largest head norm term, and from the next cache line on the number of pairs
+    unsigned long long words[(1 + kTotals) * kTotalStride] = {};
+    static_assert(sizeof(words) <= sizeof(double) * 256, "room of the partial sums");
     unsigned *const worst_dev = s.part.as<unsigned>();
-    unsigned long long *const total_dev = s.part.as<unsigned long long>() + 1;
-    unsigned long long words[2] = {0, 0};
+    unsigned long long *const totals_dev = uses > 1 ? s.part.as<unsigned long long>() + kTotalStride : nullptr;
     auto read_words = [&]() -> int {
         hipError_t e = hipMemcpyAsync(words, s.part.p, sizeof(words), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         return e == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "sparse work list", e);
     };
     auto build_work = [&]() {
-        if (hipMemsetAsync(s.part.p, 0, 2 * sizeof(unsigned long long), st) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipMemsetAsync");
+        if (hipMemsetAsync(s.part.p, 0, sizeof(words), st) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipMemsetAsync");
         hipLaunchKernelGGL(build_work_kernel, dim3((unsigned)s.wgs), dim3(kSpThreads), 0, st, x_indptr, x_indices, x_values, n,
                            s.lists.words.as<FeatureWord>(), s.lists.col_ptr.as<int>(), s.head_feat.as<int>(), s.Hn, head_min_len, s.work_count.as<int>(),
                            s.work_pairs.as<int>(), s.head_count.as<int>(), s.work_q0.as<int>(), s.work_len.as<int>(),
-                           s.work_val.as<float>(), s.XH.as<float>(), M, s.pair_off.as<int>(), total_dev);
+                           s.work_val.as<float>(), s.XH.as<float>(), M, s.pair_off.as<int>(), totals_dev);
         return hipGetLastError() == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "work list launch");
     };
     stat = build_work();
@@ -1245,7 +1258,9 @@ int SparseProducts::prepare(knm_ctx *ctx, const int64_t *x_indptr, const int64_t
     if (s.Hn > 0)
         s.share.reset(new (std::nothrow) SweepShare(ctx, s.XH.as<float>(), n, s.Hn, s.CH.as<float>(), M, s.Hn, s.Hn, sigma, 1, true));
     if (s.Hn > 0 && !s.share) return fail(ctx, KNM_ALLOC, "host allocation");
-    return uses > 1 ? s.form_pairs(words[1]) : KNM_OK;
+    unsigned long long total = 0;
+    for (int k = 1; k <= kTotals; ++k) total += words[k * kTotalStride];
+    return uses > 1 ? s.form_pairs(total) : KNM_OK;
 }
 
 // W (n x t, row-major) = K V
