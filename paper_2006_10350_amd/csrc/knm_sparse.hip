@@ -44,10 +44,19 @@ namespace {
 constexpr int kSpThreads = 256;
 constexpr int kSpWaves = kSpThreads / 64;
 constexpr int kScanChunk = 4096;  // elements per workgroup of the prefix sum
-// Rows of C per launch that takes the places in the lists: 64 entries of a list shorter than the head's span more rows than that.
-// 20000 centres of 100 entries: 0.27 ms with 1024 rows, 0.17 with 4096; the walks take the same time up to d = 4e5, and within the
-// 2 % that runs differ by at d = 2e4, where every row walks 100k updates in device memory
-constexpr int64_t kFillGroup = 4096;
+// Rows of C per launch that takes the places in the lists: no more than 64 entries of an average list span, which update neighbouring
+// accumulators then, between 512 and 4096.  20000 centres of 100 entries: 0.27 ms with 1024 rows, 0.17 with 4096; the walks take the same time up to d
+// = 4e5, and within the 2 % that runs differ by at d = 2e4.  With long lists
+// walks wait for their accumulators in device memory: values of 31015 rows against 5612 centres, 40 of 321 features each, 40.9 ms with 4096 rows, 34.9
+// with 1024, 30.1 with 512; 20000 x 20000, 100 of 1000 features, 298, 248 and 217
+constexpr int64_t kFillLeast = 512;
+inline int64_t fill_group(int64_t M, int64_t d, int64_t nnz_c)
+{
+    const double span = 64.0 * (double)M * (double)d / (double)(nnz_c > 0 ? nnz_c : 1);
+    int64_t rows = 4096;
+    while (rows > kFillLeast && (double)rows > span) rows /= 2;
+    return rows;
+}
 constexpr int kHashBits = 9;        // slots (2^9) of a wavefront's accumulator table in LDS
 constexpr int kHashSlots = 1 << kHashBits;
 constexpr int kHashMaxPairs = 320; // a row with at most this many pair updates uses the table (load <= 5/8)
@@ -968,8 +977,9 @@ struct CentreLists {
             hipLaunchKernelGGL(word_bases_kernel, grid_for(n_words), dim3(256), 0, st, counts.as<int>(), sums.as<int>(), n_words,
                                words.as<FeatureWord>());
         }
-        for (int64_t r0 = 0; r0 < M && nnz_c > 0; r0 += kFillGroup) {
-            const int64_t r1 = (r0 + kFillGroup < M) ? r0 + kFillGroup : M;
+        const int64_t group = fill_group(M, d, nnz_c);
+        for (int64_t r0 = 0; r0 < M && nnz_c > 0; r0 += group) {
+            const int64_t r1 = (r0 + group < M) ? r0 + group : M;
             hipLaunchKernelGGL(centre_entries_kernel, dim3((unsigned)((r1 - r0 + 3) / 4)), dim3(256), 0, st, c_indptr, c_indices, r0, r1,
                                words.as<FeatureWord>(), number.as<int>(), row.as<int>(), place.as<int>(), col_ptr.as<int>());
         }
