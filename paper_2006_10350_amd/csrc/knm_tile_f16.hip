@@ -450,12 +450,16 @@ __global__ __launch_bounds__(kThreads, 2) void gauss_sweep_f16_kernel(SweepArgs 
             if (m != 0) {
                 b = __builtin_ctz(m);
                 m &= m - 1;
-                float x = 0.0f; // the exponent that was used
+                float x[16]; // x[0]: the exponent that was used, of 32 by the bits of b
 #pragma unroll
-                for (int k = 0; k < 32; ++k) x = b == k ? acc[k >> 4][k & 15] : x;
+                for (int k = 0; k < 16; ++k) x[k] = (b & 16) != 0 ? acc[1][k] : acc[0][k];
+#pragma unroll
+                for (int bit = 8; bit > 0; bit >>= 1)
+#pragma unroll
+                    for (int k = 0; k < bit; ++k) x[k] = (b & bit) != 0 ? x[k + bit] : x[k];
                 const int64_t fi = fixed0 + (b >> 4) * 32 + 8 * ((b & 15) >> 2) + 4 * h + (b & 3);
                 if (fi < a.nF)
-                    term = (radial_from_exponent<KIND>(exact_exponent(a.F + fi * a.ldf, srow, d, s2)) - radial_from_exponent<KIND>(x)) * vl_t;
+                    term = (radial_from_exponent<KIND>(exact_exponent(a.F + fi * a.ldf, srow, d, s2)) - radial_from_exponent<KIND>(x[0])) * vl_t;
             }
 #pragma unroll
             for (int k = 0; k < 32; ++k) sum[k >> 4][k & 15] += (b == k) ? term : 0.0f;
