@@ -125,7 +125,8 @@ __device__ __forceinline__ void mfma_step(f32x16 &acc, const f16x8 &a, const f16
 // square root) the caller evaluates such entries again from differences and adds what the two values differ by.  A square root, an
 // exponential, a multiply-add and half a minimum take 38 cycles of issue per 64 values; with a comparison and a selection per
 // entry, which left the near pairs out, it was 44 (n = 1M, d = 17, M = 20k: 11.1 ms per product, 8.35 now;
-// integer-valued features, where every third tile has such a pair: d = 4 11.5 and 8.3, Matern 5/2 21.9 and 21.1).
+// integer-valued features, where every third tile has such a pair: d = 4 11.5 and 8.3, Matern 5/2 21.9 and 21.1).  Where most rows coincide the
+// corrections make it slower: 23541 x 2824, d = 6, four fifths zeros, Matern 3/2 648 us and 743.
 // Every instruction is its own volatile statement, in program order; a transcendental
 // result is never read by the instruction right after it.
 struct RadialConsts {
