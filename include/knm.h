@@ -287,8 +287,12 @@ int falkon_predict(knm_ctx *ctx, const float *Xtest, int64_t ntest, int d, int64
  *                   magnitude and squared norms of scaled points beyond 2^22 saturate.  Uses a
  *                   library-owned workspace for the converted operands: at most 2 GiB for
  *                   d <= 44 with t = 1, at most 8 GiB otherwise.
- *   KNM_CROSS_F32   fp32 MFMA on the unsplit features: no range limits, 3 to 5 times slower
- *                   (fp32 MFMA and the exp/FMA work share the vector ALU's issue). */
+ *   KNM_CROSS_F32   fp32 products: no range limits.  fp32 MFMA on the unsplit features, 3 to 5 times
+ *                   slower (fp32 MFMA and the exp/FMA work share the vector ALU's issue); large
+ *                   products of the Gaussian kernel with one column and up to 16 features form them
+ *                   exactly from three bf16 parts per feature on the bf16 matrix cores, at half of the
+ *                   fp32 MFMA's error and 1.2 to 1.5 times the time of the split-fp16 ones, with a
+ *                   workspace as above. */
 typedef enum { KNM_CROSS_F32 = 0, KNM_CROSS_F16X3 = 1 } knm_cross_term;
 int knm_set_cross_term(knm_ctx *ctx, int mode);
 int knm_get_cross_term(const knm_ctx *ctx); /* the mode now selected, or KNM_INVALID_ARG */
@@ -325,7 +329,7 @@ int knm_set_kernel(knm_ctx *ctx, int kind);
 int knm_set_sparse_head_limit(knm_ctx *ctx, int max_features);
 
 /* Cap, in bytes, on the library-owned workspace that holds the converted operands of the
- * split-fp16 engines (0 restores the defaults: 2 GiB, or 8 GiB for the K-loop engine).  Operands
+ * split-fp16 engines, and of the fp32 mode where it has any (0 restores the defaults: 2 GiB, or 8 GiB for the K-loop engine).  Operands
  * that do not fit are converted and swept slab by slab; results do not depend on the cap.  The
  * workspace never shrinks below what one slab needs (one stream chunk, plus the whole smaller
  * operand for the K-loop engine). */

@@ -295,6 +295,19 @@ bool use_gemm_engine(int d, int t, int cross_term, int kind)
     return t > 1 || d > (cross_term == KNM_CROSS_F16X3 ? f16_max_d() : small_max_d());
 }
 
+// Sweeps whose operands are packed into images first, and the bytes of a point there: the split-fp16 engines, and in the fp32 mode the
+// register-resident engine that has fp32 numbers in three bf16 parts, where it gains more than that costs.
+static bool packs_images(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind)
+{
+    if (cross_term == KNM_CROSS_F16X3) return true;
+    return !use_gemm_engine(d, t, cross_term, kind) && b16_pays((double)nF * (double)nS, d);
+}
+static size_t image_bytes_per_point(int d, int t, int cross_term, int kind)
+{
+    if (cross_term != KNM_CROSS_F16X3) return b16_pack_bytes_per_point(d);
+    return use_gemm_engine(d, t, cross_term, kind) ? gemm_f16_pack_bytes_per_point(d) : f16_pack_bytes_per_point(d);
+}
+
 // Chunking of the stream dimension.  More chunks = more workgroups and shorter fp32 running sums; each chunk costs one partial
 // vector that the merge pass adds up in fp64.
 struct ChunkGrid {
@@ -369,7 +382,10 @@ static int64_t choose_chunks_by_time(int64_t nF, int64_t nS, int d, int t, int c
         uneven = 0.4;
     } else {
         if (f16) per_cu = f16_workgroups_per_cu(d, kind);
-        const double ps = (f16 ? (d <= 12 ? 0.106 : d <= 28 ? 0.167 : 0.22) : 0.12 + 0.019 * d) * (kind == KNM_KERNEL_GAUSSIAN ? 1.0 : 1.6);
+        const bool parts = !f16 && packs_images(nF, nS, d, t, cross_term, kind);
+        if (parts) per_cu = b16_workgroups_per_cu(d);
+        const double ps = (f16 ? (d <= 12 ? 0.106 : d <= 28 ? 0.167 : 0.22) : parts ? 0.085 + 0.0075 * d : 0.12 + 0.019 * d) *
+                          (kind == KNM_KERNEL_GAUSSIAN ? 1.0 : 1.6);
         stage_us = 1.0e-6 * ps * (double)(g.stage * g.per_block) * 256.0 * per_cu;
     }
     const double slots = 256.0 * per_cu;
@@ -582,10 +598,10 @@ static int share_images(knm_ctx *ctx, SweepShare *sh)
     sh->decided = true;
     sh->cross_term = ctx->cross_term;
     sh->kind = ctx->kernel_kind;
-    if (ctx->cross_term != KNM_CROSS_F16X3 || ctx->static_mode) return KNM_OK;
+    if (!packs_images(sh->n[0], sh->n[1], sh->d, sh->t, ctx->cross_term, ctx->kernel_kind) || ctx->static_mode) return KNM_OK;
     const bool gemm = use_gemm_engine(sh->d, sh->t, ctx->cross_term, ctx->kernel_kind);
-    if (!gemm && (!sh->pooled || sh->d > f16_max_d())) return KNM_OK;
-    const size_t pp = gemm ? gemm_f16_pack_bytes_per_point(sh->d) : f16_pack_bytes_per_point(sh->d);
+    if (!gemm && !sh->pooled) return KNM_OK;
+    const size_t pp = image_bytes_per_point(sh->d, sh->t, ctx->cross_term, ctx->kernel_kind);
     const int64_t r0 = share_rows(sh->n, 0, sh->d, sh->t, ctx->cross_term, ctx->kernel_kind);
     const int64_t r1 = share_rows(sh->n, 1, sh->d, sh->t, ctx->cross_term, ctx->kernel_kind);
     if (pp * (size_t)(r0 + r1) > (ctx->pack_limit ? ctx->pack_limit : kShareCap)) return KNM_OK;
@@ -771,12 +787,11 @@ static int kept_partials(knm_ctx *ctx, const float *keep, int64_t nF, int64_t nS
     return e == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, "launch_kept_sum", e);
 }
 
-// Bytes of the packed-operand workspace one sweep asks for in the split-fp16 modes (0 in the
-// fp32-MFMA mode): the same rule for the sweep itself and for knm_workspace_bytes.  `limit` = the
-// caller's cap, 0 for the defaults.
-static size_t pack_bytes_wanted(int64_t nF, int d, int t, int kind, size_t limit, int64_t chunks, int64_t chunk_len)
+// Bytes of the packed-operand workspace one sweep that packs images asks for: the same rule for the sweep itself and for
+// knm_workspace_bytes.  `limit` = the caller's cap, 0 for the defaults.
+static size_t pack_bytes_wanted(int64_t nF, int d, int t, int cross_term, int kind, size_t limit, int64_t chunks, int64_t chunk_len)
 {
-    if (use_gemm_engine(d, t, KNM_CROSS_F16X3, kind)) {
+    if (use_gemm_engine(d, t, cross_term, kind)) {
         // packed images of both operands: whole if they fit 8 GiB, else the smaller one
         // whole and the other in slabs
         const size_t per_point = gemm_f16_pack_bytes_per_point(d);
@@ -789,7 +804,7 @@ static size_t pack_bytes_wanted(int64_t nF, int d, int t, int kind, size_t limit
         return want;
     }
     // packed image of the stream points: all of it, or slabs of at most 2 GiB
-    const size_t per_point = f16_pack_bytes_per_point(d);
+    const size_t per_point = image_bytes_per_point(d, t, cross_term, kind);
     size_t want = per_point * (size_t)(chunks * chunk_len);
     const size_t cap = limit ? limit : (size_t)2 << 30;
     if (want > cap) want = (cap / (per_point * chunk_len) + 1) * per_point * chunk_len;
@@ -806,17 +821,27 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
     int64_t chunk_len = 0;
     int64_t chunks = choose_chunks(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
     if (ctx->static_mode) {
-        // where these partials and the least operand images do not fit the scratch together: fewer chunks
+        // where these partials and the least operand images do not fit the scratch together: fewer chunks; the fp32 engine takes
+        // the sweep where an image of three-part numbers does not fit whatever the chunks
+        bool image = packs_images(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind);
         auto fits = [&] {
-            const bool packs = ctx->cross_term == KNM_CROSS_F16X3;
-            const size_t least = !packs ? 0
-                                 : use_gemm_engine(d, t, ctx->cross_term, ctx->kernel_kind) ? gemm_f16_min_pack_bytes(nF, chunks * chunk_len, chunk_len, d)
-                                                                                           : f16_pack_bytes_per_point(d) * (size_t)chunk_len;
+            const size_t least = !image ? 0
+                                 : use_gemm_engine(d, t, ctx->cross_term, ctx->kernel_kind)
+                                     ? gemm_f16_min_pack_bytes(nF, chunks * chunk_len, chunk_len, d)
+                                     : image_bytes_per_point(d, t, ctx->cross_term, ctx->kernel_kind) * (size_t)chunk_len;
             return sizeof(float) * (size_t)chunks * nF * t + mu_bytes_wanted(kMeanSample, d) + least + 1024 <= kStaticScratchBytes;
         };
-        if (!fits()) chunks = choose_chunks_compact(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
-        if (!fits()) chunks = choose_chunks_by_time(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, true, &chunk_len);
-        if (!fits()) chunks = choose_chunks_compact(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len); // refused below
+        auto choose = [&] {
+            chunks = choose_chunks(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
+            if (!fits()) chunks = choose_chunks_compact(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
+            if (!fits()) chunks = choose_chunks_by_time(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, true, &chunk_len);
+            if (!fits()) chunks = choose_chunks_compact(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len); // refused below
+            return fits();
+        };
+        if (!choose() && image && ctx->cross_term != KNM_CROSS_F16X3) {
+            image = false;
+            (void)choose();
+        }
     }
     if (chunks > 65535) return fail(ctx, KNM_UNSUPPORTED, "too many stream chunks");
     const bool gemm = use_gemm_engine(d, t, ctx->cross_term, ctx->kernel_kind);
@@ -910,7 +935,7 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
         // packed operands of the split-fp16 engines: what the engine would like, or (static scratch)
         // as many whole slabs as the rest of the scratch holds; the same region serves every column group
         auto pack_room = [&](size_t *want) -> int {
-            *want = pack_bytes_wanted(nF, d, t, ctx->kernel_kind, ctx->pack_limit, chunks, chunk_len);
+            *want = pack_bytes_wanted(nF, d, t, ctx->cross_term, ctx->kernel_kind, ctx->pack_limit, chunks, chunk_len);
             if (!ctx->static_mode) return KNM_OK;
             const size_t at = (ctx->static_used + 255) & ~(size_t)255;
             const size_t room = at < kStaticScratchBytes ? kStaticScratchBytes - at : 0;
@@ -919,7 +944,7 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
                 if (*want > room) *want = room;
                 if (*want < least) *want = least; // acquire() then reports that it does not fit
             } else {
-                const size_t per_chunk = f16_pack_bytes_per_point(d) * (size_t)chunk_len;
+                const size_t per_chunk = image_bytes_per_point(d, t, ctx->cross_term, ctx->kernel_kind) * (size_t)chunk_len;
                 const size_t fit = room / per_chunk * per_chunk;
                 if (*want > fit) *want = fit > 0 ? fit : per_chunk;
             }
@@ -974,7 +999,17 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
             if (kept) use_images();
             e = launch_sweep_f16(a, pack, want, ctx->stream);
         } else {
-            e = launch_sweep(a, ctx->stream);
+            // the image of three-part numbers is for speed alone: where the card, or the scratch of a call that does not
+            // allocate, has no room for it the fp32 engine takes the rows as they are
+            bool parts = packs_images(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind);
+            size_t want = 0;
+            if (parts && !kept) {
+                int st = pack_room(&want);
+                if (st) return st;
+                parts = acquire(ctx, &ctx->pack_buf, &ctx->pack_bytes, want, &pack) == KNM_OK;
+            }
+            if (parts && kept) use_images();
+            e = parts ? launch_sweep_b16(a, pack, want, ctx->stream) : launch_sweep(a, ctx->stream);
         }
         if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "launch_sweep", e);
         ctx->static_used = mark_used; // the next column group reuses the image region (same stream: ordered)
@@ -1136,12 +1171,13 @@ size_t knm_workspace_bytes(int64_t n, int64_t M, int d, int t)
                 if (c3 > 1 && sizeof(float) * (size_t)c3 * nr * t > part) part = sizeof(float) * (size_t)c3 * nr * t;
             }
         }
-        if (cross == KNM_CROSS_F16X3) {
-            const bool packs = use_gemm_engine(d, t, cross, kind) || d <= f16_max_d();
-            const size_t k1 = packs ? pack_bytes_wanted(n, d, t, kind, 0, c1, l1) : 0;
-            const size_t k2 = packs ? pack_bytes_wanted(M, d, t, kind, 0, c2, l2) : 0;
+        if (packs_images(n, M, d, t, cross, kind)) {
+            const size_t k1 = pack_bytes_wanted(n, d, t, cross, kind, 0, c1, l1);
+            const size_t k2 = pack_bytes_wanted(M, d, t, cross, kind, 0, c2, l2);
             if (k1 > pack) pack = k1;
             if (k2 > pack) pack = k2;
+        }
+        if (cross == KNM_CROSS_F16X3) {
             const size_t both = product_image_bytes(sets, d, t, kind, 0);
             if (both > 0 && both + gemm_f16_head_bytes() > pack) pack = both + gemm_f16_head_bytes();
             if (use_gemm_engine(d, t, cross, kind)) {

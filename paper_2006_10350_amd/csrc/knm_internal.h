@@ -211,6 +211,11 @@ size_t f16_pack_bytes_per_point(int d);
 // pack_buf: device workspace for the packed stream image, at least one chunk's worth
 hipError_t launch_sweep_f16(const SweepArgs &a, void *pack_buf, size_t pack_bytes, hipStream_t stream);
 int f16_workgroups_per_cu(int d, int kind);
+// the fp32 cross term of the Gaussian kernel in three bf16 parts (knm_tile_b16.hip)
+bool b16_pays(double entries, int d); // also whether it takes d
+int b16_workgroups_per_cu(int d);
+size_t b16_pack_bytes_per_point(int d);
+hipError_t launch_sweep_b16(const SweepArgs &a, void *pack_buf, size_t pack_bytes, hipStream_t stream);
 // K-loop engine (knm_gemm.hip): any d, up to gemm_max_t() columns per launch
 int gemm_max_t();
 bool gemm_leading_dimension_ok(int64_t ld); // leading dimensions the fp32 K-loop engine can index
