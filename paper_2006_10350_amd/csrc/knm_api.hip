@@ -249,6 +249,17 @@ void pool_give(knm_ctx *ctx, void *p)
     }
 }
 
+void pool_trim(knm_ctx *ctx, size_t idle)
+{
+    const std::lock_guard<std::mutex> lock(ctx->pool_lock);
+    for (size_t i = ctx->pool.size(); i-- > 0 && ctx->pool_idle > idle;)
+        if (!ctx->pool[i].used) {
+            ctx->pool_idle -= ctx->pool[i].bytes;
+            (void)hipFree(ctx->pool[i].p);
+            ctx->pool.erase(ctx->pool.begin() + (std::ptrdiff_t)i);
+        }
+}
+
 void pool_drop(knm_ctx *ctx, void *p)
 {
     const std::lock_guard<std::mutex> lock(ctx->pool_lock);

@@ -269,6 +269,35 @@ hipError_t launch_gemm_f64(int a_nt, int64_t ni, int64_t nj, int64_t K, double a
                            const double *B, int64_t ldb, double beta, double *C, int64_t ldc, hipStream_t stream,
                            int b_nt = 0, int part = 0, bool in_place = false);
 
+// The symmetric update as integer products modulo small numbers (knm_residue.hip).  An operand's rows i < n (over k < K <= residue_max_k(); a(i, k) as in
+// launch_rank_k_upper, times w[k] if given, rows of a triangular one starting at k + k0 = i) become planes of residues and
+// one exponent per row; an update takes those of the operand's rows along the contiguous index u of C and across it, v.
+// `wanted` (a device word): planes of an operand whose exponents are there already, made only where it is not 0.
+bool residue_pays(int64_t n, int64_t K, bool triangular); // of an update of n x n entries
+size_t residue_image_bytes(int64_t n, int64_t K);
+int64_t residue_max_k();
+hipError_t launch_residue_image(int form_nt, int64_t n, int64_t K, const double *A, int64_t lda, const double *w, int tri, int64_t k0, int *exps,
+                                void *img, hipStream_t stream, const int *wanted = nullptr);
+// room for the residues of the sums of an update over u x v entries, at most `cap` but for one strip of tiles
+size_t residue_bytes(int64_t u, int64_t v, size_t cap);
+struct ResidueUpdate {
+    const void *img_u, *img_v;
+    const int *differ;       // a device word: img_u stands for both sides where it is 0 (null: as given)
+    const int *exp_u, *exp_v;
+    int64_t n, K;            // of the images
+    int64_t u0, u1, v0, v1;  // C[u + v ldc] for u0 <= u < u1, v0 <= v < v1 (the firsts multiples of 256), u <= v, or u >= v with lower
+    int lower, tri;
+    int64_t k0;
+    double alpha, beta, shift;
+    double *C;
+    int64_t ldc;
+    void *bytes;
+    size_t bytes_size;
+};
+hipError_t launch_residue_update(const ResidueUpdate &p, hipStream_t stream);
+// magnitude = sqrt |w|, with_sign = that with the sign of w, *negative = whether there is one
+hipError_t launch_signed_root(const double *w, int64_t n, double *magnitude, double *with_sign, int *negative, hipStream_t stream);
+
 // Merging of block inverses: S holds sb x sb column-major blocks (sb a multiple of 128) with the inverses of the
 // 128 x 128 diagonal blocks of an upper factor R (entry (i, j), i <= j, at R[i + j ld], or R[j + i ld] with lower);
 // on return the upper triangle of every block is the inverse of R's sb x sb diagonal block (the last one ends at
@@ -376,6 +405,7 @@ hipError_t device_alloc(knm_ctx *ctx, size_t bytes, void **out);
 enum class PoolUse { kNeeded, kOptional, kForSpeed };
 hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out, PoolUse use = PoolUse::kNeeded);
 void pool_drop(knm_ctx *ctx, void *p); // back to the device
+void pool_trim(knm_ctx *ctx, size_t idle); // idle blocks beyond that many bytes, the newest first
 void pool_give(knm_ctx *ctx, void *p);
 bool spare_add(knm_ctx *ctx, int phase, void **p); // false: no host memory for it
 void spare_remove(knm_ctx *ctx, int phase, void **p);
@@ -418,6 +448,11 @@ struct DevBuf {
         owner = ctx;
         const hipError_t e = pool_take(ctx, bytes, &p);
         return e == hipSuccess ? KNM_OK : fail(ctx, KNM_ALLOC, "hipMalloc", e);
+    }
+    bool alloc_for_speed(knm_ctx *ctx, size_t bytes) // false where the card has no room to spare
+    {
+        owner = ctx;
+        return pool_take(ctx, bytes, &p, PoolUse::kForSpeed) == hipSuccess;
     }
     template <class T> T *as() { return static_cast<T *>(p); }
 };

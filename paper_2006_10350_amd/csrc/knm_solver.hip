@@ -12,6 +12,7 @@
 // The factorisations are the block
 // column update of Sec. 4 on the fp64 matrix-core products of knm_dsyrk.hip and a leaf
 // kernel; the triangular solves, vector updates and reductions are kernels of this file.
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <functional>
@@ -1248,6 +1249,40 @@ static int aux_stream(knm_ctx *ctx, hipStream_t *out)
     return KNM_OK;
 }
 
+// What building a preconditioner that the caller keeps leaves idle in the pool: up to 4 GiB (all of it at M = 20000), as fits do; the 12 GiB of
+// M = 100000 go back to the device.
+struct IdleScope {
+    knm_ctx *ctx;
+    size_t before;
+    explicit IdleScope(knm_ctx *c) : ctx(c), before(c ? c->pool_idle : 0) {}
+    ~IdleScope()
+    {
+        if (ctx) pool_trim(ctx, std::max(before, (size_t)4 << 30));
+    }
+};
+
+// Room for updates by residues, from the pool: given back when it goes out of scope, in the order of the context's stream.
+struct ResidueRoom {
+    knm_ctx *ctx;
+    bool ok = false;
+    DevBuf img[2], exps[2], bytes[2];
+    size_t bytes_size[2] = {0, 0};
+    explicit ResidueRoom(knm_ctx *c) : ctx(c) {}
+    // Operands of up to n rows over K, in `sets` sets; the sums of an n x n matrix and, with first_rows, of that many rows of it
+    // apart.  At most kBytes of either at a time.
+    static constexpr size_t kBytes = (size_t)1 << 30;
+    void take(int64_t n, int64_t K, int sets, int64_t first_rows)
+    {
+        ok = true;
+        for (int s = 0; s < sets && ok; ++s)
+            ok = img[s].alloc_for_speed(ctx, residue_image_bytes(n, K)) && exps[s].alloc_for_speed(ctx, sizeof(int) * (size_t)n);
+        // (both storages: strips of `first_rows` x n and n x n entries whichever index is the contiguous one)
+        if (first_rows > 0) bytes_size[0] = std::max(residue_bytes(first_rows, n, kBytes / 2), residue_bytes(n, first_rows, kBytes / 2));
+        bytes_size[1] = residue_bytes(n, n, kBytes);
+        for (int k = 0; k < 2 && ok; ++k) ok = bytes_size[k] == 0 || bytes[k].alloc_for_speed(ctx, bytes_size[k]);
+    }
+};
+
 // `lower`: the factor and the matrix it replaces are in lower storage (entry (r, c), r <= c, at
 // A[c + r ld]); every product below then has its two index roles exchanged.  A block row that straddles the
 // diagonal is stored on its own side only, because the other triangle belongs to the other factor.
@@ -1264,6 +1299,11 @@ static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool low
     hipStream_t aux = nullptr;
     int st = aux_stream(ctx, &aux);
     if (st) return st;
+    // The trailing updates as integer products modulo small numbers (knm_residue.hip) where that is faster and there is room: planes of
+    // a block row in two sets in turn, so that those of the next are made while the rest of the update still reads these,
+    // and the residues of the sums, of the part on either stream.
+    ResidueRoom residues(ctx);
+    if (M > b && residue_pays(M - b, b, false)) residues.take(M - b, b, 2, b);
     // on an early return the arrays may go back to the pool, whose blocks are ordered by the context's stream only
     struct AuxJoin {
         hipStream_t s;
@@ -1323,13 +1363,44 @@ static int chol_blocked(knm_ctx *ctx, double *A, int64_t ld, int64_t M, bool low
         const int64_t c0 = r0 + w;                 // first trailing row and column
         const double *Akr2 = at(r0, c0 + w2);      // block row to the right of the columns of the next one
         const int form = lower ? 1 : 0, tc = lower ? 1 : 0;
+        const bool by_residues = residues.ok && residue_pays(rest, w, false);
+        ResidueUpdate up = {};
+        if (by_residues) {
+            const int set = (int)(k & 1);
+            up.img_u = up.img_v = residues.img[set].p;
+            up.exp_u = up.exp_v = residues.exps[set].as<int>();
+            up.n = rest;
+            up.K = w;
+            up.lower = lower ? 1 : 0;
+            up.alpha = -1.0;
+            up.beta = 1.0;
+            up.C = at(c0, c0);
+            up.ldc = ld;
+            if (launch_residue_image(form, rest, w, at(r0, c0), ld, nullptr, 0, 0, residues.exps[set].as<int>(), residues.img[set].p,
+                                     ctx->stream) != hipSuccess)
+                return fail(ctx, KNM_HIP_ERROR, "trailing update launch");
+        }
+        // rows [i0, i1) of the trailing matrix from column j0 on lose their part of the update
+        auto update_by_residues = [&](int64_t i0, int64_t i1, int64_t j0, int which, hipStream_t stream) -> bool {
+            ResidueUpdate q = up;
+            (lower ? q.v0 : q.u0) = i0;
+            (lower ? q.v1 : q.u1) = i1;
+            (lower ? q.u0 : q.v0) = j0;
+            (lower ? q.u1 : q.v1) = rest;
+            q.bytes = residues.bytes[which].p;
+            q.bytes_size = residues.bytes_size[which];
+            return launch_residue_update(q, stream) == hipSuccess;
+        };
         if (hipEventRecord(ev_rows[k], ctx->stream) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipEventRecord");
         if (k > 0 && have_rest[k - 1] && hipStreamWaitEvent(ctx->stream, ev_rest[k - 1], 0) != hipSuccess)
             return fail(ctx, KNM_HIP_ERROR, "hipStreamWaitEvent");
-        if (!update_rows(r0, w, c0, w2)) return fail(ctx, KNM_HIP_ERROR, "trailing update launch");
+        if (!(by_residues ? update_by_residues(0, w2, 0, 0, ctx->stream) : update_rows(r0, w, c0, w2)))
+            return fail(ctx, KNM_HIP_ERROR, "trailing update launch");
         if (rest > w2) {
             if (hipStreamWaitEvent(aux, ev_rows[k], 0) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipStreamWaitEvent");
-            if (launch_rank_k_upper(form, rest - w2, w, -1.0, Akr2, ld, nullptr, 0, 1.0, 0.0, at(c0 + w2, c0 + w2), ld, aux,
+            if (by_residues) {
+                if (!update_by_residues(w2, rest, w2, 1, aux)) return fail(ctx, KNM_HIP_ERROR, "trailing update launch");
+            } else if (launch_rank_k_upper(form, rest - w2, w, -1.0, Akr2, ld, nullptr, 0, 1.0, 0.0, at(c0 + w2, c0 + w2), ld, aux,
                                     tc) != hipSuccess)
                 return fail(ctx, KNM_HIP_ERROR, "trailing update launch");
             if (hipEventRecord(ev_rest[k], aux) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipEventRecord");
@@ -1361,6 +1432,63 @@ static int read_bad_pivots(knm_ctx *ctx, const unsigned long long *bad, int coun
     return KNM_OK;
 }
 
+// The triangular product by residues: 1, or 0 where that is no faster or there is no room.  The contraction is taken in slabs whose
+// planes fill at most 2 GiB, the last first: its sums reach every entry.  The weights go to the two sides as their roots, so that a
+// product of entries is scaled as the sum it is part of; their signs go to one side, whose planes are made only where there are any.
+static int second_by_residues(knm_ctx *ctx, knm_precond *p, double lambda, const double *dw)
+{
+    const int64_t M = p->M;
+    if (!residue_pays(M, M, true)) return 0;
+    const int sides = dw != nullptr ? 2 : 1;
+    const int64_t per_k = (int64_t)(residue_image_bytes(M, 64) / 64) * sides;
+    int64_t depth = ((int64_t)2 << 30) / per_k;
+    if (depth < 1024) depth = 1024;
+    if (depth > residue_max_k()) depth = residue_max_k();
+    const int64_t slabs = (M + depth - 1) / depth;
+    depth = ((M + slabs - 1) / slabs + 63) / 64 * 64;
+    ResidueRoom room(ctx);
+    room.take(M, depth < M ? depth : M, sides, 0);
+    DevBuf roots, sign;
+    if (!room.ok || (dw != nullptr && !(roots.alloc_for_speed(ctx, sizeof(double) * 2 * (size_t)M) && sign.alloc_for_speed(ctx, sizeof(int)))))
+        return 0;
+    double *root[2] = {nullptr, nullptr};
+    if (dw != nullptr) {
+        root[0] = roots.as<double>();
+        root[1] = root[0] + M;
+        if (launch_signed_root(dw, M, root[0], root[1], sign.as<int>(), ctx->stream) != hipSuccess)
+            return fail(ctx, KNM_HIP_ERROR, "triangular product launch");
+    }
+    int *const exps = room.exps[0].as<int>();
+    for (int64_t k1 = M; k1 > 0;) {
+        const int64_t k0 = (k1 - 1) / depth * depth;
+        hipError_t e = hipSuccess;
+        for (int s = 0; s < sides && e == hipSuccess; ++s)
+            e = launch_residue_image(1, k1, k1 - k0, p->T + k0 * p->ld, p->ld, root[s] ? root[s] + k0 : nullptr, 1, k0, exps,
+                                     room.img[s].p, ctx->stream, s == 1 ? sign.as<int>() : nullptr);
+        ResidueUpdate up = {};
+        up.img_u = room.img[0].p;
+        up.img_v = room.img[sides - 1].p;
+        up.differ = dw != nullptr ? sign.as<int>() : nullptr;
+        up.exp_u = up.exp_v = exps;
+        up.n = k1;
+        up.K = k1 - k0;
+        up.u1 = up.v1 = k1;
+        up.lower = up.tri = 1;
+        up.k0 = k0;
+        up.alpha = 1.0 / (double)M;
+        up.beta = k1 == M ? 0.0 : 1.0;
+        up.shift = k1 == M ? lambda : 0.0;
+        up.C = p->A;
+        up.ldc = p->ld;
+        up.bytes = room.bytes[1].p;
+        up.bytes_size = room.bytes_size[1];
+        if (e == hipSuccess) e = launch_residue_update(up, ctx->stream);
+        if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "triangular product launch");
+        k1 = k0;
+    }
+    return 1;
+}
+
 // A <- upper Cholesky factor of T D T^T / M + lambda I, D = diag(dw) (identity if dw is null), and
 // the inverses of its diagonal blocks.  T is upper triangular, so entry (i, j) of the product
 // only sums over k >= max(i, j): M^3 / 3 flop instead of the M^3 of a dense rank-M update,
@@ -1372,7 +1500,9 @@ static int build_second_factor(knm_ctx *ctx, knm_precond *p, double lambda, cons
     const int64_t M = p->M;
     {
         TraceRange range("knm triangular product T D T^T");
-        if (launch_rank_k_upper(1, M, M, 1.0 / (double)M, p->T, p->ld, dw, 1, 0.0, lambda, p->A, p->ld, ctx->stream, 1) !=
+        const int by_residues = second_by_residues(ctx, p, lambda, dw);
+        if (by_residues < 0) return by_residues;
+        if (by_residues == 0 && launch_rank_k_upper(1, M, M, 1.0 / (double)M, p->T, p->ld, dw, 1, 0.0, lambda, p->A, p->ld, ctx->stream, 1) !=
             hipSuccess)
             return fail(ctx, KNM_HIP_ERROR, "triangular product launch");
     }
@@ -1481,6 +1611,7 @@ static int precond_build_impl(knm_ctx *ctx, const float *C, int64_t M, int d, in
 int precond_build(knm_ctx *ctx, const float *C, int64_t M, int d, int64_t ldc, float sigma, double lambda,
                   double jitter, knm_precond **out, int64_t *bad_pivot_or_null)
 {
+    const IdleScope idle(ctx);
     return precond_build_impl(ctx, C, M, d, ldc, sigma, lambda, jitter, true, false, out, bad_pivot_or_null);
 }
 
@@ -1501,6 +1632,7 @@ int precond_build_csr(knm_ctx *ctx, const int64_t *c_indptr, const int64_t *c_in
                       int64_t d, float sigma, double lambda, double jitter, knm_precond **out,
                       int64_t *bad_pivot_or_null)
 {
+    const IdleScope idle(ctx);
     return precond_build_csr_impl(ctx, c_indptr, c_indices, c_values, M, d, sigma, lambda, jitter, true, false, out,
                                   bad_pivot_or_null);
 }
@@ -1644,6 +1776,7 @@ int precond_reweight(knm_ctx *ctx, knm_precond *p, double lambda, const double *
     if (!p || !(lambda >= 0.0)) return fail(ctx, KNM_INVALID_ARG, "bad preconditioner argument");
     if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipSetDevice");
     int st = KNM_OK;
+    const IdleScope idle(ctx);
     DevBuf badbuf;
     st = badbuf.alloc(ctx, sizeof(unsigned long long));
     if (st) return st;
