@@ -232,6 +232,15 @@ def forms_values_once(w, cross: str, kernel: str) -> bool:
     return rows >= 1024 or (w.n + 255) // 256 * 256 <= rows
 
 
+def sums_many_columns(w, cross: str, kernel: str) -> bool:
+    """The same for products with more columns, whose sums over the kept values run on the f16 matrix cores (same rule as the library)."""
+    least = 450 if w.t <= 32 else 320 if w.t <= 64 else 210 if w.t <= 128 else 180
+    if cross != "f16x3" or kernel != "gaussian" or w.t <= 12 or w.d < least or float(w.n) * w.M < 1e8:
+        return False
+    rows = (4 << 30) // (256 * 4 * ((w.M + 127) // 128 * 128)) * 256
+    return rows >= 1024 or (w.n + 255) // 256 * 256 <= rows
+
+
 def product_leg(knm, synth, torch, ctx, w, steps: int, warmup: int, cross: str, kernel: str, inputs=None, probe=None):
     """Times `steps` full products K_nm^T (K_nm v) on workload w; returns the metrics of the leg."""
     inp = inputs or synth.make_inputs(w, device="cuda", with_targets=False)
@@ -264,9 +273,10 @@ def product_leg(knm, synth, torch, ctx, w, steps: int, warmup: int, cross: str, 
     group = (160 if kernel == "gaussian" else 128) if (k_loop and f16) else 16
     # A product that forms every value once is priced as a whole: its row sweeps of slabs and its sums over the kept values
     # (kept_rows_kernel) stand for one launch
-    once = forms_values_once(w, cross, kernel)
+    many = sums_many_columns(w, cross, kernel)
+    once = many or forms_values_once(w, cross, kernel)
     sweeps = 1 if once else 2
-    launches = sweeps * ((w.t + group - 1) // group if k_loop else 1) * steps
+    launches = sweeps * ((w.t + group - 1) // group if k_loop and not many else 1) * steps
     avg_launch_ms = (sum(row_ms) + sum(col_ms)) / launches
     # Algorithmic contraction work of one launch (one sweep): every kernel entry once, 2 d flop each.
     # Padded or augmented contraction slots, the 2 t reduction flop and the exp are not counted.
@@ -276,7 +286,7 @@ def product_leg(knm, synth, torch, ctx, w, steps: int, warmup: int, cross: str, 
     traffic, mfma_insts = counters(w.name + ("" if f16 else "_f32")) if default else (None, None)
     roofline = {
         "bound": "mfma",
-        "kernel": kernel_name + (" + kept_rows_kernel" if once else ""),
+        "kernel": kernel_name + (" + kept_many_kernel" if many else " + kept_rows_kernel" if once else ""),
         "values_formed": "once, in slabs" if once else "in each sweep",
         # the contraction's own dtype: f16 matrix cores (three split products per feature pair,
         # fp32 accumulate) in the default mode, fp32 matrix cores otherwise

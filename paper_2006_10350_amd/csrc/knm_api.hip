@@ -681,10 +681,21 @@ static bool keeping_pays(int64_t n, int64_t M, int d, int t, int cross_term, int
 // 1.14 at 400 and 0.74 at 784, where the centres' image is not kept either.
 constexpr size_t kKeepSlabCap = (size_t)4 << 30; // bytes of a slab at most
 constexpr int64_t kKeepSlabRows = 1024;          // rows of a slab at least, where there are several
+// More columns than those take the values from memory for both sums (prod_kept_many).  In ps per value at 120k x 20k: forming and storing
+// 0.15 + 0.0046 d, a sum of up to 32 columns 0.85, 64 0.95, 128 1.2, 160 1.45, against two sweeps of 0.27 + 0.0047 d, 0.45 + 0.0047 d,
+// 0.75 + 0.0055 d and 1.05 + 0.0061 d: they meet at d = 293, 260, 180 and 140.  The lines lie beyond, for rows of zeros, whose sweeps are up to a
+// fifth faster, and for few centres, whose launches and partials count: 13 columns at d = 320 1.14 times as fast at 200k x 8000 and 0.96 with rows of
+// zeros, 0.94 and 0.87 at 300k x 500; above the lines 1.06 to 1.36 at the line, 1.25 to 1.58 with 30 columns at d = 784, 1.7 to 2 with 200 at 440.
+static bool keeping_many_pays(int64_t n, int64_t M, int d, int t)
+{
+    const int least = t <= 32 ? 450 : t <= 64 ? 320 : t <= 128 ? 210 : 180;
+    return t > kept_rows_max_t() && d >= least && (double)n * (double)M >= 1.0e8;
+}
 static int64_t product_keep_rows(int64_t n, int64_t M, int d, int t, int cross_term, int kind)
 {
-    if (cross_term != KNM_CROSS_F16X3 || kind != KNM_KERNEL_GAUSSIAN || t > kept_rows_max_t() || !use_gemm_engine(d, t, cross_term, kind) ||
-        gemm_f16_matrix_reduction(d, t) || 0.14 + 0.0045 * d + (t > 5 ? 0.15 : 0.03 * t) < 1.34)
+    if (cross_term != KNM_CROSS_F16X3 || kind != KNM_KERNEL_GAUSSIAN || !use_gemm_engine(d, t, cross_term, kind)) return 0;
+    if (t > kept_rows_max_t() ? !keeping_many_pays(n, M, d, t)
+                              : gemm_f16_matrix_reduction(d, t) || 0.14 + 0.0045 * d + (t > 5 ? 0.15 : 0.03 * t) < 1.34)
         return 0;
     int64_t rows = n;
     if (kept_bytes(n, M) > kKeepSlabCap) {
@@ -694,6 +705,53 @@ static int64_t product_keep_rows(int64_t n, int64_t M, int d, int t, int cross_t
     }
     return rows;
 }
+
+// How prod_kept_many cuts the sums over `in` points for `out` results, and its workspace.  The fp32 sums run over as many points as
+// those of the engine's sweeps (over all points, `in_all`), or fewer where that fills the chip's 256 places better: the least of rounds x
+// stages of 64 points (0.35 us and 0.3 per 32 columns each, 4 us a workgroup) and the partials' way to memory and back.
+static int64_t many_chunk(int64_t in, int64_t out, int64_t in_all, int d, int t)
+{
+    int64_t longest = 0;
+    (void)choose_chunks(out, in_all, d, t, KNM_CROSS_F16X3, KNM_KERNEL_GAUSSIAN, &longest);
+    const int64_t tiles = (in + 127) / 128, blocks = (out + 255) / 256, least = (tiles * 128 + longest - 1) / longest;
+    const double stage_us = 0.35 + 0.3 * (double)((t < kept_many_max_t() ? t : kept_many_max_t()) + 31) / 32.0;
+    int64_t best = 0;
+    double best_us = 0.0;
+    for (int64_t c = least; c <= 3 * least + 16 && c <= tiles; ++c) {
+        const int64_t len = (tiles + c - 1) / c, chunks = (tiles + len - 1) / len;
+        const int64_t rounds = (blocks * chunks + 255) / 256;
+        const double us = (double)rounds * (2.0 * (double)len * stage_us + 4.0) + 1.6e-6 * (double)chunks * (double)out * (double)t;
+        if (best == 0 || us < best_us) {
+            best = len;
+            best_us = us;
+        }
+    }
+    return best * 128;
+}
+struct ManyPlan {
+    int64_t row_chunk, col_chunk;   // points per chunk of the sums over the centres, over a slab's rows
+    int64_t row_chunks, col_chunks; // at most
+    int group;                      // columns per launch
+    size_t at[7], bytes;
+    ManyPlan(int64_t n, int64_t rows, int64_t M, int d, int t)
+    {
+        group = t < kept_many_max_t() ? t : kept_many_max_t();
+        row_chunk = many_chunk(M, rows, M, d, t);
+        col_chunk = many_chunk(rows, M, n, d, t);
+        row_chunks = (M + row_chunk - 1) / row_chunk;
+        col_chunks = (rows + col_chunk - 1) / col_chunk;
+        auto padded = [](int64_t n) { return (n + 127) / 128 * 128; };
+        // values, partials of W and of U, running U, images of V and W, their columns' scales
+        const size_t pieces[7] = {kept_bytes(rows, M), sizeof(float) * (size_t)row_chunks * (size_t)rows * t,
+                                  sizeof(float) * (size_t)col_chunks * (size_t)M * t, sizeof(double) * (size_t)M * t,
+                                  vector_image_bytes(group, padded(M)), vector_image_bytes(group, padded(rows)), 2 * gemm_f16_head_bytes()};
+        bytes = 0;
+        for (int i = 0; i < 7; ++i) {
+            at[i] = bytes;
+            bytes += (pieces[i] + 255) & ~(size_t)255;
+        }
+    }
+};
 
 // Forms the kernel values of set f against set s into `keep` (the images of both sets are there).
 static int form_values(knm_ctx *ctx, SweepShare *sh, int f, int s, const float *mu, float *keep)
@@ -1173,7 +1231,10 @@ size_t knm_workspace_bytes(int64_t n, int64_t M, int d, int t)
         const size_t p2 = c2 > 1 ? sizeof(float) * (size_t)c2 * M * t : 0;
         if (p1 > part) part = p1;
         if (p2 > part) part = p2;
-        if (const int64_t rows = product_keep_rows(n, M, d, t, cross, kind)) {
+        if (const int64_t rows = product_keep_rows(n, M, d, t, cross, kind); rows > 0 && t > kept_rows_max_t()) {
+            const size_t k = ManyPlan(n, rows, M, d, t).bytes;
+            if (k > keep) keep = k;
+        } else if (rows > 0) {
             // a slab of values, the partials and running sums of the sums over it, weighted rows (256 bytes of rounding each)
             const size_t k = kept_bytes(rows, M) + p2 + sizeof(double) * 4 * (size_t)M * t + sizeof(float) * (size_t)(rows + M) * t + 1024;
             if (k > keep) keep = k;
@@ -1340,6 +1401,102 @@ static int prod_kept(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx
     return KNM_OK;
 }
 
+// u64[j] (+)= the partials' sum in a fixed order; the last slab's goes out in fp32
+__global__ __launch_bounds__(256) void add_partials_kernel(const float *__restrict__ part, int64_t n_chunks, int64_t count, int first, int last,
+                                                           double *__restrict__ u64, float *__restrict__ out)
+{
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= count) return;
+    double s = first ? 0.0 : u64[j];
+    int64_t c = 0;
+    for (; c + 4 <= n_chunks; c += 4) {
+        const float p0 = part[c * count + j], p1 = part[(c + 1) * count + j], p2 = part[(c + 2) * count + j], p3 = part[(c + 3) * count + j];
+        s += ((double)p0 + (double)p1) + ((double)p2 + (double)p3);
+    }
+    for (; c < n_chunks; ++c) s += (double)part[c * count + j];
+    if (last) out[j] = (float)s;
+    else u64[j] = s;
+}
+
+// The product with many columns from kernel values that are formed once: slab by slab of rows, the values, W from them and the slab's share
+// of U.  *done = false: no room.
+static int prod_kept_many(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx, const float *C, int64_t M, int64_t ldc, float sigma,
+                          const float *dw, const float *V, int t, float *W, float *U, int64_t rows, bool *done)
+{
+    *done = false;
+    const ManyPlan plan(n, rows, M, d, t);
+    const SlabUse slab(ctx, plan.bytes);
+    if (slab.p == nullptr) return KNM_OK;
+    auto piece = [&](int i) { return static_cast<void *>(static_cast<char *>(slab.p) + plan.at[i]); };
+    float *const values = static_cast<float *>(piece(0)), *const part_w = static_cast<float *>(piece(1)), *const part_u = static_cast<float *>(piece(2));
+    double *const u64 = static_cast<double *>(piece(3));
+    uint32_t *const scales[2] = {static_cast<uint32_t *>(piece(6)), static_cast<uint32_t *>(piece(6)) + gemm_f16_head_bytes() / sizeof(uint32_t)};
+    SweepShare share(ctx, X, n, ldx, C, M, ldc, d, sigma, t, false); // (the shift is that of the whole pair, for all slabs)
+    share.n[0] = rows;
+    const ShareScope scope(share);
+    float *mu = nullptr;
+    int st = acquire(ctx, &ctx->mu_buf, &ctx->mu_bytes, mu_bytes_wanted(share.shift_n, d), &mu);
+    if (!st) st = column_shift(ctx, share.shift_P, share.shift_n, share.shift_ld, d, sigma, mu);
+    if (st) return st;
+    ctx->mu_owner = &share;
+    st = share_images(ctx, &share);
+    if (st == KNM_ALLOC || (!st && share.img[0] == nullptr)) return KNM_OK;
+    if (st) return st;
+    auto failed = [&](hipError_t e, const char *what) { return e == hipSuccess ? KNM_OK : fail(ctx, KNM_HIP_ERROR, what, e); };
+    auto image = [&](const float *vec, const float *wgt, int64_t count, int columns, int which) {
+        return failed(launch_vector_image(vec, t, wgt, count, (count + 127) / 128 * 128, columns, scales[which], piece(4 + which), ctx->stream),
+                      "launch_vector_image");
+    };
+    KeptManyArgs k{};
+    k.values = values;
+    k.nS = M;
+    k.ldo = t;
+    for (int64_t row0 = 0; row0 < n; row0 += rows) {
+        k.nF = n - row0 < rows ? n - row0 : rows;
+        share.P[0] = X + row0 * ldx;
+        share.n[0] = k.nF;
+        share.ready[0] = 0;
+        float *const Wb = W + row0 * t;
+        {
+            TraceRange range("knm kernel values of a slab");
+            st = form_values(ctx, &share, 0, 1, mu, values);
+            if (st) return st;
+        }
+        TraceRange range("knm sums over a slab's kernel values");
+        for (int side = 0; side < 2; ++side) { // W of the slab's rows, then their share of U
+            if (side == 1 && row0 + rows >= n) mark(ctx, 1);
+            const int64_t n_in = side == 0 ? M : k.nF, n_out = side == 0 ? k.nF : M;
+            k.over_stream = side == 0;
+            k.chunk_len = side == 0 ? plan.row_chunk : plan.col_chunk;
+            k.part_stride = n_out * t;
+            for (int c = 0; c < t; c += plan.group) {
+                k.t = t - c < plan.group ? t - c : plan.group;
+                if (side == 1) st = image(Wb + c, dw != nullptr ? dw + row0 : nullptr, k.nF, k.t, 1);
+                else if (row0 == 0 || t > plan.group) st = image(V + c, nullptr, M, k.t, 0);
+                if (st) return st;
+                k.vimg = piece(4 + side);
+                k.colmax = scales[side];
+                k.part = (side == 0 ? part_w : part_u) + c;
+                st = failed(launch_kept_many(k, ctx->stream), "launch_kept_many");
+                if (st) return st;
+            }
+            const int64_t chunks = (n_in + k.chunk_len - 1) / k.chunk_len, count = n_out * t;
+            if (side == 0) st = failed(launch_merge(part_w, nullptr, chunks, count, 1, Wb, nullptr, 1, count, ctx->stream), "launch_merge");
+            else {
+                if (row0 + rows >= n) mark(ctx, 2);
+                hipLaunchKernelGGL(add_partials_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, ctx->stream, part_u, chunks, count,
+                                   row0 == 0 ? 1 : 0, row0 + rows >= n ? 1 : 0, u64, U);
+                st = failed(hipGetLastError(), "add_partials_kernel");
+            }
+            if (st) return st;
+        }
+    }
+    mark(ctx, 3);
+    mark(ctx, 4);
+    *done = true;
+    return KNM_OK;
+}
+
 static int prod_impl(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx, const float *C, int64_t M,
                      int64_t ldc, float sigma, const float *dw, const float *V, int t, float *W_or_null, float *U)
 {
@@ -1356,7 +1513,7 @@ static int prod_impl(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx
     const int64_t keep_rows = ctx->static_mode ? 0 : product_keep_rows(n, M, d, t, ctx->cross_term, ctx->kernel_kind);
     if (keep_rows > 0) {
         bool done = false;
-        st = prod_kept(ctx, X, n, d, ldx, C, M, ldc, sigma, dw, V, t, W, U, keep_rows, &done);
+        st = (t > kept_rows_max_t() ? prod_kept_many : prod_kept)(ctx, X, n, d, ldx, C, M, ldc, sigma, dw, V, t, W, U, keep_rows, &done);
         if (st || done) return st;
         begin_timing(ctx);
     }

@@ -201,16 +201,6 @@ __device__ __forceinline__ void mfma_accv(f32x16 &acc, const f16x8 &a, const f16
     acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, acc, 0, 0, 0);
 }
 
-// Power of two that brings a column with largest magnitude `bits` (a float's bit pattern) into
-// [2^13, 2^14), or its inverse; 1 for an all-zero (or denormal) column.
-__device__ __forceinline__ float column_scale(uint32_t bits, bool inverse)
-{
-    const int e = (int)((bits >> 23) & 255u);
-    if (e == 0 || e == 255) return 1.0f;
-    const int shift = 13 - (e - 127);
-    return ldexpf(1.0f, inverse ? -shift : shift);
-}
-
 // Fimg: image of the fixed points [fixed_row0, fixed_row0 + 256 n_fblocks);
 // Simg: image of the stream chunks [chunk0, chunk0 + n_chunks).
 // TP: number of vector columns, padded to a multiple of 2 unless there is only one (vector-ALU reduction).  MV: reduce
@@ -1083,10 +1073,14 @@ int gemm_f16_workgroups_per_cu(int d, int t, int kind)
 }
 static int column_groups(int t) { return t <= 32 ? 1 : (t <= 64 ? 2 : (t <= 128 ? 4 : 5)); }
 
+size_t vector_image_bytes(int t, int64_t n_padded)
+{
+    return (size_t)(n_padded / kStream) * (size_t)(column_groups(t) * 4 * kThreads) * sizeof(f16x8);
+}
 size_t gemm_f16_vector_image_bytes(int d, int t, int64_t nS_padded)
 {
     if (t <= 0 || t > gemm_f16_max_t(KNM_KERNEL_GAUSSIAN) || !reduce_on_matrix_cores(d, t)) return 0;
-    return (size_t)(nS_padded / kStream) * (size_t)(column_groups(t) * 4 * kThreads) * sizeof(f16x8);
+    return vector_image_bytes(t, nS_padded);
 }
 
 // Columns to take in the next launch when t_left are still to do.  64 or 128 columns evaluate the kernel
@@ -1104,6 +1098,32 @@ int gemm_f16_group_t(int d, int t_left, int kind, bool with_vector_image)
     if (t_left > 64 && n_kc >= 17) return 128; // in place of three
     if (t_left > 32 && n_kc >= 17) return 64;  // in place of two
     return 32;
+}
+
+hipError_t launch_vector_image(const float *vec, int64_t ldv, const float *wgt, int64_t n, int64_t n_padded, int t, uint32_t *colmax, void *vimg,
+                               hipStream_t stream)
+{
+    if (t <= 0 || t > gemm_f16_max_t(KNM_KERNEL_GAUSSIAN) || n_padded % kStream != 0) return hipErrorInvalidValue;
+    // largest magnitude of every vector column: the power-of-two scale into the fp16 range
+    // cleared by a kernel, not a memset node: the product entry points may be captured into a graph
+    hipLaunchKernelGGL(clear_head_kernel, dim3(1), dim3(kHeadBytes / sizeof(uint32_t)), 0, stream, colmax);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int64_t passes = n / (256 / t) + 1;
+    const int64_t blocks = passes > 1024 * 8 ? 1024 : (passes + 7) / 8; // eight rows per thread, or a thousand workgroups
+    hipLaunchKernelGGL(col_absmax_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, vec, ldv, wgt, n, t, colmax);
+    if (vimg != nullptr) {
+        // the vectors of the whole stream, converted once (the scales are on the device by now: same stream)
+        const dim3 vgrid((unsigned)(n_padded / kStream));
+        f16x8 *const img = static_cast<f16x8 *>(vimg);
+        switch (column_groups(t)) {
+        case 1: hipLaunchKernelGGL(pack_vectors_kernel<1>, vgrid, dim3(kThreads), 0, stream, vec, ldv, wgt, n, t, colmax, img); break;
+        case 2: hipLaunchKernelGGL(pack_vectors_kernel<2>, vgrid, dim3(kThreads), 0, stream, vec, ldv, wgt, n, t, colmax, img); break;
+        case 4: hipLaunchKernelGGL(pack_vectors_kernel<4>, vgrid, dim3(kThreads), 0, stream, vec, ldv, wgt, n, t, colmax, img); break;
+        default: hipLaunchKernelGGL(pack_vectors_kernel<5>, vgrid, dim3(kThreads), 0, stream, vec, ldv, wgt, n, t, colmax, img); break;
+        }
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_sweep_gemm_f16(const SweepArgs &a, void *pack_buf, size_t pack_bytes, hipStream_t stream)
@@ -1138,27 +1158,7 @@ hipError_t launch_sweep_gemm_f16(const SweepArgs &a, void *pack_buf, size_t pack
     }
     const bool mv = reduce_on_matrix_cores(a.d, a.t);
     if (mv) {
-        // largest magnitude of every vector column: the power-of-two scale into the fp16 range
-        // cleared by a kernel, not a memset node: the product entry points may be captured into a graph
-        hipLaunchKernelGGL(clear_head_kernel, dim3(1), dim3(kHeadBytes / sizeof(uint32_t)), 0, stream, colmax);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        const int64_t passes = a.nS / (256 / a.t) + 1;
-        const int64_t blocks = passes > 1024 * 8 ? 1024 : (passes + 7) / 8; // eight rows per thread, or a thousand workgroups
-        hipLaunchKernelGGL(col_absmax_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, a.vec, a.ldv, a.wgt, a.nS,
-                           a.t, colmax);
-        if (a.vimg != nullptr) {
-            // the vectors of the whole stream, converted once (the scales are on the device by now: same stream)
-            const dim3 vgrid((unsigned)(nSp / kStream));
-            f16x8 *const vimg = static_cast<f16x8 *>(a.vimg);
-            switch (column_groups(a.t)) {
-            case 1: hipLaunchKernelGGL(pack_vectors_kernel<1>, vgrid, dim3(kThreads), 0, stream, a.vec, a.ldv, a.wgt, a.nS, a.t, colmax, vimg); break;
-            case 2: hipLaunchKernelGGL(pack_vectors_kernel<2>, vgrid, dim3(kThreads), 0, stream, a.vec, a.ldv, a.wgt, a.nS, a.t, colmax, vimg); break;
-            case 4: hipLaunchKernelGGL(pack_vectors_kernel<4>, vgrid, dim3(kThreads), 0, stream, a.vec, a.ldv, a.wgt, a.nS, a.t, colmax, vimg); break;
-            default: hipLaunchKernelGGL(pack_vectors_kernel<5>, vgrid, dim3(kThreads), 0, stream, a.vec, a.ldv, a.wgt, a.nS, a.t, colmax, vimg); break;
-            }
-        }
-        e = hipGetLastError();
+        const hipError_t e = launch_vector_image(a.vec, a.ldv, a.wgt, a.nS, nSp, a.t, colmax, a.vimg, stream);
         if (e != hipSuccess) return e;
     }
 

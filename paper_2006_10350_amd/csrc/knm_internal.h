@@ -110,6 +110,21 @@ struct KeptRowsArgs {
     int64_t chunk_len;   // a multiple of kKeptTile
 };
 hipError_t launch_kept_rows(const KeptRowsArgs &a, hipStream_t stream);
+// Sums with up to kept_many_max_t() columns over kept values, from the vectors' packed image (launch_vector_image) of the points summed over,
+// in fp32 over chunks of chunk_len of them (a multiple of 128)
+struct KeptManyArgs {
+    const float *values;
+    int64_t nF, nS;
+    bool over_stream;
+    const void *vimg;
+    const uint32_t *colmax;
+    int t;
+    int64_t chunk_len;
+    float *part; // part[chunk * part_stride + i * ldo + c]
+    int64_t part_stride, ldo;
+};
+int kept_many_max_t();
+hipError_t launch_kept_many(const KeptManyArgs &a, hipStream_t stream);
 // forms the values only: a.keep from the images a.fimg, a.simg of kept_rows() points each (packed here unless ready)
 hipError_t launch_keep_f16(const SweepArgs &a, hipStream_t stream);
 
@@ -230,6 +245,10 @@ int gemm_f16_max_t(int kind); // columns per launch at most
 int gemm_f16_group_t(int d, int t_left, int kind, bool with_vector_image); // columns the next launch should take
 // bytes of the packed vector image of a launch with t columns over nS_padded stream points (0: no such image)
 size_t gemm_f16_vector_image_bytes(int d, int t, int64_t nS_padded);
+// colmax (gemm_f16_head_bytes()) and, unless null, the packed image vimg of n vectors with t columns (times wgt), padded to n_padded
+hipError_t launch_vector_image(const float *vec, int64_t ldv, const float *wgt, int64_t n, int64_t n_padded, int t, uint32_t *colmax, void *vimg,
+                               hipStream_t stream);
+size_t vector_image_bytes(int t, int64_t n_padded);
 int gemm_f16_workgroups_per_cu(int d, int t, int kind); // of a launch with t columns and the packed vector image
 bool gemm_f16_matrix_reduction(int d, int t);           // the reduction against t columns runs on the matrix cores
 // sums over the stream points run through a chunk in fp32 (else those of a tile are added in fp64)

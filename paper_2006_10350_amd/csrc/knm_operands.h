@@ -57,6 +57,16 @@ __device__ __forceinline__ void norm_digits(float n, _Float16 (&q)[4])
     q[0] = (_Float16)(-q1); q[1] = (_Float16)(-q2); q[2] = (_Float16)(-q3); q[3] = (_Float16)(-q4);
 }
 
+// Power of two that brings a column with largest magnitude `bits` (a float's bit pattern) into
+// [2^13, 2^14), or its inverse; 1 for an all-zero (or denormal) column.
+__device__ __forceinline__ float column_scale(uint32_t bits, bool inverse)
+{
+    const int e = (int)((bits >> 23) & 255u);
+    if (e == 0 || e == 255) return 1.0f;
+    const int shift = 13 - (e - 127);
+    return ldexpf(1.0f, inverse ? -shift : shift);
+}
+
 // Branch-free row loads: virtual features [base, base + N) of `row` minus the common shift `mu`
 // (skipped if !shifted), zero beyond d or for an invalid row.  Out-of-range features read element 0
 // of the row and are zeroed by a select, so all loads issue back to back; `row` must point at a
