@@ -105,6 +105,34 @@ __device__ __forceinline__ void load_features(const float *__restrict__ row, con
     }
 }
 
+// Sums over the 32 lanes of each half-wave of 32 values a lane, sum[b][r]: lane l of a half gets that of value (l / 16, l % 16).
+// Every exchange with a lane farther away halves the values that are left: 31 exchanges in 5 dependent steps, in place of 160 in 160
+// where every lane summed every value (about 5 us at the end of a workgroup); the order of a sum is the same.
+__device__ __forceinline__ float half_wave_sums(float (&sum)[2][16])
+{
+    const int lane = (int)(threadIdx.x & 31u);
+    float v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const bool up = (lane & 16) != 0;
+        const float lo = sum[0][r], hi = sum[1][r]; // (values: a choice between elements would become an index)
+        const float keep = up ? hi : lo, give = up ? lo : hi;
+        v[r] = keep + __shfl_xor(give, 16);
+    }
+#pragma unroll
+    for (int n = 8; n > 0; n >>= 1)
+#pragma unroll
+        for (int r = 0; r < n; ++r) {
+            const bool up = (lane & n) != 0;
+            const float lo = v[r], hi = v[r + n];
+            const float keep = up ? hi : lo, give = up ? lo : hi;
+            v[r] = keep + __shfl_xor(give, n);
+        }
+    return v[0];
+}
+// and the fixed point, from the wavefront's first, that this value of a pair of 32 x 32 accumulators belongs to (half-wave h)
+__device__ __forceinline__ int half_wave_point(int lane, int h) { return (lane >> 4) * 32 + 8 * ((lane & 15) >> 2) + 4 * h + (lane & 3); }
+
 // Wait states between the last 32 x 32 MFMA written in inline assembly and the first read of its
 // result by other instructions (the compiler cannot insert them for instructions it does not see).
 __device__ __forceinline__ void mfma_results_ready()

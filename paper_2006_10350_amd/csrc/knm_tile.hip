@@ -159,11 +159,21 @@ __global__ __launch_bounds__(kThreads, (KS <= 15 ? 3 : 1)) void gauss_sweep_kern
         const int64_t idx = fixed0 + rb * 32 + row;
         const bool valid = idx < a.nF;
         const float *p = a.F + (valid ? idx : 0) * a.ldf;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) { // (every load is on its way before the first is used)
+            const int k = 4 * (s / 2) + 2 * h + (s % 2);
+            const bool in = valid && k < d;
+            const float v = p[in ? k : 0], m = a.mu[k < d ? k : 0];
+            af[rb][s] = in ? v - m : 0.0f;
+        }
+    }
+#pragma unroll
+    for (int rb = 0; rb < R; ++rb) {
+        const bool valid = fixed0 + rb * 32 + row < a.nF;
         float nrm = 0.0f;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            const int k = 4 * (s / 2) + 2 * h + (s % 2);
-            float v = (valid && k < d) ? p[k] - a.mu[k < d ? k : 0] : 0.0f;
+            const float v = af[rb][s];
             nrm = fmaf(v, v, nrm);
             af[rb][s] = 2.0f * s2 * v;
         }
@@ -263,19 +273,9 @@ __global__ __launch_bounds__(kThreads, (KS <= 15 ? 3 : 1)) void gauss_sweep_kern
     }
     // ---- reduce over the 32 stream lanes of each half-wave and store ----------------------
     float *out = a.out + (int64_t)blockIdx.y * a.chunk_stride;
-#pragma unroll
-    for (int rb = 0; rb < R; ++rb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float v = sum[rb][r];
-            v += __shfl_xor(v, 16);
-            v += __shfl_xor(v, 8);
-            v += __shfl_xor(v, 4);
-            v += __shfl_xor(v, 2);
-            v += __shfl_xor(v, 1);
-            const int64_t idx = fixed0 + rb * 32 + 8 * (r / 4) + 4 * h + (r % 4);
-            if (row == 0 && idx < a.nF) out[idx * a.ldo] = v;
-        }
+    const float total = half_wave_sums(sum);
+    const int64_t idx = fixed0 + half_wave_point(row, h);
+    if (idx < a.nF) out[idx * a.ldo] = total;
 }
 
 // out[j] = sum of the chunk partials of entry j in fp64.  A wavefront takes 64 entries and every SLICES-th chunk, and the sums of

@@ -196,14 +196,15 @@ __global__ __launch_bounds__(kThreads, waves_of(NM)) void gauss_sweep_b16_kernel
 {
     int64_t fblock, chunk_local;
     const int grouped = n_chunks & ~7; // chunks that are dealt to one XCD each
-    if ((int64_t)blockIdx.x < (int64_t)grouped * n_fblocks) {
-        const int64_t slot = (int64_t)blockIdx.x >> 3;
-        chunk_local = (slot / n_fblocks) * 8 + (blockIdx.x & 7);
-        fblock = slot % n_fblocks;
+    const unsigned blocks = (unsigned)n_fblocks; // (the grid's size fits 31 bits)
+    if (blockIdx.x < (unsigned)grouped * blocks) {
+        const unsigned slot = blockIdx.x >> 3;
+        chunk_local = (slot / blocks) * 8 + (blockIdx.x & 7);
+        fblock = slot % blocks;
     } else {
-        const int64_t rest = (int64_t)blockIdx.x - (int64_t)grouped * n_fblocks;
-        fblock = rest % n_fblocks;
-        chunk_local = grouped + rest / n_fblocks;
+        const unsigned rest = blockIdx.x - (unsigned)grouped * blocks;
+        fblock = rest % blocks;
+        chunk_local = grouped + rest / blocks;
     }
 
     constexpr int UPS = kTilesPerStage * NM * 64; // units per stage
@@ -217,17 +218,7 @@ __global__ __launch_bounds__(kThreads, waves_of(NM)) void gauss_sweep_b16_kernel
     const int row = lane & 31;
     const int h = lane >> 5;
 
-    // fixed operand: 2 blocks of 32 points per wavefront, in registers
     const int64_t fixed0 = (fblock * kWaves + wave) * 64;
-    unit_t f[2][NM];
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-        const int64_t idx = fixed0 + rb * 32 + row;
-        const bool valid = idx < a.nF;
-        const float *p = a.F + (valid ? idx : 0) * a.ldf;
-        make_units<true, NM>(p, a.mu, a.d, gamma, valid, h, f[rb]);
-    }
-
     float sum[2][16];
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
@@ -256,6 +247,21 @@ __global__ __launch_bounds__(kThreads, waves_of(NM)) void gauss_sweep_b16_kernel
         vs = valid ? vraw * wraw : 0.0f;
     };
 
+    if (n_stages > 0) {
+        issue(0, 0);
+        fetch(0);
+    }
+
+    // fixed operand: 2 blocks of 32 points per wavefront, in registers
+    unit_t f[2][NM];
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+        const int64_t idx = fixed0 + rb * 32 + row;
+        const bool valid = idx < a.nF;
+        const float *p = a.F + (valid ? idx : 0) * a.ldf;
+        make_units<true, NM>(p, a.mu, a.d, gamma, valid, h, f[rb]);
+    }
+
     // accumulators of the tile in flight and of the tile being finished
     f32x16 accA[2], accB[2];
 #pragma unroll
@@ -264,10 +270,6 @@ __global__ __launch_bounds__(kThreads, waves_of(NM)) void gauss_sweep_b16_kernel
         for (int r = 0; r < 16; ++r) { accA[rb][r] = 0.0f; accB[rb][r] = 0.0f; }
     float vl_prev = 0.0f; // zero weight: the first "previous tile" contributes nothing
 
-    if (n_stages > 0) {
-        issue(0, 0);
-        fetch(0);
-    }
     for (int st = 0; st < n_stages; ++st) {
         const int buf = st & 1;
         if (tid < kStage) vv[buf][tid] = vs;
@@ -309,19 +311,9 @@ __global__ __launch_bounds__(kThreads, waves_of(NM)) void gauss_sweep_b16_kernel
 
     // reduce over the 32 stream lanes of each half-wave and store
     float *out = a.out + chunk * a.chunk_stride;
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float v = sum[rb][r];
-            v += __shfl_xor(v, 16);
-            v += __shfl_xor(v, 8);
-            v += __shfl_xor(v, 4);
-            v += __shfl_xor(v, 2);
-            v += __shfl_xor(v, 1);
-            const int64_t idx = fixed0 + rb * 32 + 8 * (r / 4) + 4 * h + (r % 4);
-            if (row == 0 && idx < a.nF) out[idx * a.ldo] = v;
-        }
+    const float total = half_wave_sums(sum);
+    const int64_t idx = fixed0 + half_wave_point(row, h);
+    if (idx < a.nF) out[idx * a.ldo] = total;
 }
 
 template <int NM>
