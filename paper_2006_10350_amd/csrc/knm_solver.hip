@@ -32,7 +32,7 @@ struct knm_precond {
     double *A = nullptr;   // = buf + 2: lower storage (what is in memory is A^T, a lower triangle)
     // inverses of the sb x sb diagonal blocks of T and A (column-major blocks, each mirrored onto
     // its lower triangle, the last one padded with the identity), used by the blocked
-    // triangular solves; xw (2 M kSolveCols entries) holds the solution, and for several columns the right-hand side, of a
+    // triangular solves; xw (4 M kSolveCols entries) holds the solution, and for several columns the right-hand side, of a
     // solve under way
     int sb = 0;
     double *Tdinv = nullptr;
@@ -351,13 +351,18 @@ __global__ __launch_bounds__(256) void panel_update_t_kernel(const double *__res
 // bandwidth of the factor, which is read once for all columns (a 16 x 16 x 4 instruction takes 512 bytes of it in 64
 // cycles: 19 TB/s over the chip).  Right-hand sides and solution live as [row][16] arrays, unused columns zero.
 // 10 columns at M = 10000: 5.2 ms for the four solves of an iteration as vector-ALU passes over 8 and 2 columns,
-// 1.07 ms with 32 outputs and 8 wavefronts per workgroup (62 to 250 workgroups of a panel, 64 of a diagonal block), 0.83 ms now.
+// 1.07 ms with 32 outputs and 8 wavefronts per workgroup (62 to 250 workgroups of a panel, 64 of a diagonal block), 0.83 ms with 16 of either, 0.70 ms now.
 constexpr int kSolveCols = 16;
 constexpr int kSkinnyThreads = 1024, kSkinnyWaves = kSkinnyThreads / 64;
 typedef double solve_d4 __attribute__((ext_vector_type(4)));
 // Outputs of a workgroup, whose 16 wavefronts share the contraction 32 at a time: 16 NT.  A product of at most 2048
 // outputs (a diagonal block) is 128 workgroups with NT = 1.
 constexpr int64_t kSkinnyNarrowUpTo = 2048;
+// Up to this many such workgroups two share the contraction, each with its own part of the sums (`half` entries apart), so that
+// they fill the chip: every right-hand side and solution of a solve is the sum of two parts, which its readers form, always in that order.
+// M = 10000: diagonal block 16.1 -> 12.3 us, panel of 2000 rows 17.8 -> 13.8, of 4000 rows 24.0 -> 19.9 and 32.2 -> 23.1; of
+// 6000 rows (two each on half of the CUs) 26 -> 34.
+constexpr unsigned kSkinnySplitUpTo = 128;
 
 // adds up the wavefronts' accumulators; this thread's entry of the tile (threads below 256 NT): accumulator t = tid / 256,
 // register (tid / 64) % 4 of lane tid % 64
@@ -382,30 +387,33 @@ template <int NT> __device__ __forceinline__ double skinny_reduce(double (*red)[
 // has rows t mod NT.
 template <int NT>
 __global__ __launch_bounds__(kSkinnyThreads) void skinny_n_kernel(const double *__restrict__ P, int64_t ld, int64_t rows,
-                                                                 int nk, const double *__restrict__ x, double *__restrict__ b)
+                                                                 int nk, const double *__restrict__ x, double *__restrict__ b,
+                                                                 int64_t half)
 {
     typedef double row_t __attribute__((ext_vector_type(NT)));
     __shared__ double red[kSkinnyWaves][NT][4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l15 = lane & 15, q = lane >> 4;
+    const int step = kSkinnyWaves * 32 * (int)gridDim.y;
     const int64_t row0 = (int64_t)blockIdx.x * (16 * NT);
     const double *p = P + (row0 + NT * l15 < rows ? row0 + NT * l15 : 0);
     solve_d4 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = solve_d4{0.0, 0.0, 0.0, 0.0};
-    for (int k0 = wave * 32; k0 < nk; k0 += kSkinnyWaves * 32) {
+    for (int k0 = ((int)blockIdx.y * kSkinnyWaves + wave) * 32; k0 < nk; k0 += step) {
         row_t a[8];
-        double bv[8];
+        double bv[8], b2[8];
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int k = k0 + 4 * s + q, kc = k < nk ? k : nk - 1;
             a[s] = *reinterpret_cast<const row_t *>(p + (int64_t)kc * ld);
             bv[s] = x[(int64_t)kc * kSolveCols + l15];
+            b2[s] = x[half + (int64_t)kc * kSolveCols + l15];
         }
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             const bool in = k0 + 4 * s + q < nk;
-            const double bs = in ? bv[s] : 0.0;
+            const double bs = in ? bv[s] + b2[s] : 0.0;
 #pragma unroll
             for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? a[s][t] : 0.0, bs, acc[t], 0, 0, 0);
         }
@@ -413,7 +421,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_n_kernel(const double *
     const double s = skinny_reduce<NT>(red, acc);
     const int t = threadIdx.x >> 8, i = 4 * ((threadIdx.x >> 6) & 3) + q;
     const int64_t r = row0 + NT * i + t;
-    if (t < NT && r < rows) b[r * kSolveCols + l15] -= s;
+    if (t < NT && r < rows) b[blockIdx.y * half + r * kSolveCols + l15] -= s;
 }
 
 // MODE 0: b[j, c] -= sum_{i < nk} P[i + j ld] x[i, c], j < outs.  MODE 1, 2: b[j, c] = the same sum over i >= j, i <= j (a
@@ -421,7 +429,8 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_n_kernel(const double *
 // lane holds 8 consecutive i of its column, 32 per 4 lane groups.
 template <int MODE, int NT>
 __global__ __launch_bounds__(kSkinnyThreads) void skinny_t_kernel(const double *__restrict__ P, int64_t ld, int64_t outs,
-                                                                 int nk, const double *__restrict__ x, double *__restrict__ b)
+                                                                 int nk, const double *__restrict__ x, double *__restrict__ b,
+                                                                 int64_t half)
 {
     __shared__ double red[kSkinnyWaves][NT][4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -437,9 +446,10 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_t_kernel(const double *
     }
     const int first = MODE == 1 ? (int)tile0 & ~31 : 0;
     const int last = MODE == 2 && tile0 + 16 * NT < nk ? (int)tile0 + 16 * NT : nk;
-    for (int i0 = first + wave * 32; i0 < last; i0 += kSkinnyWaves * 32) {
+    const int step = kSkinnyWaves * 32 * (int)gridDim.y;
+    for (int i0 = first + ((int)blockIdx.y * kSkinnyWaves + wave) * 32; i0 < last; i0 += step) {
         solve_d2 a[NT][4];
-        double bv[8];
+        double bv[8], b2[8];
         const int ib = i0 + 8 * q; // nk and ld are such that 8 entries from an in-range multiple of 8 stay inside the array
         const bool any = ib < nk;
 #pragma unroll
@@ -450,11 +460,15 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_t_kernel(const double *
                 a[t][s] = *reinterpret_cast<const solve_d2 *>(p[t] + i);
             }
 #pragma unroll
-        for (int s = 0; s < 8; ++s) bv[s] = x[(int64_t)(ib + s < nk ? ib + s : 0) * kSolveCols + l15];
+        for (int s = 0; s < 8; ++s) {
+            const int64_t at = (int64_t)(ib + s < nk ? ib + s : 0) * kSolveCols + l15;
+            bv[s] = x[at];
+            b2[s] = x[half + at];
+        }
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int i = ib + s;
-            const double bs = i < nk ? bv[s] : 0.0;
+            const double bs = i < nk ? bv[s] + b2[s] : 0.0;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const int j = (int)tile0 + 16 * t + l15;
@@ -467,27 +481,31 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_t_kernel(const double *
     const int t = threadIdx.x >> 8;
     const int64_t j = tile0 + 16 * t + 4 * ((threadIdx.x >> 6) & 3) + q;
     if (t < NT && j < outs) {
-        if (MODE == 0) b[j * kSolveCols + l15] -= s;
-        else b[j * kSolveCols + l15] = s;
+        double *const out = b + blockIdx.y * half + j * kSolveCols + l15;
+        if (MODE == 0) *out -= s;
+        else *out = s;
     }
 }
 
 // [row][16] <- tc columns of a column-major array (zero from tc on), and back
-__global__ void cols_to_rows16_kernel(const double *__restrict__ B, int64_t ldb, int64_t M, int tc, double *__restrict__ out)
+__global__ void cols_to_rows16_kernel(const double *__restrict__ B, int64_t ldb, int64_t M, int tc, double *__restrict__ out, int64_t half)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t r = e % M;
     const int c = (int)(e / M);
-    if (c < kSolveCols) out[r * kSolveCols + c] = c < tc ? B[(int64_t)c * ldb + r] : 0.0;
+    if (c >= kSolveCols) return;
+    out[r * kSolveCols + c] = c < tc ? B[(int64_t)c * ldb + r] : 0.0;
+    out[half + r * kSolveCols + c] = 0.0;
 }
 // (with add: plus scale add, same layout as B)
-__global__ void rows16_to_cols_kernel(const double *__restrict__ in, int64_t M, int tc, double *__restrict__ B, int64_t ldb,
+__global__ void rows16_to_cols_kernel(const double *__restrict__ in, int64_t half, int64_t M, int tc, double *__restrict__ B, int64_t ldb,
                                       const double *__restrict__ add, double scale)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t r = e % M;
     const int c = (int)(e / M);
-    if (c < tc) B[(int64_t)c * ldb + r] = in[r * kSolveCols + c] + (add != nullptr ? scale * add[(int64_t)c * ldb + r] : 0.0);
+    if (c < tc)
+        B[(int64_t)c * ldb + r] = (in[r * kSolveCols + c] + in[half + r * kSolveCols + c]) + (add != nullptr ? scale * add[(int64_t)c * ldb + r] : 0.0);
 }
 
 // ---- leaf of the blocked factorisation --------------------------------------------------------
@@ -984,9 +1002,10 @@ int tri_solve(knm_ctx *ctx, const knm_precond *p, const double *R, const double 
         const double *bin = in + (int64_t)c0 * M;
         double *bout = out + (int64_t)c0 * M;
         const double *badd = add != nullptr ? add + (int64_t)c0 * M : nullptr;
-        double *rhs = p->xw + M * kSolveCols; // several columns: right-hand side and solution as [row][16] arrays
+        const int64_t half = 2 * M * kSolveCols;
+        double *rhs = p->xw + M * kSolveCols; // several columns: right-hand side and solution as [row][16] arrays, in two parts each
         if (tc > 1)
-            hipLaunchKernelGGL(cols_to_rows16_kernel, grid1(M * kSolveCols), dim3(256), 0, ctx->stream, bin, M, M, tc, rhs);
+            hipLaunchKernelGGL(cols_to_rows16_kernel, grid1(M * kSolveCols), dim3(256), 0, ctx->stream, bin, M, M, tc, rhs, half);
         // one column: the right-hand side so far (`in` up to the first panel update), and where the solution goes
         double *const work = p->xw;
         double *const sol = badd != nullptr ? p->xw + M : bout;
@@ -999,18 +1018,19 @@ int tri_solve(knm_ctx *ctx, const knm_precond *p, const double *R, const double 
             const int64_t lo = trans ? k0 + nbk : 0, hi = trans ? M : k0;
             if (tc > 1) {
                 double *x = p->xw + k0 * kSolveCols;
-                // the diagonal block, then the panel of the entries still to be solved
+                // the diagonal block (of at most 2048, always by two), then the panel of the entries still to be solved
                 auto diagonal = [&](auto kernel) {
-                    hipLaunchKernelGGL(kernel, dim3((unsigned)((nbk + 15) / 16)), dim3(kSkinnyThreads), 0, ctx->stream, Sk, (int64_t)sb,
-                                       (int64_t)nbk, nbk, rhs + k0 * kSolveCols, x);
+                    hipLaunchKernelGGL(kernel, dim3((unsigned)((nbk + 15) / 16), 2), dim3(kSkinnyThreads), 0, ctx->stream, Sk, (int64_t)sb,
+                                       (int64_t)nbk, nbk, rhs + k0 * kSolveCols, x, half);
                 };
                 if (trans) diagonal(skinny_t_kernel<2, 1>);
                 else diagonal(skinny_t_kernel<1, 1>);
                 if (hi == lo) continue;
                 const bool narrow = hi - lo <= kSkinnyNarrowUpTo;
-                const dim3 pgrid((unsigned)(narrow ? (hi - lo + 15) / 16 : (hi - lo + 31) / 32));
+                const unsigned tiles = (unsigned)(narrow ? (hi - lo + 15) / 16 : (hi - lo + 31) / 32);
+                const dim3 pgrid(tiles, tiles <= kSkinnySplitUpTo ? 2 : 1);
                 auto panel = [&](auto kernel, const double *P) {
-                    hipLaunchKernelGGL(kernel, pgrid, dim3(kSkinnyThreads), 0, ctx->stream, P, ld, hi - lo, nbk, x, rhs + lo * kSolveCols);
+                    hipLaunchKernelGGL(kernel, pgrid, dim3(kSkinnyThreads), 0, ctx->stream, P, ld, hi - lo, nbk, x, rhs + lo * kSolveCols, half);
                 };
                 if (trans == lower) // panel entries R(r, k0 + j) or R(k0 + j, r) contiguous in r
                     narrow ? panel(skinny_n_kernel<1>, R + lo + k0 * ld) : panel(skinny_n_kernel<2>, R + lo + k0 * ld);
@@ -1031,7 +1051,7 @@ int tri_solve(knm_ctx *ctx, const knm_precond *p, const double *R, const double 
                                    dim3(256), 0, ctx->stream, R, ld, k0, nbk, lo, hi, sol + k0, b, work);
         }
         if (tc > 1)
-            hipLaunchKernelGGL(rows16_to_cols_kernel, grid1(M * tc), dim3(256), 0, ctx->stream, p->xw, M, tc, bout, M, badd, scale);
+            hipLaunchKernelGGL(rows16_to_cols_kernel, grid1(M * tc), dim3(256), 0, ctx->stream, p->xw, half, M, tc, bout, M, badd, scale);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "blocked triangular solve", e);
@@ -1549,7 +1569,7 @@ static int precond_build_from(knm_ctx *ctx, int64_t M, const std::function<int(d
     p->A = p->buf ? p->buf + 2 : nullptr;
     if (e == hipSuccess) e = take(&p->Tdinv, nblk * p->sb * p->sb);
     if (e == hipSuccess) e = take(&p->Adinv, nblk * p->sb * p->sb);
-    if (e == hipSuccess) e = take(&p->xw, 2 * M * kSolveCols);
+    if (e == hipSuccess) e = take(&p->xw, 4 * M * kSolveCols);
     if (e == hipSuccess && M >= kProductSolveMinM) e = take(&p->blk, (int64_t)p->sb * p->sb);
     if (e != hipSuccess) {
         (void)hipGetLastError();
