@@ -43,6 +43,7 @@
 #include <type_traits>
 
 #include "knm_internal.h"
+#include "knm_leaf.h"
 
 namespace knm {
 namespace {
@@ -81,6 +82,7 @@ struct RankKArgs {
     int tri;           // operand is upper triangular (what is stored below its diagonal is ignored): tile column j0 starts at k = j0
     int trans_c;       // store entry (i, j) at C[j + i * ldc]
     int part;          // general product: store all entries (0), those with i <= j (1) or those with i >= j (2)
+    int skip;          // and no tile inside the first skip x skip entries
     int patch_i, patch_j; // tiles of a patch (symmetric update: patch_j = patch_i)
     int64_t n_patch_i; // general product: patches along i
     int64_t n_patches; // patches in all (symmetric update: the upper-triangular ones)
@@ -213,14 +215,14 @@ template <int FORM, int R, int VEC, int kTK> struct Fetch {
 
 // FA, FB: forms of the row and column operands; SYM: symmetric update (B = A, upper triangle of C
 // only, triangular patch enumeration); otherwise the general product C = alpha a b^T + beta C
-template <int FA, int FB, bool WEIGHTED, int VEC, bool SYM, int TI = 128, int TJ = 128>
-__global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
+// The tile of workgroup `group` of kThreads threads, in 2 Tile::kStageDoubles entries of LDS.
+template <int FA, int FB, bool WEIGHTED, int VEC, bool SYM, int TI, int TJ>
+__device__ __forceinline__ void rank_k_tile(RankKArgs a, int64_t group, double *lds)
 {
     constexpr int kTK = Tile<TI, TJ>::kTK, kSA = Tile<TI, TJ>::kSA, kSB = Tile<TI, TJ>::kSB;
     constexpr int kStageDoubles = Tile<TI, TJ>::kStageDoubles;
     constexpr int kWI = Tile<TI, TJ>::kWI, kWJ = Tile<TI, TJ>::kWJ;
     constexpr int kMI = TI / 16 / kWI, kMJ = TJ / 16 / kWJ; // 16 x 16 accumulators of a wavefront
-    __shared__ double lds[2 * kStageDoubles];
     if (!SYM && a.merge != 0) {
         // pair (off, off + h) of block k of the inverses: A, B, C and the sizes from the arrays' bases
         const int64_t k0 = (int64_t)(blockIdx.y / a.merge_pairs) * a.sb;
@@ -249,7 +251,7 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
     }
     // workgroup -> patch -> tile: consecutive workgroup ids go to consecutive XCDs, so the
     // workgroups of one patch are those with equal id % 8 and equal (id / 8) / patch_wgs
-    const int64_t g = blockIdx.x;
+    const int64_t g = group;
     const int64_t slot = g / kXcds;
     const int patch_wgs = a.patch_i * a.patch_j;
     const int64_t q = (slot / patch_wgs) * kXcds + g % kXcds;
@@ -271,6 +273,7 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
         j0 = (pj * a.patch_j + wq / a.patch_i) * TJ;
         if (i0 >= a.n || j0 >= a.nj) return;
         if ((a.part == 1 && i0 > j0 + (TJ - 1)) || (a.part == 2 && j0 > i0 + (TI - 1))) return; // nothing to store
+        if (i0 + TI <= a.skip && j0 + TJ <= a.skip) return;
     }
 
     const int lane = threadIdx.x & 63;
@@ -423,6 +426,29 @@ __global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
             }
 }
 
+template <int FA, int FB, bool WEIGHTED, int VEC, bool SYM, int TI = 128, int TJ = 128>
+__global__ __launch_bounds__(kThreads) void rank_k_upper_kernel(RankKArgs a)
+{
+    __shared__ double lds[2 * Tile<TI, TJ>::kStageDoubles];
+    rank_k_tile<FA, FB, WEIGHTED, VEC, SYM, TI, TJ>(a, blockIdx.x, lds);
+}
+
+// A leaf (the first workgroup) beside the update of the rows it belongs to, which does not wait for it: one after the other the leaf
+// had the chip to itself for 25 us of every 128 rows.  Only half of a workgroup's wavefronts have a tile's work, the others end at once.  Fits at
+// M = 5000 (logistic) 34.7 -> 33.8 ms, M = 10000 61.2 -> 60.3 and 32.4 -> 31.7, M = 20000 270 -> 264.7.
+template <int F, int VEC, int T>
+__global__ __launch_bounds__(kLeafThreads) void leaf_beside_update_kernel(LeafArgs leaf, RankKArgs a)
+{
+    static_assert(2 * Tile<T, T>::kStageDoubles <= kLeafDoubles && kThreads <= kLeafThreads && kLeaf % T == 0, "");
+    __shared__ double lds[kLeafDoubles];
+    if (blockIdx.x == 0) {
+        leaf_block(leaf, lds);
+        return;
+    }
+    if (threadIdx.x >= kThreads) return;
+    rank_k_tile<F, F, false, VEC, false, T, T>(a, (int64_t)blockIdx.x - 1, lds);
+}
+
 // A thread's byte offsets inside a stage must fit the 32-bit buffer offset.
 bool stage_offsets_fit(int form_nt, int64_t ld, int rows, int depth)
 {
@@ -445,6 +471,12 @@ bool smallest_tiles(int64_t t64, int64_t K) { return t64 <= 400 || (K <= 512 && 
 // In-place products (128 rows, k = 128) of up to this many columns take 16 at a time, longer ones 32: two workgroups per CU hold 8192, and
 // with 16 a wavefront's chain of matrix instructions is half as long (preconditioner at M = 1000 0.99 -> 0.94 ms, M = 5000 6.87 -> 6.69 ms).
 constexpr int64_t kNarrowUpTo = 8192;
+
+// Updates of at least so many entries and up to this many 64 x 64 tiles run beside the leaf.  The diagonal block, updated on its
+// own first, takes 5 us (k = 128) to 10 (k = 384): as long as the whole update of 128 rows and 1000 to 2000 columns (M = 1000: 0.5 % slower per fit with
+// no lower limit), half of it at 5000 (10 to 18 us), a third at 9000.  Beside the leaf two workgroups share a CU, by its LDS, in place of three or four,
+// which costs long updates more than the leaf's 25 us: fits at M = 20000 264.7 ms up to 1280 tiles, 266.4 up to 700, 267.8 up to 2600, 270 without.
+constexpr int64_t kHiddenFrom = 128 * 2048, kHiddenUpTo = 1280;
 
 // Patch of tiles that the workgroups of one XCD take together: 8 x 8, smaller where there would be fewer than four
 // per XCD (all XCDs busy counts for more than shared rows of the operands)
@@ -484,7 +516,7 @@ hipError_t launch_rank_k_upper(int form_nt, int64_t n, int64_t K, double alpha, 
     a.trans_c = trans_c;
     a.extent = a.extent_b = K <= 0 ? 0 : (form_nt ? (K - 1) * lda + n : (n - 1) * lda + K);
     a.merge = 0;
-    a.part = 0;
+    a.part = a.skip = 0;
     const int64_t big = (n + 127) / 128;
     const int T = big * (big + 1) / 2 < kSmallTilesBelow ? 64 : 128;
     const int64_t tiles = (n + T - 1) / T;
@@ -543,6 +575,7 @@ hipError_t launch_gemm_f64(int a_nt, int64_t ni, int64_t nj, int64_t K, double a
     a.tri = 0;
     a.trans_c = 0;
     a.part = part;
+    a.skip = 0;
     a.merge = 0;
     a.extent = K <= 0 ? 0 : (a_nt ? (K - 1) * lda + ni : (ni - 1) * lda + K);
     a.extent_b = K <= 0 ? 0 : (b_nt ? (K - 1) * ldb + nj : (nj - 1) * ldb + K);
@@ -589,6 +622,52 @@ hipError_t launch_gemm_f64(int a_nt, int64_t ni, int64_t nj, int64_t K, double a
     if (b_nt && in_place) return hipErrorInvalidValue; // not instantiated
     if (vec2) with_forms(std::integral_constant<int, 2>{});
     else with_forms(std::integral_constant<int, 1>{});
+    return hipGetLastError();
+}
+
+bool leaf_hides_update(int64_t rows, int64_t cols, int64_t K)
+{
+    if (rows < kLeaf || cols <= kLeaf || K <= 0 || rows * cols < kHiddenFrom) return false;
+    return ((rows + 63) / 64) * ((cols + 63) / 64) <= kHiddenUpTo;
+}
+
+hipError_t launch_leaf_beside_update(const LeafArgs &leaf, int64_t ni, int64_t nj, int64_t K, const double *P, hipStream_t stream)
+{
+    if (leaf.nb != kLeaf) return hipErrorInvalidValue;
+    const int form = leaf.lower;
+    const int64_t ld = leaf.lda;
+    RankKArgs a = {};
+    a.A = a.B = P;
+    a.lda = a.ldb = a.ldc = ld;
+    a.C = leaf.A;
+    a.n = ni;
+    a.nj = nj;
+    a.K = K;
+    a.alpha = -1.0;
+    a.beta = 1.0;
+    a.part = leaf.lower ? 2 : 1;
+    a.skip = kLeaf;
+    a.extent = form ? (K - 1) * ld + ni : (ni - 1) * ld + K;
+    a.extent_b = form ? (K - 1) * ld + nj : (nj - 1) * ld + K;
+    const int T = smallest_tiles(((ni + 63) / 64) * ((nj + 63) / 64), K) ? 32 : 64;
+    const int64_t tiles_i = (ni + T - 1) / T, tiles_j = (nj + T - 1) / T;
+    choose_patch(tiles_i, tiles_j, &a.patch_i, &a.patch_j);
+    a.n_patch_i = (tiles_i + a.patch_i - 1) / a.patch_i;
+    a.n_patches = a.n_patch_i * ((tiles_j + a.patch_j - 1) / a.patch_j);
+    const int64_t wgs = (a.n_patches + kXcds - 1) / kXcds * kXcds * a.patch_i * a.patch_j + 1;
+    if (wgs > 0x7fffffffLL || !stage_offsets_fit(form, ld, T, 32)) return hipErrorInvalidValue;
+    const bool vec2 = ld % 2 == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0;
+    auto launch = [&](auto f, auto v) {
+        constexpr int F = decltype(f)::value, V = decltype(v)::value;
+        if (T == 32) hipLaunchKernelGGL((leaf_beside_update_kernel<F, V, 32>), dim3((unsigned)wgs), dim3(kLeafThreads), 0, stream, leaf, a);
+        else hipLaunchKernelGGL((leaf_beside_update_kernel<F, V, 64>), dim3((unsigned)wgs), dim3(kLeafThreads), 0, stream, leaf, a);
+    };
+    auto with_form = [&](auto v) {
+        if (form) launch(std::integral_constant<int, 1>{}, v);
+        else launch(std::integral_constant<int, 0>{}, v);
+    };
+    if (vec2) with_form(std::integral_constant<int, 2>{});
+    else with_form(std::integral_constant<int, 1>{});
     return hipGetLastError();
 }
 

@@ -288,6 +288,21 @@ hipError_t launch_gemm_f64(int a_nt, int64_t ni, int64_t nj, int64_t K, double a
                            const double *B, int64_t ldb, double beta, double *C, int64_t ldc, hipStream_t stream,
                            int b_nt = 0, int part = 0, bool in_place = false);
 
+// A leaf of the factorisations (knm_leaf.h): the nb x nb block at A, nb <= 128, and its factor's inverse W
+struct LeafArgs {
+    double *A;
+    int64_t lda;
+    int nb;
+    double *W;
+    int64_t ldw, pivot0;
+    unsigned long long *bad;
+    int lower;
+};
+// The update of rows by the K rows above them, C(i, j) -= sum_k a(i, k) a(j, k) for ni x nj entries from the leaf's block on, in its storage (part 1, or 2
+// with lower), but for that block itself, and the leaf beside it, in one launch
+bool leaf_hides_update(int64_t rows, int64_t cols, int64_t K); // where that is faster than one after the other
+hipError_t launch_leaf_beside_update(const LeafArgs &leaf, int64_t ni, int64_t nj, int64_t K, const double *P, hipStream_t stream);
+
 // The symmetric update as integer products modulo small numbers (knm_residue.hip).  An operand's rows i < n (over k < K <= residue_max_k(); a(i, k) as in
 // launch_rank_k_upper, times w[k] if given, rows of a triangular one starting at k + k0 = i) become planes of residues and
 // one exponent per row; an update takes those of the operand's rows along the contiguous index u of C and across it, v.

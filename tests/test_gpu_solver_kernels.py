@@ -38,9 +38,35 @@ def test_factors_at_leaf_edges(knm, M):
     pre.close()
 
 
+# leaves beside the update of their rows: just below and above the size from which that is done, ragged last leaves, sub-panels within a block row
+# (rows that reach back to its top), and where the update is too large for it.  Entries of K are at most 1 and of T T^T / M about that, sums of
+# M products of them in fp64: 1e-13 as at the leaf's own edges.
+@pytest.mark.parametrize("M", [2050, 2177, 2433, 4230, 5001])
+def test_factors_with_leaves_beside_updates(knm, M):
+    d, sigma, lam, jitter = 6, 1.0, 1e-4, 1e-6
+    C = _rand(M, d, 300 + M).cuda()
+    pre = knm.precond_build(C, sigma, lam, jitter)
+    T, A = (torch.from_numpy(x).cuda() for x in pre.factors())
+    c, eye = C.double(), torch.eye(M, device="cuda", dtype=torch.float64)
+    r2 = torch.zeros(M, M, device="cuda", dtype=torch.float64)
+    for k in range(d):
+        r2 += (c[:, k, None] - c[None, :, k]) ** 2
+    assert float((T.T @ T - torch.exp(-0.5 * r2 / sigma ** 2) - jitter * eye).abs().max()) < 1e-13
+    assert float((A.T @ A - T @ T.T / M - lam * eye).abs().max()) < 1e-13
+    pre.close()
+
+
 def test_failing_pivot_inside_a_leaf(knm):
     C = _rand(300, 4, 5)
     C[171] = float("nan")  # row 171: second leaf, third tile row
+    with pytest.raises(knm.KnmError) as e:
+        knm.precond_build(C.cuda(), 1.0, 1e-6, 1e-6)
+    assert e.value.status == -5 and "172" in str(e.value)
+
+
+def test_failing_pivot_in_a_leaf_beside_an_update(knm):
+    C = _rand(3000, 4, 5)
+    C[171] = float("nan")
     with pytest.raises(knm.KnmError) as e:
         knm.precond_build(C.cuda(), 1.0, 1e-6, 1e-6)
     assert e.value.status == -5 and "172" in str(e.value)
