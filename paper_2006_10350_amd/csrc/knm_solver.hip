@@ -599,6 +599,75 @@ __global__ __launch_bounds__(256) void cg_direction_kernel(int64_t M, const doub
     if (blockIdx.x == 0 && threadIdx.x == 0) rho_next[c] = rn;
 }
 
+// All three steps after an application of the operator, one workgroup per column, for M up to kCgAtOnce: 1024 blocks entries, four per
+// thread, in the same partials and order as dot_partial_kernel, cg_step_kernel and cg_direction_kernel.  Bound by latency: M = 1000 5 us in place of 9
+// and two gaps between launches.  Longer vectors are more than a CU brings in as fast as the chip.
+constexpr int64_t kCgAtOnce = 4096;
+__global__ __launch_bounds__(1024) void cg_update_kernel(int64_t M, const double *__restrict__ rho, double *__restrict__ rho_next,
+                                                        double *__restrict__ p, const double *__restrict__ q, double *__restrict__ b,
+                                                        double *__restrict__ r)
+{
+    __shared__ double sh[2][4][4], part[2][4];
+    const int64_t c = blockIdx.x;
+    const int wave = threadIdx.x >> 6, blocks = blockDim.x >> 8;
+    double pv[4], qv[4], rv[4], bv[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int64_t i = threadIdx.x + (int64_t)blockDim.x * k, j = c * M + (i < M ? i : 0);
+        pv[k] = p[j];
+        qv[k] = q[j];
+        rv[k] = r[j];
+        bv[k] = b[j];
+    }
+    auto total = [&](int which, double s) { // of every thread's s, as block_sum and partials_sum have it
+        s = wave_sum(s);
+        if ((threadIdx.x & 63) == 0) sh[which][wave >> 2][wave & 3] = s;
+        __syncthreads();
+        const double *const w = sh[which][threadIdx.x & 3];
+        if (threadIdx.x < (unsigned)blocks) part[which][threadIdx.x] = (w[0] + w[1]) + (w[2] + w[3]);
+        __syncthreads();
+        return partials_sum(part[which], blocks);
+    };
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (threadIdx.x + (int64_t)blockDim.x * k < M) s += pv[k] * qv[k];
+    const double pq = total(0, s);
+    const double a = (pq != 0.0) ? rho[c] / pq : 0.0;
+    s = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        rv[k] = rv[k] - a * qv[k];
+        if (threadIdx.x + (int64_t)blockDim.x * k < M) s += rv[k] * rv[k];
+    }
+    const double rn = total(1, s);
+    const double e = (rho[c] != 0.0) ? rn / rho[c] : 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int64_t i = threadIdx.x + (int64_t)blockDim.x * k;
+        if (i >= M) continue;
+        b[c * M + i] = bv[k] + a * pv[k];
+        r[c * M + i] = rv[k];
+        p[c * M + i] = rv[k] + e * pv[k];
+    }
+    if (threadIdx.x == 0) rho_next[c] = rn;
+}
+
+// The steps of CG after an application of the operator: q = H p in hand, rho = r . r
+void launch_cg_update(hipStream_t stream, int64_t M, int t, const double *rho, double *rho_next, double *p, const double *q, double *b, double *r,
+                      double *part_pq, double *part_rr)
+{
+    const int blocks = red_blocks(M);
+    const dim3 vgrid((unsigned)blocks, (unsigned)t), vblock(256);
+    if (M <= kCgAtOnce) {
+        hipLaunchKernelGGL(cg_update_kernel, dim3((unsigned)t), dim3(256u * blocks), 0, stream, M, rho, rho_next, p, q, b, r);
+        return;
+    }
+    hipLaunchKernelGGL(dot_partial_kernel, vgrid, vblock, 0, stream, p, q, M, part_pq);
+    hipLaunchKernelGGL(cg_step_kernel, vgrid, vblock, 0, stream, M, rho, part_pq, p, q, b, r, part_rr);
+    hipLaunchKernelGGL(cg_direction_kernel, vgrid, vblock, 0, stream, M, rho, rho_next, part_rr, r, p);
+}
+
 // y32 <- (y += x) rounded
 __global__ void add_round_kernel(int64_t n, const double *__restrict__ x, double *__restrict__ y, float *__restrict__ y32)
 {
@@ -1610,9 +1679,7 @@ static int fit_core(knm_ctx *ctx, const KernelOps &ops, knm_precond *p, const fl
         st = linop_cols(ctx, p, wk, ops, lambda, dp, t, dq);
         if (st) return st;
         const double *now = rho + (size_t)it * t;
-        hipLaunchKernelGGL(dot_partial_kernel, vgrid, vblock, 0, ctx->stream, dp, dq, M, part_pq);
-        hipLaunchKernelGGL(cg_step_kernel, vgrid, vblock, 0, ctx->stream, M, now, part_pq, dp, dq, db, dr, part_rr);
-        hipLaunchKernelGGL(cg_direction_kernel, vgrid, vblock, 0, ctx->stream, M, now, rho + (size_t)(it + 1) * t, part_rr, dr, dp);
+        launch_cg_update(ctx->stream, M, t, now, rho + (size_t)(it + 1) * t, dp, dq, db, dr, part_pq, part_rr);
     }
     // alpha = T^-1 A^-1 beta
     st = tri_solve(ctx, p, p->A, p->Adinv, false, db, wk.v.as<double>(), t);
@@ -1818,9 +1885,7 @@ static int logfalkon_core(knm_ctx *ctx, const KernelOps &ops, const std::functio
         for (int it = 0; it < iters[k]; ++it) {
             st = linop_cols(ctx, p, wk, ops, mu, dp, 1, dq, dw.as<float>());
             if (st) return st;
-            hipLaunchKernelGGL(dot_partial_kernel, vgrid, vblock, 0, ctx->stream, dp, dq, M, part_pq);
-            hipLaunchKernelGGL(cg_step_kernel, vgrid, vblock, 0, ctx->stream, M, rho + it, part_pq, dp, dq, db, dr, part_rr);
-            hipLaunchKernelGGL(cg_direction_kernel, vgrid, vblock, 0, ctx->stream, M, rho + it, rho + it + 1, part_rr, dr, dp);
+            launch_cg_update(ctx->stream, M, 1, rho + it, rho + it + 1, dp, dq, db, dr, part_pq, part_rr);
         }
         // alpha += T^-1 A^-1 beta
         st = tri_solve(ctx, p, p->A, p->Adinv, false, db, wk.v.as<double>(), 1);
