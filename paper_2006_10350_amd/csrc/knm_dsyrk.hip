@@ -468,6 +468,11 @@ constexpr int64_t kSmallTilesBelow = 1024;
 // 512 rows, k = 512: 2500 columns 44.5 and 34.3, 5000 (632) 62.9 and 62.6, 8700 (1088) 98.9 and 114.7.
 bool smallest_tiles(int64_t t64, int64_t K) { return t64 <= 400 || (K <= 512 && t64 <= 640); }
 
+// Triangular products of up to this many 64 x 64 tiles (n = 1400) take 32 x 32 ones: a tile that starts at k = 0 is one chain over the whole of k, which
+// a quarter of the matrix instructions and twice the depth of a stage make half as long (n = 1000: 46 -> 23 us).  The trailing updates of the
+// factorisations run behind other work and lose by it (0.2 % of a fit).
+constexpr int64_t kSmallestUpTo = 256;
+
 // In-place products (128 rows, k = 128) of up to this many columns take 16 at a time, longer ones 32: two workgroups per CU hold 8192, and
 // with 16 a wavefront's chain of matrix instructions is half as long (preconditioner at M = 1000 0.99 -> 0.94 ms, M = 5000 6.87 -> 6.69 ms).
 constexpr int64_t kNarrowUpTo = 8192;
@@ -518,7 +523,8 @@ hipError_t launch_rank_k_upper(int form_nt, int64_t n, int64_t K, double alpha, 
     a.merge = 0;
     a.part = a.skip = 0;
     const int64_t big = (n + 127) / 128;
-    const int T = big * (big + 1) / 2 < kSmallTilesBelow ? 64 : 128;
+    const int64_t half = (n + 63) / 64;
+    const int T = big * (big + 1) / 2 >= kSmallTilesBelow ? 128 : tri && half * (half + 1) / 2 <= kSmallestUpTo ? 32 : 64;
     const int64_t tiles = (n + T - 1) / T;
     choose_patch((tiles + 1) / 2, tiles, &a.patch_i, &a.patch_j); // half of the square of tiles
     if (a.patch_j < a.patch_i) a.patch_i = a.patch_j;
@@ -536,7 +542,8 @@ hipError_t launch_rank_k_upper(int form_nt, int64_t n, int64_t K, double alpha, 
     auto launch = [&](auto form, auto weighted, auto vec) {
         constexpr int F = decltype(form)::value, V = decltype(vec)::value;
         constexpr bool WT = decltype(weighted)::value;
-        if (T == 64) hipLaunchKernelGGL((rank_k_upper_kernel<F, F, WT, V, true, 64, 64>), grid, block, 0, stream, a);
+        if (T == 32) hipLaunchKernelGGL((rank_k_upper_kernel<F, F, WT, V, true, 32, 32>), grid, block, 0, stream, a);
+        else if (T == 64) hipLaunchKernelGGL((rank_k_upper_kernel<F, F, WT, V, true, 64, 64>), grid, block, 0, stream, a);
         else hipLaunchKernelGGL((rank_k_upper_kernel<F, F, WT, V, true>), grid, block, 0, stream, a);
     };
     auto with_vec = [&](auto form, auto weighted) {

@@ -135,3 +135,9 @@ def test_block_product_matches_definition(knm, ni, nj, k, a_nt):
     torch.cuda.synchronize()
     ref = 2.0 * a @ b.T
     assert np.abs(Cn.cpu().numpy().T - ref).max() <= 1e-13 * np.abs(ref).max() * max(k, 8)
+
+
+# 32 x 32 tiles: less than one, remainders, and the largest that takes them (1408: 64 x 64 up from 1409)
+@pytest.mark.parametrize("n", [31, 33, 97, 1000, 1408, 1409])
+def test_triangular_operand_in_small_tiles(knm, n):
+    test_triangular_operand_and_overwrite(knm, n)
