@@ -254,29 +254,32 @@ __global__ __launch_bounds__(256) void diag_apply_kernel(const double *__restric
 }
 
 constexpr int kPanelWaves = 16; // wavefronts of a panel_update_n workgroup, sharing the columns
-constexpr int kPanelRows = 32;  // rows of a panel_update_n workgroup, two per lane
-constexpr int kPanelCols = 4;   // columns of one panel_update_t wavefront
+// Rows of a panel_update_n workgroup: 32, and 16 up to this many, which would be at most 64 workgroups of 32 (2048 x 2048: 17.7 -> 12.9 us; 4096 rows
+// the same, 6144 21.9 -> 29.5).
+constexpr int64_t kPanelShortUpTo = 2048;
 
 // b[r] = src[r] - sum_j P[r + (k0 + j) ld] x[j] for r in [r_lo, r_hi)  (x = the solved block, nbk entries; src: the
 // right-hand side so far, b itself from the second block on): the rows above the block of an upper-storage factor
 // in its plain solve, the rows below the block of a lower-storage factor in its transposed solve.  ld and r_lo even, R 16-byte
-// aligned, column entries up to the next even row readable.  16 lanes take 32 rows of a column, the four lane groups of 16
-// wavefronts 64 columns at a time, eight loads in flight each: with 64 rows per workgroup of 8 wavefronts an update of 3000 rows
+// aligned, column entries up to the next even row readable.  ROWS / 2 lanes take ROWS rows of a column, the lane groups of
+// 16 wavefronts 64 columns (of 32 rows) at a time, eight loads in flight each: with 64 rows per workgroup of 8 wavefronts an update of 3000 rows
 // had 46 workgroups.
+template <int ROWS>
 __global__ __launch_bounds__(kPanelWaves * 64) void panel_update_n_kernel(const double *__restrict__ R, int64_t M,
                                                                          int64_t k0, int nbk, int64_t r_lo,
                                                                          int64_t r_hi, const double *__restrict__ x,
                                                                          const double *src, double *b)
 {
-    __shared__ double part[kPanelWaves][kPanelRows];
+    __shared__ double part[kPanelWaves][ROWS];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int l15 = lane & 15, q = lane >> 4;
-    const int64_t r = r_lo + (int64_t)blockIdx.x * kPanelRows + 2 * l15;
+    constexpr int kLanes = ROWS / 2, kGroups = 64 / kLanes; // lanes along a column, columns at a time
+    const int l = lane % kLanes, q = lane / kLanes;
+    const int64_t r = r_lo + (int64_t)blockIdx.x * ROWS + 2 * l;
     const double *p = R + (r < r_hi ? r : r_lo) + k0 * M;
-    constexpr int kStep = 4 * kPanelWaves;
+    constexpr int kStep = kGroups * kPanelWaves;
     double s0 = 0.0, s1 = 0.0;
-    for (int j0 = 4 * w + q; j0 < nbk; j0 += 8 * kStep) {
+    for (int j0 = kGroups * w + q; j0 < nbk; j0 += 8 * kStep) {
         solve_d2 a[8];
         double xv[8];
 #pragma unroll
@@ -292,17 +295,18 @@ __global__ __launch_bounds__(kPanelWaves * 64) void panel_update_n_kernel(const 
                 s1 = fma(a[u][1], xv[u], s1);
             }
     }
-    s0 += __shfl_xor(s0, 32);
-    s1 += __shfl_xor(s1, 32);
-    s0 += __shfl_xor(s0, 16);
-    s1 += __shfl_xor(s1, 16);
+#pragma unroll
+    for (int m = 32; m >= kLanes; m >>= 1) {
+        s0 += __shfl_xor(s0, m);
+        s1 += __shfl_xor(s1, m);
+    }
     if (q == 0) {
-        part[w][2 * l15] = s0;
-        part[w][2 * l15 + 1] = s1;
+        part[w][2 * l] = s0;
+        part[w][2 * l + 1] = s1;
     }
     __syncthreads();
-    const int64_t row = r_lo + (int64_t)blockIdx.x * kPanelRows + threadIdx.x;
-    if (threadIdx.x < kPanelRows && row < r_hi) {
+    const int64_t row = r_lo + (int64_t)blockIdx.x * ROWS + threadIdx.x;
+    if (threadIdx.x < ROWS && row < r_hi) {
         double s = 0.0;
 #pragma unroll
         for (int u = 0; u < kPanelWaves; ++u) s += part[u][threadIdx.x];
@@ -312,40 +316,38 @@ __global__ __launch_bounds__(kPanelWaves * 64) void panel_update_n_kernel(const 
 
 // b[j] = src[j] - sum_i P[(k0 + i) + j ld] x[i] for j in [j0, j1)  (x = the solved block, nbk entries): the
 // columns right of the block of an upper-storage factor in its transposed solve, the columns left of
-// the block of a lower-storage factor in its plain solve.  One wavefront per kPanelCols columns, lanes
-// along the rows.
-__global__ __launch_bounds__(256) void panel_update_t_kernel(const double *__restrict__ R, int64_t M, int64_t k0,
-                                                            int nbk, int64_t j0, int64_t j1,
-                                                            const double *__restrict__ x, const double *src, double *b)
+// the block of a lower-storage factor in its plain solve.  One wavefront per column, lanes along the rows, 1024 entries in flight as in
+// diag_apply_kernel; R 16-byte aligned, ld and k0 even, column entries up to the next even row readable.  Four columns per wavefront, 8-byte loads
+// of 256 entries of each in flight, were too few wavefronts for a short panel (2048 x 2048 14.3 us, 8.7 now; 2048 x 10240 37.1, 32.3) and no faster
+// for a long one.
+__global__ __launch_bounds__(256) void panel_update_t_kernel(const double *__restrict__ R, int64_t M, int64_t k0, int nbk, int64_t j0, int64_t j1,
+                                                                  const double *__restrict__ x, const double *src, double *b)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t jb = j0 + wave * kPanelCols;
-    if (jb >= j1) return;
-    const double *p[kPanelCols];
-    double s[kPanelCols];
+    const int64_t j = j0 + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (j >= j1) return;
+    const double *p = R + k0 + j * M;
+    constexpr int kFlight = 8;
+    double s0 = 0.0, s1 = 0.0;
+    for (int i0 = 2 * lane; i0 < nbk; i0 += 128 * kFlight) {
+        solve_d2 a[kFlight];
+        double x0[kFlight], x1[kFlight];
 #pragma unroll
-    for (int c = 0; c < kPanelCols; ++c) {
-        const int64_t j = (jb + c < j1) ? jb + c : j1 - 1; // a clamped column is computed and dropped
-        p[c] = R + k0 + j * M;
-        s[c] = 0.0;
-    }
-    int i = lane;
-    for (; i + 64 < nbk; i += 128) {
-        const double x0 = x[i], x1 = x[i + 64];
+        for (int u = 0; u < kFlight; ++u) { // (an entry past the end is taken from the column's first pair and dropped)
+            const int i = i0 + 128 * u, ia = i < nbk ? i : 0;
+            a[u] = *reinterpret_cast<const solve_d2 *>(p + ia);
+            x0[u] = x[ia];
+            x1[u] = x[ia + 1 < nbk ? ia + 1 : 0];
+        }
 #pragma unroll
-        for (int c = 0; c < kPanelCols; ++c) s[c] += p[c][i] * x0 + p[c][i + 64] * x1;
+        for (int u = 0; u < kFlight; ++u) {
+            const int i = i0 + 128 * u;
+            if (i < nbk) s0 = fma(a[u][0], x0[u], s0);
+            if (i + 1 < nbk) s1 = fma(a[u][1], x1[u], s1);
+        }
     }
-    if (i < nbk) {
-        const double x0 = x[i];
-#pragma unroll
-        for (int c = 0; c < kPanelCols; ++c) s[c] += p[c][i] * x0;
-    }
-#pragma unroll
-    for (int c = 0; c < kPanelCols; ++c) {
-        const double tot = wave_sum(s[c]);
-        if (lane == 0 && jb + c < j1) b[jb + c] = src[jb + c] - tot;
-    }
+    const double s = wave_sum(s0 + s1);
+    if (lane == 0) b[j] = src[j] - s;
 }
 
 // 2 to 16 right-hand sides: the same steps as skinny products on the fp64 matrix cores, still bound by the
@@ -846,12 +848,14 @@ int tri_solve(knm_ctx *ctx, const knm_precond *p, const double *R, const double 
                                trans ? 0 : 1, b + k0, sol + k0, badd != nullptr ? badd + k0 : nullptr, scale,
                                badd != nullptr ? bout + k0 : nullptr, out32 != nullptr ? out32 + k0 : nullptr);
             if (hi == lo) continue;
+            auto panel = [&](auto kernel, int outs, int threads) { // outs: of a workgroup
+                hipLaunchKernelGGL(kernel, dim3((unsigned)((hi - lo + outs - 1) / outs)), dim3(threads), 0, ctx->stream, R, ld, k0, nbk, lo, hi, sol + k0, b,
+                                   work);
+            };
             if (trans == lower)
-                hipLaunchKernelGGL(panel_update_n_kernel, dim3((unsigned)((hi - lo + kPanelRows - 1) / kPanelRows)),
-                                   dim3(kPanelWaves * 64), 0, ctx->stream, R, ld, k0, nbk, lo, hi, sol + k0, b, work);
+                hi - lo <= kPanelShortUpTo ? panel(panel_update_n_kernel<16>, 16, kPanelWaves * 64) : panel(panel_update_n_kernel<32>, 32, kPanelWaves * 64);
             else
-                hipLaunchKernelGGL(panel_update_t_kernel, dim3((unsigned)((hi - lo + 4 * kPanelCols - 1) / (4 * kPanelCols))),
-                                   dim3(256), 0, ctx->stream, R, ld, k0, nbk, lo, hi, sol + k0, b, work);
+                panel(panel_update_t_kernel, 4, 256);
         }
         if (tc > 1)
             hipLaunchKernelGGL(rows16_to_cols_kernel, grid1(M * tc), dim3(256), 0, ctx->stream, p->xw, half, M, tc, bout, M, badd, scale);
