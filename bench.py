@@ -283,7 +283,8 @@ def product_leg(knm, synth, torch, ctx, w, steps: int, warmup: int, cross: str, 
     flop_per_launch = entries * 2.0 * w.d
     tflops = flop_per_launch / (avg_launch_ms * 1e-3) / 1e12
     default = kernel == "gaussian"
-    traffic, mfma_insts = counters(w.name + ("" if f16 else "_f32")) if default else (None, None)
+    # (no counters have been taken of the sums over many columns)
+    traffic, mfma_insts = counters(w.name + ("" if f16 else "_f32")) if default and not many else (None, None)
     roofline = {
         "bound": "mfma",
         "kernel": kernel_name + (" + kept_many_kernel" if many else " + kept_rows_kernel" if once else ""),
