@@ -233,8 +233,12 @@ def forms_values_once(w, cross: str, kernel: str) -> bool:
 
 
 def sums_many_columns(w, cross: str, kernel: str) -> bool:
-    """The same for products with more columns, whose sums over the kept values run on the f16 matrix cores (same rule as the library)."""
+    """The same for products with more columns, whose sums over the kept values run on the f16 matrix cores, as those of the sweeps of
+    every column group do (same rule as the library)."""
     least = 450 if w.t <= 32 else 320 if w.t <= 64 else 210 if w.t <= 128 else 180
+    last = (w.t - 1) % 160 + 1
+    if last <= 16 and not (last >= 8 and 4 * (3 + last) >= 3 * ((w.d + 15) // 16) + 1):
+        return False
     if cross != "f16x3" or kernel != "gaussian" or w.t <= 12 or w.d < least or float(w.n) * w.M < 1e8:
         return False
     rows = (4 << 30) // (256 * 4 * ((w.M + 127) // 128 * 128)) * 256

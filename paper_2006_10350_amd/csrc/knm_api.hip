@@ -686,10 +686,14 @@ constexpr int64_t kKeepSlabRows = 1024;          // rows of a slab at least, whe
 // 0.75 + 0.0055 d and 1.05 + 0.0061 d: they meet at d = 293, 260, 180 and 140.  The lines lie beyond, for rows of zeros, whose sweeps are up to a
 // fifth faster, and for few centres, whose launches and partials count: 13 columns at d = 320 1.14 times as fast at 200k x 8000 and 0.96 with rows of
 // zeros, 0.94 and 0.87 at 300k x 500; above the lines 1.06 to 1.36 at the line, 1.25 to 1.58 with 30 columns at d = 784, 1.7 to 2 with 200 at 440.
+// Only where the sweeps' own sums run on the matrix cores, in every launch: 13 to 16 columns from 337 to 401 features on, and what a multiple of 160
+// leaves, are summed by the vector ALU there, without the halves of values and vectors, and this kernel's sums are up to 1.7 (W) and 4.2 (U) times
+// as far from 64 bits (d = 450, 13 columns; d = 784, 16); with matrix-core sums on both sides 0.99 to 1.01 times.
 static bool keeping_many_pays(int64_t n, int64_t M, int d, int t)
 {
     const int least = t <= 32 ? 450 : t <= 64 ? 320 : t <= 128 ? 210 : 180;
-    return t > kept_rows_max_t() && d >= least && (double)n * (double)M >= 1.0e8;
+    const int last = (t - 1) % kept_many_max_t() + 1; // columns of the last launch
+    return t > kept_rows_max_t() && d >= least && gemm_f16_matrix_reduction(d, last) && (double)n * (double)M >= 1.0e8;
 }
 static int64_t product_keep_rows(int64_t n, int64_t M, int d, int t, int cross_term, int kind)
 {
