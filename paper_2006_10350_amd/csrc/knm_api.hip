@@ -366,8 +366,8 @@ static int64_t choose_chunks_compact(int64_t nF, int64_t nS, int d, int t, int c
 // at d = 50, 100, 200, 440 and 784, 1 and 10 columns, 60k x 10k, 300k x 3k and 15k x 15k points, both sweeps: within 2 % in 59 of
 // 60, 4.7 % in one.  n = 60k, d = 784, M = 10k, 10 columns ran
 // 1175 workgroups of 16 tiles on 512 places: 2.48 ms per sweep, 2.0 ms cut finer.
-// (any_length: the choice by time alone, whatever the length of fp32 sums)
-static int64_t choose_chunks_by_time(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind, bool any_length, int64_t *chunk_len)
+// (any_length: the choice by time alone, whatever the length of fp32 sums; parts: of the engine that has fp32 numbers in three parts)
+static int64_t choose_chunks_by_time(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind, bool any_length, bool parts, int64_t *chunk_len)
 {
     const bool gemm = use_gemm_engine(d, t, cross_term, kind);
     const bool f16 = cross_term == KNM_CROSS_F16X3;
@@ -393,7 +393,6 @@ static int64_t choose_chunks_by_time(int64_t nF, int64_t nS, int d, int t, int c
         uneven = 0.4;
     } else {
         if (f16) per_cu = f16_workgroups_per_cu(d, kind);
-        const bool parts = !f16 && packs_images(nF, nS, d, t, cross_term, kind);
         if (parts) per_cu = b16_workgroups_per_cu(d);
         const double ps = (f16 ? (d <= 12 ? 0.106 : d <= 28 ? 0.167 : 0.22) : parts ? 0.085 + 0.0075 * d : 0.12 + 0.019 * d) *
                           (kind == KNM_KERNEL_GAUSSIAN ? 1.0 : 1.6);
@@ -408,7 +407,14 @@ static int64_t choose_chunks_by_time(int64_t nF, int64_t nS, int d, int t, int c
     // matrix-core reduction cut into 1 chunk in place of 16 the error of W against 64 bits went from 2.7e-7 to 3.1e-5
     // (n = 4.6M, M = 90k, 19 columns, v >= 0), and from 2.5e-7 to 4.4e-7 in U at n = 120k, M = 20k, 144 columns
     const bool fp32_sums = !gemm || (f16 ? gemm_f16_fp32_sums(d, t, kind) : gemm_fp32_sums(t));
-    const int64_t least = fp32_sums && !any_length && most > g.min_chunks ? most : g.min_chunks;
+    int64_t least = fp32_sums && !any_length && most > g.min_chunks ? most : g.min_chunks;
+    if (parts && !any_length) {
+        // no longer than the fp32 MFMA engine has them either: where it cut 3000 points into 6 chunks and this one would into 2 (d = 13, 120000 rows),
+        // errors of W against 64 bits were up to 1.5 and of U up to 2 times those of that engine
+        int64_t fp32_len = 0;
+        const int64_t fp32_chunks = choose_chunks_by_time(nF, nS, d, t, cross_term, kind, false, false, &fp32_len);
+        if (fp32_chunks > least) least = fp32_chunks;
+    }
     const int64_t by_bytes = (int64_t)(((size_t)48 << 20) / (sizeof(float) * (size_t)nF * t));
     if (by_bytes > most) most = by_bytes;
     double best = 0.0;
@@ -448,9 +454,17 @@ static int64_t choose_chunks_by_time(int64_t nF, int64_t nS, int d, int t, int c
     return (g.stages + len - 1) / len;
 }
 
+static bool three_parts(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind)
+{
+    return cross_term != KNM_CROSS_F16X3 && packs_images(nF, nS, d, t, cross_term, kind);
+}
+int64_t choose_chunks_for(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind, bool parts, int64_t *chunk_len)
+{
+    return choose_chunks_by_time(nF, nS, d, t, cross_term, kind, false, parts, chunk_len);
+}
 int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind, int64_t *chunk_len)
 {
-    return choose_chunks_by_time(nF, nS, d, t, cross_term, kind, false, chunk_len);
+    return choose_chunks_for(nF, nS, d, t, cross_term, kind, three_parts(nF, nS, d, t, cross_term, kind), chunk_len);
 }
 
 static bool bad_geom(const void *X, int64_t n, int d, int64_t ldx, const void *C, int64_t M, int64_t ldc,
@@ -907,7 +921,9 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
         auto choose = [&] {
             chunks = choose_chunks(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
             if (!fits()) chunks = choose_chunks_compact(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
-            if (!fits()) chunks = choose_chunks_by_time(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, true, &chunk_len);
+            if (!fits())
+                chunks = choose_chunks_by_time(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, true,
+                                               three_parts(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind), &chunk_len);
             if (!fits()) chunks = choose_chunks_compact(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len); // refused below
             return fits();
         };

@@ -457,6 +457,8 @@ struct ShareScope {
 bool use_gemm_engine(int d, int t, int cross_term, int kind);
 // number of stream chunks for a sweep over nS stream points against nF fixed points
 int64_t choose_chunks(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind, int64_t *chunk_len);
+// the same with the engine given that takes a sweep of the fp32 mode: three-part numbers or fp32 MFMA
+int64_t choose_chunks_for(int64_t nF, int64_t nS, int d, int t, int cross_term, int kind, bool parts, int64_t *chunk_len);
 int do_knm_v(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx, const float *C, int64_t M,
              int64_t ldc, float sigma, const float *V, int t, float *W);
 // U = K^T (wgt .* W) as fp32 rows (U) or, if U64 is not null, as fp64 rows (M x t, row-major) that

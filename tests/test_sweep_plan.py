@@ -30,6 +30,14 @@ def plan():
             return choose(nF, nS, d, t, cross, kind, ctypes.byref(length)), length.value
 
         @staticmethod
+        def fp32_mfma_chunks(nF, nS, d):
+            length = ctypes.c_int64()
+            chunks = lib._ZN3knm17choose_chunks_forElliiiibPl
+            chunks.restype = ctypes.c_int64
+            chunks.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_bool, ctypes.c_void_p]
+            return chunks(nF, nS, d, 1, F32, GAUSSIAN, False, ctypes.byref(length)), length.value
+
+        @staticmethod
         def engine(d, t, cross, kind):
             """(K-loop engine?, points per stage, fixed points per block, sums through a chunk in fp32?)"""
             if lib._ZN3knm15use_gemm_engineEiiii(d, t, cross, kind) & 1:
@@ -71,6 +79,16 @@ def test_chunks_cover_the_stream_within_their_bounds(plan):
             assert length <= compact, shape
         if 4 * chunks * nF * t > 48 << 20:
             assert chunks <= max(-(-nS // compact), 1), shape
+
+
+def test_sums_of_three_part_products_are_no_longer_than_the_fp32_engines(plan):
+    rng = random.Random(4)
+    shapes = [(120_000, 3000), (3000, 120_000), (40_000, 9000), (9000, 40_000), (1_000_003, 20_001), (20_001, 1_000_003)]
+    shapes += [tuple(int(10 ** rng.uniform(2, 7.2)) for _ in range(2)) for _ in range(500)]
+    for nF, nS in shapes:
+        for d in range(1, 18):
+            chunks, length = plan.chunks(nF, nS, d, 1, F32, GAUSSIAN)
+            assert length <= plan.fp32_mfma_chunks(nF, nS, d)[1], (nF, nS, d)
 
 
 def test_every_workgroup_pair_is_taken_once(tmp_path):
