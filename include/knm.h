@@ -289,7 +289,7 @@ int falkon_predict(knm_ctx *ctx, const float *Xtest, int64_t ntest, int d, int64
  *                   d <= 44 with t = 1, at most 8 GiB otherwise.
  *   KNM_CROSS_F32   fp32 products: no range limits.  fp32 MFMA on the unsplit features, 3 to 5 times
  *                   slower (fp32 MFMA and the exp/FMA work share the vector ALU's issue); large
- *                   products of the Gaussian kernel with one column and up to 16 features form them
+ *                   products of the Gaussian kernel with one column and up to 14 features form them
  *                   exactly from three bf16 parts per feature on the bf16 matrix cores, at half of the
  *                   fp32 MFMA's error and 1.2 to 1.5 times the time of the split-fp16 ones, with a
  *                   workspace as above. */

@@ -1,17 +1,18 @@
 // Gaussian-kernel tile engine with the fp32 cross term on the bf16 matrix cores:
-//     out[f] = sum_s k(F_f, S_s) vec[s]          (KNM_CROSS_F32, d <= 16, one column per launch)
+//     out[f] = sum_s k(F_f, S_s) vec[s]          (KNM_CROSS_F32, d <= 14, one column per launch)
 //
 // Same computation as knm_tile.hip, whose fp32 MFMA shares the vector ALU's issue with the exp/FMA work that finishes every
 // kernel value, so that its time is that of both.  A bf16 MFMA has 16 times the rate and runs beside the vector ALU.
-// bf16 has the exponents of fp32 and 8 bits of its 24, so an fp32 number is the sum of three of them, rounded to nearest each
-// time, whatever its magnitude: z = z1 + z2 + z3 exactly, |z2| <= 2^-8 |z|, |z3| <= 2^-16 |z|, and nothing has to be clamped.  Of the nine products of
-// two such sums the six with
+// bf16 has the exponents of fp32 and 8 bits of its 24, so a number is the sum of three of them, rounded to nearest each
+// time, whatever its magnitude and to 2^-27 of it: z = z1 + z2 + z3, |z2| <= 2^-9 |z|, |z3| <= 2^-18 |z|, and nothing has to be clamped.  Of the nine
+// products of two such sums the six with
 //     f1 x1, f1 x2, f2 x1, f2 x2, f1 x3, f3 x1
-// are formed (exactly, and added in fp32); f2 x3, f3 x2 and f3 x3 are below 2^-24 of f x, a rounding that fp32 would make
-// as well, and of either sign.  The exponent log2 k = <zf, zx> - |zf|^2 / 2 - |zx|^2 / 2 of z = x sqrt(log2 e) / sigma takes 6 contraction slots per
+// are formed (exactly, and added in fp32); f2 x3, f3 x2 and f3 x3 are below 2^-26 of f x together, a quarter of the
+// rounding of an fp32 number, and of either sign.  The exponent log2 k = <zf, zx> - |zf|^2 / 2 - |zx|^2 / 2 of z = x sqrt(log2 e) / sigma takes 6 contraction slots per
 // feature and 8 for the two norm terms, 16 slots to an MFMA: 4 MFMAs of 32 cycles per 32 x 32 tile at d = 9, where fp32 has 7 of 64.
-// 1M x 20k, d = 9: 11.7 -> 5.1 ms per product, d = 4 6.7 -> 3.8, d = 14 13.5 -> 6.8.  Error against 64 bits over d = 1 to 16, normal and tabular rows,
-// three sigmas (100k x 4k, geometric means): W 0.65 and U 0.55 times that of the fp32 MFMA engine.
+// 1M x 20k, d = 9: 11.7 -> 5.1 ms per product, d = 4 6.7 -> 3.8, d = 14 13.5 -> 6.8.  Error against 64 bits relative to that of the fp32 MFMA engine, over
+// d = 1 to 14, normal rows and half whole-valued, half skewed ones, three sigmas, vectors of either sign and positive ones, 120000 x 3000 and 40000 x 9000: W
+// 0.56 and U 0.34 (geometric means), at most 1.05 (W, d = 5, 40000 x 9000) and 1.04 (U, d = 12, 2.6e-8: the rounding of the result).
 // Bound by the exp/FMA work of the vector ALU and the matrix cores beside it, which overlap in part: 256 clocks of MFMA and 384 of
 // exp/FMA per pair of tiles take 630 at d = 9.
 //
@@ -38,22 +39,27 @@ constexpr int waves_of(int nm) { return nm <= 4 ? 3 : 2; } // wavefronts per SIM
 // MFMAs of a tile: 16 slots each; and the features that fit so many
 constexpr int mfmas_of(int d) { return d <= 4 ? 2 : (kSlots * d + kNormSlots + 15) / 16; }
 constexpr int features_of(int nm) { return (16 * nm - kNormSlots) / kSlots; }
-// From 17 features on the large terms fill two MFMAs and the error of W is up to 1.27 times that of the fp32 engine (U's is still half of it), for
-// 9 to 12.7 ms in place of 15.5 to 20 at d = 20 to 28, 1M x 20k).
-constexpr int kMaxD = 16;
+// The large terms, f1 x1 and part 1 of both norms, fit one MFMA up to 14 features.  From 15 on they take two, and what the first of these cuts off the second
+// does not bring back: errors of up to 4.8 times those of the fp32 engine (d = 16, skewed rows, half the usual sigma).  (9 to 12.7 ms in place of 15.5
+// to 20 at d = 20 to 28, 1M x 20k, but for that.)
+constexpr int kMaxD = 14;
+static_assert(features_of(mfmas_of(kMaxD)) + 2 <= 16, "the large terms of a sum in one instruction");
 
 // bits of x rounded to bf16; x becomes the remainder
-template <typename T> __device__ __forceinline__ uint32_t take_bf16(T &x)
+__device__ __forceinline__ uint32_t take_bf16(double &x)
 {
     const __bf16 z = (__bf16)(float)x;
-    x -= (T)(float)z;
+    x -= (double)(float)z;
     return __builtin_bit_cast(unsigned short, z);
 }
 
-// What slot s holds.  The slots begin with the zeros that fill the first MFMA, then come the products from the least to the largest,
-// f1 x3, f3 x1, f2 x2, parts 2 to 4 of the norm terms, f1 x2, f2 x1, f1 x1, part 1 of the norm terms: the matrix cores cut off
-// what lies below the last bit of the largest term of a sum, so the small terms are added up before the large ones come in
-// (feature by feature, all six products of one side by side: error of W 1.07 times that of the fp32 engine in place of 0.84).
+// What slot s holds: the products from the least to the largest, f1 x3, f3 x1, f2 x2, parts 2 to 4 of the norm terms, f1 x2, f2 x1, f1 x1, part 1 of the
+// norm terms, behind the zeros that fill the first MFMA; up to 9 features in the opposite order.  The matrix cores cut off what lies below the last bit of
+// the largest term of a sum, always to the same side.  With the large terms last that happens once, but at their magnitude, and what it cuts off
+// is the same for many pairs: U, which sums them twice, had 1.2 times the error of the fp32 engine on positive vectors at d = 2 and 1.15 at d = 6.  With the large terms
+// first they have cancelled before the others come in, and every further MFMA cuts at the magnitude of the exponent alone: 0.42 and 0.40 times;
+// but W was up to 1.18 times that engine's from 12 features on, five or six MFMAs, where the first order has 0.52 to 0.82 and U at most
+// 0.6.  (Feature by feature, all six products of one side by side: W 1.07 times in place of 0.84 over all d.)
 struct Slot {
     int feature = -1, part = 0; // part of that feature
     int norm = -1;              // or part of the norm term, 0 to 3, of this side
@@ -63,7 +69,7 @@ template <bool FIXED, int NM> constexpr Slot slot_at(int s)
 {
     constexpr int D = features_of(NM);
     Slot r;
-    s -= 16 * NM - kSlots * D - kNormSlots;
+    s = NM <= 4 ? kSlots * D + kNormSlots - 1 - s : s - (16 * NM - kSlots * D - kNormSlots);
     if (s < 0) return r;
     int n = -1; // part of the fixed (0 to 3) or stream side's (4 to 7) norm term
     if (s < 3 * D) {
@@ -82,9 +88,10 @@ template <bool FIXED, int NM> constexpr Slot slot_at(int s)
     return r;
 }
 
-// The slots of half-wave h of a point: 8 of each MFMA.  Features z = gamma (p - mu), rounded once to fp32 and the same on both sides, norm term
-// -|z|^2 / 2 of the rounded features in fp64, four parts of it (32 bits): what is left of the exponent of two coincident points is what
-// the products leave out.
+// The slots of half-wave h of a point: 8 of each MFMA.  Features z = gamma (p - mu) in fp64, of which the parts are taken, the same on both sides; norm
+// term -|z|^2 / 2 of the sums of the parts in fp64, four parts of it (32 bits): what is left of the exponent of two coincident points is what
+// the products leave out.  (Rounded to fp32 before, whole-valued features were off by the same amount in many rows: errors of U on skewed and whole-valued
+// rows up to 1.4 times those of the fp32 engine at d = 13.)
 template <bool FIXED, int NM>
 __device__ __forceinline__ void make_units(const float *__restrict__ p, const float *__restrict__ mu, int d, double gamma, bool valid, int h,
                                            unit_t (&units)[NM])
@@ -96,10 +103,11 @@ __device__ __forceinline__ void make_units(const float *__restrict__ p, const fl
     double norm = 0.0;
 #pragma unroll
     for (int k = 0; k < D; ++k) {
-        float z = (float)(gamma * (double)x[k]);
-        norm = fma(-0.5 * (double)z, (double)z, norm);
+        double z = gamma * (double)x[k], rest = z;
 #pragma unroll
-        for (int q = 0; q < 3; ++q) part[k][q] = take_bf16(z);
+        for (int q = 0; q < 3; ++q) part[k][q] = take_bf16(rest);
+        z -= rest;
+        norm = fma(-0.5 * z, z, norm);
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) norm_part[q] = take_bf16(norm);
@@ -358,8 +366,7 @@ hipError_t launch_sweep_b16(const SweepArgs &a, void *pack_buf, size_t pack_byte
     case 3: return launch_nm<3>(a, pack_buf, pack_bytes, stream);
     case 4: return launch_nm<4>(a, pack_buf, pack_bytes, stream);
     case 5: return launch_nm<5>(a, pack_buf, pack_bytes, stream);
-    case 6: return launch_nm<6>(a, pack_buf, pack_bytes, stream);
-    default: return launch_nm<7>(a, pack_buf, pack_bytes, stream);
+    default: return launch_nm<6>(a, pack_buf, pack_bytes, stream);
     }
 }
 

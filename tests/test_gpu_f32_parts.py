@@ -91,3 +91,13 @@ def test_parts_have_no_range_limits(knm, f32):
     rest[far] = False
     assert torch.equal(W[rest], plain[rest])
     assert _err(U, _reference(X[rest], C, 2.0, v)[1]) < TOL
+
+
+# Bound: U rounded to fp32 is off by 2^-24 / sqrt(3) of itself at most in the rms, about 2.5e-8 over all mantissas; what the matrix cores cut off, always
+# to one side, may shift each of the two sums of positive terms by a quarter of its last bit, 3e-8 together.
+@pytest.mark.parametrize("d", [1, 2, 3, 4, 6])
+def test_what_the_matrix_cores_cut_off_does_not_add_up(knm, f32, d):
+    X, v = _rows(40000, d, 30 + d), _rows(9000, 1, 7).abs()
+    C, sigma = X[:9000].contiguous(), 0.75 * math.sqrt(d)
+    W, U = _reference(X, C, sigma, v)
+    assert _err(knm.knm_prod(X, C, sigma, v, ctx=f32), U) < 3.9e-8
