@@ -66,9 +66,10 @@ int knm_max_t(void);
  * share a feature take up to 4 GiB), of which up to 16 GiB stay with the context between calls, or 4 GiB while less than a sixteenth of the
  * device's memory is free; while a fit runs it also keeps the converted points (up to 8 GiB, or
  * the cap set with knm_set_pack_limit) and, where forming the kernel values takes longer than reading them (from 110 to 320
- * features on, by size and columns; from 25 to 70 in the fp32-MFMA mode), the values of k(X, C) themselves (fp32, up to 8 GiB).  Kernel values, slabs
- * and pair lists are taken only where a sixteenth of the device's memory stays free beside them, and these and a fit's converted points are given up
- * when something else of the context finds no room: the sweeps then form the values each time.
+ * features on, by size and columns; from 25 to 70 in the fp32-MFMA mode), the values of k(X, C) themselves (fp32, up to 8 GiB).  Kernel values, slabs,
+ * pair lists and the converted points of the fp32 mode are taken only where a sixteenth of the device's memory stays free beside them, and the first three
+ * and a fit's converted points are given up when something else of the context finds no room: the sweeps then form the values each time
+ * (in the fp32 mode by the fp32 matrix instructions).  Where there is no such room the last bits of results differ.
  * knm_release_workspace waits for the context's stream and gives all of it back to the device;
  * later calls take what they need anew. */
 size_t knm_workspace_bytes(int64_t n, int64_t M, int d, int t);

@@ -164,6 +164,14 @@ int ensure(knm_ctx *ctx, float **buf, size_t *cur, size_t need)
     return KNM_OK;
 }
 
+static bool is_capturing(knm_ctx *ctx)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(ctx->stream, &status);
+    if (e != hipSuccess) (void)hipGetLastError(); // (the null stream beside one that is captured)
+    return e != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
 static size_t pool_bytes(knm_ctx *ctx, const void *p)
 {
     const std::lock_guard<std::mutex> lock(ctx->pool_lock);
@@ -184,6 +192,22 @@ static bool leaves_room(size_t bytes)
     if (hipMemGetInfo(&free, &total) == hipSuccess) return free >= bytes && free - bytes >= total / 16;
     (void)hipGetLastError();
     return false;
+}
+
+// ensure() for what is for speed alone: false, with everything as it was, where the card has no room to spare or the stream is being captured
+static bool ensure_for_speed(knm_ctx *ctx, float **buf, size_t *cur, size_t need)
+{
+    if (*cur >= need) return true;
+    if (is_capturing(ctx) || !leaves_room(need)) return false;
+    void *p = nullptr;
+    {
+        const std::lock_guard<std::mutex> lock(ctx->pool_lock);
+        if (alloc_locked(ctx, need, &p, true) != hipSuccess) return false;
+    }
+    if (*buf) (void)hipFree(*buf);
+    *buf = static_cast<float *>(p);
+    *cur = need;
+    return true;
 }
 
 hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out, PoolUse use)
@@ -632,8 +656,9 @@ static int share_images(knm_ctx *ctx, SweepShare *sh)
     if (pp * (size_t)(r0 + r1) > (ctx->pack_limit ? ctx->pack_limit : kShareCap)) return KNM_OK;
     if (sh->pooled) {
         for (int k = 0; k < 2; ++k)
-            if (pool_take(ctx, pp * (size_t)(k == 0 ? r0 : r1), &sh->img[k], PoolUse::kOptional) != hipSuccess) {
-                // no room: the sweeps pack slab by slab
+            if (pool_take(ctx, pp * (size_t)(k == 0 ? r0 : r1), &sh->img[k],
+                          ctx->cross_term == KNM_CROSS_F16X3 ? PoolUse::kOptional : PoolUse::kForSpeed) != hipSuccess) {
+                // no room: the sweeps pack slab by slab (or not at all)
                 if (sh->img[0]) pool_give(ctx, sh->img[0]);
                 sh->img[0] = sh->img[1] = nullptr;
                 return KNM_OK;
@@ -831,10 +856,7 @@ struct SlabUse {
     void *p = nullptr;
     SlabUse(knm_ctx *c, size_t bytes) : ctx(c)
     {
-        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-        const hipError_t e = hipStreamIsCapturing(ctx->stream, &status);
-        if (e != hipSuccess) (void)hipGetLastError(); // (the null stream beside one that is captured)
-        const bool capturing = e != hipSuccess || status != hipStreamCaptureStatusNone;
+        const bool capturing = is_capturing(ctx);
         if (ctx->slab == nullptr || ctx->slab_bytes < bytes) {
             if (capturing) return;
             drop_slab(ctx);
@@ -907,28 +929,27 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
 {
     int64_t chunk_len = 0;
     int64_t chunks = choose_chunks(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
+    // the engine that has fp32 numbers in three parts takes the sweep, unless there is no room for its image
+    bool parts = three_parts(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind);
     if (ctx->static_mode) {
-        // where these partials and the least operand images do not fit the scratch together: fewer chunks; the fp32 engine takes
-        // the sweep where an image of three-part numbers does not fit whatever the chunks
-        bool image = packs_images(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind);
+        // where these partials and the least operand images do not fit the scratch together: fewer chunks; the fp32 MFMA engine takes
+        // the sweep, cut as it would be without the other engine, where an image of three-part numbers does not fit whatever the chunks
         auto fits = [&] {
-            const size_t least = !image ? 0
+            const size_t least = !parts && ctx->cross_term != KNM_CROSS_F16X3 ? 0
                                  : use_gemm_engine(d, t, ctx->cross_term, ctx->kernel_kind)
                                      ? gemm_f16_min_pack_bytes(nF, chunks * chunk_len, chunk_len, d)
                                      : image_bytes_per_point(d, t, ctx->cross_term, ctx->kernel_kind) * (size_t)chunk_len;
             return sizeof(float) * (size_t)chunks * nF * t + mu_bytes_wanted(kMeanSample, d) + least + 1024 <= kStaticScratchBytes;
         };
         auto choose = [&] {
-            chunks = choose_chunks(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
+            chunks = choose_chunks_for(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, parts, &chunk_len);
             if (!fits()) chunks = choose_chunks_compact(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len);
-            if (!fits())
-                chunks = choose_chunks_by_time(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, true,
-                                               three_parts(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind), &chunk_len);
+            if (!fits()) chunks = choose_chunks_by_time(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, true, parts, &chunk_len);
             if (!fits()) chunks = choose_chunks_compact(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind, &chunk_len); // refused below
             return fits();
         };
-        if (!choose() && image && ctx->cross_term != KNM_CROSS_F16X3) {
-            image = false;
+        if (!choose() && parts) {
+            parts = false;
             (void)choose();
         }
     }
@@ -1088,14 +1109,17 @@ static int sweep(knm_ctx *ctx, const float *F, int64_t nF, int64_t ldf, const fl
             if (kept) use_images();
             e = launch_sweep_f16(a, pack, want, ctx->stream);
         } else {
-            // the image of three-part numbers is for speed alone: where the card, or the scratch of a call that does not
-            // allocate, has no room for it the fp32 engine takes the rows as they are
-            bool parts = packs_images(nF, nS, d, t, ctx->cross_term, ctx->kernel_kind);
+            // the image of three-part numbers is for speed alone: where the card has no room to spare for it the fp32 MFMA engine
+            // takes the rows as they are
             size_t want = 0;
             if (parts && !kept) {
                 int st = pack_room(&want);
+                if (!st && ctx->static_mode) st = acquire(ctx, &ctx->pack_buf, &ctx->pack_bytes, want, &pack);
                 if (st) return st;
-                parts = acquire(ctx, &ctx->pack_buf, &ctx->pack_bytes, want, &pack) == KNM_OK;
+                if (!ctx->static_mode) {
+                    parts = ensure_for_speed(ctx, &ctx->pack_buf, &ctx->pack_bytes, want);
+                    pack = ctx->pack_buf;
+                }
             }
             if (parts && kept) use_images();
             e = parts ? launch_sweep_b16(a, pack, want, ctx->stream) : launch_sweep(a, ctx->stream);

@@ -114,3 +114,68 @@ def test_products_with_many_columns_that_keep_values(run):
             kept += once
         assert 0 < kept < {len(shapes)}
         """)
+
+
+# The image of three-part numbers is for speed alone: it leaves a sixteenth of the card free and every other buffer where it is, and a call that
+# does without it has no error to report
+def test_three_part_images_leave_room(run):
+    run("""
+        import time
+        n, M, d, t = 4_000_000, 20_000, 9, 1
+        card = 288 << 30
+        hip.fake_set_total(card)
+        assert lib.knm_set_cross_term(ctx, 0) == 0
+
+        def others_leave(bytes):
+            hip.fake_set_budget(hip.fake_live() + bytes)
+            time.sleep(0.06)
+
+        def engines():
+            return launched("gauss_sweep_b16_kernel"), launched("gauss_sweep_kernel")
+
+        others_leave(card // 16 + (256 << 20))  # W and the partials, but not 512 MB of image as well
+        assert prod(n, M, d, t) == 0
+        assert launched("gauss_sweep_b16_kernel") == 1  # the sweep over the rows packs the 20000 centres: 2.5 MB
+        assert launched("gauss_sweep_kernel") == 1
+        assert lib.knm_last_error(ctx) == b"" and lib.knm_workspace_held(ctx) < 256 << 20
+        # nothing is allocated under capture, not even where there is room by then
+        others_leave(card)
+        held = lib.knm_workspace_held(ctx)
+        hip.fake_set_capturing(1)
+        assert prod(n, M, d, t) == 0 and engines() == (1, 1) and lib.knm_workspace_held(ctx) == held
+        hip.fake_set_capturing(0)
+        assert prod(n, M, d, t) == 0 and engines() == (2, 0)
+        hip.fake_set_capturing(1)
+        assert prod(n, M, d, t) == 0 and engines() == (2, 0)
+        """)
+
+
+def test_a_static_call_without_room_for_a_three_part_image(run):
+    run("""
+        assert lib.knm_set_cross_term(ctx, 0) == 0
+        without = 0
+        for n in range(16_300_000, 16_777_216, 8192):
+            st = prod_static(n, 3000, 9, 1)
+            assert st in (0, -2)
+            if st == 0:
+                assert lib.knm_last_error(ctx) == b"", n
+                without += launched("gauss_sweep_kernel") > 0
+        assert without > 0
+        """)
+
+
+# A fit in the fp32 mode keeps its images only where there is room to spare
+def test_three_part_images_of_a_fit_leave_room(run):
+    run("""
+        lib.falkon_fit.argtypes = [P, P, L, I, L, P, I, P, L, L, F, D, D, I, P, P]
+        card, n, d, M = 288 << 30, 20_000_000, 9, 1000
+        hip.fake_set_total(card)
+        assert lib.knm_set_cross_term(ctx, 0) == 0
+        for left, b16 in ((card, 7), (card // 16 + (1 << 30), 3)):  # 2.5 GB of image for the sums over the rows
+            hip.fake_set_budget(left)
+            lib.knm_release_workspace(ctx)
+            rec.forget()
+            assert lib.falkon_fit(ctx, x, n, d, d, v, 1, cen, M, d, 1.0, 1e-4, 1e-6, 3, u, None) == 0
+            assert launched("gauss_sweep_b16_kernel") == b16 and launched("gauss_sweep_kernel") == 7 - b16, launched("gauss_sweep_b16_kernel")
+            assert lib.knm_last_error(ctx) == b""
+        """)
