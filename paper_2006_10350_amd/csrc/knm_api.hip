@@ -273,6 +273,12 @@ void pool_give(knm_ctx *ctx, void *p)
     }
 }
 
+size_t pool_idle_bytes(knm_ctx *ctx)
+{
+    const std::lock_guard<std::mutex> lock(ctx->pool_lock);
+    return ctx->pool_idle;
+}
+
 void pool_trim(knm_ctx *ctx, size_t idle)
 {
     const std::lock_guard<std::mutex> lock(ctx->pool_lock);

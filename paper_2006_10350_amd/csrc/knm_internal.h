@@ -439,6 +439,7 @@ hipError_t device_alloc(knm_ctx *ctx, size_t bytes, void **out);
 enum class PoolUse { kNeeded, kOptional, kForSpeed };
 hipError_t pool_take(knm_ctx *ctx, size_t bytes, void **out, PoolUse use = PoolUse::kNeeded);
 void pool_drop(knm_ctx *ctx, void *p); // back to the device
+size_t pool_idle_bytes(knm_ctx *ctx);
 void pool_trim(knm_ctx *ctx, size_t idle); // idle blocks beyond that many bytes, the newest first
 void pool_give(knm_ctx *ctx, void *p);
 bool spare_add(knm_ctx *ctx, int phase, void **p); // false: no host memory for it
@@ -477,6 +478,11 @@ struct DevBuf {
     void free()
     {
         if (p) pool_give(owner, p);
+        p = nullptr;
+    }
+    void drop() // back to the device
+    {
+        if (p) pool_drop(owner, p);
         p = nullptr;
     }
     int alloc(knm_ctx *ctx, size_t bytes)

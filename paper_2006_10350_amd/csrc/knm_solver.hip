@@ -1081,7 +1081,7 @@ static int aux_stream(knm_ctx *ctx, hipStream_t *out)
 struct IdleScope {
     knm_ctx *ctx;
     size_t before;
-    explicit IdleScope(knm_ctx *c) : ctx(c), before(c ? c->pool_idle : 0) {}
+    explicit IdleScope(knm_ctx *c) : ctx(c), before(c ? pool_idle_bytes(c) : 0) {}
     ~IdleScope()
     {
         if (ctx) pool_trim(ctx, std::max(before, (size_t)4 << 30));
@@ -1107,6 +1107,8 @@ struct ResidueRoom {
         if (first_rows > 0) bytes_size[0] = std::max(residue_bytes(first_rows, n, kBytes / 2), residue_bytes(n, first_rows, kBytes / 2));
         bytes_size[1] = residue_bytes(n, n, kBytes);
         for (int k = 0; k < 2 && ok; ++k) ok = bytes_size[k] == 0 || bytes[k].alloc_for_speed(ctx, bytes_size[k]);
+        if (!ok) // (what was found goes back to the device: the card is nearly full)
+            for (DevBuf *part : {&img[0], &img[1], &exps[0], &exps[1], &bytes[0], &bytes[1]}) part->drop();
     }
 };
 

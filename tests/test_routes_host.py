@@ -10,6 +10,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(os.path.dirname(HERE), "paper_2006_10350_amd", "libknm.so")
 
 RECORD = """
+#define _GNU_SOURCE
+#include <dlfcn.h>
+#include <stddef.h>
 #include <stdint.h>
 #include <string.h>
 typedef struct { uint32_t x, y, z; } dim3;
@@ -18,6 +21,7 @@ static const void *functions[kFunctions];
 static const char *names[kFunctions];
 static long counts[kFunctions];
 static int known;
+static size_t live; /* device memory held at most when a leaf of a factorisation was launched */
 void __hipRegisterFunction(void **modules, const void *host, char *device, const char *name, unsigned limit, void *tid, void *bid, void *block,
                            void *grid, int *size)
 {
@@ -30,7 +34,11 @@ int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t ld
 {
     (void)grid; (void)block; (void)args; (void)lds; (void)stream;
     for (int i = 0; i < known; ++i)
-        if (functions[i] == f) ++counts[i];
+        if (functions[i] == f) {
+            ++counts[i];
+            size_t (*held)(void) = (size_t (*)(void))dlsym(RTLD_DEFAULT, "fake_live");
+            if (strstr(names[i], "leaf") && held() > live) live = held();
+        }
     return 0;
 }
 long launched(const char *part) /* launches of kernels with this in their (mangled) name */
@@ -40,7 +48,12 @@ long launched(const char *part) /* launches of kernels with this in their (mangl
         if (strstr(names[i], part)) n += counts[i];
     return n;
 }
-void forget(void) { memset(counts, 0, sizeof counts); }
+size_t live_at_most(void) { return live; }
+void forget(void)
+{
+    memset(counts, 0, sizeof counts);
+    live = 0;
+}
 """
 
 HEAD = """
@@ -178,4 +191,44 @@ def test_three_part_images_of_a_fit_leave_room(run):
             assert lib.falkon_fit(ctx, x, n, d, d, v, 1, cen, M, d, 1.0, 1e-4, 1e-6, 3, u, None) == 0
             assert launched("gauss_sweep_b16_kernel") == b16 and launched("gauss_sweep_kernel") == 7 - b16, launched("gauss_sweep_b16_kernel")
             assert lib.knm_last_error(ctx) == b""
+        """)
+
+
+# Factorisations: by residues from the sizes that residue_pays says, where the card has room to spare; by fp64 products elsewhere, and then none of the
+# room that was found for a part of the arrays is held while the factorisation runs
+def test_factorisations_by_residues(run):
+    run("""
+        import time
+        pays = lib._ZN3knm12residue_paysEllb
+        pays.argtypes, pays.restype = [L, L, c.c_bool], c.c_bool
+        lib.precond_build.argtypes = [P, P, L, I, L, F, D, D, P, P]
+        lib.precond_free.argtypes = [P]
+        rec.live_at_most.restype = Z
+
+        def build(M):
+            rec.forget()
+            p = P()
+            assert lib.precond_build(ctx, cen, M, 8, 8, 1.0, 1e-6, 1e-6, c.byref(p), None) == 0
+            assert lib.precond_free(p) == 0
+            return launched("residue_gemm_kernel")
+
+        def width(M):  # of a block row
+            return min(((M + 7) // 8 + 255) // 256 * 256, 4096)
+
+        tri = next(M for M in range(1000, 9000) if pays(M, M, True))
+        rows = next(M for M in range(1000, 9000) if pays(M - width(M), width(M), False))
+        assert 3000 < tri < 4500 < rows < 6000, (tri, rows)
+        assert build(tri - 1) == 0 and build(tri) == 1 and build(rows - 1) == 1
+        assert build(rows) >= 3  # and a block row of each factor
+
+        M, card = 20000, 288 << 30
+        hip.fake_set_total(card)
+        assert build(M) > 10
+        lib.knm_release_workspace(ctx)
+        full = 8 * (M + 3) * M + 2 * 8 * 2048 * (M + 2048) + (256 << 20)  # factors, inverted blocks, some vectors
+        hip.fake_set_budget(card // 16 + full + (900 << 20))  # room for planes of one block row (0.76 GB), not for those of two
+        time.sleep(0.06)
+        assert build(M) == 0 and launched("rank_k_upper_kernel") > 0
+        assert rec.live_at_most() < full
+        assert lib.knm_last_error(ctx) == b""
         """)
