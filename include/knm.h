@@ -24,7 +24,9 @@
  *    The solver entry points allocate and synchronise.
  *  - Return value: KNM_OK (0) or a negative knm_status.  No exception crosses the ABI.
  *  - Indices are 64-bit; n * d and n * M may exceed 2^32.
- *  - Results are deterministic: partial sums are merged in a fixed order (no atomics).
+ *  - Results are deterministic: partial sums are merged in a fixed order (no atomics; the sparse entry points excepted).  Some buffers are for speed alone
+ *    and are taken only where the device has room to spare (see knm_workspace_bytes, precond_residue_update): on a card that is nearly full, other kernels
+ *    do the work without them, and the last bits of products, factors and fits are not those of a card with room.
  */
 #ifndef KNM_H
 #define KNM_H
@@ -187,6 +189,19 @@ int falkon_linop(knm_ctx *ctx, const knm_precond *p,
  * the call is asynchronous on the context's stream. */
 int precond_rank_k_update(knm_ctx *ctx, int form_nt, int64_t n, int64_t k, double alpha, const double *A, int64_t lda,
                           const double *w_or_null, int triangular, double beta, double shift, double *C, int64_t ldc);
+
+/* The same update as integer products modulo 15 small numbers on the int8 matrix cores: what the factorisations and precond_reweight
+ * take for their large updates (from about 3500 centres on for the triangular product, 5300 for block rows), where the card has room.  n, k >= 1;
+ * lower != 0: entry (i, j), i <= j, is C[j + i ldc] (else C[i + j ldc] as above); triangular needs k == n; the contraction is taken in slabs of
+ * `slab` (a multiple of 64 up to 65536; 0 = chosen by the library).
+ * Accuracy: entry (i, j) is off by about 2^-59 of the product of the norms of rows i and j of the operand (of w^1/2 a, with weights), whatever its own size, and
+ * rounded to fp64: relative to those norms no more than running fp64 sums are, while single entries that are far below
+ * them have fewer correct digits.  The same holds for the factors that precond_get_factors and precond_get_block return: T^T T and A^T A are as close
+ * to the matrices that they factor as by fp64 updates or closer, measured by the diagonals, but small entries of the factors are only
+ * that accurate relative to the diagonal.
+ * KNM_ALLOC where a sixteenth of the card would not stay free. */
+int precond_residue_update(knm_ctx *ctx, int form_nt, int lower, int64_t n, int64_t k, int64_t slab, double alpha, const double *A,
+                           int64_t lda, const double *w_or_null, int triangular, double beta, double shift, double *C, int64_t ldc);
 
 /* General fp64 block product on the matrix cores, the building block of the first two steps of the
  * block Cholesky column update (Sec. 4, block Cholesky paragraph: factor the diagonal tile, solve

@@ -1,4 +1,4 @@
-// fp64 symmetric updates of the preconditioner as integer products modulo 14 small numbers (residue number system, Chinese
+// fp64 symmetric updates of the preconditioner as integer products modulo 15 small numbers (residue number system, Chinese
 // remainder theorem), on the int8 matrix cores:
 //
 //   C[i, j] = alpha * sum_k w[k] a(i, k) a(j, k) + beta * C[i, j] + shift * [i == j],   i <= j
@@ -7,20 +7,24 @@
 // rank_k_upper_kernel forms them on the fp64 matrix cores).  The scheme is the one published for emulating fp64 products by int8 ones (Ozaki,
 // Uchino, Imamura, "Ozaki Scheme II: a GEMM-oriented emulation of floating-point matrix multiplication using an integer modular
 // technique", 2025), in its plainest form:
-//   1. Row i of a (over k) is scaled by a power of two so that its norm is at most 2^54 and rounded to integers X(i, k).  By
-//      Cauchy and Schwarz every sum over k of X(i, k) X(j, k) lies within +-2^108.
-//   2. X is reduced modulo 14 pairwise coprime numbers up to 256, whose product P is 2^109.8: 14 planes of int8.
+//   1. Row i of a (over k) is scaled by a power of two so that its norm is at most 2^58 and rounded to integers X(i, k).  By
+//      Cauchy and Schwarz every sum over k of X(i, k) X(j, k) lies within +-2^116.
+//   2. X is reduced modulo 15 pairwise coprime numbers up to 256, whose product P is 2^117.4: 15 planes of int8.
 //   3. Per modulus a product of int8 matrices with exact int32 sums (at most 65536 terms of 2^14), reduced modulo the same number:
 //      one byte per entry of C and modulus.
-//   4. The 14 bytes give the sum itself, as the fraction sum_s r_s c_s / m_s of P modulo 1 (c_s the inverse of P / m_s modulo m_s), added in
-//      fixed point to 2^-68 and taken to its nearest int64 in units of 2^-64, then scaled back and added to C in fp64.
-// Only step 1 rounds: an entry of a by at most 2^-54 of its row's norm, so an entry of the sum by about
-// 4e-17 |a_i| |a_j|, where running fp64 sums of K terms leave more: factors of kernel matrices of 5000 to 8000 centres (normal, skewed and
-// image-like rows), T^T T - K_MM in extended precision 2e-17 to 3.7e-16 in place of 3.8e-17 to 8.7e-16 rms, A^T A relative to its
-// diagonal 4e-18 to 2.7e-17 in place of 1.8e-17 to 4.3e-17.
+//   4. The 15 bytes give the sum itself, as the fraction sum_s r_s c_s / m_s of P modulo 1 (c_s the inverse of P / m_s modulo m_s), added in
+//      fixed point to 2^-80 and rounded to the nearest int64 in units of 2^-64, then scaled back and added to C in fp64.
+// Only step 1 rounds, and it rounds relative to a row's norm: an entry of a that is at least 2^-5 of it keeps all of its 53 bits, a smaller one
+// is off by at most 2^-58 of the norm, whatever its own size.  An entry of the sum is so off by about 2e-18 |a_i| |a_j|, where running fp64 sums
+// are off by their own last bits, sum by sum:
+// block rows of 1024 of the factors of kernel matrices of 6144 centres (normal, skewed and image-like rows at their usual length scales, and length
+// scales 0.25 to 0.4 times those), rms 2e-18 to 8e-17 of |a_i| |a_j| in place of 4.4e-17 to 1.1e-15, largest 2.0e-16 to 5.8e-16 in place of 3.1e-15 to 1.1e-14, all
+// entries together (2-norm) 2e-17 to 2.3e-16 in place of 5.5e-16 to 1.5e-15; triangular products 2.3e-18 to 3.9e-18 in place of 4.7e-17 to 8.9e-17 rms.
+// What Cholesky factors are good for, T^T T = K_MM to a small multiple of 2^-53 of its diagonal, is measured by the rows' norms.  Entries of
+// the sum that are far below them, of rows that are large where the other is small, have fewer correct digits of their own than fp64 sums would give them.
 //
-// The fp64 matrix cores reach 64 TFLOP/s on large updates; int8 has 64 times their rate, of which 14 moduli, the power limit (operands that
-// are random bytes: 2.7e15 operations a second from registers, 1.9e15 with their loads) and the passes over the bytes leave 115 to 125.
+// The fp64 matrix cores reach 64 TFLOP/s on large updates; int8 has 64 times their rate, of which 15 moduli, the power limit (operands that
+// are random bytes: 2.7e15 operations a second from registers, 1.9e15 with their loads) and the passes over the bytes leave 79 to 100.
 #include <type_traits>
 
 #include "knm_internal.h"
@@ -32,9 +36,11 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kModuli = 14;
-constexpr int kModulus[kModuli] = {256, 253, 251, 247, 241, 239, 233, 229, 227, 223, 217, 211, 199, 197};
-constexpr int kNormBits = 54;
+constexpr int kModuli = 15;
+constexpr int kModulus[kModuli] = {256, 253, 251, 247, 241, 239, 233, 229, 227, 223, 217, 211, 199, 197, 193};
+// With 14 moduli and 54 bits the operands' rounding, 3e-17 |a_i| |a_j|, was above that of fp64 sums where these are small: later block rows, narrow
+// kernels, skewed rows.
+constexpr int kNormBits = 58;
 constexpr int kDead = -(1 << 30); // exponent of a row that is not finite
 
 constexpr unsigned __int128 product_of_moduli()
@@ -45,7 +51,7 @@ constexpr unsigned __int128 product_of_moduli()
 }
 constexpr unsigned __int128 kProduct = product_of_moduli();
 static_assert(kProduct > ((unsigned __int128)1 << (2 * kNormBits + 1)) + ((unsigned __int128)1 << 90), "sums of either sign, with the rounding of X");
-// fraction c_s / m_s of modulus s in four digits of 20 bits (the sum of 14 bytes times a digit fits 32 bits)
+// fraction c_s / m_s of modulus s in four digits of 20 bits (the sum of 15 bytes times a digit, and half of 2^16, fits 32 bits)
 constexpr uint32_t fraction_digit(int s, int digit)
 {
     const unsigned m = (unsigned)kModulus[s];
@@ -80,14 +86,27 @@ constexpr int kPatchU = 4, kPatchV = 8;              // tiles that an XCD's work
 constexpr int kXcds = 8;
 constexpr int64_t kTileBytes = (int64_t)kTileU * kTileV;
 
-// Remainders by fp64 arithmetic: for a whole x below 2^54 x - m rint(x / m), in -128 .. 127 (a quotient next to a half may be rounded the
-// other way; no modulus but 256 is above 253).  Numbers below 2^51 are rounded by adding 1.5 2^52, which leaves them, as
-// integers, in the low bits.
+// Remainders by fp64 arithmetic: x - m rint(x / m) of a whole x up to 2^58.  Numbers below 2^51 are rounded by adding 1.5 2^52, which leaves
+// them, as integers, in the low bits.  1 / m is not exact: a quotient may be off by more than a half, the remainder by as much of m
+// beyond it, and where that can leave -128 .. 127 m is taken off or added once more.
 constexpr double kRound = 6755399441055744.0;
+constexpr bool beyond_int8(int m, int bits) // (1 / m is a multiple of 2^-60 for m <= 256)
+{
+    const __int128 miss = (__int128)(uint64_t)((1.0 / (double)m) * 0x1p60) * m - ((__int128)1 << 60);
+    const double most = 0.5 * m + (double)(miss < 0 ? -miss : miss) * (bits < 60 ? 1.0 / (double)((uint64_t)1 << (60 - bits)) : 1.0);
+    return most >= 128.0 && m != 256;
+}
 __device__ __forceinline__ uint32_t remainder_bits(double x, double m, double inv)
 {
     const double q = fma(x, inv, kRound) - kRound;
     return (uint32_t)__builtin_bit_cast(uint64_t, fma(-m, q, x) + kRound); // the low byte counts
+}
+template <int M> __device__ __forceinline__ uint32_t remainder_of(double x) // of an operand
+{
+    const uint32_t bits = remainder_bits(x, (double)M, 1.0 / (double)M);
+    if constexpr (!beyond_int8(M, kNormBits)) return bits;
+    const int v = (int)bits;
+    return (uint32_t)(v > 127 ? v - M : v < -127 ? v + M : v);
 }
 // low bytes of four words as one
 __device__ __forceinline__ uint32_t low_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
@@ -104,12 +123,12 @@ template <int FORM>
 __device__ __forceinline__ double element(const double *__restrict__ A, int64_t lda, int64_t i, int64_t k, const double *__restrict__ w, int tri,
                                           int64_t k0)
 {
-    double x = A[FORM == 0 ? k + i * lda : i + k * lda];
-    if (tri && k + k0 < i) x = 0.0;
+    if (tri && k + k0 < i) return 0.0;
+    const double x = A[FORM == 0 ? k + i * lda : i + k * lda];
     return w != nullptr ? x * w[k] : x;
 }
 
-// Power of two by which row i is scaled: its norm becomes at most 2^54 and (but for rows of extreme magnitude) more than 2^53.
+// Power of two by which row i is scaled: its norm becomes at most 2^58 and (but for rows of extreme magnitude) more than 2^57.
 // In two launches, sums of squares and maxima of slices of k, then what they come to: every sum has one order.
 // FORM 0: a wavefront per row and slice; FORM 1: 64 rows by four wavefronts, which share a slice.
 constexpr int kSlices = 16;
@@ -186,6 +205,19 @@ __global__ __launch_bounds__(256) void residue_scale_kernel(const double *__rest
     exps[i] = e;
 }
 
+template <int S> __device__ __forceinline__ void write_residues(const double (&x)[16], u32x4 *out, int64_t plane)
+{
+    if constexpr (S < kModuli) {
+        constexpr int m = kModulus[S];
+        u32x4 u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            u[q] = low_bytes(remainder_of<m>(x[4 * q]), remainder_of<m>(x[4 * q + 1]), remainder_of<m>(x[4 * q + 2]), remainder_of<m>(x[4 * q + 3]));
+        out[S * plane] = u;
+        write_residues<S + 1>(x, out, plane);
+    }
+}
+
 // Planes of residues: the unit of row i and k = 16 h .. 16 h + 15 of a chunk of 32 is 16 bytes, 64 units (32 rows x 2) a cell of 1 KB, the cells
 // of 32 rows one behind the other along k.  A wavefront makes a cell of every plane.
 template <int FORM>
@@ -211,16 +243,7 @@ __global__ __launch_bounds__(kThreads) void residue_convert_kernel(const double 
 #pragma unroll
     for (int q = 0; q < 16; ++q) x[q] = e == kDead ? 0.0 : rint(ldexp(x[q], e));
     u32x4 *out = img + (block * k_chunks + chunk) * 64 + lane;
-#pragma unroll
-    for (int s = 0; s < kModuli; ++s) {
-        const double m = (double)kModulus[s], inv = 1.0 / (double)kModulus[s];
-        u32x4 u;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            u[q] = low_bytes(remainder_bits(x[4 * q], m, inv), remainder_bits(x[4 * q + 1], m, inv), remainder_bits(x[4 * q + 2], m, inv),
-                             remainder_bits(x[4 * q + 3], m, inv));
-        out[(int64_t)s * row_blocks * k_chunks * 64] = u;
-    }
+    write_residues<0>(x, out, row_blocks * k_chunks * 64);
 }
 
 struct ResidueArgs {
@@ -261,7 +284,7 @@ template <int S = 0> __device__ __forceinline__ void modulus_of(int s, double &m
 
 // One tile of C modulo one number per workgroup: 256 x 128, four wavefronts of 128 x 64, contraction in stages of 64 through a ring of three
 // in LDS that loads which write LDS directly fill two stages ahead.  Two workgroups per CU.  Bound by the int8 matrix cores at the power
-// limit: n = 17408, k = 2560 5.5 ms, 4.0 with operands of zeros.  256 x 256 tiles, by eight wavefronts or by four of 128 x 128, which read a third
+// limit: n = 17408, k = 2560 5.5 ms with 14 moduli, 4.0 with operands of zeros.  256 x 256 tiles, by eight wavefronts or by four of 128 x 128, which read a third
 // less through the L2, took as long or 3 % longer.
 __global__ __launch_bounds__(kThreads, 2) void residue_gemm_kernel(ResidueArgs a)
 {
@@ -380,7 +403,7 @@ __global__ __launch_bounds__(kThreads, 2) void residue_gemm_kernel(ResidueArgs a
         }
 }
 
-// The sums from their residues, and C from them: a wavefront per 32 x 32 block.  Bound by memory: 14 bytes read, C read and written.
+// The sums from their residues, and C from them: a wavefront per 32 x 32 block.  Bound by memory: 15 bytes read, C read and written.
 __global__ __launch_bounds__(kThreads) void residue_combine_kernel(ResidueArgs a)
 {
     const int lane = threadIdx.x & 63;
@@ -418,7 +441,7 @@ __global__ __launch_bounds__(kThreads) void residue_combine_kernel(ResidueArgs a
             for (int k = 0; k < 4; ++k) d[k] += __mul24(b, (int)kFractions.digit[s][k]);
         }
         // the digits' sums as a fraction of 2^64, modulo 1
-        const uint64_t f = ((uint64_t)(int64_t)d[0] << 44) + ((uint64_t)(int64_t)d[1] << 24) + ((uint64_t)(int64_t)d[2] << 4) + (uint64_t)(int64_t)(d[3] >> 16);
+        const uint64_t f = ((uint64_t)(int64_t)d[0] << 44) + ((uint64_t)(int64_t)d[1] << 24) + ((uint64_t)(int64_t)d[2] << 4) + (uint64_t)(int64_t)((d[3] + 32768) >> 16);
         const double c = (double)(int64_t)f;
         double sum = fma(c, kScaleLo, c * kScaleHi);
         sum = eu == kDead || ev[e] == kDead ? __builtin_nan("") : ldexp(sum, -(eu + ev[e]));
@@ -445,14 +468,15 @@ __global__ void signed_root_kernel(const double *__restrict__ w, int64_t n, doub
 
 } // namespace
 
-// Microseconds measured: 136e6 flop each for the int8 products, 46 bytes an entry of C at 6 TB/s, 22 an element of the operand at 3.2, launches;
-// the fp64 matrix cores 50e6 to 64e6 flop.  n = 17408, k = 2560: 12.2 -> 7.0 ms; 8704, 1280: 1.9 -> 1.1; 4360, 640: 0.25 and 0.26.
+// Microseconds measured: 127e6 flop each for the int8 products, 49 bytes an entry of C at 6 TB/s, 23 an element of the operand at 3.2, launches;
+// the fp64 matrix cores 50e6 to 64e6 flop.  n = 17408, k = 2560: 12.2 -> 7.7 ms; 8704, 1280: 2.0 -> 1.2; 4352, 1024: 0.44 -> 0.30.  Triangular products
+// go by it from 3488 centres on, block rows from 5304.
 bool residue_pays(int64_t n, int64_t K, bool triangular)
 {
     if (K <= 0 || n <= 0) return false;
     const double entries = 0.5 * (double)n * (double)n, elements = (double)n * (double)K * (triangular ? 0.5 : 1.0);
     const double flop = 2.0 * entries * (double)K * (triangular ? 1.0 / 3.0 : 1.0);
-    return flop / 136e6 + entries * 46.0 / 6.0e6 + elements * 22.0 / 3.2e6 + 40.0 < 0.9 * flop / 52e6;
+    return flop / 127e6 + entries * 49.0 / 6.0e6 + elements * 23.0 / 3.2e6 + 40.0 < 0.9 * flop / 52e6;
 }
 
 size_t residue_image_bytes(int64_t n, int64_t K) { return (size_t)kModuli * (size_t)padded_rows(n) * (size_t)padded_k(K); }

@@ -521,7 +521,7 @@ inline dim3 grid1(int64_t n, int threads = 256) { return dim3((unsigned)((n + th
 
 // ---- fp64 vector work of the CG driver -----------------------------------------------------
 // Every sum is a fixed number of block partials, added up in a fixed order by each block of the kernel that
-// needs the total, so a fit is reproducible from run to run.  The scalars of CG stay on the device: an iteration takes three
+// needs the total, so a fit repeats itself bit for bit (where the card has room for what is for speed alone, or never has).  The scalars of CG stay on the device: an iteration takes three
 // launches for all columns and the host never waits (with the two scalars of a column read back and five launches per
 // column, 10 columns cost 50 launches and 20 synchronisations per iteration: 0.5 ms of the 4.4 ms at
 // n = 60k, M = 10k).
@@ -1272,58 +1272,61 @@ static int read_bad_pivots(knm_ctx *ctx, const unsigned long long *bad, int coun
     return KNM_OK;
 }
 
-// The triangular product by residues: 1, or 0 where that is no faster or there is no room.  The contraction is taken in slabs whose
-// planes fill at most 2 GiB, the last first: its sums reach every entry.  The weights go to the two sides as their roots, so that a
-// product of entries is scaled as the sum it is part of; their signs go to one side, whose planes are made only where there are any.
-static int second_by_residues(knm_ctx *ctx, knm_precond *p, double lambda, const double *dw)
+// The update of launch_rank_k_upper (there: form_nt, w, tri; lower: entry (i, j), i <= j, at C[j + i ldc]; tri needs K = n) by residues: 1, or 0 where there is
+// no room.  The contraction is taken in slabs of `depth` (0: whose planes fill at most 2 GiB), the last first: with tri its sums reach every entry.  The
+// weights go to the two sides as their roots, so that a product of entries is scaled as the sum it is part of; their signs go to one
+// side, whose planes are made only where there are any.
+static int rank_k_by_residues(knm_ctx *ctx, int form_nt, int lower, int64_t n, int64_t K, int64_t depth, double alpha, const double *A, int64_t lda,
+                              const double *w, int tri, double beta, double shift, double *C, int64_t ldc)
 {
-    const int64_t M = p->M;
-    if (!residue_pays(M, M, true)) return 0;
-    const int sides = dw != nullptr ? 2 : 1;
-    const int64_t per_k = (int64_t)(residue_image_bytes(M, 64) / 64) * sides;
-    int64_t depth = ((int64_t)2 << 30) / per_k;
-    if (depth < 1024) depth = 1024;
-    if (depth > residue_max_k()) depth = residue_max_k();
-    const int64_t slabs = (M + depth - 1) / depth;
-    depth = ((M + slabs - 1) / slabs + 63) / 64 * 64;
+    const int sides = w != nullptr ? 2 : 1;
+    if (depth <= 0) {
+        const int64_t per_k = (int64_t)(residue_image_bytes(n, 64) / 64) * sides;
+        depth = ((int64_t)2 << 30) / per_k;
+        if (depth < 1024) depth = 1024;
+        if (depth > residue_max_k()) depth = residue_max_k();
+        const int64_t slabs = (K + depth - 1) / depth;
+        depth = ((K + slabs - 1) / slabs + 63) / 64 * 64;
+    }
     ResidueRoom room(ctx);
-    room.take(M, depth < M ? depth : M, sides, 0);
+    room.take(n, depth < K ? depth : K, sides, 0);
     DevBuf roots, sign;
-    if (!room.ok || (dw != nullptr && !(roots.alloc_for_speed(ctx, sizeof(double) * 2 * (size_t)M) && sign.alloc_for_speed(ctx, sizeof(int)))))
+    if (!room.ok || (w != nullptr && !(roots.alloc_for_speed(ctx, sizeof(double) * 2 * (size_t)K) && sign.alloc_for_speed(ctx, sizeof(int)))))
         return 0;
     double *root[2] = {nullptr, nullptr};
-    if (dw != nullptr) {
+    if (w != nullptr) {
         root[0] = roots.as<double>();
-        root[1] = root[0] + M;
-        if (launch_signed_root(dw, M, root[0], root[1], sign.as<int>(), ctx->stream) != hipSuccess)
-            return fail(ctx, KNM_HIP_ERROR, "triangular product launch");
+        root[1] = root[0] + K;
+        if (launch_signed_root(w, K, root[0], root[1], sign.as<int>(), ctx->stream) != hipSuccess)
+            return fail(ctx, KNM_HIP_ERROR, "update by residues");
     }
     int *const exps = room.exps[0].as<int>();
-    for (int64_t k1 = M; k1 > 0;) {
-        const int64_t k0 = (k1 - 1) / depth * depth;
+    for (int64_t k1 = K; k1 > 0;) {
+        const int64_t k0 = (k1 - 1) / depth * depth, rows = tri ? k1 : n;
         hipError_t e = hipSuccess;
         for (int s = 0; s < sides && e == hipSuccess; ++s)
-            e = launch_residue_image(1, k1, k1 - k0, p->T + k0 * p->ld, p->ld, root[s] ? root[s] + k0 : nullptr, 1, k0, exps,
+            e = launch_residue_image(form_nt, rows, k1 - k0, A + (form_nt ? k0 * lda : k0), lda, root[s] ? root[s] + k0 : nullptr, tri, k0, exps,
                                      room.img[s].p, ctx->stream, s == 1 ? sign.as<int>() : nullptr);
         ResidueUpdate up = {};
         up.img_u = room.img[0].p;
         up.img_v = room.img[sides - 1].p;
-        up.differ = dw != nullptr ? sign.as<int>() : nullptr;
+        up.differ = w != nullptr ? sign.as<int>() : nullptr;
         up.exp_u = up.exp_v = exps;
-        up.n = k1;
+        up.n = rows;
         up.K = k1 - k0;
-        up.u1 = up.v1 = k1;
-        up.lower = up.tri = 1;
+        up.u1 = up.v1 = rows;
+        up.lower = lower;
+        up.tri = tri;
         up.k0 = k0;
-        up.alpha = 1.0 / (double)M;
-        up.beta = k1 == M ? 0.0 : 1.0;
-        up.shift = k1 == M ? lambda : 0.0;
-        up.C = p->A;
-        up.ldc = p->ld;
+        up.alpha = alpha;
+        up.beta = k1 == K ? beta : 1.0;
+        up.shift = k1 == K ? shift : 0.0;
+        up.C = C;
+        up.ldc = ldc;
         up.bytes = room.bytes[1].p;
         up.bytes_size = room.bytes_size[1];
         if (e == hipSuccess) e = launch_residue_update(up, ctx->stream);
-        if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "triangular product launch");
+        if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "update by residues", e);
         k1 = k0;
     }
     return 1;
@@ -1340,7 +1343,8 @@ static int build_second_factor(knm_ctx *ctx, knm_precond *p, double lambda, cons
     const int64_t M = p->M;
     {
         TraceRange range("knm triangular product T D T^T");
-        const int by_residues = second_by_residues(ctx, p, lambda, dw);
+        const int by_residues = !residue_pays(M, M, true) ? 0
+                                                          : rank_k_by_residues(ctx, 1, 1, M, M, 0, 1.0 / (double)M, p->T, p->ld, dw, 1, 0.0, lambda, p->A, p->ld);
         if (by_residues < 0) return by_residues;
         if (by_residues == 0 && launch_rank_k_upper(1, M, M, 1.0 / (double)M, p->T, p->ld, dw, 1, 0.0, lambda, p->A, p->ld, ctx->stream, 1) !=
             hipSuccess)
@@ -1567,6 +1571,18 @@ int precond_rank_k_update(knm_ctx *ctx, int form_nt, int64_t n, int64_t k, doubl
                                        ctx->stream);
     if (e != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "rank-k update launch", e);
     return KNM_OK;
+}
+
+int precond_residue_update(knm_ctx *ctx, int form_nt, int lower, int64_t n, int64_t k, int64_t slab, double alpha, const double *A, int64_t lda,
+                           const double *w_or_null, int triangular, double beta, double shift, double *C, int64_t ldc)
+{
+    if (!ctx) return KNM_INVALID_ARG;
+    if (n <= 0 || k <= 0 || slab < 0 || !A || !C || ldc < n || lda < (form_nt ? n : k)) return fail(ctx, KNM_INVALID_ARG, "bad rank-k update argument");
+    if (slab % 64 != 0 || slab > residue_max_k()) return fail(ctx, KNM_INVALID_ARG, "slabs are multiples of 64 up to 65536");
+    if (triangular && (!form_nt || k != n)) return fail(ctx, KNM_INVALID_ARG, "triangular operand needs the row-contiguous form and k = n");
+    if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, KNM_HIP_ERROR, "hipSetDevice");
+    const int done = rank_k_by_residues(ctx, form_nt, lower, n, k, slab, alpha, A, lda, w_or_null, triangular, beta, shift, C, ldc);
+    return done < 0 ? done : done == 0 ? fail(ctx, KNM_ALLOC, "no room for an update by residues") : KNM_OK;
 }
 
 int precond_block_product(knm_ctx *ctx, int a_nt, int64_t ni, int64_t nj, int64_t k, double alpha, const double *A,
