@@ -86,19 +86,20 @@ int knm_v(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx,
           const float *V, int t, float *W);
 
 /* U[M x t] = K_nm^T (K_nm V), the product evaluated once per conjugate-gradient
- * iteration (Section 3.1, "Blockwise K_nm-vector product"); K_nm is never formed as a whole (from about 230 features on the
- * kernel values of a slab of rows, up to 4 GiB, are kept from K V to their share of K^T; where there is no room for one, the values are formed
- * twice, and the last bits of W differ).
+ * iteration (Section 3.1, "Blockwise K_nm-vector product"); K_nm is never formed as a whole.  With the default arithmetic, the Gaussian kernel and
+ * many features the kernel values of a slab of rows, up to 4 GiB, are kept from K V to their share of K^T: up to 12 columns from about 230 features on;
+ * from n M = 1e8 on also 17 to 32 columns from 450 features on, 33 to 64 from 320, 65 to 128 from 210, more from 180 (but not where a multiple
+ * of 160 leaves few that the vector ALU sums).  Where there is no room for a slab or for both sets' images (see knm_set_pack_limit) the values are formed twice, and the last
+ * bits of W, with more than 12 columns of U as well, differ.
  * If W_or_null is not NULL it also receives W[n x t] = K_nm V. */
 int knm_prod(knm_ctx *ctx, const float *X, int64_t n, int d, int64_t ldx,
              const float *C, int64_t M, int64_t ldc, float sigma,
              const float *V, int t, float *W_or_null, float *U);
 
 /* knm_prod for callers that cannot allocate device memory: code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc.  Same arguments and result as knm_prod (up to the last bits where the
- * array below holds fewer partials than knm_prod would make, and where knm_prod keeps kernel values, which rounds W in another order: up to
- * 12 columns and from about 230 features on), except that
- * W (n x t) must be given.  The call allocates nothing: the chunk partials, the common shift and the
+ * serving loops, harnesses that forbid hipMalloc.  Same arguments and result as knm_prod, except that
+ * W (n x t) must be given, and up to the last bits: where the array below holds fewer partials than knm_prod would make or, in the fp32 mode, no
+ * image beside them (the fp32 matrix instructions take such a sweep), and where knm_prod keeps kernel values (see there), which this call never does.  The call allocates nothing: the chunk partials, the common shift and the
  * converted operands of the split-fp16 engines live in a static device array of
  * knm_static_scratch_bytes() bytes (64 MiB) that every GPU the library runs on holds until the process
  * ends.  Shapes whose sweeps do not fit that array (the packed operands are cut into slabs, so this is
@@ -346,7 +347,9 @@ int knm_set_sparse_head_limit(knm_ctx *ctx, int max_features);
 
 /* Cap, in bytes, on the library-owned workspace that holds the converted operands of the
  * split-fp16 engines, and of the fp32 mode where it has any (0 restores the defaults: 2 GiB, or 8 GiB for the K-loop engine).  Operands
- * that do not fit are converted and swept slab by slab; results do not depend on the cap.  The
+ * that do not fit are converted and swept slab by slab; results do not depend on the cap, but for the last bits of products and fits that
+ * form their kernel values once (see knm_prod and knm_workspace_bytes): they need the images of both sets whole, and form the values in every sweep
+ * under a smaller cap.  The
  * workspace never shrinks below what one slab needs (one stream chunk, plus the whole smaller
  * operand for the K-loop engine). */
 int knm_set_pack_limit(knm_ctx *ctx, size_t bytes);

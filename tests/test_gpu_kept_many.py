@@ -58,3 +58,28 @@ def test_products_with_many_columns(knm, n, M, d, t):
     weighted = knm.knm_prod_weighted(X, C, sigma, wgt, V)
     for c in range(t - 1):
         assert _err(weighted[:, c], Uw[:, c]) < TOL, c
+
+
+# Products that would keep their kernel values and cannot: both images beyond the cap, no room for a slab, the call that allocates nothing.  Two sweeps,
+# as far from 64 bits as with kept values, and the same to the last bits whatever the reason.
+@pytest.mark.parametrize("n,M,d,t", [(20_001, 5001, 320, 33), (30_003, 3400, 460, 17)])
+def test_products_with_many_columns_without_kept_values(knm, n, M, d, t):
+    X, C = _rows(n, d, 1), _rows(M, d, 2)
+    C[:1000] = X[:1000]
+    sigma, V = 0.75 * math.sqrt(d), _rows(M, t, 3).abs() + 0.01
+    W, U = _reference(X, C, sigma, V)
+    kept = knm.knm_prod(X, C, sigma, V, return_w=True)
+    ctx = knm.Context()
+    ctx.set_pack_limit(1 << 20)
+    capped = knm.knm_prod(X, C, sigma, V, return_w=True, ctx=ctx)
+    Us, Ws = torch.empty_like(U, dtype=torch.float32), torch.empty_like(W, dtype=torch.float32)
+    knm.knm_prod_static(X, C, sigma, V, Ws, Us, ctx=ctx)
+    free, total = torch.cuda.mem_get_info()
+    others = torch.empty(max(free - total // 16 + (256 << 20), 1), device="cuda", dtype=torch.uint8)
+    full = knm.knm_prod(X, C, sigma, V, return_w=True, ctx=knm.Context())
+    del others
+    torch.cuda.empty_cache()
+    for u, w in (kept, capped, full, (Us, Ws)):
+        assert _err(w, W) < TOL and _err(u, U) < TOL
+    assert torch.equal(capped[0], full[0]) and torch.equal(capped[1], full[1])
+    assert not torch.equal(kept[0], full[0])  # (by kept values)
