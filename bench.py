@@ -210,11 +210,14 @@ def counters(workload: str):
 def engine_of(w, cross: str, kernel: str):
     """Which tile engine the library runs for this shape (same rule as the library): the K-loop engine
     for t > 1 or for d beyond the register-resident engine's limit (44 features with the split-fp16
-    cross term, the default, 28 for the kernels of the distance; 64 with fp32 MFMA, Gaussian only)."""
+    cross term, the default, 28 for the kernels of the distance; 64 with fp32 MFMA, Gaussian only).  Large products of the fp32 mode with up to
+    14 features run on the bf16 matrix cores, three parts of every feature."""
     k_loop = w.t > 1 or w.d > (44 if cross == "f16x3" else 64) or (kernel != "gaussian" and (cross != "f16x3" or w.d > 28))
     f16 = cross == "f16x3"
     name = (("gauss_gemm_f16_kernel" if f16 else "gauss_gemm_kernel") if k_loop
             else ("gauss_sweep_f16_kernel" if f16 else "gauss_sweep_kernel"))
+    if not (k_loop or f16) and w.d <= 14 and float(w.n) * w.M * (0.05 + 0.006 * w.d) > 7.0e6:
+        name = "gauss_sweep_b16_kernel"
     return name, k_loop, f16
 
 
@@ -273,6 +276,7 @@ def product_leg(knm, synth, torch, ctx, w, steps: int, warmup: int, cross: str, 
     s_per_product = elapsed / steps
     entries = float(w.n) * float(w.M)
     kernel_name, k_loop, f16 = engine_of(w, cross, kernel)
+    b16 = kernel_name == "gauss_sweep_b16_kernel"  # (the bf16 and fp16 matrix cores have one peak)
     # columns per launch of the K-loop engines (split-fp16: with its packed vector image)
     group = (160 if kernel == "gaussian" else 128) if (k_loop and f16) else 16
     # A product that forms every value once is priced as a whole: its row sweeps of slabs and its sums over the kept values
@@ -287,19 +291,19 @@ def product_leg(knm, synth, torch, ctx, w, steps: int, warmup: int, cross: str, 
     flop_per_launch = entries * 2.0 * w.d
     tflops = flop_per_launch / (avg_launch_ms * 1e-3) / 1e12
     default = kernel == "gaussian"
-    # (no counters have been taken of the sums over many columns)
-    traffic, mfma_insts = counters(w.name + ("" if f16 else "_f32")) if default and not many else (None, None)
+    # (no counters have been taken of the sums over many columns and of the products in three parts)
+    traffic, mfma_insts = counters(w.name + ("" if f16 else "_f32")) if default and not many and not b16 else (None, None)
     roofline = {
         "bound": "mfma",
         "kernel": kernel_name + (" + kept_many_kernel" if many else " + kept_rows_kernel" if once else ""),
         "values_formed": "once, in slabs" if once else "in each sweep",
         # the contraction's own dtype: f16 matrix cores (three split products per feature pair,
-        # fp32 accumulate) in the default mode, fp32 matrix cores otherwise
-        "contraction_dtype": "f16" if f16 else "f32",
+        # fp32 accumulate) in the default mode, bf16 (six products of three parts) or fp32 matrix cores otherwise
+        "contraction_dtype": "f16" if f16 else "bf16" if b16 else "f32",
         "achieved": tflops,
-        "peak": PEAK_FP16_MFMA_TFLOPS if f16 else PEAK_FP32_MFMA_TFLOPS,
+        "peak": PEAK_FP16_MFMA_TFLOPS if f16 or b16 else PEAK_FP32_MFMA_TFLOPS,
         "unit": "TFLOP/s",
-        "frac": tflops / (PEAK_FP16_MFMA_TFLOPS if f16 else PEAK_FP32_MFMA_TFLOPS),
+        "frac": tflops / (PEAK_FP16_MFMA_TFLOPS if f16 or b16 else PEAK_FP32_MFMA_TFLOPS),
         "traffic": traffic,
         "avg_launch_ms": avg_launch_ms,
         # (in slabs the two alternate; the library's events tell only the last slab's sums from what comes before them)

@@ -129,6 +129,22 @@ def test_products_with_many_columns_that_keep_values(run):
         """)
 
 
+# bench.py names the engine that the library takes
+def test_the_engine_that_the_benchmark_names(run):
+    shapes = [(n, M, d, t, cross, kind) for n, M in ((5_900_000, 100_000), (60_000, 2000), (9000, 9000), (2000, 500)) for d in (1, 8, 14, 15, 28, 29, 44, 45, 64, 65)
+              for t in (1, 2) for cross, kind in ((1, 0), (0, 0), (1, 1), (0, 1))]
+    run(f"""
+        import sys, types
+        sys.path.insert(0, {os.path.dirname(HERE)!r})
+        import bench
+        for n, M, d, t, cross, kind in {shapes!r}:
+            assert lib.knm_set_cross_term(ctx, cross) == 0 and lib.knm_set_kernel(ctx, kind) == 0
+            assert prod_static(n, M, d, t) == 0 or prod(n, M, d, t) == 0
+            name = bench.engine_of(types.SimpleNamespace(n=n, M=M, d=d, t=t), "f16x3" if cross else "f32", "laplacian" if kind else "gaussian")[0]
+            assert launched(name) > 0, (n, M, d, t, cross, kind, name)
+        """)
+
+
 # The image of three-part numbers is for speed alone: it leaves a sixteenth of the card free and every other buffer where it is, and a call that
 # does without it has no error to report
 def test_three_part_images_leave_room(run):
