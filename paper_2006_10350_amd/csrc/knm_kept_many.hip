@@ -6,7 +6,7 @@
 // runs over, and a sum of 32 columns per group; a value is read once for all columns.  A lane of the product's second operand holds 8 values of one such
 // point: over the stream points two units of 4 rows, over the fixed ones 8 values of as many units.  Values and vectors come by loads that
 // write LDS directly, two stages of 32 points ahead of their use; a lane fetches the unit whose place in LDS is its own, so that a block's units
-// lie where both ways of reading it are free of bank conflicts.
+// lie where reading it over the stream has no bank conflicts, and reading it over the fixed points 7 % of the clocks in them.
 // Bound by the matrix cores (busy half of the clocks, at 1.6 to 1.9 GHz) and the values' bandwidth together, 120000 x 20000 values, 144 columns:
 // 2.9 ms over the centres, 2.8 over the rows (3.3 TB/s); with the values in registers a stage ahead 3.0 and 3.2; vectors read where they are used 3.7
 // and 3.0; values through the caches 3.2 and 3.0.

@@ -1,4 +1,4 @@
-"""The fp32 cross term from three bf16 parts (large products with up to 16 features in the fp32 mode) against 64 bits.
+"""The fp32 cross term from three bf16 parts (large products with up to 14 features in the fp32 mode) against 64 bits.
 
 Error bound of the rows used here: an exponent is a sum of terms of at most 16 in size, rounded to 2^-24 of that when the large terms
 come in, so a kernel value is off by at most about 1e-6 of itself; weights are positive, so sums are no further off.
