@@ -454,6 +454,7 @@ __global__ __launch_bounds__(kThreads) void residue_combine_kernel(ResidueArgs a
     }
 }
 
+__global__ void clear_word_kernel(int *word) { *word = 0; }
 // (negative: raised where a weight has a sign; it may not be a number either)
 __global__ void signed_root_kernel(const double *__restrict__ w, int64_t n, double *__restrict__ magnitude, double *__restrict__ with_sign,
                                    int *__restrict__ negative)
@@ -577,8 +578,8 @@ hipError_t launch_residue_update(const ResidueUpdate &p, hipStream_t stream)
 
 hipError_t launch_signed_root(const double *w, int64_t n, double *magnitude, double *with_sign, int *negative, hipStream_t stream)
 {
-    hipError_t e = hipMemsetAsync(negative, 0, sizeof(int), stream);
-    if (e != hipSuccess) return e;
+    // (cleared by a kernel: precond_residue_update may be captured into a graph, where memset nodes are to be avoided)
+    hipLaunchKernelGGL(clear_word_kernel, dim3(1), dim3(1), 0, stream, negative);
     hipLaunchKernelGGL(signed_root_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, w, n, magnitude, with_sign, negative);
     return hipGetLastError();
 }
